@@ -78,6 +78,20 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
                    d->dilation_h, d->dilation_w, d->signed_codes, d->depthwise, d->groups > 1 ? d->groups : 1);
 }
 
+// Whether fewpix_kernel takes the layer (automatic choice only: any override of the table-tile
+// kernels keeps the layer on them).  Under 2e6 lookups staging the table (about 6 us) costs more
+// than direct_kernel's table reads (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us; 1 x 2048 x 1000:
+// 11 against 16.5 us).  From 4e6 on it competes with the table tiles: 15 % under their expected
+// time, since both estimates are off by about that much (ResNet-50 layers at batch 1: 14 x 14 and
+// 7 x 7 layers 21-36 us against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
+static bool fewpix_pays(const Geom& g, const Options& o) {
+  if (g.T != 1 || o.variant || o.split_k || o.tile || o.row_tiles || o.share_order || o.combine || o.tables) return false;
+  const double n = (double)g.M * g.K * g.Cout;
+  if (n < 2.0e6 || !fewpix_shape(g)) return false;
+  if (n < 4.0e6 || !tab_supported(g)) return fewpix_cost(g) < 5e-6 + 5.5e-12 * n;
+  return 1.1 * fewpix_cost(g) < tab_plan(g, o).cost;
+}
+
 // 1 = direct (or depthwise) kernels, 0 = table-tile kernels with the planner's lane assignment,
 // 2 / 3 = table-tile kernels with that lane assignment
 static int choose_variant(const Geom& g, const Options& o) {
@@ -86,23 +100,21 @@ static int choose_variant(const Geom& g, const Options& o) {
   if (o.variant == 2 || o.variant == 3) return o.variant;
   // Tiny problems do not amortize the table set-up.
   if ((double)g.M * g.K * g.Cout < 4.0e6) return 1;
-  // A dense layer of few rows fills 1/32 of the lanes of a table tile: whole table in LDS instead.
-  if (g.T == 1 && fewrows_shape(g)) return 1;
-  return 0;
+  return fewpix_pays(g, o) ? 1 : 0;  // few output pixels: whole table in LDS instead of table tiles
 }
 
 // Kernels that take one table at a time and need neither preparation nor scratch.
 static int run_untiled(const Geom& g, const QParams& qp, const Options& o, const uint8_t* x, const uint8_t* w,
                        const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s) {
   const bool dw = g.mult && o.variant != 1 && dw_supported(g, x, w, lut);
-  const bool rows = !dw && o.variant != 1 && (double)g.M * g.K * g.Cout >= 4.0e6 && fewrows_supported(g, lut);
+  const bool few = !g.mult && fewpix_pays(g, o);
   const size_t per_table = (size_t)g.M * g.Cout;
   for (int t = 0; t < g.T; ++t) {
     const uint16_t* lt = lut + (size_t)t * 65536;
     int32_t* at = acc_out ? acc_out + t * per_table : nullptr;
     float* yt = y_out ? y_out + t * per_table : nullptr;
     const hipError_t e = dw     ? launch_dw(g, qp, x, w, lt, at, yt, s)
-                         : rows ? launch_fewrows(g, qp, x, w, lt, at, yt, s)
+                         : few  ? launch_fewpix(g, qp, x, w, lt, at, yt, s)
                                 : launch_direct(g, qp, x, w, lt, at, yt, s);
     if (e != hipSuccess) return AX_ERR_HIP;
   }

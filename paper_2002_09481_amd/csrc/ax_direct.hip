@@ -6,6 +6,7 @@
 // are a coalesced 64-byte read and the lookups fall into one 512-byte table row.  It is
 // used for tiny problems and for shapes the table-tile kernels do not take.
 #include <algorithm>
+#include <cmath>
 
 #include "ax_internal.h"
 
@@ -438,132 +439,292 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
   }
 }
 
-// Dense layers with few rows (a fully connected layer on a small batch: M <= 64 rows of x [M, K],
-// filters [K, Cout]).  The table-tile kernels would fill 1/32 of their lanes; here a workgroup
-// keeps the whole table in LDS, as the depthwise kernel does, and takes four output columns: lane
-// l of every wave walks the taps k = l, l + 64, ..., wave v the rows v, v + 16, ...  Per tap a
-// lane reads its four filter codes (one dword) and, per row, one activation code (consecutive
-// lanes, consecutive bytes) and gathers four 2-byte entries; the 64 partial sums of a wave meet
-// in a butterfly of lane exchanges.  One launch, no preparation, no scratch.
-// MPW: rows per wave (M <= 16 * MPW).
-template <int MPW>
-__global__ __launch_bounds__(1024) void fewrows_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
-                                                        const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
-                                                        int32_t* __restrict__ acc_out, float* __restrict__ y_out,
-                                                        int w_dwords) {
+// Layers of few output pixels (the deep layers of a network at batch 1, a fully connected layer at a
+// small batch).  A table tile would spend more on assembling its tables than on the lookups they
+// serve; here every workgroup keeps the whole table in LDS, as the depthwise kernel does, and
+// gathers 2-byte entries.  A tile is P pixels x 4 CL output channels, the taps are cut into 1024 / CL
+// slices of four consecutive taps in turn: a lane reads one dword of activations per pixel and one
+// dword of filter codes per tap and makes 16 P lookups of them, so that a lookup costs one address
+// addition, one gather and one accumulation.  Lanes of neighbouring slices lie side by side; their
+// sums meet in DPP additions, those of the waves in 64-bit LDS atomics (two 32-bit sums at a time,
+// neither reaches 2^32; integer, any order gives the same bits).  One launch, no preparation, no
+// scratch.  Workgroups walk over tiles, so a table is staged once per compute unit.
+// Bound: the random 2-byte gather rate of the LDS (5.2 T lookups/s) plus about 6 us of launch and
+// staging.  Measured (table tiles or the former one-purpose dense kernel -> this one): 7 x 7 x 512
+// 3 x 3 113 -> 35 us, 14 x 14 x 256 3 x 3 44 -> 35 us, 14 x 14 x 1024 1 x 1 30 -> 23 us, dense
+// 1 x 2048 x 1000 380 -> 10 us, 8 x 4096 x 4096 175 -> 44 us, 32 x 2048 x 1000 27.7 -> 25.3 us.
+// Seven pixels of four channels (28 sums) are what 128 registers hold with a step's codes in flight.
+// DWORDS: Cin % 4 == 0 and x dword aligned: four consecutive taps are one dword of one pixel.
+template <int P, bool DWORDS>
+__global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
+                                                       const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
+                                                       int32_t* __restrict__ acc_out, float* __restrict__ y_out,
+                                                       int cl_log2, int w_dwords, int lut_vec) {
   __shared__ uint32_t tab[256 * kDwRow];
+  __shared__ __align__(16) uint32_t accs[P * 256];  // [pixel][channel of the tile]
+  __shared__ uint32_t sps[P], sfs[256];
   QParams qp = qp_in;
   if (qp.dq) {
     qp.x_zp = qp.dq->x_zp;
     qp.w_zp = qp.dq->w_zp;
+    qp.pad_code = qp.x_zp;
     qp.scale = qp.dq->x_scale * qp.dq->w_scale;
   }
-  const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
-  const uint32_t flip8 = g.sgn ? 0x80u : 0u;
-  {
-    const uint4* __restrict__ src = reinterpret_cast<const uint4*>(lut);
-    const int rowflip = g.sgn ? (0x80 << 5) : 0;  // see dw_kernel
-    for (int i = threadIdx.x; i < 8192; i += 1024) {
-      uint4 v = src[i ^ rowflip];
-      uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
-      dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
-    }
-  }
-  __syncthreads();
-  const char* tabb = reinterpret_cast<const char*>(tab);
+  const uint32_t flip8 = g.sgn ? 0x80808080u : 0u;
+  const uint32_t pad4 = ((uint32_t)qp.pad_code & 0xffu) * 0x01010101u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int K = g.K, M = g.M, J = g.Cout;
-  const int n0 = blockIdx.x * 4;
-  uint32_t acc[MPW][4], sp[MPW], sf[4] = {0, 0, 0, 0};
+  const int sl_log2 = 6 - cl_log2;                  // slices side by side in a wave
+  const int cl = lane >> sl_log2;                   // channel group of the lane
+  const int CT = 4 << cl_log2;                      // channels per tile
+  const int slices = 1024 >> cl_log2;
+  const int slice = (wave << sl_log2) + (lane & ((1 << sl_log2) - 1));
+  const int K = g.K, J = g.Cout, M = g.M;
+  const int K4 = (K + 3) >> 2;
+  const int nct = (J + CT - 1) / CT, ntiles = nct * ((M + P - 1) / P);
+  for (int i = threadIdx.x; i < P * 256; i += 1024) accs[i] = 0;
+  if (threadIdx.x < 256) sfs[threadIdx.x] = 0;
+  if (threadIdx.x < P) sps[threadIdx.x] = 0;
+  const char* tabb = reinterpret_cast<const char*>(tab);
+  const uint32_t rowbytes = (uint32_t)(kDwRow * 4);
+  bool staged = false;
+
+  // Channel tiles go fastest: workgroup b runs on XCD b mod 8, so where their number is a multiple of
+  // eight each XCD's L2 fetches one eighth of the filters.
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int pt = tile / nct;
+    const int j0 = (tile - pt * nct) * CT, m0 = pt * P;
+    const int co0 = j0 + 4 * cl;
+    int by[P], bx[P], nb[P];
 #pragma unroll
-  for (int i = 0; i < MPW; ++i) {
-    sp[i] = 0;
+    for (int p = 0; p < P; ++p) {
+      const int m = min(m0 + p, M - 1);
+      const int n = m / (g.OH * g.OW), r = m - n * (g.OH * g.OW);
+      const int oy = r / g.OW;
+      by[p] = oy * g.sh - g.ph;
+      bx[p] = (r - oy * g.OW) * g.sw - g.pw;
+      nb[p] = n * g.H;
+    }
+    // offsets into x and w are below 2^31
+    auto load = [&](int k4, uint32_t (&xd)[P], uint32_t (&wd)[4]) {
+      const int k = 4 * k4;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0;
-  }
-  const uint8_t* xr[MPW];
-  bool live[MPW];
+      for (int e = 0; e < 4; ++e) {
+        if (w_dwords) {
+          const int co = min(co0, J - 4);  // Cout % 4 == 0: a group lies wholly inside or outside
+          wd[e] = *reinterpret_cast<const uint32_t*>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)co));
+        } else {
+          const uint32_t wo = (uint32_t)min(k + e, K - 1) * (uint32_t)J;
+          wd[e] = 0;
 #pragma unroll
-  for (int i = 0; i < MPW; ++i) {
-    live[i] = wave + 16 * i < M;  // wave-uniform
-    xr[i] = x + (size_t)min(wave + 16 * i, M - 1) * K;
-  }
+          for (int j = 0; j < 4; ++j) wd[e] |= (uint32_t)w[wo + (uint32_t)min(co0 + j, J - 1)] << (8 * j);
+        }
+      }
+      if constexpr (DWORDS) {
+        const int tap = k / g.Cin, ci = k - tap * g.Cin;
+        const int ky = tap / g.KW, kx = tap - ky * g.KW;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
+          const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+          const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
+          const uint32_t v = *reinterpret_cast<const uint32_t*>(x + (pix * (uint32_t)g.Cin + (uint32_t)ci));
+          xd[p] = inside ? v : pad4;
+        }
+      } else {
+#pragma unroll
+        for (int p = 0; p < P; ++p) xd[p] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int ke = min(k + e, K - 1);
+          const int tap = ke / g.Cin, ci = ke - tap * g.Cin;
+          const int ky = tap / g.KW, kx = tap - ky * g.KW;
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
+            const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+            const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
+            const uint32_t v = x[pix * (uint32_t)g.Cin + (uint32_t)ci];
+            xd[p] |= (inside ? v : (pad4 & 0xffu)) << (8 * e);
+          }
+        }
+      }
+    };
+
+    uint32_t acc[P][4], sp[P], sf[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      sp[p] = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[p][j] = 0;
+    }
+    uint32_t xd[P], wd[4];
+    if (slice < K4) load(slice, xd, wd);  // the first codes travel while the table is staged
+    if (!staged) {
+      staged = true;
+      // signed activations index the table by code + 128: rows are staged in that order, entries with
+      // 32768 added (both come off again in the epilogue), as in dw_kernel
+      const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
+      if (lut_vec) {
+        const uint4* __restrict__ src = reinterpret_cast<const uint4*>(lut);
+        const int rowflip = g.sgn ? (0x80 << 5) : 0;
 #pragma unroll 4
-  for (int k = lane; k < K; k += 64) {
-    uint32_t wd;
-    const uint8_t* wp = w + (size_t)k * J + n0;
-    if (w_dwords) {
-      wd = *reinterpret_cast<const uint32_t*>(wp);
-    } else {
-      wd = (uint32_t)wp[0] | ((uint32_t)wp[1] << 8) | ((uint32_t)wp[2] << 16) | ((uint32_t)wp[3] << 24);
+        for (int i0 = 0; i0 < 8192; i0 += 1024) {
+          const int i = i0 + threadIdx.x;
+          const uint4 v = src[i ^ rowflip];
+          uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
+          dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
+        }
+      } else {  // a table that is only 2-byte aligned
+        const int rowflip = g.sgn ? (0x80 << 7) : 0;
+        for (int i = threadIdx.x; i < 32768; i += 1024) {
+          const uint32_t lo = lut[2 * (i ^ rowflip)], hi = lut[2 * (i ^ rowflip) + 1];
+          tab[(i >> 7) * kDwRow + (i & 127)] = (lo | (hi << 16)) ^ flip16;
+        }
+      }
+      __syncthreads();
     }
-    uint32_t wb2[4];  // 2 * filter code pattern = byte offset within a table row
+    for (int k4 = slice; k4 < K4; k4 += slices) {
+      uint32_t xs[P], ws[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t b = (wd >> (8 * j)) & 0xffu;
-      wb2[j] = b << 1;
-      sf[j] += b ^ flip8;  // code + 128 for signed codes
-    }
+      for (int p = 0; p < P; ++p) xs[p] = xd[p] ^ flip8;
 #pragma unroll
-    for (int i = 0; i < MPW; ++i) {
-      if (!live[i]) continue;
-      const uint32_t a = (uint32_t)xr[i][k] ^ flip8;
-      sp[i] += a;
+      for (int e = 0; e < 4; ++e) ws[e] = wd[e];
+      if (k4 + slices < K4) load(k4 + slices, xd, wd);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] += *reinterpret_cast<const uint16_t*>(tabb + (a * (uint32_t)(kDwRow * 4) + wb2[j]));
-    }
-  }
-  // sums over the 64 lanes of the wave
+      for (int e = 0; e < 4; ++e) {
+        if (!DWORDS && 4 * k4 + e >= K) break;
+        uint32_t wb2[4];  // 2 * filter code = byte offset within a table row
 #pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
+        for (int j = 0; j < 4; ++j) wb2[j] = (j ? ws[e] >> (8 * j - 1) : ws[e] << 1) & 0x1feu;
+        const uint32_t wf = ws[e] ^ flip8;  // code + 128 for signed codes
 #pragma unroll
-    for (int j = 0; j < 4; ++j) sf[j] += (uint32_t)__shfl_xor((int)sf[j], s, 64);
+        for (int j = 0; j < 4; ++j) sf[j] += (wf >> (8 * j)) & 0xffu;
 #pragma unroll
-    for (int i = 0; i < MPW; ++i) {
-      sp[i] += (uint32_t)__shfl_xor((int)sp[i], s, 64);
+        for (int p = 0; p < P; ++p) {
+          const uint32_t a = (xs[p] >> (8 * e)) & 0xffu;
+          sp[p] += a;
+          const uint32_t row = __umul24(a, rowbytes);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] += (uint32_t)__shfl_xor((int)acc[i][j], s, 64);
-    }
-  }
-  if (lane != 0) return;
-  const uint32_t bias = g.sgn ? 32768u * (uint32_t)K : 0u;
-  const int off128 = g.sgn ? 128 * K : 0;
-  const long long kzz = (long long)K * qp.x_zp * qp.w_zp;
-#pragma unroll
-  for (int i = 0; i < MPW; ++i) {
-    if (!live[i]) continue;
-    const size_t o = (size_t)(wave + 16 * i) * J + n0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t av = (int32_t)(acc[i][j] - bias);
-      if (acc_out) acc_out[o + j] = av;
-      if (y_out) {
-        const long long corr = (long long)av - (long long)qp.w_zp * ((int32_t)sp[i] - off128) -
-                               (long long)qp.x_zp * ((int32_t)sf[j] - off128) + kzz;
-        y_out[o + j] = (float)corr * qp.scale;
+          for (int j = 0; j < 4; ++j) {
+            // an instruction, since the optimizer turns the sums over an unrolled step into trees that
+            // keep every gathered entry alive
+            const uint32_t v = *reinterpret_cast<const uint16_t*>(tabb + (row + wb2[j]));
+            asm("v_add_u32 %0, %1, %0" : "+v"(acc[p][j]) : "v"(v));
+          }
+        }
+        // one tap's gathers in flight at a time: more of them would not fit the registers
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+    // Sums over the slices that lie side by side in the wave, within rows of 16 lanes: afterwards every
+    // lane of a group of 1 << dpp_log2 holds them.  After the first steps the lanes of a quad (of
+    // eight) are equal, so the mirrored lane stands for the lane of the other half.
+    const int dpp_log2 = min(sl_log2, 4);
+    auto wave_sum = [&](uint32_t v) -> uint32_t {
+      if (dpp_log2 > 0) v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+      if (dpp_log2 > 1) v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true);   // lane ^ 2
+      if (dpp_log2 > 2) v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true);  // mirrored in 8
+      if (dpp_log2 > 3) v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xf, 0xf, true);  // mirrored in 16
+      return v;
+    };
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      sp[p] = wave_sum(sp[p]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[p][j] = wave_sum(acc[p][j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sf[j] = wave_sum(sf[j]);
+    if ((lane & ((1 << dpp_log2) - 1)) == 0) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        unsigned long long* dst = reinterpret_cast<unsigned long long*>(accs + p * 256 + 4 * cl);
+        atomicAdd(dst, acc[p][0] | ((unsigned long long)acc[p][1] << 32));
+        atomicAdd(dst + 1, acc[p][2] | ((unsigned long long)acc[p][3] << 32));
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) atomicAdd(&sfs[4 * cl + j], sf[j]);
+      if (cl == 0) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) atomicAdd(&sps[p], sp[p]);
+      }
+    }
+    __syncthreads();
+    const uint32_t bias = g.sgn ? 32768u * (uint32_t)K : 0u;
+    const int off128 = g.sgn ? 128 * K : 0;
+    const long long kzz = (long long)K * qp.x_zp * qp.w_zp;
+    for (int i = threadIdx.x; i < P * CT; i += 1024) {
+      const int p = i >> (cl_log2 + 2), c = i & (CT - 1);
+      if (m0 + p < M && j0 + c < J) {
+        const int32_t av = (int32_t)(accs[p * 256 + c] - bias);
+        const size_t o = (size_t)(m0 + p) * J + j0 + c;
+        if (acc_out) acc_out[o] = av;
+        if (y_out) {
+          const long long corr = (long long)av - (long long)qp.w_zp * ((int32_t)sps[p] - off128) -
+                                 (long long)qp.x_zp * ((int32_t)sfs[c] - off128) + kzz;
+          y_out[o] = (float)corr * qp.scale;
+        }
+      }
+    }
+    __syncthreads();
+    if (tile + (int)gridDim.x < ntiles) {  // uniform
+      for (int i = threadIdx.x; i < P * CT; i += 1024) accs[(i >> (cl_log2 + 2)) * 256 + (i & (CT - 1))] = 0;
+      if (threadIdx.x < 256) sfs[threadIdx.x] = 0;
+      if (threadIdx.x < P) sps[threadIdx.x] = 0;
+      __syncthreads();
+    }
   }
 }
 
-bool fewrows_shape(const Geom& g) {
-  return g.mult == 0 && g.groups == 1 && g.KH == 1 && g.KW == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 &&
-         g.M <= 64 && g.Cout % 4 == 0 && g.Cout >= 256 && g.K >= 64 && g.K <= 32768;
+// Tile shape of fewpix_kernel and the time it is expected to take.
+struct FewpixPlan { int P, cl_log2; double cost; };
+
+static FewpixPlan fewpix_plan(const Geom& g, bool dwords) {
+  static const int kPixels[] = {1, 2, 4, 7, 8};  // 7: images of 7 x 7, 14 x 14, 28 x 28 ... pixels
+  const int K4 = (g.K + 3) / 4, cus = cu_count();
+  FewpixPlan best{1, 0, 1e30};
+  for (int P : kPixels) {
+    if (!dwords && P > 4) break;  // the byte form of the kernel has no registers for more
+    for (int c = 0; c <= 6; ++c) {
+      const double tiles = std::ceil((double)g.M / P) * std::ceil((double)g.Cout / (4 << c));
+      const int slices = 1024 >> c;
+      const double iters = (double)((K4 + slices - 1) / slices);
+      // 16 waves of 16 P gathers, 6.2 clocks each, and the address work and loads around them (narrow
+      // tiles fetch a 128-byte line of the filters for every few bytes); per tile one memory round
+      // trip, the sums and the stores; 6 us of launch and table staging.  Within 15 % of the times of
+      // the ResNet-50 layers at batch 1 to 8.
+      const double t_iter = 16.0 * (16.0 * P * 6.2 + (dwords ? 100.0 : 550.0) + 8.0 * (64 >> c)) / 2.4e9;
+      const double t = 6e-6 + std::ceil(tiles / cus) * (iters * t_iter + 2.5e-6 + P * (4 << c) * 1e-9);
+      if (t < best.cost) best = FewpixPlan{P, c, t};
+    }
+  }
+  return best;
 }
 
-bool fewrows_supported(const Geom& g, const uint16_t* lut) { return fewrows_shape(g) && ((uintptr_t)lut & 15) == 0; }
+bool fewpix_shape(const Geom& g) {
+  return g.mult == 0 && g.groups == 1 && g.Cout >= 4 && g.K >= 64 && g.K <= 32768;
+}
 
-hipError_t launch_fewrows(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
-                          int32_t* acc_out, float* y_out, hipStream_t s) {
-  const int w_dwords = ((uintptr_t)w & 3) == 0 ? 1 : 0;  // Cout % 4 == 0: every group of four codes is then a dword
-  const dim3 grid((unsigned)(g.Cout / 4));
-  if (g.M <= 16)
-    hipLaunchKernelGGL((fewrows_kernel<1>), grid, dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, w_dwords);
-  else if (g.M <= 32)
-    hipLaunchKernelGGL((fewrows_kernel<2>), grid, dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, w_dwords);
-  else
-    hipLaunchKernelGGL((fewrows_kernel<4>), grid, dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, w_dwords);
+double fewpix_cost(const Geom& g) { return fewpix_plan(g, g.Cin % 4 == 0).cost; }
+
+hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
+                         int32_t* acc_out, float* y_out, hipStream_t s) {
+  const bool dwords = g.Cin % 4 == 0 && ((uintptr_t)x & 3) == 0;
+  const int w_dwords = (g.Cout % 4 == 0 && ((uintptr_t)w & 3) == 0) ? 1 : 0;
+  const int lut_vec = ((uintptr_t)lut & 15) == 0 ? 1 : 0;
+  const FewpixPlan p = fewpix_plan(g, dwords);
+  const long long tiles = (long long)((g.M + p.P - 1) / p.P) * ((g.Cout + (4 << p.cl_log2) - 1) / (4 << p.cl_log2));
+  const int grid = (int)std::min<long long>(cu_count(), tiles);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2, w_dwords, lut_vec);
+  };
+  switch (p.P) {
+    case 1: if (dwords) go(fewpix_kernel<1, true>); else go(fewpix_kernel<1, false>); break;
+    case 2: if (dwords) go(fewpix_kernel<2, true>); else go(fewpix_kernel<2, false>); break;
+    case 4: if (dwords) go(fewpix_kernel<4, true>); else go(fewpix_kernel<4, false>); break;
+    case 7: go(fewpix_kernel<7, true>); break;
+    default: go(fewpix_kernel<8, true>); break;
+  }
   return hipGetLastError();
 }
 

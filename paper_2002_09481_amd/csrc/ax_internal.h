@@ -88,12 +88,12 @@ bool dw_supported(const Geom& g, const uint8_t* x, const uint8_t* w, const uint1
 hipError_t launch_dw(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
                      int32_t* acc_out, float* y_out, hipStream_t s);
 
-// Dense layers of at most 64 rows with the whole table in LDS (ax_direct.hip): fewrows_shape says
-// whether the geometry is one, fewrows_supported whether the table pointer fits as well.
-bool fewrows_shape(const Geom& g);
-bool fewrows_supported(const Geom& g, const uint16_t* lut);
-hipError_t launch_fewrows(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
-                          int32_t* acc_out, float* y_out, hipStream_t s);
+// Layers of few output pixels with the whole table in LDS (ax_direct.hip): fewpix_shape says whether
+// the kernel takes the geometry, fewpix_cost the time it is expected to take (seconds).
+bool fewpix_shape(const Geom& g);
+double fewpix_cost(const Geom& g);
+hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
+                         int32_t* acc_out, float* y_out, hipStream_t s);
 
 // Table-tile kernels (ax_tab.hip).  Device memory of a layer comes in two blocks: the prepared
 // constants (re-laid-out table, packed filters and their sums, coefficients) and the per-call
@@ -108,6 +108,7 @@ struct TabPlan {
   int pre;          // 1: the main kernel copies ready-made tables from the prepared block
   int nti;          // tiles along the lane dimension
   int ih;           // their height in lane elements (multiple of 64, nti * ih >= I)
+  double cost;      // expected time of a call, seconds (the planner's model)
   int xcd;          // 1: shares of work numbered XCD by XCD, 0: in launch order
   size_t off_rows;   // prepared block
   size_t off_qd;     // prepared block

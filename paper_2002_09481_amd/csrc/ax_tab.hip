@@ -1407,6 +1407,13 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
                         (best.partials == 0 && best.nti >= kPreRowTiles && tabs_bytes <= kPreTablesMax);
   p.pre = (v == 2 && g.T == 1 && g.K <= 16384 && (best.tile == 2 || best.tile == 4) && tabs_bytes <= ((size_t)1 << 30) &&
            (o.tables ? o.tables == 2 : pre_pays)) ? 1 : 0;
+  // Expected time of a call, for the choice against fewpix_kernel: the model above, corrected by what
+  // the ResNet-50 layers at batch 1 to 8 and dense layers of 1 to 256 rows measured.  It overrates
+  // layers with pieces (measured / model 0.7-0.75 with ready-made tables, 0.75-0.83 without, 0.95 with channel lanes) and
+  // underrates whole tiles (1.2), the packing of the activations for channel lanes (a launch of
+  // about 9 us) and fix-up passes over many pieces of a tile (0.15 us each: 1 x 2048 x 1000 42 us).
+  p.cost = best.cost * (!best.partials ? 1.15 : p.pre ? 0.72 : v == 3 ? 0.95 : 0.8) + (v == 3 ? 9e-6 : 0.0) +
+           (best.partials && !p.combine ? 0.15e-6 * best.most : 0.0);
   p.off_tabs = prep;
   if (p.pre) prep += up256(tabs_bytes);
   if (v == 2) {

@@ -1,0 +1,79 @@
+"""Layers of few output pixels (whole table in LDS, taps over the lanes) and tiny layers (several
+threads per output) against the oracle, at the edges of their tiles: pixels per tile 1, 2, 4, 7, 8,
+channel groups and tap slices that do not divide, byte-granular operands, unaligned pointers."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import assert_parity, check_layer, to_dev
+from oracle import oracle
+from paper_2002_09481_amd import binding as ax
+from paper_2002_09481_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+L = I.Layer
+
+
+def _dense(M, K, N):
+    return L("dense", M, 1, 1, K, 1, 1, N, dense=True, x_dist="relu", w_dist="normal")
+
+
+def _conv(N, H, W, Cin, k, Cout, stride=1, pad=0):
+    return L("conv", N, H, W, Cin, k, k, Cout, stride, pad, x_dist="relu", w_dist="normal")
+
+
+FEW = [_dense(1, 2048, 1000), _dense(2, 2051, 1001), _dense(3, 4100, 340), _dense(7, 1536, 257), _dense(8, 1024, 516),
+       _dense(9, 777, 333), _dense(33, 2048, 1000), _dense(50, 516, 1030), _dense(64, 100, 1000), _dense(1, 32768, 68),
+       _conv(1, 7, 7, 512, 3, 128, 1, 1), _conv(1, 14, 14, 256, 1, 516), _conv(1, 13, 15, 260, 1, 300, 2),
+       _conv(2, 9, 5, 132, 3, 70, 2, 1), _conv(1, 14, 13, 50, 5, 70, 1, 2), _conv(1, 28, 28, 128, 1, 512),
+       _conv(3, 6, 7, 64, 3, 257, 1, 2)]
+TINY = [_conv(1, 16, 16, 8, 3, 8, 1, 1), _conv(1, 3, 3, 4, 3, 5, 1, 1), _dense(1, 1, 1), _dense(1, 2048, 100), _dense(2, 63, 7),
+        _dense(1, 64, 1001), _dense(1, 32768, 3), _conv(2, 20, 20, 3, 5, 9, 2, 2), _conv(1, 60, 60, 4, 1, 70)]
+
+
+@pytest.mark.parametrize("layer", FEW + TINY, ids=lambda l: "%dx%dx%d" % (l.M, l.K, l.Cout))
+def test_against_the_oracle(layer):
+    desc = (ax._dense_desc(layer.N, layer.K, layer.Cout) if layer.dense else
+            ax._conv_desc((layer.N, layer.H, layer.W, layer.Cin), (layer.KH, layer.KW, layer.Cin, layer.Cout), layer.stride, layer.pad))
+    with ax.AxLayer(desc, I.Quant(1.0, 0, 1.0, 0, None)) as h:
+        assert h.plan()["variant"] == 1 and h.prepared_bytes == 0
+    check_layer(layer, 3, I.lut_random_error(5))
+
+
+@pytest.mark.parametrize("shape", [(1, 7, 7, 256, 3, 128, 1, 1, 2), (2, 13, 9, 66, 3, 65, 2, 2, 1), (1, 5, 5, 8, 3, 9, 1, 1, 1)],
+                         ids=["dwords", "bytes", "tiny"])
+def test_signed_codes_pad_code_and_dilation(shape):
+    n, hh, ww, cin, k, cout, stride, pad, dil = shape
+    rng = np.random.default_rng(11)
+    x = rng.integers(-128, 128, (n, hh, ww, cin), dtype=np.int8)
+    w = rng.integers(-128, 128, (k, k, cin, cout), dtype=np.int8)
+    lut = I.lut_signed_random_error(3)
+    q = I.Quant(0.02, -7, 0.01, 5, -100)
+    acc, y = ax.ax_conv2d_ex(to_dev(x), to_dev(w), ax.lut_to_device(lut), stride, pad, q, dil)
+    torch.cuda.synchronize()
+    acc_ref, y_ref = oracle.conv2d_ex(x, w, lut, stride, pad, q, dilation=dil, signed=True)
+    assert_parity(acc.cpu().numpy(), y.cpu().numpy(), acc_ref, y_ref)
+
+
+@pytest.mark.parametrize("off", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (2, 3, 1)])
+def test_unaligned_operands(off):
+    """Operands that start at any byte, tables at any entry."""
+    layer = _dense(5, 1024, 516)
+    x, w, q = I.make_operands(layer, 4)
+    lut = I.lut_random_error(6)
+
+    def shifted(a, o):
+        flat = torch.empty(a.size + 8, dtype=torch.from_numpy(a.reshape(-1)[:1].copy()).dtype, device="cuda")
+        v = flat[o:o + a.size]
+        v.copy_(torch.from_numpy(a.reshape(-1)))
+        return v.view(a.shape)
+
+    xd = shifted(np.ascontiguousarray(x.reshape(5, -1)), off[0])
+    wd = shifted(np.ascontiguousarray(w.reshape(1024, 516)), off[1])
+    ld = shifted(np.ascontiguousarray(lut).reshape(-1).view(np.int16), off[2])
+    acc, y = ax.ax_dense(xd, wd, ld, q)
+    torch.cuda.synchronize()
+    acc_ref, y_ref = oracle.dense(x.reshape(5, -1), w.reshape(1024, 516), lut, q)
+    assert_parity(acc.cpu().numpy(), y.cpu().numpy(), acc_ref, y_ref)
