@@ -138,12 +138,10 @@ constexpr int kDwRow = 129;    // dwords per table row in LDS
 
 // KS: kernel height = width known at compile time (taps fully unrolled, so that the loads of all
 // taps of an item are in flight together), or 0 for any kernel size.
-// HOIST (3x3, not GEN): the grid stride is a multiple of the channel groups, so a thread keeps its
-// four channels for every item: the filter codes are loaded once and kept, pre-shifted, in registers.
 // GEN: any channel multiplier and channel count: output channel co reads input channel co / mult and
 // filter code w[tap * Cout + co]; codes are loaded byte by byte and the last group of a pixel may
 // hold fewer than four channels.  Otherwise multiplier 1 and Cin % 4 == 0: one dword per tap and operand.
-template <int KS, bool HOIST, bool GEN>
+template <int KS, bool GEN>
 __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                    const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
                                                    int32_t* __restrict__ acc_out, float* __restrict__ y_out,
@@ -189,16 +187,6 @@ __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const u
   auto entry = [&](uint32_t a, uint32_t b2) -> uint32_t {  // b2 = 2 * filter code
     return *reinterpret_cast<const uint16_t*>(tabb + (a * (uint32_t)(kDwRow * 4) + b2));
   };
-  uint32_t wb2[HOIST ? KS * KS : 1][4];  // 2 * filter code = byte offset within a table row
-  if constexpr (HOIST) {
-    const uint32_t c4 = (blockIdx.x * 1024u + threadIdx.x) % C4;
-#pragma unroll
-    for (int t = 0; t < KS * KS; ++t) {
-      const uint32_t wd = *reinterpret_cast<const uint32_t*>(w + (size_t)t * g.Cin + 4u * c4);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wb2[t][j] = ((wd >> (8 * j)) & 0xffu) << 1;
-    }
-  }
   for (uint32_t it = blockIdx.x * 1024u + threadIdx.x; it < items; it += gridDim.x * 1024u) {
     const uint32_t c4 = it % C4;
     const uint32_t pix = it / C4;
@@ -216,15 +204,6 @@ __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const u
       for (int j = 0; j < 4; ++j) {
         const uint32_t a = (xs >> (8 * j)) & 0xffu, b = (wd >> (8 * j)) & 0xffu;
         acc[j] += entry(a, b << 1);
-        sp[j] += a;
-      }
-    };
-    auto tap_hoisted = [&](uint32_t xd, int t) {
-      const uint32_t xs = xd ^ flip8;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t a = (xs >> (8 * j)) & 0xffu;
-        acc[j] += entry(a, wb2[HOIST ? t : 0][j]);
         sp[j] += a;
       }
     };
@@ -267,13 +246,11 @@ __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const u
             const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
             xd[ky * KS + kx] = pad4;
             if (inside) xd[ky * KS + kx] = *reinterpret_cast<const uint32_t*>(xn + ((size_t)iy * g.W + ix) * g.Cin);
-            if constexpr (!HOIST) wd[ky * KS + kx] = *reinterpret_cast<const uint32_t*>(wc + (size_t)(ky * KS + kx) * g.Cin);
+            wd[ky * KS + kx] = *reinterpret_cast<const uint32_t*>(wc + (size_t)(ky * KS + kx) * g.Cin);
           }
         }
 #pragma unroll
-        for (int t = 0; t < KS * KS; ++t) {
-          if constexpr (HOIST) tap_hoisted(xd[t], t); else tap(xd[t], wd[t]);
-        }
+        for (int t = 0; t < KS * KS; ++t) tap(xd[t], wd[t]);
       } else {
         for (int ky = 0; ky < KH; ++ky) {
           const int iy = by + ky * g.dh;
@@ -318,20 +295,22 @@ __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const u
   }
 }
 
-// 3 x 3 depthwise layers with multiplier 1 whose channel-group count divides 1024 (every thread
-// keeps its four channels, the filter codes stay pre-shifted in registers) and 16-byte aligned
-// outputs: PX items (pixels) per thread and iteration.  All loads of the PX items are issued
-// before the first lookup, so that a wave has PX times the lookups to cover one memory round trip
-// with (the workgroup fills the compute unit's LDS, so more waves are not to be had).
+// 3 x 3 depthwise layers with multiplier 1 and a channel count divisible by four: every thread keeps
+// its four channels, so the filter codes stay pre-shifted in registers; PX items (pixels) per thread
+// and iteration.  All loads of the PX items are issued before the first lookup, so that a wave has PX
+// times the lookups to cover one memory round trip with (the workgroup fills the compute unit's LDS, so more waves are not to be had).
 // Bound: vector issue, about as much for the addresses of the codes as for the lookups, next to the
 // gathers (5.2 T/s).  So the position of an item is carried on by additions (no divisions) and a tap
 // is one 32-bit offset from a uniform step; a lookup is a byte extract and one multiply-add, which
 // took half-rate sub-dword multiplies before.  The first codes and the filters travel while the
 // table is staged.  112 x 112 x 32 at batch 32: 36.6 -> 31.6 us, both outputs written.
+// Channel-group counts that do not divide 1024, on the general kernel before -> here, batch 32:
+// 56 x 56 x 96 37.8 -> 26.8 us, 14 x 14 x 576 19.6 -> 15.6 us, 56 x 56 x 144 stride 2 19.1 -> 15.9 us.
 template <int PX>
 __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                     const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
-                                                    int32_t* __restrict__ acc_out, float* __restrict__ y_out) {
+                                                    int32_t* __restrict__ acc_out, float* __restrict__ y_out,
+                                                    int vec_out) {
   __shared__ uint32_t tab[256 * kDwRow];
   __shared__ int32_t sfs[kDwMaxC];
   QParams qp = qp_in;
@@ -346,7 +325,10 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
   const uint32_t C4 = (uint32_t)g.Cout / 4u;
   const uint32_t items = (uint32_t)g.M * C4;
   const uint32_t pad4 = ((uint32_t)qp.pad_code & 0xffu) * 0x01010101u;
-  const uint32_t gid = blockIdx.x * 1024u + threadIdx.x, stride = gridDim.x * 1024u;
+  // the grid stride is a multiple of the channel groups; the up to C4 - 1 threads beyond it get no item
+  const uint32_t stride = gridDim.x * 1024u / C4 * C4;
+  const uint32_t tid = blockIdx.x * 1024u + threadIdx.x;
+  const uint32_t gid = tid < stride ? tid : items + tid;
   const uint32_t c4 = gid % C4;  // the same for every item of this thread: stride % C4 == 0
   // Position of the next item to load and the way from one item to the next (the same for all threads).
   uint32_t nx = gid;  // its number
@@ -452,8 +434,16 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
         yv[j] = (float)corr * qp.scale;
       }
       const size_t o = (size_t)it * 4u;  // = pixel * Cout + 4 * c4
-      if (acc_out) *reinterpret_cast<int4*>(acc_out + o) = make_int4(av[0], av[1], av[2], av[3]);
-      if (y_out) *reinterpret_cast<float4*>(y_out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
+      if (vec_out) {  // 16-byte aligned outputs
+        if (acc_out) *reinterpret_cast<int4*>(acc_out + o) = make_int4(av[0], av[1], av[2], av[3]);
+        if (y_out) *reinterpret_cast<float4*>(y_out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (acc_out) acc_out[o + j] = av[j];
+          if (y_out) y_out[o + j] = yv[j];
+        }
+      }
     }
     it0 += PX * stride;
     if (it0 < items) load();
@@ -766,19 +756,14 @@ hipError_t launch_dw(const Geom& g, const QParams& qp, const uint8_t* x, const u
   const int vec_out = (g.Cout % 4 == 0 && (((uintptr_t)acc_out | (uintptr_t)y_out) & 15) == 0) ? 1 : 0;
   // one dword per tap and operand needs multiplier 1, whole groups of four channels and aligned tensors
   const bool fast = g.mult == 1 && g.Cin % 4 == 0 && (((uintptr_t)x | (uintptr_t)w) & 3) == 0;
-  const bool keeps_channels = fast && 1024 % C4 == 0;  // the grid stride is then a multiple of the channel groups
   if (!fast)
-    hipLaunchKernelGGL((dw_kernel<0, false, true>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
-  else if (g.KH == 3 && g.KW == 3 && keeps_channels && vec_out)
-    hipLaunchKernelGGL((dw3_kernel<2>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out);
-  else if (g.KH == 3 && g.KW == 3 && keeps_channels)
-    hipLaunchKernelGGL((dw_kernel<3, true, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
-  else if (g.KH == 3 && g.KW == 3)
-    hipLaunchKernelGGL((dw_kernel<3, false, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
+    hipLaunchKernelGGL((dw_kernel<0, true>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
+  else if (g.KH == 3 && g.KW == 3)  // 4e6 lookups are over 1e5 items: the grid has more threads than channel groups
+    hipLaunchKernelGGL((dw3_kernel<2>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
   else if (g.KH == 5 && g.KW == 5)
-    hipLaunchKernelGGL((dw_kernel<5, false, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
+    hipLaunchKernelGGL((dw_kernel<5, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
   else
-    hipLaunchKernelGGL((dw_kernel<0, false, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
+    hipLaunchKernelGGL((dw_kernel<0, false>), dim3(blocks), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, vec_out);
   return hipGetLastError();
 }
 
