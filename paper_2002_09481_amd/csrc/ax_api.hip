@@ -81,8 +81,8 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // Whether fewpix_kernel takes the layer (automatic choice only: any override of the table-tile
 // kernels keeps the layer on them).  Under 2e6 lookups staging the table (about 6 us) costs more
 // than direct_kernel's table reads (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us; 1 x 2048 x 1000:
-// 11 against 16.5 us).  From 4e6 on it competes with the table tiles: 15 % under their expected
-// time, since both estimates are off by about that much (ResNet-50 layers at batch 1: 14 x 14 and
+// 11 against 16.5 us).  From 4e6 on it competes with the table tiles: a tenth under their expected
+// time, since both estimates are off by that much (ResNet-50 layers at batch 1: 14 x 14 and
 // 7 x 7 layers 21-36 us against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
 static bool fewpix_pays(const Geom& g, const Options& o) {
   if (g.T != 1 || o.variant || o.split_k || o.tile || o.row_tiles || o.share_order || o.combine || o.tables) return false;

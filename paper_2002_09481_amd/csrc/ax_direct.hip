@@ -12,8 +12,7 @@
 
 namespace ax {
 
-//
-// Such problems give few threads, each with a serial chain of dependent loads (code, then entry), so
+// Tiny problems give few threads, each with a serial chain of dependent loads (code, then entry), so
 // their time is that chain and not any bandwidth: S threads of a block share the taps of an output
 // (thread s takes the taps s, s + S, ...) and their sums meet in LDS.  Calls with S = 1 before and S
 // by launch_direct's rule after: 16x16x8 3x3 to 8 channels 18.3 -> 13.6 us, dense 1 x 2048 x 1000
