@@ -449,6 +449,14 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
   }
 }
 
+// One load of a T from an address of any alignment (the unaligned access mode of global loads).
+template <typename T>
+__device__ __forceinline__ T load_any(const void* p) {
+  T v;
+  __builtin_memcpy(&v, p, sizeof(T));
+  return v;
+}
+
 // Layers of few output pixels (the deep layers of a network at batch 1, a fully connected layer at a
 // small batch).  A table tile would spend more on assembling its tables than on the lookups they
 // serve; here every workgroup keeps the whole table in LDS, as the depthwise kernel does, and
@@ -464,12 +472,16 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
 // 3 x 3 113 -> 35 us, 14 x 14 x 256 3 x 3 44 -> 35 us, 14 x 14 x 1024 1 x 1 30 -> 23 us, dense
 // 1 x 2048 x 1000 380 -> 10 us, 8 x 4096 x 4096 175 -> 44 us, 32 x 2048 x 1000 27.7 -> 25.3 us.
 // Seven pixels of four channels (28 sums) are what 128 registers hold with a step's codes in flight.
-// DWORDS: Cin % 4 == 0 and x dword aligned: four consecutive taps are one dword of one pixel.
+// DWORDS: Cin % 4 == 0: four consecutive taps are one dword of one pixel.
+// Operands may start at any byte and tables at any entry, as on the table tiles, whose preparation
+// re-lays them: dwords and staged 16-byte pieces are loaded at their own alignment (load_any).  A form
+// that went byte by byte instead for an x off a dword boundary took 63 us against 40.5 us on the
+// table tiles for 396 x 128 x 2001.
 template <int P, bool DWORDS>
 __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                        const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
                                                        int32_t* __restrict__ acc_out, float* __restrict__ y_out,
-                                                       int cl_log2, int w_dwords, int lut_vec) {
+                                                       int cl_log2, int w_dwords) {
   __shared__ uint32_t tab[256 * kDwRow];
   __shared__ __align__(16) uint32_t accs[P * 256];  // [pixel][channel of the tile]
   __shared__ uint32_t sps[P], sfs[256];
@@ -521,7 +533,7 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
       for (int e = 0; e < 4; ++e) {
         if (w_dwords) {
           const int co = min(co0, J - 4);  // Cout % 4 == 0: a group lies wholly inside or outside
-          wd[e] = *reinterpret_cast<const uint32_t*>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)co));
+          wd[e] = load_any<uint32_t>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)co));
         } else {
           const uint32_t wo = (uint32_t)min(k + e, K - 1) * (uint32_t)J;
           wd[e] = 0;
@@ -537,7 +549,7 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
           const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
           const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
           const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
-          const uint32_t v = *reinterpret_cast<const uint32_t*>(x + (pix * (uint32_t)g.Cin + (uint32_t)ci));
+          const uint32_t v = load_any<uint32_t>(x + (pix * (uint32_t)g.Cin + (uint32_t)ci));
           xd[p] = inside ? v : pad4;
         }
       } else {
@@ -574,22 +586,13 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
       // signed activations index the table by code + 128: rows are staged in that order, entries with
       // 32768 added (both come off again in the epilogue), as in dw_kernel
       const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
-      if (lut_vec) {
-        const uint4* __restrict__ src = reinterpret_cast<const uint4*>(lut);
-        const int rowflip = g.sgn ? (0x80 << 5) : 0;
+      const int rowflip = g.sgn ? (0x80 << 5) : 0;
 #pragma unroll 4
-        for (int i0 = 0; i0 < 8192; i0 += 1024) {
-          const int i = i0 + threadIdx.x;
-          const uint4 v = src[i ^ rowflip];
-          uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
-          dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
-        }
-      } else {  // a table that is only 2-byte aligned
-        const int rowflip = g.sgn ? (0x80 << 7) : 0;
-        for (int i = threadIdx.x; i < 32768; i += 1024) {
-          const uint32_t lo = lut[2 * (i ^ rowflip)], hi = lut[2 * (i ^ rowflip) + 1];
-          tab[(i >> 7) * kDwRow + (i & 127)] = (lo | (hi << 16)) ^ flip16;
-        }
+      for (int i0 = 0; i0 < 8192; i0 += 1024) {
+        const int i = i0 + threadIdx.x;
+        const uint4 v = load_any<uint4>(lut + 8 * (i ^ rowflip));
+        uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
+        dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
       }
       __syncthreads();
     }
@@ -719,14 +722,13 @@ double fewpix_cost(const Geom& g) { return fewpix_plan(g, g.Cin % 4 == 0).cost; 
 
 hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
                          int32_t* acc_out, float* y_out, hipStream_t s) {
-  const bool dwords = g.Cin % 4 == 0 && ((uintptr_t)x & 3) == 0;
-  const int w_dwords = (g.Cout % 4 == 0 && ((uintptr_t)w & 3) == 0) ? 1 : 0;
-  const int lut_vec = ((uintptr_t)lut & 15) == 0 ? 1 : 0;
+  const bool dwords = g.Cin % 4 == 0;
+  const int w_dwords = g.Cout % 4 == 0 ? 1 : 0;
   const FewpixPlan p = fewpix_plan(g, dwords);
   const long long tiles = (long long)((g.M + p.P - 1) / p.P) * ((g.Cout + (4 << p.cl_log2) - 1) / (4 << p.cl_log2));
   const int grid = (int)std::min<long long>(cu_count(), tiles);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2, w_dwords, lut_vec);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2, w_dwords);
   };
   switch (p.P) {
     case 1: if (dwords) go(fewpix_kernel<1, true>); else go(fewpix_kernel<1, false>); break;

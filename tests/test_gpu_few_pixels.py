@@ -77,3 +77,41 @@ def test_unaligned_operands(off):
     torch.cuda.synchronize()
     acc_ref, y_ref = oracle.dense(x.reshape(5, -1), w.reshape(1024, 516), lut, q)
     assert_parity(acc.cpu().numpy(), y.cpu().numpy(), acc_ref, y_ref)
+
+
+def _at(t, off):
+    """A copy of a device tensor that starts `off` elements past an allocation's start."""
+    flat = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+    v = flat[off:off + t.numel()]
+    v.copy_(t.reshape(-1))
+    return v.view(t.shape)
+
+
+@pytest.mark.parametrize("which", ["x", "w", "lut"])
+def test_unaligned_operands_cost_no_other_form(which):
+    """A layer chosen for the few-pixel kernel stays as fast whatever byte its operands start at (the choice
+    knows the geometry only): its results are the oracle's, and a call takes at most 1.35 times the aligned
+    one's time.  Loads that straddle a cache line cost a few percent; a byte-by-byte form took 1.7 times."""
+    layer = _conv(1, 14, 14, 256, 3, 256, 1, 1)
+    x, w, q = I.make_operands(layer, 8)
+    lut = I.lut_random_error(9)
+    xd, wd, ld = to_dev(x), to_dev(w), ax.lut_to_device(lut).view(torch.int16).reshape(-1)
+    moved = {"x": (_at(xd, 1), wd, ld), "w": (xd, _at(wd, 3), ld), "lut": (xd, wd, _at(ld, 1))}[which]
+    acc = torch.empty((1, 14, 14, 256), dtype=torch.int32, device="cuda")
+    y = torch.empty(acc.shape, dtype=torch.float32, device="cuda")
+
+    def us(a, b, t):
+        best = 1e9
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                ax.ax_conv2d(a, b, t, 1, 1, q, acc_out=acc, y_out=y)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 50.0)
+        return best
+
+    aligned, unaligned = us(xd, wd, ld), us(*moved)
+    assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *oracle.conv2d(x, w, lut, 1, 1, q))
+    assert unaligned < 1.35 * aligned, (aligned, unaligned)
