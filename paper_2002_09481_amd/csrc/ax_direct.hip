@@ -473,15 +473,15 @@ __device__ __forceinline__ T load_any(const void* p) {
 // 1 x 2048 x 1000 380 -> 10 us, 8 x 4096 x 4096 175 -> 44 us, 32 x 2048 x 1000 27.7 -> 25.3 us.
 // Seven pixels of four channels (28 sums) are what 128 registers hold with a step's codes in flight.
 // DWORDS: Cin % 4 == 0: four consecutive taps are one dword of one pixel.
-// Operands may start at any byte and tables at any entry, as on the table tiles, whose preparation
-// re-lays them: dwords and staged 16-byte pieces are loaded at their own alignment (load_any).  A form
-// that went byte by byte instead for an x off a dword boundary took 63 us against 40.5 us on the
-// table tiles for 396 x 128 x 2001.
+// Operands may start at any byte and tables at any entry, and Cout need not be a multiple of four: dwords
+// and the staged pieces of the table are loaded at their own alignment (load_any), the last dword of a
+// filter row ends with the row.  Byte by byte instead, x off a dword boundary took 63 us against 40.5 us
+// on the table tiles (396 x 128 x 2001), filter rows of 1001 codes 49.2 us against 32.2 us (8 x 8192).
 template <int P, bool DWORDS>
 __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                        const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
                                                        int32_t* __restrict__ acc_out, float* __restrict__ y_out,
-                                                       int cl_log2, int w_dwords) {
+                                                       int cl_log2) {
   __shared__ uint32_t tab[256 * kDwRow];
   __shared__ __align__(16) uint32_t accs[P * 256];  // [pixel][channel of the tile]
   __shared__ uint32_t sps[P], sfs[256];
@@ -515,7 +515,10 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int pt = tile / nct;
     const int j0 = (tile - pt * nct) * CT, m0 = pt * P;
-    const int co0 = j0 + 4 * cl;
+    // the lane's four channels; where fewer are left the dword ends with the filter row and its surplus
+    // is shifted out (lanes wholly beyond the row get some codes, whose sums are not stored)
+    const int co0 = j0 + 4 * cl, wcol = min(co0, J - 4);
+    const uint32_t wshift = (8u * (uint32_t)(co0 - wcol)) & 31u;
     int by[P], bx[P], nb[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -530,17 +533,8 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
     auto load = [&](int k4, uint32_t (&xd)[P], uint32_t (&wd)[4]) {
       const int k = 4 * k4;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (w_dwords) {
-          const int co = min(co0, J - 4);  // Cout % 4 == 0: a group lies wholly inside or outside
-          wd[e] = load_any<uint32_t>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)co));
-        } else {
-          const uint32_t wo = (uint32_t)min(k + e, K - 1) * (uint32_t)J;
-          wd[e] = 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) wd[e] |= (uint32_t)w[wo + (uint32_t)min(co0 + j, J - 1)] << (8 * j);
-        }
-      }
+      for (int e = 0; e < 4; ++e)
+        wd[e] = load_any<uint32_t>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)wcol)) >> wshift;
       if constexpr (DWORDS) {
         const int tap = k / g.Cin, ci = k - tap * g.Cin;
         const int ky = tap / g.KW, kx = tap - ky * g.KW;
@@ -723,12 +717,11 @@ double fewpix_cost(const Geom& g) { return fewpix_plan(g, g.Cin % 4 == 0).cost; 
 hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
                          int32_t* acc_out, float* y_out, hipStream_t s) {
   const bool dwords = g.Cin % 4 == 0;
-  const int w_dwords = g.Cout % 4 == 0 ? 1 : 0;
   const FewpixPlan p = fewpix_plan(g, dwords);
   const long long tiles = (long long)((g.M + p.P - 1) / p.P) * ((g.Cout + (4 << p.cl_log2) - 1) / (4 << p.cl_log2));
   const int grid = (int)std::min<long long>(cu_count(), tiles);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2, w_dwords);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2);
   };
   switch (p.P) {
     case 1: if (dwords) go(fewpix_kernel<1, true>); else go(fewpix_kernel<1, false>); break;

@@ -87,6 +87,20 @@ def _at(t, off):
     return v.view(t.shape)
 
 
+def _us(call):
+    """Microseconds of a call among others (the smallest of eight means of 20)."""
+    best = 1e9
+    for _ in range(8):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(20):
+            call()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1) * 50.0)
+    return best
+
+
 @pytest.mark.parametrize("which", ["x", "w", "lut"])
 def test_unaligned_operands_cost_no_other_form(which):
     """A layer chosen for the few-pixel kernel stays as fast whatever byte its operands start at (the choice
@@ -101,17 +115,36 @@ def test_unaligned_operands_cost_no_other_form(which):
     y = torch.empty(acc.shape, dtype=torch.float32, device="cuda")
 
     def us(a, b, t):
-        best = 1e9
-        for _ in range(8):
-            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            e0.record()
-            for _ in range(20):
-                ax.ax_conv2d(a, b, t, 1, 1, q, acc_out=acc, y_out=y)
-            e1.record()
-            torch.cuda.synchronize()
-            best = min(best, e0.elapsed_time(e1) * 50.0)
-        return best
+        return _us(lambda: ax.ax_conv2d(a, b, t, 1, 1, q, acc_out=acc, y_out=y))
 
     aligned, unaligned = us(xd, wd, ld), us(*moved)
     assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *oracle.conv2d(x, w, lut, 1, 1, q))
     assert unaligned < 1.35 * aligned, (aligned, unaligned)
+
+
+@pytest.mark.parametrize("M, K, N", [(8, 8192, 1001), (1, 32768, 497), (48, 13600, 39), (9, 3096, 709)])
+def test_odd_channel_counts_cost_no_other_form(M, K, N):
+    """A channel count that is no multiple of four costs what the next multiple costs: filters are read by the
+    dword either way (byte by byte the first two took 1.5 and 2.1 times as long)."""
+    layer = _dense(M, K, N)
+    x, w, q = I.make_operands(layer, 10)
+    lut = I.lut_random_error(11)
+    xd, ld = to_dev(x).view(M, K), ax.lut_to_device(lut)
+    wide = -(-N // 4) * 4
+    wd = to_dev(w).view(K, N)
+    w4 = torch.zeros((K, wide), dtype=torch.uint8, device="cuda")
+    w4[:, :N] = wd
+
+    def prepared(wt, n):
+        h = ax.AxLayer(ax._dense_desc(M, K, n), q)
+        assert h.plan()["variant"] == 1
+        h.prepare(wt, ld)
+        acc, y = h.run(xd)
+        return h, acc, y
+
+    h, acc, y = prepared(wd, N)
+    h4, acc4, y4 = prepared(w4, wide)
+    odd, even = _us(lambda: h.run(xd, acc, y)), _us(lambda: h4.run(xd, acc4, y4))
+    acc_ref, y_ref = oracle.dense(x.reshape(M, K), w.reshape(K, N), lut, q)
+    assert_parity(acc.cpu().numpy(), y.cpu().numpy(), acc_ref, y_ref)
+    assert odd < 1.25 * even, (odd, even)
