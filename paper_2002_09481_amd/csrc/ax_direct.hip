@@ -508,18 +508,20 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
   if (threadIdx.x < P) sps[threadIdx.x] = 0;
   const char* tabb = reinterpret_cast<const char*>(tab);
   const uint32_t rowbytes = (uint32_t)(kDwRow * 4);
-  bool staged = false;
 
+  int j0, m0, wcol, by[P], bx[P], nb[P];
+  uint32_t wshift;
   // Channel tiles go fastest: workgroup b runs on XCD b mod 8, so where their number is a multiple of
   // eight each XCD's L2 fetches one eighth of the filters.
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  auto locate = [&](int tile) {
     const int pt = tile / nct;
-    const int j0 = (tile - pt * nct) * CT, m0 = pt * P;
+    j0 = (tile - pt * nct) * CT;
+    m0 = pt * P;
     // the lane's four channels; where fewer are left the dword ends with the filter row and its surplus
     // is shifted out (lanes wholly beyond the row get some codes, whose sums are not stored)
-    const int co0 = j0 + 4 * cl, wcol = min(co0, J - 4);
-    const uint32_t wshift = (8u * (uint32_t)(co0 - wcol)) & 31u;
-    int by[P], bx[P], nb[P];
+    const int co0 = j0 + 4 * cl;
+    wcol = min(co0, J - 4);
+    wshift = (8u * (uint32_t)(co0 - wcol)) & 31u;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int m = min(m0 + p, M - 1);
@@ -529,43 +531,70 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
       bx[p] = (r - oy * g.OW) * g.sw - g.pw;
       nb[p] = n * g.H;
     }
-    // offsets into x and w are below 2^31
-    auto load = [&](int k4, uint32_t (&xd)[P], uint32_t (&wd)[4]) {
-      const int k = 4 * k4;
+  };
+  // offsets into x and w are below 2^31
+  auto load = [&](int k4, uint32_t (&xd)[P], uint32_t (&wd)[4]) {
+    const int k = 4 * k4;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        wd[e] = load_any<uint32_t>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)wcol)) >> wshift;
-      if constexpr (DWORDS) {
-        const int tap = k / g.Cin, ci = k - tap * g.Cin;
+    for (int e = 0; e < 4; ++e)
+      wd[e] = load_any<uint32_t>(w + ((uint32_t)min(k + e, K - 1) * (uint32_t)J + (uint32_t)wcol)) >> (DWORDS ? 0 : wshift);
+    if constexpr (DWORDS) {
+      const int tap = k / g.Cin, ci = k - tap * g.Cin;
+      const int ky = tap / g.KW, kx = tap - ky * g.KW;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
+        const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+        const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
+        const uint32_t v = load_any<uint32_t>(x + (pix * (uint32_t)g.Cin + (uint32_t)ci));
+        xd[p] = inside ? v : pad4;
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < P; ++p) xd[p] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ke = min(k + e, K - 1);
+        const int tap = ke / g.Cin, ci = ke - tap * g.Cin;
         const int ky = tap / g.KW, kx = tap - ky * g.KW;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
           const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
           const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
           const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
-          const uint32_t v = load_any<uint32_t>(x + (pix * (uint32_t)g.Cin + (uint32_t)ci));
-          xd[p] = inside ? v : pad4;
-        }
-      } else {
-#pragma unroll
-        for (int p = 0; p < P; ++p) xd[p] = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ke = min(k + e, K - 1);
-          const int tap = ke / g.Cin, ci = ke - tap * g.Cin;
-          const int ky = tap / g.KW, kx = tap - ky * g.KW;
-#pragma unroll
-          for (int p = 0; p < P; ++p) {
-            const int iy = by[p] + ky * g.dh, ix = bx[p] + kx * g.dw;
-            const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
-            const uint32_t pix = inside ? (uint32_t)(nb[p] + iy) * (uint32_t)g.W + (uint32_t)ix : 0u;
-            const uint32_t v = x[pix * (uint32_t)g.Cin + (uint32_t)ci];
-            xd[p] |= (inside ? v : (pad4 & 0xffu)) << (8 * e);
-          }
+          const uint32_t v = x[pix * (uint32_t)g.Cin + (uint32_t)ci];
+          xd[p] |= (inside ? v : (pad4 & 0xffu)) << (8 * e);
         }
       }
-    };
-
+    }
+  };
+  uint32_t xd[P], wd[4];
+  int tile = blockIdx.x;  // the grid has no more workgroups than there are tiles
+  // the first codes travel while the table is staged (the byte form, which assembles its dwords at once,
+  // would wait for them)
+  if constexpr (DWORDS) {
+    locate(tile);
+    if (slice < K4) load(slice, xd, wd);
+  }
+  {
+    // signed activations index the table by code + 128: rows are staged in that order, entries with
+    // 32768 added (both come off again in the epilogue), as in dw_kernel
+    const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
+    const int rowflip = g.sgn ? (0x80 << 5) : 0;
+#pragma unroll 4
+    for (int i0 = 0; i0 < 8192; i0 += 1024) {
+      const int i = i0 + threadIdx.x;
+      const uint4 v = load_any<uint4>(lut + 8 * (i ^ rowflip));
+      uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
+      dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
+    }
+    __syncthreads();
+  }
+  for (;;) {
+    if constexpr (!DWORDS) {
+      locate(tile);
+      if (slice < K4) load(slice, xd, wd);
+    }
     uint32_t acc[P][4], sp[P], sf[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -573,29 +602,12 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[p][j] = 0;
     }
-    uint32_t xd[P], wd[4];
-    if (slice < K4) load(slice, xd, wd);  // the first codes travel while the table is staged
-    if (!staged) {
-      staged = true;
-      // signed activations index the table by code + 128: rows are staged in that order, entries with
-      // 32768 added (both come off again in the epilogue), as in dw_kernel
-      const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
-      const int rowflip = g.sgn ? (0x80 << 5) : 0;
-#pragma unroll 4
-      for (int i0 = 0; i0 < 8192; i0 += 1024) {
-        const int i = i0 + threadIdx.x;
-        const uint4 v = load_any<uint4>(lut + 8 * (i ^ rowflip));
-        uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
-        dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
-      }
-      __syncthreads();
-    }
     for (int k4 = slice; k4 < K4; k4 += slices) {
       uint32_t xs[P], ws[4];
 #pragma unroll
       for (int p = 0; p < P; ++p) xs[p] = xd[p] ^ flip8;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ws[e] = wd[e];
+      for (int e = 0; e < 4; ++e) ws[e] = wd[e] >> (DWORDS ? wshift : 0);  // the byte form waits for its codes anyway
       if (k4 + slices < K4) load(k4 + slices, xd, wd);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -622,6 +634,14 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
         // one tap's gathers in flight at a time: more of them would not fit the registers
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    // the next tile's first codes travel while this one's sums meet (3 % of a call of several rounds)
+    const int mt = m0, jt = j0;
+    tile += (int)gridDim.x;
+    const bool more = tile < ntiles;  // uniform
+    if (DWORDS && more) {
+      locate(tile);
+      if (slice < K4) load(slice, xd, wd);
     }
     // Sums over the slices that lie side by side in the wave, within rows of 16 lanes: afterwards every
     // lane of a group of 1 << dpp_log2 holds them.  After the first steps the lanes of a quad (of
@@ -662,9 +682,9 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
     const long long kzz = (long long)K * qp.x_zp * qp.w_zp;
     for (int i = threadIdx.x; i < P * CT; i += 1024) {
       const int p = i >> (cl_log2 + 2), c = i & (CT - 1);
-      if (m0 + p < M && j0 + c < J) {
+      if (mt + p < M && jt + c < J) {
         const int32_t av = (int32_t)(accs[p * 256 + c] - bias);
-        const size_t o = (size_t)(m0 + p) * J + j0 + c;
+        const size_t o = (size_t)(mt + p) * J + jt + c;
         if (acc_out) acc_out[o] = av;
         if (y_out) {
           const long long corr = (long long)av - (long long)qp.w_zp * ((int32_t)sps[p] - off128) -
@@ -673,13 +693,12 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
         }
       }
     }
+    if (!more) break;
     __syncthreads();
-    if (tile + (int)gridDim.x < ntiles) {  // uniform
-      for (int i = threadIdx.x; i < P * CT; i += 1024) accs[(i >> (cl_log2 + 2)) * 256 + (i & (CT - 1))] = 0;
-      if (threadIdx.x < 256) sfs[threadIdx.x] = 0;
-      if (threadIdx.x < P) sps[threadIdx.x] = 0;
-      __syncthreads();
-    }
+    for (int i = threadIdx.x; i < P * CT; i += 1024) accs[(i >> (cl_log2 + 2)) * 256 + (i & (CT - 1))] = 0;
+    if (threadIdx.x < 256) sfs[threadIdx.x] = 0;
+    if (threadIdx.x < P) sps[threadIdx.x] = 0;
+    __syncthreads();
   }
 }
 
