@@ -581,10 +581,14 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
     // 32768 added (both come off again in the epilogue), as in dw_kernel
     const uint32_t flip16 = g.sgn ? 0x80008000u : 0u;
     const int rowflip = g.sgn ? (0x80 << 5) : 0;
-#pragma unroll 4
-    for (int i0 = 0; i0 < 8192; i0 += 1024) {
-      const int i = i0 + threadIdx.x;
-      const uint4 v = load_any<uint4>(lut + 8 * (i ^ rowflip));
+    uint4 piece[8];  // all in flight together
+#pragma unroll
+    for (int n = 0; n < 8; ++n) piece[n] = load_any<uint4>(lut + 8 * ((n * 1024 + (int)threadIdx.x) ^ rowflip));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int i = n * 1024 + threadIdx.x;
+      const uint4 v = piece[n];
       uint32_t* dst = tab + (i >> 5) * kDwRow + (i & 31) * 4;
       dst[0] = v.x ^ flip16; dst[1] = v.y ^ flip16; dst[2] = v.z ^ flip16; dst[3] = v.w ^ flip16;
     }
