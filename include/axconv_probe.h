@@ -58,6 +58,20 @@ int ax_probe_layer_kernel_ms(const ax_layer_t* layer, const void* x, int32_t* ac
                              float* y_out, void* workspace, size_t workspace_bytes, int reps,
                              float* ms, void* hip_stream);
 
+/*
+ * Which kernel a layer handle's calls run and how it cuts the layer (host arithmetic only, nothing is
+ * launched): finer than ax_layer_plan, which gives variant 1 for every kernel that prepares nothing.
+ *   kernel      0 = table tiles (see ax_layer_plan), 1 = direct kernel, 2 = few output pixels (whole
+ *               table in LDS, tiles of pixels x channels), 3 = depthwise (whole table in LDS; a table
+ *               that is not 16-byte aligned takes the direct kernel instead)
+ *   pixels, channels, tiles   of a few-pixel layer (0 otherwise)
+ *   workgroups  of kernels 2 and 3 (0 otherwise); the tiles of kernel 2 are dealt out to them in turn
+ *   threads     per output of the direct kernel (0 otherwise)
+ * Any output pointer may be NULL.
+ */
+int ax_probe_layer_route(const ax_layer_t* layer, int* kernel, int* pixels, int* channels, int* tiles,
+                         int* workgroups, int* threads);
+
 #ifdef __cplusplus
 }
 #endif

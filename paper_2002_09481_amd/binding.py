@@ -52,6 +52,7 @@ EXPORTS = [  # include/axconv.h
 ]
 PROBE_EXPORTS = [  # include/axconv_probe.h
     "ax_probe_lds_gather", "ax_probe_copy", "ax_probe_mac", "ax_probe_layer_kernel_ms",
+    "ax_probe_layer_route",
 ]
 
 
@@ -125,6 +126,8 @@ def lib():
     L.ax_conv2d_backward_workspace_bytes.restype = sz
     L.ax_probe_layer_kernel_ms.argtypes = [vp, vp, vp, vp, vp, sz, ci, ctypes.POINTER(ctypes.c_float), vp]
     L.ax_probe_layer_kernel_ms.restype = ci
+    L.ax_probe_layer_route.argtypes = [vp] + [ip] * 6
+    L.ax_probe_layer_route.restype = ci
     L.ax_probe_copy.argtypes = [vp, vp, sz, vp]
     L.ax_probe_copy.restype = ci
     L.ax_conv2d_multi_lut.argtypes = [vp, ci, ci, ci, ci, vp, ci, ci, ci, vp, ci, ci, ci, ci, ci,
@@ -563,6 +566,15 @@ class AxLayer:
         _check(lib().ax_layer_plan_paths(self._h, *[ctypes.byref(o) for o in paths]))
         return {"variant": out[0].value, "tile": out[1].value, "workgroups": out[2].value, "pieces": out[3].value,
                 "combine": paths[0].value, "tables": paths[1].value}
+
+    def route(self) -> dict:
+        """ax_probe_layer_route: which kernel the calls run ("tiles", "direct", "fewpix", "depthwise") and how
+        it cuts the layer."""
+        out = [ctypes.c_int(0) for _ in range(6)]
+        _check(lib().ax_probe_layer_route(self._h, *[ctypes.byref(o) for o in out]))
+        k, pixels, channels, tiles, workgroups, threads = [o.value for o in out]
+        return {"kernel": ("tiles", "direct", "fewpix", "depthwise")[k], "pixels": pixels, "channels": channels,
+                "tiles": tiles, "workgroups": workgroups, "threads": threads}
 
     def prepare(self, w, luts, prepared=None, stream=None):
         cdt = torch.int8 if self.desc.signed_codes else torch.uint8

@@ -78,44 +78,42 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
                    d->dilation_h, d->dilation_w, d->signed_codes, d->depthwise, d->groups > 1 ? d->groups : 1);
 }
 
-// Whether fewpix_kernel takes the layer (automatic choice only: any override of the table-tile
-// kernels keeps the layer on them).  Under 2e6 lookups staging the table (about 6 us) costs more
-// than direct_kernel's table reads (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us; 1 x 2048 x 1000:
-// 11 against 16.5 us).  From 4e6 on it competes with the table tiles: a tenth under their expected
-// time, since both estimates are off by that much (ResNet-50 layers at batch 1: 14 x 14 and
-// 7 x 7 layers 21-36 us against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
-static bool fewpix_pays(const Geom& g, const Options& o) {
-  if (g.T != 1 || o.variant || o.split_k || o.tile || o.row_tiles || o.share_order || o.combine || o.tables) return false;
+// A layer goes to fewpix_kernel in the automatic choice only: any override of the table-tile kernels
+// keeps it on them.  Under 2e6 lookups staging the table (about 6 us) costs more than direct_kernel's
+// table reads (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us; 1 x 2048 x 1000: 11 against 16.5 us).
+// From 4e6 on it competes with the table tiles: a tenth under their expected time, since both
+// estimates are off by that much (ResNet-50 layers at batch 1: 14 x 14 and 7 x 7 layers 21-36 us
+// against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
+// Tiny problems (under 4e6 lookups) do not amortize the set-up of the table tiles, and these do not
+// take depthwise layers (no shared table-side operand): both leave neither family set.
+Route choose_route(const Geom& g, const Options& o) {
+  Route r{};
+  const bool automatic =
+      !(o.variant || o.split_k || o.tile || o.row_tiles || o.share_order || o.combine || o.tables) && g.T == 1;
   const double n = (double)g.M * g.K * g.Cout;
-  if (n < 2.0e6 || !fewpix_shape(g)) return false;
-  if (n < 4.0e6 || !tab_supported(g)) return fewpix_cost(g) < 5e-6 + 5.5e-12 * n;
-  return 1.1 * fewpix_cost(g) < tab_plan(g, o).cost;
-}
-
-// 1 = direct (or depthwise) kernels, 0 = table-tile kernels with the planner's lane assignment,
-// 2 / 3 = table-tile kernels with that lane assignment
-static int choose_variant(const Geom& g, const Options& o) {
-  if (o.variant == 1) return 1;
-  if (!tab_supported(g)) return 1;  // incl. depthwise layers: no shared table-side operand
-  if (o.variant == 2 || o.variant == 3) return o.variant;
-  // Tiny problems do not amortize the table set-up.
-  if ((double)g.M * g.K * g.Cout < 4.0e6) return 1;
-  return fewpix_pays(g, o) ? 1 : 0;  // few output pixels: whole table in LDS instead of table tiles
+  const bool tiny = n < 4.0e6 && o.variant != 2 && o.variant != 3;
+  r.tab = o.variant != 1 && !tiny && tab_supported(g);
+  if (r.tab) r.p = tab_plan(g, o);
+  if (automatic && n >= 2.0e6 && fewpix_shape(g)) {
+    r.fp = fewpix_plan(g);
+    r.few = r.tab ? 1.1 * r.fp.cost < r.p.cost : r.fp.cost < 5e-6 + 5.5e-12 * n;
+    if (r.few) r.tab = false;
+  }
+  return r;
 }
 
 // Kernels that take one table at a time and need neither preparation nor scratch.
-static int run_untiled(const Geom& g, const QParams& qp, const Options& o, const uint8_t* x, const uint8_t* w,
-                       const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s) {
+static int run_untiled(const Geom& g, const QParams& qp, const Options& o, const Route& r, const uint8_t* x,
+                       const uint8_t* w, const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s) {
   const bool dw = g.mult && o.variant != 1 && dw_supported(g, x, w, lut);
-  const bool few = !g.mult && fewpix_pays(g, o);
   const size_t per_table = (size_t)g.M * g.Cout;
   for (int t = 0; t < g.T; ++t) {
     const uint16_t* lt = lut + (size_t)t * 65536;
     int32_t* at = acc_out ? acc_out + t * per_table : nullptr;
     float* yt = y_out ? y_out + t * per_table : nullptr;
-    const hipError_t e = dw     ? launch_dw(g, qp, x, w, lt, at, yt, s)
-                         : few  ? launch_fewpix(g, qp, x, w, lt, at, yt, s)
-                                : launch_direct(g, qp, x, w, lt, at, yt, s);
+    const hipError_t e = dw      ? launch_dw(g, qp, x, w, lt, at, yt, s)
+                         : r.few ? launch_fewpix(g, r.fp, qp, x, w, lt, at, yt, s)
+                                 : launch_direct(g, qp, x, w, lt, at, yt, s);
     if (e != hipSuccess) return AX_ERR_HIP;
   }
   return AX_OK;
@@ -123,14 +121,11 @@ static int run_untiled(const Geom& g, const QParams& qp, const Options& o, const
 
 int run_layer(const Geom& g, const QParams& qp, const Options& o, const uint8_t* x, const uint8_t* w,
               const uint16_t* lut, int32_t* acc_out, float* y_out, void* ws, size_t ws_bytes, hipStream_t s) {
-  const int v = choose_variant(g, o);
-  if (v == 1) return run_untiled(g, qp, o, x, w, lut, acc_out, y_out, s);
-  Options ov = o;
-  ov.variant = v;
-  const TabPlan p = tab_plan(g, ov);
-  if (!ws || ws_bytes < p.prep_total + p.ws_total || ((uintptr_t)ws & 255)) return AX_ERR_WORKSPACE;
+  const Route r = choose_route(g, o);
+  if (!r.tab) return run_untiled(g, qp, o, r, x, w, lut, acc_out, y_out, s);
+  if (!ws || ws_bytes < r.p.prep_total + r.p.ws_total || ((uintptr_t)ws & 255)) return AX_ERR_WORKSPACE;
   uint8_t* wsb = static_cast<uint8_t*>(ws);
-  const hipError_t e = launch_tab(g, qp, p, x, w, lut, acc_out, y_out, wsb, wsb + p.prep_total, kPhAll, 1, s);
+  const hipError_t e = launch_tab(g, qp, r.p, x, w, lut, acc_out, y_out, wsb, wsb + r.p.prep_total, kPhAll, 1, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 
@@ -154,12 +149,8 @@ static int run(const Geom& g, const ax_quant_t* q, const ax_tune_t* tune, const 
 }
 
 size_t layer_workspace(const Geom& g, const Options& o) {
-  const int v = choose_variant(g, o);
-  if (v == 1) return 256;
-  Options ov = o;
-  ov.variant = v;
-  const TabPlan p = tab_plan(g, ov);
-  return p.prep_total + p.ws_total;
+  const Route r = choose_route(g, o);
+  return r.tab ? r.p.prep_total + r.p.ws_total : 256;
 }
 
 static size_t workspace_of(const Geom& g, const ax_tune_t* tune) {
@@ -264,15 +255,7 @@ extern "C" int ax_layer_create(const ax_conv_desc_t* desc, int num_luts, const a
   L->g = g;
   L->qp = qp;
   L->o = o;
-  const int v = choose_variant(g, o);
-  L->tab = v != 1;
-  if (L->tab) {
-    Options ov = o;
-    ov.variant = v;
-    L->p = tab_plan(g, ov);
-  } else {
-    L->p = TabPlan{};
-  }
+  L->r = choose_route(g, o);
   L->w = nullptr;
   L->lut = nullptr;
   L->prepared = nullptr;
@@ -284,11 +267,11 @@ extern "C" int ax_layer_create(const ax_conv_desc_t* desc, int num_luts, const a
 extern "C" void ax_layer_destroy(ax_layer_t* layer) { delete layer; }
 
 extern "C" size_t ax_layer_prepared_bytes(const ax_layer_t* layer) {
-  return layer && layer->tab ? layer->p.prep_total : 0;
+  return layer && layer->r.tab ? layer->r.p.prep_total : 0;
 }
 
 extern "C" size_t ax_layer_workspace_bytes(const ax_layer_t* layer) {
-  return layer && layer->tab ? layer->p.ws_total : 0;
+  return layer && layer->r.tab ? layer->r.p.ws_total : 0;
 }
 
 extern "C" int ax_layer_prepare(ax_layer_t* layer, const void* w, const void* luts, void* prepared,
@@ -296,9 +279,9 @@ extern "C" int ax_layer_prepare(ax_layer_t* layer, const void* w, const void* lu
   if (!layer || !w || !luts) return AX_ERR_NULL;
   if ((uintptr_t)luts & 1) return AX_ERR_ALIGN;
   layer->ready = false;
-  if (layer->tab) {
-    if (!prepared || prepared_bytes < layer->p.prep_total || ((uintptr_t)prepared & 255)) return AX_ERR_WORKSPACE;
-    const hipError_t e = launch_tab(layer->g, layer->qp, layer->p, nullptr, static_cast<const uint8_t*>(w),
+  if (layer->r.tab) {
+    if (!prepared || prepared_bytes < layer->r.p.prep_total || ((uintptr_t)prepared & 255)) return AX_ERR_WORKSPACE;
+    const hipError_t e = launch_tab(layer->g, layer->qp, layer->r.p, nullptr, static_cast<const uint8_t*>(w),
                                     static_cast<const uint16_t*>(luts), nullptr, nullptr, prepared, nullptr, kPhConst,
                                     1, (hipStream_t)hip_stream);
     if (e != hipSuccess) return AX_ERR_HIP;
@@ -312,8 +295,8 @@ extern "C" int ax_layer_prepare(ax_layer_t* layer, const void* w, const void* lu
 
 namespace ax {
 size_t scratch_need(const ax_layer* layer, const void* x) {
-  if (!layer || !layer->tab) return 0;
-  const TabPlan& p = layer->p;
+  if (!layer || !layer->r.tab) return 0;
+  const TabPlan& p = layer->r.p;
   // unsigned activations read in place leave the last part of the scratch unused
   const bool unused = p.variant == 2 && !layer->g.sgn && reads_in_place(layer->g, x);
   return p.ws_total - (unused ? p.ws_apack : 0);
@@ -327,15 +310,15 @@ int run_prepared(const ax_layer* layer, const void* x, int32_t* acc_out, float* 
   int rc = check_io(x, layer->w, layer->lut, acc_out, y_out);
   if (rc) return rc;
   const uint8_t* xb = static_cast<const uint8_t*>(x);
-  if (!layer->tab) {
+  if (!layer->r.tab) {
     if (!(phases & kPhMain)) return AX_OK;
     for (int r = 0; r < main_reps; ++r) {
-      rc = run_untiled(layer->g, layer->qp, layer->o, xb, layer->w, layer->lut, acc_out, y_out, s);
+      rc = run_untiled(layer->g, layer->qp, layer->o, layer->r, xb, layer->w, layer->lut, acc_out, y_out, s);
       if (rc) return rc;
     }
     return AX_OK;
   }
-  const TabPlan& p = layer->p;
+  const TabPlan& p = layer->r.p;
   const size_t need = scratch_need(layer, x);
   if (need && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return AX_ERR_WORKSPACE;
   const hipError_t e = launch_tab(layer->g, layer->qp, p, xb, layer->w, layer->lut, acc_out, y_out, layer->prepared,
@@ -352,17 +335,17 @@ extern "C" int ax_layer_run(const ax_layer_t* layer, const void* x, int32_t* acc
 
 extern "C" int ax_layer_plan(const ax_layer_t* layer, int* variant, int* tile, int* workgroups, int* pieces) {
   if (!layer) return AX_ERR_NULL;
-  if (variant) *variant = layer->tab ? layer->p.variant : 1;
-  if (tile) *tile = layer->tab ? layer->p.tile + 1 : 0;
-  if (workgroups) *workgroups = layer->tab ? layer->p.G : 0;
-  if (pieces) *pieces = layer->tab ? layer->p.partials : 0;
+  if (variant) *variant = layer->r.tab ? layer->r.p.variant : 1;
+  if (tile) *tile = layer->r.tab ? layer->r.p.tile + 1 : 0;
+  if (workgroups) *workgroups = layer->r.tab ? layer->r.p.G : 0;
+  if (pieces) *pieces = layer->r.tab ? layer->r.p.partials : 0;
   return AX_OK;
 }
 
 extern "C" int ax_layer_plan_paths(const ax_layer_t* layer, int* combine, int* tables) {
   if (!layer) return AX_ERR_NULL;
-  if (combine) *combine = (layer->tab && layer->p.partials > 0) ? (layer->p.combine ? 2 : 1) : 0;
-  if (tables) *tables = layer->tab ? (layer->p.pre ? 2 : 1) : 0;
+  if (combine) *combine = (layer->r.tab && layer->r.p.partials > 0) ? (layer->r.p.combine ? 2 : 1) : 0;
+  if (tables) *tables = layer->r.tab ? (layer->r.p.pre ? 2 : 1) : 0;
   return AX_OK;
 }
 

@@ -706,13 +706,11 @@ __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, con
   }
 }
 
-// Tile shape of fewpix_kernel and the time it is expected to take.
-struct FewpixPlan { int P, cl_log2; double cost; };
-
-static FewpixPlan fewpix_plan(const Geom& g, bool dwords) {
+FewpixPlan fewpix_plan(const Geom& g) {
+  const bool dwords = g.Cin % 4 == 0;
   static const int kPixels[] = {1, 2, 4, 7, 8};  // 7: images of 7 x 7, 14 x 14, 28 x 28 ... pixels
   const int K4 = (g.K + 3) / 4, cus = cu_count();
-  FewpixPlan best{1, 0, 1e30};
+  FewpixPlan best{1, 0, 0, 1e30};
   for (int P : kPixels) {
     if (!dwords && P > 4) break;  // the byte form of the kernel has no registers for more
     for (int c = 0; c <= 6; ++c) {
@@ -725,7 +723,7 @@ static FewpixPlan fewpix_plan(const Geom& g, bool dwords) {
       // the ResNet-50 layers at batch 1 to 8.
       const double t_iter = 16.0 * (16.0 * P * 6.2 + (dwords ? 100.0 : 550.0) + 8.0 * (64 >> c)) / 2.4e9;
       const double t = 6e-6 + std::ceil(tiles / cus) * (iters * t_iter + 2.5e-6 + P * (4 << c) * 1e-9);
-      if (t < best.cost) best = FewpixPlan{P, c, t};
+      if (t < best.cost) best = FewpixPlan{P, c, (long long)tiles, t};
     }
   }
   return best;
@@ -735,14 +733,10 @@ bool fewpix_shape(const Geom& g) {
   return g.mult == 0 && g.groups == 1 && g.Cout >= 4 && g.K >= 64 && g.K <= 32768;
 }
 
-double fewpix_cost(const Geom& g) { return fewpix_plan(g, g.Cin % 4 == 0).cost; }
-
-hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
-                         int32_t* acc_out, float* y_out, hipStream_t s) {
+hipError_t launch_fewpix(const Geom& g, const FewpixPlan& p, const QParams& qp, const uint8_t* x, const uint8_t* w,
+                         const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s) {
   const bool dwords = g.Cin % 4 == 0;
-  const FewpixPlan p = fewpix_plan(g, dwords);
-  const long long tiles = (long long)((g.M + p.P - 1) / p.P) * ((g.Cout + (4 << p.cl_log2) - 1) / (4 << p.cl_log2));
-  const int grid = (int)std::min<long long>(cu_count(), tiles);
+  const int grid = (int)std::min<long long>(cu_count(), p.tiles);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(1024), 0, s, g, qp, x, w, lut, acc_out, y_out, p.cl_log2);
   };
@@ -765,11 +759,14 @@ bool dw_supported(const Geom& g, const uint8_t* x, const uint8_t* w, const uint1
   return (double)g.M * g.Cout * g.K >= 4.0e6;
 }
 
+int dw_workgroups(const Geom& g) {
+  const uint64_t items = (uint64_t)g.M * (((uint32_t)g.Cout + 3u) / 4u);
+  return (int)std::min<uint64_t>((uint64_t)cu_count(), (items + 1023) / 1024);
+}
+
 hipError_t launch_dw(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
                      int32_t* acc_out, float* y_out, hipStream_t s) {
-  const uint32_t C4 = ((uint32_t)g.Cout + 3u) / 4u;
-  const uint64_t items = (uint64_t)g.M * C4;
-  const uint32_t blocks = (uint32_t)std::min<uint64_t>((uint64_t)cu_count(), (items + 1023) / 1024);
+  const uint32_t blocks = (uint32_t)dw_workgroups(g);
   const int vec_out = (g.Cout % 4 == 0 && (((uintptr_t)acc_out | (uintptr_t)y_out) & 15) == 0) ? 1 : 0;
   // one dword per tap and operand needs multiplier 1, whole groups of four channels and aligned tensors
   const bool fast = g.mult == 1 && g.Cin % 4 == 0 && (((uintptr_t)x | (uintptr_t)w) & 3) == 0;
@@ -784,12 +781,17 @@ hipError_t launch_dw(const Geom& g, const QParams& qp, const uint8_t* x, const u
   return hipGetLastError();
 }
 
+int direct_threads(const Geom& g) {
+  // enough for one wave on every SIMD, at least four taps each
+  int S = 1;
+  while (S < 64 && (uint64_t)g.M * g.Cout * S < (uint64_t)cu_count() * 256 && g.K >= 16 * S) S *= 4;
+  return S;
+}
+
 hipError_t launch_direct(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w,
                          const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s) {
   const uint64_t total = (uint64_t)g.M * g.Cout;
-  // threads per output: enough for one wave on every SIMD, at least four taps each
-  int S = 1;
-  while (S < 64 && total * S < (uint64_t)cu_count() * 256 && g.K >= 16 * S) S *= 4;
+  const int S = direct_threads(g);
   const uint32_t blocks = (uint32_t)((total * S + 255) / 256);
   switch (S) {
     case 1: hipLaunchKernelGGL((direct_kernel<1>), dim3(blocks), dim3(256), 0, s, g, qp, x, w, lut, acc_out, y_out); break;

@@ -78,22 +78,30 @@ int make_geom(int N, int H, int W, int Cin, int KH, int KW, int Cout, int sh, in
               int dh = 1, int dw = 1, int sgn = 0, int depthwise = 0, int groups = 1);
 int geom_of_desc(const ax_conv_desc_t* d, Geom* g);
 
-// Direct kernel (ax_direct.hip): needs no workspace.
+// Direct kernel (ax_direct.hip): needs no workspace.  direct_threads: threads per output.
+int direct_threads(const Geom& g);
 hipError_t launch_direct(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w,
                          const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s);
 
 // Depthwise kernel with the whole table in LDS (ax_direct.hip); dw_supported tells whether the
 // layer and its pointers fit it.
+int dw_workgroups(const Geom& g);
 bool dw_supported(const Geom& g, const uint8_t* x, const uint8_t* w, const uint16_t* lut);
 hipError_t launch_dw(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
                      int32_t* acc_out, float* y_out, hipStream_t s);
 
 // Layers of few output pixels with the whole table in LDS (ax_direct.hip): fewpix_shape says whether
-// the kernel takes the geometry, fewpix_cost the time it is expected to take (seconds).
+// the kernel takes the geometry, fewpix_plan the tile it then uses.
+struct FewpixPlan {
+  int P;            // pixels per tile
+  int cl_log2;      // 4 << cl_log2 channels per tile
+  long long tiles;  // at most one workgroup per compute unit walks over them
+  double cost;      // expected time of a call, seconds
+};
 bool fewpix_shape(const Geom& g);
-double fewpix_cost(const Geom& g);
-hipError_t launch_fewpix(const Geom& g, const QParams& qp, const uint8_t* x, const uint8_t* w, const uint16_t* lut,
-                         int32_t* acc_out, float* y_out, hipStream_t s);
+FewpixPlan fewpix_plan(const Geom& g);
+hipError_t launch_fewpix(const Geom& g, const FewpixPlan& p, const QParams& qp, const uint8_t* x, const uint8_t* w,
+                         const uint16_t* lut, int32_t* acc_out, float* y_out, hipStream_t s);
 
 // Table-tile kernels (ax_tab.hip).  Device memory of a layer comes in two blocks: the prepared
 // constants (re-laid-out table, packed filters and their sums, coefficients) and the per-call
@@ -127,6 +135,15 @@ int cu_count();  // compute units of the current device
 bool tab_supported(const Geom& g);
 int tab_num_tiles();
 TabPlan tab_plan(const Geom& g, const Options& o);
+// The kernel family of a layer and its plan, from geometry and options alone (ax_api.hip): decided once
+// per call or handle.  Neither tab nor few: depthwise or direct kernel.
+struct Route {
+  bool tab;        // table-tile kernels
+  TabPlan p;       // valid when tab
+  bool few;        // fewpix_kernel
+  FewpixPlan fp;   // valid when few
+};
+Route choose_route(const Geom& g, const Options& o);
 // Enqueue the parts named by `phases`; the main kernel `main_reps` times (measurement helpers
 // launch it repeatedly between two events; layer calls pass 1).
 hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const uint8_t* x,
@@ -155,8 +172,7 @@ struct ax_layer {
   ax::Geom g;
   ax::QParams qp;
   ax::Options o;
-  bool tab;        // table-tile kernels (else the direct / depthwise kernels)
-  ax::TabPlan p;   // valid when tab
+  ax::Route r;
   const uint8_t* w;     // as given to ax_layer_prepare
   const uint16_t* lut;
   void* prepared;

@@ -351,3 +351,19 @@ extern "C" int ax_probe_layer_kernel_ms(const ax_layer_t* layer, const void* x, 
   if (e1) (void)hipEventDestroy(e1);
   return rc;
 }
+
+extern "C" int ax_probe_layer_route(const ax_layer_t* layer, int* kernel, int* pixels, int* channels, int* tiles,
+                                    int* workgroups, int* threads) {
+  using namespace ax;
+  if (!layer) return AX_ERR_NULL;
+  const Route& r = layer->r;
+  const bool dw = layer->g.mult && layer->o.variant != 1 && dw_supported(layer->g, nullptr, nullptr, nullptr);
+  const bool direct = !r.tab && !r.few && !dw;
+  if (kernel) *kernel = r.tab ? 0 : r.few ? 2 : dw ? 3 : 1;
+  if (pixels) *pixels = r.few ? r.fp.P : 0;
+  if (channels) *channels = r.few ? 4 << r.fp.cl_log2 : 0;
+  if (tiles) *tiles = r.few ? (int)r.fp.tiles : 0;
+  if (workgroups) *workgroups = r.few ? (int)std::min<long long>(cu_count(), r.fp.tiles) : dw ? dw_workgroups(layer->g) : 0;
+  if (threads) *threads = direct ? direct_threads(layer->g) : 0;
+  return AX_OK;
+}

@@ -1,0 +1,54 @@
+"""Which kernel a layer handle runs (host arithmetic, no GPU): decided when the handle is made, in
+agreement with its plan, and left on the table tiles by every tuning override."""
+
+import os
+
+import pytest
+
+from paper_2002_09481_amd import binding as ax
+from paper_2002_09481_amd import inputs as I
+
+pytestmark = pytest.mark.skipif(not os.path.exists(ax.LIB_PATH), reason="libaxconv.so not built")
+
+Q = I.Quant(1.0, 0, 1.0, 0, None)
+ZERO = {"variant": 0, "split_k": 0, "tile": 0, "row_tiles": 0, "share_order": 0, "combine": 0, "tables": 0}
+
+
+def route(desc, tune=None, num_luts=1):
+    with ax.AxLayer(desc, Q, num_luts=num_luts, tune=dict(ZERO, **tune) if tune else None) as h:
+        r, plan = h.route(), h.plan()
+        assert (r["kernel"] == "tiles") == (plan["variant"] != 1) == (h.prepared_bytes > 0)
+        assert (r["kernel"] == "fewpix") == (r["tiles"] > 0) == (r["pixels"] > 0)
+        assert (r["kernel"] == "direct") == (r["threads"] > 0)
+        return r
+
+
+FEW = ax._conv_desc((1, 14, 14, 256), (3, 3, 256, 256), 1, 1)
+
+
+def test_one_kernel_of_every_kind():
+    assert route(FEW)["kernel"] == "fewpix"
+    assert route(ax._conv_desc((32, 56, 56, 64), (3, 3, 64, 64), 1, 1))["kernel"] == "tiles"
+    assert route(ax._conv_desc((1, 16, 16, 8), (3, 3, 8, 8), 1, 1))["kernel"] == "direct"
+    assert route(ax._conv_desc((2, 28, 28, 32), (3, 3, 8, 32), 1, 1, groups=4))["kernel"] == "direct"
+    assert route(ax._conv_desc((32, 112, 112, 32), (3, 3, 32, 1), 1, 1, depthwise=True))["kernel"] == "depthwise"
+    assert route(ax._conv_desc((1, 16, 16, 8), (3, 3, 8, 1), 1, 1, depthwise=True))["kernel"] == "direct"
+
+
+@pytest.mark.parametrize("tune", [{"variant": 2}, {"variant": 3}, {"split_k": 2}, {"tile": 3}, {"row_tiles": 1},
+                                  {"share_order": 1}, {"combine": 1}, {"tables": 1}], ids=lambda t: next(iter(t)))
+def test_overrides_stay_on_the_table_tiles(tune):
+    assert route(FEW, tune)["kernel"] == "tiles"
+
+
+def test_direct_override_and_several_tables():
+    assert route(FEW, {"variant": 1})["kernel"] == "direct"
+    assert route(FEW, num_luts=2)["kernel"] == "tiles"
+
+
+def test_tiles_cover_the_layer():
+    for m, k, n in [(1, 2048, 1000), (7, 1536, 257), (50, 516, 1030), (129, 95, 2681), (5634, 1000, 5), (332, 112, 1926)]:
+        r = route(ax._dense_desc(m, k, n))
+        assert r["kernel"] == "fewpix"
+        assert r["tiles"] == -(-m // r["pixels"]) * -(-n // r["channels"])
+        assert 1 <= r["workgroups"] <= r["tiles"]
