@@ -63,6 +63,34 @@ def test_prepared_layer_matches_oracle_on_every_call(li, ti):
                             "%s tune %d call %d" % (layer.name, ti, call))
 
 
+# layers that the automatic choice leaves on the table tiles, and what it takes for them: lanes, combination of
+# shared tiles (0: none are shared), tables (2: ready-made)
+AUTOMATIC = [
+    (L(8, 14, 14, 256, 1, 1, 520, 1, 0), (2, 1, 1)), (L(3, 28, 28, 64, 3, 3, 64, 1, 1), (2, 1, 2)),
+    (L(24, 30, 30, 20, 5, 5, 40, 1, 2), (2, 1, 2)),  # materialized patches
+    (L(277, 1, 1, 77, 1, 1, 512), (2, 0, 1)), (L(2164, 1, 1, 75, 1, 1, 42), (2, 0, 2)),
+    (L(906, 1, 1, 101, 1, 1, 393), (2, 2, 1)), (L(3320, 1, 1, 69, 1, 1, 18), (2, 2, 2)),
+    (L(370, 1, 1, 74, 1, 1, 1357), (3, 0, 1)), (L(128, 1, 1, 2048, 1, 1, 2048), (3, 1, 1)),
+    (L(344, 1, 1, 94, 1, 1, 1037), (3, 2, 1)),
+]
+
+
+@pytest.mark.parametrize("layer, want", AUTOMATIC, ids=lambda v: v.name if isinstance(v, I.Layer) else "")
+def test_automatic_choice_on_the_table_tiles(layer, want):
+    lut = I.lut_random_error(47)
+    x0, w, q = I.make_operands(layer, 7200)
+    with ax.AxLayer(ax._conv_desc(x0.shape, w.shape, layer.stride, layer.pad), q, tune=_tune()) as h:
+        plan = h.plan()
+        assert (plan["variant"], plan["combine"], plan["tables"]) == want
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        for call in range(2):
+            x = x0 if call == 0 else I.make_operands(layer, 7201)[0]
+            acc, y = h.run(G.to_dev(x))
+            torch.cuda.synchronize()
+            G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *oracle.conv2d(x, w, lut, layer.stride, layer.pad, q),
+                            "%s call %d" % (layer.name, call))
+
+
 def test_prepare_again_with_other_filters_and_table_and_another_block():
     """A handle can be prepared again (other filters, other table) into another device block: the
     calls that follow use the new constants, the old block is left alone."""

@@ -49,7 +49,7 @@ def _check(layer, T, seed, **kw):
 
 
 LAYERS = [
-    L(1, 5, 5, 1, 3, 3, 1, 1, 1),                 # one-thread-per-output kernel, table by table
+    L(1, 5, 5, 1, 3, 3, 1, 1, 1),                 # direct kernel, table by table
     L(2, 9, 7, 5, 3, 3, 6, 2, 1),
     L(1, 40, 40, 16, 3, 3, 72, 1, 1),             # several ragged channel tiles
     L(2, 30, 30, 20, 5, 5, 9, 2, 2),              # materialized patches

@@ -250,15 +250,15 @@ def test_float_entry_points_reject_bad_arguments():
 EX_LAYERS = [
     # N, H, W, Cin, KH, KW, last, stride, pad, dilation, depthwise   (last = Cout, or the multiplier)
     (2, 9, 8, 5, 3, 3, 6, 1, 2, 2, False),
-    (1, 40, 40, 16, 3, 3, 72, 1, 2, 2, False),              # table-tile path, implicit patch view
+    (1, 40, 40, 16, 3, 3, 72, 1, 2, 2, False),              # variant 2: implicit patch view; few-pixel kernel when chosen
     (2, 30, 30, 20, 5, 5, 9, 2, 4, (2, 1), False),          # materialized patches
-    (1, 7, 7, 256, 3, 3, 512, 1, 1, 1, False),              # lanes over channels when chosen
+    (1, 7, 7, 256, 3, 3, 512, 1, 1, 1, False),              # variant 3: lanes over channels; few-pixel kernel when chosen
     (2, 8, 8, 6, 3, 3, 2, 1, 1, 1, True),
     (8, 56, 56, 64, 3, 3, 1, 1, 1, 1, True),                # depthwise kernel with the table in LDS
 ]
 
 
-@pytest.mark.parametrize("variant", [0, 1, 3])
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
 @pytest.mark.parametrize("signed", [False, True])
 @pytest.mark.parametrize("case", EX_LAYERS, ids=lambda c: "x".join(str(v) for v in c[:7]) + ("_dw" if c[10] else ""))
 def test_float_layer_with_the_full_parameter_set(case, signed, variant):

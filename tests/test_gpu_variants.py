@@ -165,8 +165,8 @@ DEPTHWISE_LDS = [
 @pytest.mark.parametrize("signed", [False, True])
 @pytest.mark.parametrize("case", DEPTHWISE_LDS, ids=lambda c: "x".join(map(str, c)))
 def test_depthwise_layers_table_in_lds(case, signed, variant):
-    """variant 0 takes the LDS-table depthwise kernel for these sizes, variant 1 forces the
-    one-thread-per-output kernel; both must match the oracle."""
+    """variant 0 takes the LDS-table depthwise kernel for these sizes, variant 1 forces the direct
+    kernel; both must match the oracle."""
     ax.ax_set_option("variant", variant)
     N, H, W, Cin, KH, KW, mult, s, p, d = case
     x, w, q = _operands((N, H, W, Cin, KH, KW, Cin * mult), 300 + Cin, signed, depthwise=True, mult=mult)
