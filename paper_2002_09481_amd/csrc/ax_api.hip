@@ -78,14 +78,16 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
                    d->dilation_h, d->dilation_w, d->signed_codes, d->depthwise, d->groups > 1 ? d->groups : 1);
 }
 
-// A layer goes to fewpix_kernel in the automatic choice only: any override of the table-tile kernels
-// keeps it on them.  Under 2e6 lookups staging the table (about 6 us) costs more than direct_kernel's
-// table reads (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us; 1 x 2048 x 1000: 11 against 16.5 us).
-// From 4e6 on it competes with the table tiles: a tenth under their expected time, since both
-// estimates are off by that much (ResNet-50 layers at batch 1: 14 x 14 and 7 x 7 layers 21-36 us
+// Tiny problems (under 4e6 lookups) do not amortize the set-up of the table tiles, and depthwise layers
+// have no shared table-side operand: neither gets table tiles.
+// fewpix_kernel is taken by the automatic choice only: any override of the table-tile kernels keeps the
+// layer on them.  Under 2e6 lookups staging the table costs more than direct_kernel's table reads
+// (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us).  From there to 4e6 it competes with direct_kernel:
+// 294 of 316 random layers of that range go to it, in 292 of them it is the faster one (2.048e6 lookups,
+// 1 x 2048 x 1000: 11 against 16.5 us); a second round of tiles never paid (3876 x 64 x 16: 20.8 against
+// 12.5 us).  From 4e6 on it competes with the table tiles: a tenth under their expected time, since both
+// estimates are off by at least that much (ResNet-50 layers at batch 1: 14 x 14 and 7 x 7 layers 21-36 us
 // against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
-// Tiny problems (under 4e6 lookups) do not amortize the set-up of the table tiles, and these do not
-// take depthwise layers (no shared table-side operand): both leave neither family set.
 Route choose_route(const Geom& g, const Options& o) {
   Route r{};
   const bool automatic =
@@ -96,7 +98,7 @@ Route choose_route(const Geom& g, const Options& o) {
   if (r.tab) r.p = tab_plan(g, o);
   if (automatic && n >= 2.0e6 && fewpix_shape(g)) {
     r.fp = fewpix_plan(g);
-    r.few = r.tab ? 1.1 * r.fp.cost < r.p.cost : r.fp.cost < 5e-6 + 5.5e-12 * n;
+    r.few = r.tab ? 1.1 * r.fp.cost < r.p.cost : r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();
     if (r.few) r.tab = false;
   }
   return r;

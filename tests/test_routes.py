@@ -52,3 +52,8 @@ def test_tiles_cover_the_layer():
         assert r["kernel"] == "fewpix"
         assert r["tiles"] == -(-m // r["pixels"]) * -(-n // r["channels"])
         assert 1 <= r["workgroups"] <= r["tiles"]
+
+
+@pytest.mark.parametrize("m, k, n", [(2520, 64, 22), (3876, 64, 16), (3174, 128, 9)])
+def test_no_second_round_of_tiles_under_four_million_lookups(m, k, n):
+    assert route(ax._dense_desc(m, k, n))["kernel"] == "direct"
