@@ -123,15 +123,16 @@ typedef struct {
                            Cin and Cout multiples of n; input and output channels are cut into n
                            contiguous blocks and output block g sums over the taps of input block
                            g only: filters [KH, KW, Cin/n, Cout], K = KH*KW*Cin/n in the
-                           correction.  Grouped layers run on the one-thread-per-output kernel
-                           (functional, not tuned); the backward pass does not take them.       */
+                           correction.  Grouped layers run on the direct kernel (functional, not
+                           tuned); the backward pass does not take them.                        */
 } ax_conv_desc_t;
 
 /*
  * Tuning overrides for one call or one layer handle.  Every field 0 (or a NULL pointer where a
  * tune is accepted) selects the automatic choice; results never depend on them (integer addition
  * is associative), only run time does.  The tests force them to reach every kernel path.
- *   variant      1 = direct kernel: one thread per output, table read from global memory
+ *   variant      1 = direct kernel: table read from global memory, one thread per output or, for
+ *                    few outputs, 4, 16 or 64
  *                2 = table-tile kernel, lanes over output pixels
  *                3 = table-tile kernel, lanes over output channels
  *   split_k      n >= 1 (at most 64): n equal workgroup shares per output tile (n slices of the
@@ -224,7 +225,9 @@ size_t ax_conv2d_multi_lut_workspace_bytes(int N, int H, int W, int Cin, int KH,
  *              is still in use on another stream).  May be 0 bytes (NULL is then accepted).
  *   workspace  ax_layer_workspace_bytes() bytes of per-call scratch, as for ax_conv2d.
  * w and luts given to ax_layer_prepare must stay valid and unchanged while the handle is used:
- * layers that take the direct or the depthwise kernel read them in every call.
+ * layers that take the direct kernel, the depthwise kernel or the one for few output pixels
+ * (ax_layer_plan: variant 1; most layers of a network at batch 1) copy nothing and read them in
+ * every call.
  * A handle may be used from one host thread at a time.  Runs that use the same prepared block
  * must not overlap in time on the device (one stream, or streams ordered by events): where
  * several workgroups share an output tile the main kernel keeps the tile's arrival counter in
@@ -261,8 +264,9 @@ int ax_layer_run_static(const ax_layer_t* layer, const void* x, int32_t* acc_out
 size_t ax_static_scratch_bytes(void);
 
 /* What the handle's calls run (host arithmetic only): variant as in ax_tune_t (1, 2 or 3), tile
- * configuration (0 for the direct and depthwise kernels), grid size of the main kernel and
- * number of partial tile pieces it produces.  Any output pointer may be NULL. */
+ * configuration (0 for the kernels that prepare nothing: direct, few output pixels, depthwise,
+ * all variant 1), grid size of the main kernel and number of partial tile pieces it produces.
+ * Any output pointer may be NULL. */
 int ax_layer_plan(const ax_layer_t* layer, int* variant, int* tile, int* workgroups, int* pieces);
 /* The two remaining choices of the plan, in the values of ax_tune_t: combine (0: no shared tiles,
  * 1: second kernel, 2: inside the main kernel) and tables (0: not a table-tile layer, 1: assembled

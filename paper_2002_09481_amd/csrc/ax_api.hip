@@ -81,13 +81,15 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // Tiny problems (under 4e6 lookups) do not amortize the set-up of the table tiles, and depthwise layers
 // have no shared table-side operand: neither gets table tiles.
 // fewpix_kernel is taken by the automatic choice only: any override of the table-tile kernels keeps the
-// layer on them.  Under 2e6 lookups staging the table costs more than direct_kernel's table reads
-// (M = 500, K = 100, Cout = 30: 9.8 against 7.7 us).  From there to 4e6 it competes with direct_kernel:
-// 294 of 316 random layers of that range go to it, in 292 of them it is the faster one (2.048e6 lookups,
-// 1 x 2048 x 1000: 11 against 16.5 us); a second round of tiles never paid (3876 x 64 x 16: 20.8 against
-// 12.5 us).  From 4e6 on it competes with the table tiles: a tenth under their expected time, since both
-// estimates are off by at least that much (ResNet-50 layers at batch 1: 14 x 14 and 7 x 7 layers 21-36 us
-// against 30-113 us, 56 x 56 layers 28-41 us against 23-26 us).
+// layer on them.  Under 2e6 lookups it is not asked: staging the table is most of its time there, and of
+// random layers of 1 to 2 million lookups 22 in 284 are slower on it than on direct_kernel (the others
+// faster, 1.4 times in the middle).  From 2e6 to 4e6 it competes with direct_kernel: of 316 random layers
+// 295 go to it and 2 of these are slower there (1 x 2048 x 1000: 7.6 against 13.0 us); a second round
+// of tiles never paid (3876 x 64 x 16: 20.8 against 12.5 us).  From 4e6 on it competes with the table
+// tiles and is taken at a tenth under their expected time: of 826 random layers that go to it 8 are more
+// than 3 % slower than on the tiles (by 18 % at most), 269 of 519 near the line that stay on the tiles
+// would be faster on it.  The estimates scatter by more than that tenth, so a wider margin loses as many
+// as it mends.
 Route choose_route(const Geom& g, const Options& o) {
   Route r{};
   const bool automatic =

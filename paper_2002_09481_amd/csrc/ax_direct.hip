@@ -14,9 +14,9 @@ namespace ax {
 
 // Tiny problems give few threads, each with a serial chain of dependent loads (code, then entry), so
 // their time is that chain and not any bandwidth: S threads of a block share the taps of an output
-// (thread s takes the taps s, s + S, ...) and their sums meet in LDS.  Calls with S = 1 before and S
-// by launch_direct's rule after: 16x16x8 3x3 to 8 channels 18.3 -> 13.6 us, dense 1 x 2048 x 1000
-// 380 -> 13 us.
+// (thread s takes the taps s, s + S, ...) and their sums meet in LDS.  S = 1 against S by
+// direct_threads, calls in a chain on the device: 16 x 16 x 8 3 x 3 to 8 channels 17.3 -> 5.0 us, dense
+// 500 x 100 x 30 21.7 -> 7.8 us.
 template <int S>
 __global__ __launch_bounds__(256) void direct_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                       const uint8_t* __restrict__ w,
@@ -297,14 +297,15 @@ __global__ __launch_bounds__(1024) void dw_kernel(Geom g, QParams qp_in, const u
 // 3 x 3 depthwise layers with multiplier 1 and a channel count divisible by four: every thread keeps
 // its four channels, so the filter codes stay pre-shifted in registers; PX items (pixels) per thread
 // and iteration.  All loads of the PX items are issued before the first lookup, so that a wave has PX
-// times the lookups to cover one memory round trip with (the workgroup fills the compute unit's LDS, so more waves are not to be had).
-// Bound: vector issue, about as much for the addresses of the codes as for the lookups, next to the
-// gathers (5.2 T/s).  So the position of an item is carried on by additions (no divisions) and a tap
+// times the lookups to cover one memory round trip with (the workgroup fills the compute unit's LDS, so
+// more waves are not to be had).
+// Bound: vector issue, about as much for the addresses of the codes as for the lookups, and the gathers:
+// the vector units issue in 73 % of the busy cycles, the LDS is active in 72 %.  So the position of an item is carried on by additions (no divisions) and a tap
 // is one 32-bit offset from a uniform step; a lookup is a byte extract and one multiply-add, which
 // took half-rate sub-dword multiplies before.  The first codes and the filters travel while the
-// table is staged.  112 x 112 x 32 at batch 32: 36.6 -> 31.6 us, both outputs written.
+// table is staged.  112 x 112 x 32 at batch 32: 37.1 -> 32.4 us, both outputs written.
 // Channel-group counts that do not divide 1024, on the general kernel before -> here, batch 32:
-// 56 x 56 x 96 37.8 -> 26.8 us, 14 x 14 x 576 19.6 -> 15.6 us, 56 x 56 x 144 stride 2 19.1 -> 15.9 us.
+// 56 x 56 x 96 37.6 -> 26.9 us, 14 x 14 x 576 19.5 -> 15.6 us, 56 x 56 x 144 stride 2 19.4 -> 16.1 us.
 template <int PX>
 __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                     const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
@@ -467,16 +468,22 @@ __device__ __forceinline__ T load_any(const void* p) {
 // sums meet in DPP additions, those of the waves in 64-bit LDS atomics (two 32-bit sums at a time,
 // neither reaches 2^32; integer, any order gives the same bits).  One launch, no preparation, no
 // scratch.  Workgroups walk over tiles, so a table is staged once per compute unit.
-// Bound: the random 2-byte gather rate of the LDS (5.2 T lookups/s) plus about 6 us of launch and
-// staging.  Measured (table tiles or the former one-purpose dense kernel -> this one): 7 x 7 x 512
-// 3 x 3 113 -> 35 us, 14 x 14 x 256 3 x 3 44 -> 35 us, 14 x 14 x 1024 1 x 1 30 -> 23 us, dense
-// 1 x 2048 x 1000 380 -> 10 us, 8 x 4096 x 4096 175 -> 44 us, 32 x 2048 x 1000 27.7 -> 25.3 us.
-// Seven pixels of four channels (28 sums) are what 128 registers hold with a step's codes in flight.
+// Bound: waits.  On the layers of the ResNet-50 shape at batch 1 the LDS is active in 63 % of the
+// cycles of the busy compute units (38 % bank conflicts of the random 2-byte gathers), the vector units
+// issue in 54 %, and a wave waits in 57 % of its cycles: for its own gathers, of which at most two are in
+// flight, and at the barriers between staging, lookups, sums and stores.  3.3 to 4.2 T lookups/s after
+// about 5 us of launch and staging; the gathers alone would allow 5.2 T/s.
+// Measured, calls in a chain on the device, before (T: table tiles, D: direct_kernel with one thread per
+// output, F: a kernel for dense layers of few rows) -> here: 7 x 7 x 512 3 x 3 T 111.5 -> 32.8 us,
+// 14 x 14 x 256 3 x 3 T 42.4 -> 32.2 us, 14 x 14 x 1024 1 x 1 to 256 T 28.5 -> 20.8 us, dense
+// 1 x 2048 x 1000 D 378 -> 7.6 us, 8 x 4096 x 4096 F 173 -> 40.6 us, 32 x 2048 x 1000 F 26.9 -> 23.6 us.
+// Eight pixels of four channels (32 sums) are what 128 registers hold with a step's codes in flight.
 // DWORDS: Cin % 4 == 0: four consecutive taps are one dword of one pixel.
 // Operands may start at any byte and tables at any entry, and Cout need not be a multiple of four: dwords
 // and the staged pieces of the table are loaded at their own alignment (load_any), the last dword of a
 // filter row ends with the row.  Byte by byte instead, x off a dword boundary took 63 us against 40.5 us
-// on the table tiles (396 x 128 x 2001), filter rows of 1001 codes 49.2 us against 32.2 us (8 x 8192).
+// on the table tiles (396 x 128 x 2001; 32.8 us now, 33 us aligned), filter rows of 1001 codes 49.2 us
+// against 32.2 us (8 x 8192).
 template <int P, bool DWORDS>
 __global__ __launch_bounds__(1024) void fewpix_kernel(Geom g, QParams qp_in, const uint8_t* __restrict__ x,
                                                        const uint8_t* __restrict__ w, const uint16_t* __restrict__ lut,
@@ -719,8 +726,9 @@ FewpixPlan fewpix_plan(const Geom& g) {
       const double iters = (double)((K4 + slices - 1) / slices);
       // 16 waves of 16 P gathers, 6.2 clocks each, and the address work and loads around them (narrow
       // tiles fetch a 128-byte line of the filters for every few bytes); per tile one memory round
-      // trip, the sums and the stores; 6 us of launch and table staging.  Within 15 % of the times of
-      // the ResNet-50 layers at batch 1 to 8.
+      // trip, the sums and the stores; 6 us of launch and table staging.  Meant for the order of the
+      // shapes: over 1100 random layers with dwords a call takes 0.6 to 1.15 of it (5 to 95 %, the
+      // most in layers of several rounds), over 230 of the byte form 0.58 to 0.82.
       const double t_iter = 16.0 * (16.0 * P * 6.2 + (dwords ? 100.0 : 550.0) + 8.0 * (64 >> c)) / 2.4e9;
       const double t = 6e-6 + std::ceil(tiles / cus) * (iters * t_iter + 2.5e-6 + P * (4 << c) * 1e-9);
       if (t < best.cost) best = FewpixPlan{P, c, (long long)tiles, t};
