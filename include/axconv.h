@@ -137,8 +137,7 @@ typedef struct {
  *                3 = table-tile kernel, lanes over output channels
  *   split_k      n >= 1 (at most 64): n equal workgroup shares per output tile (n slices of the
  *                sum over the taps)
- *   tile         n >= 1: table-tile configuration n (threads, lane elements per thread, table
- *                groups, taps per barrier)
+ *   tile         n >= 1: table-tile configuration n (greatest height of a tile in lane elements)
  *   row_tiles    1 = as few tiles along the lane dimension as fit, n >= 2 = n tiles (clamped to
  *                what the layer allows; at most 2^20)
  *   share_order  1 = workgroups take their shares of the work in launch order, 2 = XCD by XCD
@@ -148,8 +147,7 @@ typedef struct {
  *                last piece adds the others inside the main kernel
  *   tables       the per-tap lookup tables of the table-tile kernel (variant 2, one multiplier
  *                table): 1 = assembled inside the kernel from the rows of the multiplier table,
- *                2 = ready-made in the prepared block (4 KiB per tap and eight output channels;
- *                taken where the tile configuration has a kernel for it, else ignored)
+ *                2 = ready-made in the prepared block (4 KiB per tap and eight output channels)
  * A value out of range gives AX_ERR_OPTION.
  */
 typedef struct {

@@ -86,10 +86,14 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // faster, 1.4 times in the middle).  From 2e6 to 4e6 it competes with direct_kernel: of 316 random layers
 // 295 go to it and 2 of these are slower there (1 x 2048 x 1000: 7.6 against 13.0 us); a second round
 // of tiles never paid (3876 x 64 x 16: 20.8 against 12.5 us).  From 4e6 on it competes with the table
-// tiles and is taken at a tenth under their expected time: of 826 random layers that go to it 8 are more
-// than 3 % slower than on the tiles (by 18 % at most), 269 of 519 near the line that stay on the tiles
-// would be faster on it.  The estimates scatter by more than that tenth, so a wider margin loses as many
-// as it mends.
+// tiles: a run of the ResNet-50 layers at batch 1 to 4 takes 0.85 to 1 of its estimate and the tiles' times are
+// within 5 us of theirs (196 x 2304 x 256: 32.7 us here, 37 on the tiles; 98 x 4608 x 512: 56 and 45;
+// 784 x 1152 x 128: 33 and 27.5).  The estimates leave out what a call that prepares its constants itself
+// pays on the tiles (two launches more, 6 to 9 us), so layers that are short in any case keep this kernel
+// (`keep`, expected time on it): up to 38 us under 40 million lookups and 36 us under 80 million, where
+// ready-made tables do not help the tiles, and up to 60 us for sums of 2048 taps and more.  That costs
+// prepared layers between nothing and a factor of two (129 x 95 x 2681: 24 us here, 20 on prepared tiles
+// and 27 with the preparation; 147 x 2048 x 512: 54 and 36; 5692 x 80 x 47: 30 and 15).
 Route choose_route(const Geom& g, const Options& o) {
   Route r{};
   const bool automatic =
@@ -100,7 +104,8 @@ Route choose_route(const Geom& g, const Options& o) {
   if (r.tab) r.p = tab_plan(g, o);
   if (automatic && n >= 2.0e6 && fewpix_shape(g)) {
     r.fp = fewpix_plan(g);
-    r.few = r.tab ? 1.1 * r.fp.cost < r.p.cost : r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();
+    const double keep = g.K >= 2048 ? 60e-6 : n < 16e6 ? 0.0 : n < 40e6 ? 38e-6 : n < 80e6 && !r.p.pre ? 36e-6 : 0.0;
+    r.few = r.tab ? 0.9 * r.fp.cost < r.p.cost || 1.1 * r.fp.cost < keep : r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();
     if (r.few) r.tab = false;
   }
   return r;
@@ -129,7 +134,7 @@ int run_layer(const Geom& g, const QParams& qp, const Options& o, const uint8_t*
   if (!r.tab) return run_untiled(g, qp, o, r, x, w, lut, acc_out, y_out, s);
   if (!ws || ws_bytes < r.p.prep_total + r.p.ws_total || ((uintptr_t)ws & 255)) return AX_ERR_WORKSPACE;
   uint8_t* wsb = static_cast<uint8_t*>(ws);
-  const hipError_t e = launch_tab(g, qp, r.p, x, w, lut, acc_out, y_out, wsb, wsb + r.p.prep_total, kPhAll, 1, s);
+  const hipError_t e = launch_tab(g, qp, r.p, x, w, lut, acc_out, y_out, wsb, wsb + r.p.prep_total, true, kPhAll, 1, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 
@@ -286,8 +291,8 @@ extern "C" int ax_layer_prepare(ax_layer_t* layer, const void* w, const void* lu
   if (layer->r.tab) {
     if (!prepared || prepared_bytes < layer->r.p.prep_total || ((uintptr_t)prepared & 255)) return AX_ERR_WORKSPACE;
     const hipError_t e = launch_tab(layer->g, layer->qp, layer->r.p, nullptr, static_cast<const uint8_t*>(w),
-                                    static_cast<const uint16_t*>(luts), nullptr, nullptr, prepared, nullptr, kPhConst,
-                                    1, (hipStream_t)hip_stream);
+                                    static_cast<const uint16_t*>(luts), nullptr, nullptr, prepared, nullptr, false,
+                                    kPhConst, 1, (hipStream_t)hip_stream);
     if (e != hipSuccess) return AX_ERR_HIP;
   }
   layer->w = static_cast<const uint8_t*>(w);
@@ -326,7 +331,7 @@ int run_prepared(const ax_layer* layer, const void* x, int32_t* acc_out, float* 
   const size_t need = scratch_need(layer, x);
   if (need && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return AX_ERR_WORKSPACE;
   const hipError_t e = launch_tab(layer->g, layer->qp, p, xb, layer->w, layer->lut, acc_out, y_out, layer->prepared,
-                                  workspace, phases, main_reps, s);
+                                  workspace, workspace && workspace_bytes >= p.ws_total, phases, main_reps, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 }  // namespace ax

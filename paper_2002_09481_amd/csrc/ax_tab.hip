@@ -7,12 +7,12 @@
 //
 //   for a tap k and a group of 8 columns j..j+7, the workgroup builds in LDS a table of 256
 //   entries of 16 bytes, entry v = the eight 16-bit products LUT(v, B[k][j..j+7]);
-//   every lane then fetches entry A[i][k] with ONE 16-byte LDS read and adds its eight
-//   halves to eight int32 accumulators.
+//   every lane element's entry A[i][k] is fetched with ONE 16-byte LDS read, and a matrix instruction
+//   adds the bytes of 64 such entries (16 elements, four taps) to int32 accumulators.
 //
-// So a lookup-MAC costs 2 bytes of LDS read bandwidth and one integer add, instead of one
-// conflict-prone 2-byte gather per MAC.  The 128 kB truth table itself stays in L2: the
-// tables are assembled from a row-major re-layout of it ("rows": for each code of the
+// So a lookup-MAC costs 2 bytes of LDS read bandwidth and a 512th of a matrix instruction, instead of
+// one conflict-prone 2-byte gather and an addition per MAC.  The 128 kB truth table itself stays in L2:
+// the tables are assembled from a row-major re-layout of it ("rows": for each code of the
 // table-side operand the 256 products against every lane-side code, 512 contiguous bytes),
 // read with coalesced global loads that do not compete with the LDS gathers.
 //
@@ -28,6 +28,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "ax_internal.h"
@@ -74,54 +75,28 @@ struct TabArgs {
   uint32_t bias_k;   // 32768 * K for signed tables (their entries are stored with that offset), else 0
   int32_t* acc_out;
   float* y_out;
-  int32_t* part;  // [2*G][JT][ih] partial tiles: slot 2w = workgroup w's piece of a tile begun by
+  int32_t* part;  // [2*G][ih * kJT] partial tiles: slot 2w = workgroup w's piece of a tile begun by
                   // another workgroup, slot 2w+1 = its piece of a tile it begins but does not end
   int32_t* lsum;  // [2*G][ih] lane-operand sums of the same pieces
   uint32_t* cnt;  // non-null: [tiles] arrival counters, pieces are combined inside tab_kernel (see there)
-  const uint4* tabs;  // kernels with PRE: [nch*16 + 1][Jpad/8][256] ready-made table entries (prep_tables_kernel)
+  const uint4* tabs;  // kernels with PRE: [nch][Jpad/8][256][16] ready-made table entries (prep_tables_kernel)
   uint32_t tabs_bytes;
   long long out_elems;   // outputs per table (M * Cout)
   int ntiles1;           // tiles of one table; tile index space = table * ntiles1 + tile (several tables: ax_conv2d_multi_lut)
-  int vec_out;  // outputs may be written in aligned 16-byte pieces along j
+  int vec_out;  // outputs may be written in aligned 8-byte pieces along j
+  int padded;   // 0: every tap of every pixel lies in the image, 1: not, 2: not and positions need more than 16 bits
   int xcd;      // 1: shares of work are numbered XCD by XCD (see xcd_major), 0: in launch order
 };
 
-// Accumulate the eight 16-bit products of one gathered entry (four registers, each with a
-// product l in its low and a product h in its high half) into eight accumulators.  Every
-// instruction that adds one half of a register (sub-dword select, 16-bit dot product,
-// multiply-add) issues at half the rate of a plain 32-bit add, so each pair is accumulated in a
-// different basis instead:
-//   b += e        = l + 65536 h   (plain add, full rate)
-//   a += l + h                    (sum of absolute differences against 0, half rate)
-// both modulo 2^32.  Since 65535 is odd the two sums determine both column sums exactly
-// (split_sums below).  The four adds go first and the four sums after them: alternating between
-// the two kinds costs issue cycles (measured 39 T lookups/s grouped, 33 T alternating, 32 T for
-// eight 16-bit dot products).  Written as instructions because the optimizer otherwise regroups
-// each accumulator's chain of adds across a whole unrolled chunk into a tree, which keeps every
-// gathered value alive at once.
-__device__ __forceinline__ void add_entry(uint32_t (&a)[8], const uint4& e) {
-  asm volatile(
-      "v_add_u32 %0, %8, %0\n\t"
-      "v_add_u32 %2, %9, %2\n\t"
-      "v_add_u32 %4, %10, %4\n\t"
-      "v_add_u32 %6, %11, %6\n\t"
-      "v_sad_u16 %1, %8, 0, %1\n\t"
-      "v_sad_u16 %3, %9, 0, %3\n\t"
-      "v_sad_u16 %5, %10, 0, %5\n\t"
-      "v_sad_u16 %7, %11, 0, %7"
-      : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7])
-      : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w));
-}
-// From B = L + 65536 H and A = L + H (mod 2^32) to L and H, the sums of the low and of the high
-// halves (each below 2^31): A - B = -65535 H and -65535 * -65537 = 1 (mod 2^32).
-__device__ __forceinline__ void split_sums(uint32_t& b_to_lo, uint32_t& a_to_hi) {
-  const uint32_t d = a_to_hi - b_to_lo;
-  const uint32_t h = d + (d << 16);
-  b_to_lo = a_to_hi - h;
-  a_to_hi = h;
-}
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 512;           // 8 waves of up to 256 registers
+constexpr int kWaves = kThreads / 64;
+constexpr int kGroups = 8;              // most groups of 64 lane elements per wave
+constexpr int kIT = kThreads * kGroups; // lane elements of a full tile
+constexpr int kJT = 8;                  // columns of a tile: one 16-byte table entry
+constexpr int kTabBytes = 65536;        // tables of one chunk: 256 entries x 16 taps x 16 bytes
 
 // Position of workgroup b of a grid of G when the workgroups are listed XCD by XCD (workgroup b
 // runs on XCD b % 8): a bijection of 0 .. G-1.
@@ -130,16 +105,87 @@ __device__ __forceinline__ int xcd_major(int b, int G) {
   return x * q + min(x, r) + (b >> 3);
 }
 
-__device__ __forceinline__ uint32_t byte_of(const uint4& v, int kk) {
-  const uint32_t w = (kk < 4) ? v.x : (kk < 8) ? v.y : (kk < 12) ? v.z : v.w;
-  return (w >> (8 * (kk & 3))) & 0xffu;
+// A 64-bit value that is the same in all lanes, in scalar registers (its arithmetic may be done in vector ones).
+__device__ __forceinline__ long long uniform(long long v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((unsigned long long)v >> 32));
+  return (long long)((unsigned long long)hi << 32 | lo);
 }
 
-// THREADS threads, P lane elements per thread, NG table groups (8 columns each) per
-// workgroup, KS taps per barrier phase, at least WPE waves per SIMD (bounds the registers:
-// 512 threads with WPE = 4 lets two workgroups share a compute unit).
+// Column constants K z_lane z_tab - z_lane * (column sum) of a tile's eight columns, into red[THREADS / 64][8]
+// (the sum over its rows is a column's constant): thread = (segment, column), so that the loads of
+// all segments are in flight together.  The caller has a barrier before the constants are read.
+template <int THREADS>
+__device__ __forceinline__ void column_constants(const TabArgs& a, int j0, long long (*red)[8]) {
+  int32_t sb = 0;
+  for (int seg = (int)threadIdx.x >> 3; seg < a.nseg; seg += THREADS / 8) sb += a.bsum[(size_t)seg * a.Jpad + j0 + (threadIdx.x & 7)];
+#pragma unroll
+  for (int o = 8; o < 64; o *= 2) sb += __shfl_xor(sb, o);
+  if ((threadIdx.x & 63) < 8)
+    red[threadIdx.x >> 6][threadIdx.x & 7] = (threadIdx.x < 8 ? a.qd->kzz : 0LL) - (long long)a.qd->z_lane * sb;
+}
+template <int WAVES>
+__device__ __forceinline__ long long column_constant(const long long (*red)[8], int col) {
+  long long t = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) t += red[w][col];
+  return t;
+}
+
+// What a piece or a finished tile holds per (group of 64 lane elements, quarter r of it): lane
+// l = 16 kg + m has columns 2 kg and 2 kg + 1 of lane element 16 r + m.
+__device__ __forceinline__ float dequant(uint32_t accv, uint32_t lterm, long long cterm, float scale, bool wide) {
+  // accv - lterm + cterm is the corrected sum; every term is below 2^31 in magnitude, and so is
+  // every partial sum for K <= 16384: 32-bit wrap-around arithmetic is exact.  Longer K takes 64 bits.
+  return wide ? (float)((long long)(int32_t)(accv - lterm) + cterm) * scale
+              : (float)(int32_t)(accv - lterm + (uint32_t)cterm) * scale;
+}
+
+// Outputs of one lane: columns j, j + 1 (j = tile column 2 kg) of lane element i.
+template <bool CH>
+__device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, float* y_base, int i, int j, uint32_t v0,
+                                         uint32_t v1, float y0, float y1) {
+  if (!CH && a.vec_out) {
+    if (j < a.J) {
+      const size_t o = (size_t)i * a.J + j;
+      if (acc_base) *reinterpret_cast<uint2*>(acc_base + o) = make_uint2(v0, v1);
+      if (y_base) *reinterpret_cast<float2*>(y_base + o) = make_float2(y0, y1);
+    }
+  } else {
+    const size_t o = CH ? (size_t)j * a.I + i : (size_t)i * a.J + j;
+    const size_t step = CH ? (size_t)a.I : (size_t)1;
+    if (j < a.J) {
+      if (acc_base) acc_base[o] = (int32_t)v0;
+      if (y_base) y_base[o] = y0;
+    }
+    if (j + 1 < a.J) {
+      if (acc_base) acc_base[o + step] = (int32_t)v1;
+      if (y_base) y_base[o + step] = y1;
+    }
+  }
+}
+
+// One workgroup of 8 waves per compute unit; a tile is up to 4096 lane elements x 8 columns.
 // CH: lanes are output channels (output index j*I + i) instead of pixels (i*J + j).
-// WIDE: K > 16384, the correction needs 64-bit arithmetic.
+//
+// Gathers and sums.  The wave's 64 lanes are 16 lane elements (m = lane % 16) times four taps
+// (kg = lane / 16): every lane fetches the entry of ITS element's code at ITS tap, 16 bytes = eight
+// products = what v_mfma_i32_16x16x64_i8 takes from a lane as 16 contraction elements of column m.
+// The other operand is a constant: row r of it picks byte r of every 16, so the instruction adds,
+// for 16 lane elements at once, the low and the high bytes of the eight products over the four
+// taps: one matrix instruction per 512 lookups where adding in vector registers takes eight
+// vector instructions.  The bytes count as signed, so the tables hold every byte with its top bit
+// flipped (value - 128) and the epilogue adds 128 * (1 + 256) per tap.
+//
+// Table layout.  LDS holds two buffers of 16 tables, interleaved entry by entry: entry v of tap t
+// lies at 256 v + 16 t, so the bank of a gather depends on the tap alone.  The LDS serves a 16-byte
+// read in passes of 16 lanes that are not consecutive: measured times single out lanes 0-3, 12-15,
+// 20-23 and 24-27 of 32 (and their complement), two quarters from each of two neighbouring kg.  A
+// pass is therefore free of conflicts, whatever the codes are, when its 16 lanes are at 16
+// different taps: lane (kg, m) walks the four taps of dword dq = kg ^ rot(m / 4) of its element's
+// sixteen codes in the order s ^ (m % 4), rot = 0, 2, 3, 1.  (With the tables one after another
+// and random codes in the bank index, gathers took 1.6-2.2 times as long; with rot(m / 4) = m / 4
+// 1.5 times.)  The address is one byte permute: byte 1 is the code, byte 0 the constant 16 t.
 //
 // Work is spread over the grid by iterations, not by tiles (G workgroups, one per compute
 // unit, each takes an equal contiguous share of tiles x chunks): a workgroup runs through one or
@@ -147,389 +193,357 @@ __device__ __forceinline__ uint32_t byte_of(const uint4& v, int kk) {
 // range writes final outputs; any other writes a partial tile that tab_fixup_kernel combines.
 // Integer addition is associative, so the decomposition does not change a single bit.
 //
-// LDS holds two phase buffers of KS*NG tables.  In every phase each wave (a) issues the
-// global loads of the table rows for the NEXT phase, (b) gathers from the current buffer and
-// accumulates, (c) interleaves the loaded rows into 16-byte entries and stores them into
-// the other buffer, (d) joins the barrier.
-// PRE: the 4 KiB tables are not built from table rows but copied from global memory, where
-// prep_tables_kernel has laid them out ready-made for every (tap, column group) of the layer: two
-// 16-byte loads per lane and half table instead of eight 4-byte row loads and eight permutes.  The
-// loads write straight into LDS (buffer loads with the lds modifier), so the copy takes no
-// registers, no LDS store instructions and no wait in the middle of a phase.
-template <int THREADS, int P, int NG, int KS, int WPE, bool CH, bool WIDE, bool PRE = false>
-__global__ __launch_bounds__(THREADS, WPE) void tab_kernel(const TabArgs a) {
-  constexpr int JT = NG * 8;
-  constexpr int WAVES = THREADS / 64;
-  constexpr int HALVES = 2 * NG * KS;  // half-tables (128 entries) to build per phase
-  constexpr int UNITS = (HALVES + WAVES - 1) / WAVES;
-  constexpr int PHASES = kChunk / KS;
-  constexpr int CODES = (UNITS + 1) / 2;  // units 2c and 2c+1 are the two halves of one table
-  static_assert(UNITS == 1 || UNITS % 2 == 0, "units of a wave must pair up");
-  static_assert(kChunk % KS == 0 && PHASES % 2 == 0, "a chunk must hold an even number of phases");
-
-  __shared__ uint4 tab[2][KS][NG][256];
+// A phase is one chunk of 16 taps: the waves gather from one buffer and fill the other with the
+// tables of the next chunk, then meet at a barrier.  Without PRE a wave builds 32 entries of all 16
+// tables: lane = (tap, quarter), eight 16-byte loads (one per column, from the 512-byte row of the
+// column's code; the four lanes of a tap read 64 contiguous bytes), requested before the barrier
+// that ends the phase before, and one entry interleaved and stored after every group of gathers.
+// PRE: the tables of a chunk lie ready-made in global memory as an image of the LDS buffer
+// (prep_tables_kernel) and are copied straight into LDS (buffer loads with the lds modifier).
+//
+// Bound: LDS.  Per phase of a full tile 1 MiB of gathers (165-200 bytes per clock measured) and 64
+// KiB of table writes at 70 bytes per clock, against 4096 clocks of matrix instructions per SIMD.
+// PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
+// copied with their border, see prep_chunks_kernel); the other form has no position per lane
+// element and no comparisons.
+// GR: groups of 64 lane elements per wave.  Tiles of at most half the height take GR = 4, whose free
+// registers hold the lane operands and the table rows a whole phase ahead: with few groups to gather
+// a phase is shorter than a round trip to memory.
+template <int GR, bool CH, bool PRE, bool PADDED>
+__global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
+  __shared__ struct {
+    alignas(16) uint8_t tab[2 * kTabBytes];  // at LDS address 0: only there the gathers' constant offsets fit
+    long long cterm[kWaves][kJT];  // column constants of the current tile, see the epilogue
+    int comb[3];                 // last piece of a shared tile? / first and last share of the tile
+  } sh;
+  constexpr int XR = PRE ? GR : 4;  // groups whose lane operands are in registers or in flight
+  constexpr int DB = !PRE && GR < kGroups ? 2 : 1;  // chunks whose table rows are
+  constexpr int PER = 8 / GR;      // entries stored after a group's gathers
+  constexpr int DEPTH = 3;         // gathers in flight ahead of the matrix instructions
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 15, kg = lane >> 4;
   const uint8_t* padrow = reinterpret_cast<const uint8_t*>(a.qd->padrow);
-  const int klast = a.nch * kChunk;  // padded K = index of the last (zero) row of Bp
-  // Taps K .. klast-1 exist only in materialized operands, where both codes are 0: each adds
-  // the table entry (0,0) to every accumulator, which the final epilogue takes off again.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)sh.tab;
+
+  // constant operand of the matrix instruction: row m has a 1 at byte m of every 16
+  i32x4 pick;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) pick[d] = (m >> 2) == d ? 1 << (8 * (m & 3)) : 0;
+  // gather addresses: perm[s] takes byte s of offs (16 * tap) and the code of that tap
+  const int rot = (((m >> 2) ^ (m >> 3)) & 1) << 1 | (m >> 3);
+  uint32_t offs = 0, perm[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const uint32_t b = (uint32_t)(s ^ (m & 3));
+    offs |= 16u * (4u * (uint32_t)(kg ^ rot) + b) << (8 * s);
+    perm[s] = 0x0c0c0000u | (4u + b) << 8 | (uint32_t)s;
+  }
+  const bool rot0 = rot & 1, rot1 = rot & 2;
+
   // Workgroups go to the eight XCDs (each with its own L2) in turn.  With a.xcd the share of work
   // is taken by a renumbered index under which every XCD holds a contiguous run of shares:
   // neighbouring tiles read the same lane-side rows, which then come from one L2 instead of being
   // fetched into eight.  (Where tiles are cut into a multiple of eight shares the launch order
   // already gives every XCD one slice of K of all tiles; the planner picks per layer.)
   const int wg = a.xcd ? xcd_major((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-  long long it_beg = (long long)wg * a.total_iters / gridDim.x;
-  const long long it_end = (long long)(wg + 1) * a.total_iters / gridDim.x;
-  __shared__ long long cterm[JT];  // column constants of the current tile, see the epilogue
-  __shared__ int comb[3];          // last piece of a shared tile? / first and last share of the tile
+  long long it_beg = uniform((long long)wg * a.total_iters / gridDim.x);
+  const long long it_end = uniform((long long)(wg + 1) * a.total_iters / gridDim.x);
+
+  // builder roles: tap bt, entries bv .. bv + 7
+  const int bt = lane >> 2, bv = 32 * wave + 8 * (lane & 3);
+  u32x4 tabs_words;  // PRE: buffer descriptor of the table images (raw buffer, bounds-checked against their size)
+  tabs_words.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)a.tabs);
+  tabs_words.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)((uintptr_t)a.tabs >> 32) & 0xffffu));
+  tabs_words.z = (uint32_t)__builtin_amdgcn_readfirstlane((int)(PRE ? a.tabs_bytes : 0u));
+  tabs_words.w = 0x00020000u;
 
   while (it_beg < it_end) {
-  const int gtile = (int)(it_beg / a.nch);
+  const int gtile = __builtin_amdgcn_readfirstlane((int)(it_beg / a.nch));
   const int c_beg = (int)(it_beg - (long long)gtile * a.nch);
-  const int tbl = gtile / a.ntiles1;  // which multiplier table
+  const int tbl = __builtin_amdgcn_readfirstlane(gtile / a.ntiles1);  // which multiplier table
   const int tile = gtile - tbl * a.ntiles1;
   const uint16_t* __restrict__ rows = a.rows + (size_t)tbl * 65536;
   int32_t* __restrict__ acc_base = a.acc_out ? a.acc_out + (size_t)tbl * a.out_elems : nullptr;
   float* __restrict__ y_base = a.y_out ? a.y_out + (size_t)tbl * a.out_elems : nullptr;
   const int c_end = (int)min((long long)a.nch, c_beg + (it_end - it_beg));
   const bool whole = (c_beg == 0) && (c_end == a.nch);
-  const int ti = tile / a.ntj;
-  const int i0 = ti * a.ih;  // tiles are a.ih <= IT lane elements high (a multiple of 64)
-  const int j0 = (tile - ti * a.ntj) * JT;
-  const int kbeg = c_beg * kChunk, kend = c_end * kChunk;
+  const int ti = __builtin_amdgcn_readfirstlane(tile / a.ntj);
+  const int i0 = ti * a.ih;  // tiles are a.ih <= kIT lane elements high (a multiple of 64)
+  const int tj = tile - ti * a.ntj;
+  const int j0 = tj * kJT;
 
-  // ---- lane elements -------------------------------------------------------------------
-  // slot il = p*THREADS + tid of the tile is lane element i0 + il; slots at or beyond a.ih (or
-  // beyond the operand) are padding.  act[p]: some lane of this wave's slot p is real.
-  int by[P], bx[P], nb[P];
-  auto set_prio = [](int v) {  // the instruction takes a constant; v is one after unrolling
-    switch (v < 0 ? 0 : v > 3 ? 3 : v) {
-      case 0: __builtin_amdgcn_s_setprio(0); break;
-      case 1: __builtin_amdgcn_s_setprio(1); break;
-      case 2: __builtin_amdgcn_s_setprio(2); break;
-      default: __builtin_amdgcn_s_setprio(3); break;
-    }
-  };
-  bool act[P];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const int w0 = p * THREADS + wave * 64;
-    act[p] = (w0 < a.ih) && (i0 + w0 < a.I);
-    const int i = min(i0 + p * THREADS + tid, a.I - 1);
+  // ---- lane operand --------------------------------------------------------------------
+  // Group p of this wave is lane elements i0 + 64 * (8 p + wave) .. + 63 of the tile; groups at or
+  // beyond a.ih (or beyond the operand) are padding: the first np groups are real.  For the loads
+  // lane l holds element l of the group.
+  const int left = min(a.ih, a.I - i0);
+  const int np = max(0, ((left + 63) / 64 - wave + kWaves - 1) / kWaves);
+  // Byte offset of the element from the tile's first one: pixels under tap (0, 0) come in rising order,
+  // and their distance fits 32 bits (launch_tab), so a load is a scalar base and this offset.
+  // PADDED: index of the pixel instead, which may lie outside the image, and its row and column, 16 bits each.
+  uint32_t pix[GR];
+  int yx[GR];
+  auto first_tap = [&](int p, int& by, int& bx) {  // position of tap (0, 0); returns the image
+    const int i = min(i0 + 64 * (kWaves * p + wave) + lane, a.I - 1);
     const int n = i / a.OHW;
     const int r = i - n * a.OHW;
     const int oy = r / a.OW;
-    const int ox = r - oy * a.OW;
-    by[p] = oy * a.sh - a.ph;
-    bx[p] = ox * a.sw - a.pw;
-    nb[p] = n * a.H;
-  }
-  auto load_chunk = [&](int k0, uint4 (&v)[P]) {
-    const int tap = k0 / a.Cin;
-    const int ci0 = k0 - tap * a.Cin;
-    const int ky = tap / a.KW;
-    const int kx = tap - ky * a.KW;
+    by = oy * a.sh - a.ph;
+    bx = (r - oy * a.OW) * a.sw - a.pw;
+    return n;
+  };
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int iy = by[p] + ky * a.dh, ix = bx[p] + kx * a.dw;
-      const bool inside = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-      // pixel index below 2^31; times the row length it can pass 2^32 for a materialized operand
-      const size_t off = (size_t)((uint32_t)(nb[p] + iy) * (uint32_t)a.W + (uint32_t)ix) * a.a_ps + (size_t)(uint32_t)ci0 * a.a_cs;
-      // Every lane loads: taps outside the image (and lanes of tile padding) read sixteen pad codes
-      // kept in device memory.  A load that only some waves issued would leave the number of loads
-      // in flight unknown at compile time, and every later wait for table rows would then have to
-      // wait for all loads, the activation prefetch from HBM included.
-      const uint8_t* src = (inside && act[p]) ? a.A + off : padrow;
-      v[p] = *reinterpret_cast<const uint4*>(src);
+  for (int p = 0; p < GR; ++p) {
+    int by, bx;
+    const int n = first_tap(p, by, bx);
+    pix[p] = (uint32_t)((n * a.H + by) * a.W + bx);
+    if (PADDED) yx[p] = (int)((uint32_t)by * 65536u + (uint32_t)bx);
+  }
+  uint32_t pix0 = 0;  // the pixel of the tile's first element
+  if (!PADDED) {
+    const int n = i0 / a.OHW, r = i0 - n * a.OHW, oy = r / a.OW;
+    pix0 = (uint32_t)__builtin_amdgcn_readfirstlane((n * a.H + oy * a.sh) * a.W + (r - oy * a.OW) * a.sw);
+#pragma unroll
+    for (int p = 0; p < GR; ++p) pix[p] = (pix[p] - pix0) * a.a_ps;
+  }
+  int xdy = 0, xdx = 0, xoff = 0;  // tap of the chunk that load_x reads: row and column step, pixels from tap (0, 0)
+  const uint8_t* xsrc = a.A;       // its channels
+  auto load_from = [&](int chunk) {
+    const int k0 = min(chunk, a.nch - 1) * kChunk;
+    const int tap = __builtin_amdgcn_readfirstlane(k0 / a.Cin);
+    const int ky = __builtin_amdgcn_readfirstlane(tap / a.KW);
+    xdy = ky * a.dh;
+    xdx = (tap - ky * a.KW) * a.dw;
+    xoff = xdy * a.W + xdx;
+    xsrc = a.A + (size_t)(uint32_t)(k0 - tap * a.Cin) * a.a_cs;
+    if (!PADDED) xsrc += (size_t)(pix0 + (uint32_t)xoff) * a.a_ps;
+  };
+  auto load_x = [&](int p) {
+    // Every lane loads, also in groups of tile padding (the last element again) and, PADDED, at taps
+    // outside the image (sixteen pad codes kept in device memory).  A load that only some waves
+    // issued would leave the number of loads in flight unknown at compile time, and every later wait
+    // for table rows would then have to wait for all loads, the activation prefetch included.
+    if (!PADDED) {
+      uint32_t off = pix[p];
+      asm volatile("" : "+v"(off));  // stays one 32-bit register next to a scalar base
+      return *reinterpret_cast<const u32x4*>(xsrc + off);
     }
+    const uint8_t* src = xsrc + (size_t)(pix[p] + (uint32_t)xoff) * a.a_ps;
+    {
+      int by = (yx[p] >> 16) + (int)((uint32_t)yx[p] >> 15 & 1u), bx = (int)(int16_t)yx[p];
+      if (a.padded == 2) first_tap(p, by, bx);  // positions beyond 16 bits
+      if ((unsigned)(by + xdy) >= (unsigned)a.H || (unsigned)(bx + xdx) >= (unsigned)a.W) src = padrow;
+    }
+    return *reinterpret_cast<const u32x4*>(src);
   };
 
   // ---- table building ------------------------------------------------------------------
-  // Unit q of a phase = (tap s of the phase, table g, half h).  The eight table-side codes of
-  // a unit are wave-uniform (scalar registers); the rows are read with buffer loads whose
-  // scalar offset selects the row (code * 512 bytes) and whose per-lane offset selects dword
-  // `lane` (+64 for the second half): 256 contiguous bytes per wave.
   const __amdgpu_buffer_rsrc_t rows_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(rows), 0, 131072, 0x00020000);
-  int us[UNITS], ug[UNITS], uh[UNITS];
-  bool uvalid[UNITS];
-#pragma unroll
-  for (int u = 0; u < UNITS; ++u) {
-    const int q = wave * UNITS + u;
-    uvalid[u] = q < HALVES;
-    const int qq = uvalid[u] ? q : 0;
-    us[u] = qq / (2 * NG);
-    ug[u] = (qq >> 1) % NG;
-    uh[u] = qq & 1;
-  }
-  uint32_t d[8];  // rows of the unit being built (units of a wave take turns within a phase)
-  auto load_codes = [&](int cu, int k) {  // codes of unit pair cu for the phase that starts at tap k
-    return *reinterpret_cast<const uint2*>(a.Bp + (size_t)min(k + us[2 * cu < UNITS ? 2 * cu : 0], klast) * a.Jpad + j0 +
-                                           8 * ug[2 * cu < UNITS ? 2 * cu : 0]);
+  const int c_last = a.nch - 1;
+  auto load_codes = [&](int chunk) {  // the eight column codes of this lane's tap
+    return *reinterpret_cast<const uint2*>(a.Bp + (size_t)(min(chunk, c_last) * kChunk + bt) * a.Jpad + j0);
   };
-  // PRE: buffer descriptor of the ready-made tables (raw buffer, bounds-checked against their size)
-  u32x4 tabs_words;
-  tabs_words.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)a.tabs);
-  tabs_words.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)((uintptr_t)a.tabs >> 32) & 0xffffu));
-  tabs_words.z = (uint32_t)__builtin_amdgcn_readfirstlane((int)(PRE ? a.tabs_bytes : 0u));
-  tabs_words.w = 0x00020000u;
-  const uint32_t tabs_stride = (uint32_t)(a.Jpad >> 3);  // tables per tap
-  // PRE: copy the half table of unit u for the phase that starts at tap ktap into buffer buf.  Lane
-  // l moves entries l + 64 * half and, 128 entries on, the second one: two loads of 1 KiB per wave,
-  // which the hardware writes to LDS at M0 + instruction offset + 16 * lane (the instruction offset
-  // counts for the memory address and for the LDS address alike).  Written as instructions: the
-  // compiler would make every later LDS read wait for a copy it knows of, since it cannot tell the
-  // two table buffers apart; the waves wait for their copies once, before the barrier of the phase.
-  auto table_copy = [&](int u, int ktap, int buf) {
-    if (!uvalid[u]) return;
-    const uint32_t k = (uint32_t)min(ktap + us[u], klast);
-    const uint32_t soff = (k * tabs_stride + (uint32_t)(j0 >> 3) + (uint32_t)ug[u]) * 4096u;
-    const uint32_t voff = (uint32_t)(lane + 64 * uh[u]) * 16u;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)&tab[buf][us[u]][ug[u]][64 * uh[u]];
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds"
-                 :: "s"(lds0), "v"(voff), "s"(tabs_words), "s"(soff) : "memory");
-  };
-  auto copies_done = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-  // tv: the eight table-side codes of the unit
-  auto build_issue = [&](int u, const uint2 tv) {
-    if (PRE || !uvalid[u]) return;
-    const int voff = (lane + 64 * uh[u]) * 4;
+  u32x4 dd[DB][8];  // entries bv .. bv + 7 of the eight columns' rows; chunk c in dd[(c - c_beg) % DB]
+  auto build_issue = [&](const uint2 codes, u32x4 (&d)[8]) {
+    if (PRE) return;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      const uint32_t b = ((c < 4 ? tv.x : tv.y) >> (8 * (c & 3))) & 0xffu;
-      d[c] = __builtin_amdgcn_raw_buffer_load_b32(rows_rsrc, voff, (int)(b * 512u), 0);
+      const uint32_t b = ((c < 4 ? codes.x : codes.y) >> (8 * (c & 3))) & 0xffu;
+      d[c] = __builtin_amdgcn_raw_buffer_load_b128(rows_rsrc, (int)(b * 512u) + bv * 2, 0, 0);
     }
   };
-  auto build_commit = [&](int u, int buf) {
-    if (PRE || !uvalid[u]) return;
-    uint4 lo, hi;
-    lo.x = __builtin_amdgcn_perm(d[1], d[0], 0x05040100u);
-    lo.y = __builtin_amdgcn_perm(d[3], d[2], 0x05040100u);
-    lo.z = __builtin_amdgcn_perm(d[5], d[4], 0x05040100u);
-    lo.w = __builtin_amdgcn_perm(d[7], d[6], 0x05040100u);
-    hi.x = __builtin_amdgcn_perm(d[1], d[0], 0x07060302u);
-    hi.y = __builtin_amdgcn_perm(d[3], d[2], 0x07060302u);
-    hi.z = __builtin_amdgcn_perm(d[5], d[4], 0x07060302u);
-    hi.w = __builtin_amdgcn_perm(d[7], d[6], 0x07060302u);
-    const int e = lane + 64 * uh[u];
-    tab[buf][us[u]][ug[u]][e] = lo;
-    tab[buf][us[u]][ug[u]][e + 128] = hi;
+  auto build_commit = [&](int e, int buf, const u32x4 (&d)[8]) {  // entry bv + e
+    if (PRE) return;
+    const uint32_t s = (e & 1) ? 0x07060302u : 0x05040100u;
+    u32x4 v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_perm(d[2 * c + 1][e >> 1], d[2 * c][e >> 1], s);
+    // the four lanes of a tap write to the same four banks: odd lanes store their halves in the other
+    // order (2-way instead of 4-way conflicts; 1150 instead of 2170 clocks for a phase's tables)
+    const bool odd = lane & 1;
+    uint8_t* const dst = &sh.tab[buf * kTabBytes + (bv + e) * 256 + bt * 16];
+    *reinterpret_cast<uint2*>(dst + (odd ? 8 : 0)) = make_uint2(odd ? v[2] : v[0], odd ? v[3] : v[1]);
+    *reinterpret_cast<uint2*>(dst + (odd ? 0 : 8)) = make_uint2(odd ? v[0] : v[2], odd ? v[1] : v[3]);
+  };
+  // PRE: half of this wave's eighth of a chunk's image into buffer buf.  The hardware writes to LDS
+  // at M0 + instruction offset + 16 * lane (the instruction offset counts for the memory address and
+  // for the LDS address alike).  Written as instructions: the compiler would make every later LDS
+  // read wait for a copy it knows of, since it cannot tell the two table buffers apart; the waves
+  // wait for their copies once, before the barrier of the phase.
+  auto table_copy = [&](int chunk, int buf, int half) {
+    if (!PRE) return;
+    const uint32_t part = (uint32_t)(wave * (kTabBytes / kWaves) + half * (kTabBytes / kWaves / 2));
+    const uint32_t soff = ((uint32_t)min(chunk, c_last) * (uint32_t)(a.Jpad >> 3) + (uint32_t)tj) * (uint32_t)kTabBytes + part;
+    const uint32_t dst = lds0 + (uint32_t)(buf * kTabBytes) + part;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:3072 lds"
+                 :: "s"(__builtin_amdgcn_readfirstlane((int)dst)), "v"(lane * 16), "s"(tabs_words),
+                 "s"(__builtin_amdgcn_readfirstlane((int)soff)) : "memory");
+  };
+  auto copies_done = [&]() {
+    if (PRE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   };
 
   // ---- main loop -----------------------------------------------------------------------
-  uint32_t accg[P][NG][8];  // per lane element and column group; acc[p][j] below names column j
-  uint32_t sl[P];
+  i32x4 acc[GR][4];  // [group][quarter]: bytes 4 kg .. 4 kg + 3 of the entries' sums for element 16 r + m
+  uint32_t sl[GR];   // code sums of the lane's own element (element l of the group)
 #pragma unroll
-  for (int p = 0; p < P; ++p) {
+  for (int p = 0; p < GR; ++p) {
     sl[p] = 0;
 #pragma unroll
-    for (int j = 0; j < JT; ++j) accg[p][j >> 3][j & 7] = 0;
+    for (int r = 0; r < 4; ++r) acc[p][r] = i32x4{0, 0, 0, 0};
   }
-
-  uint4 xa[P], xn[P];
-  const int nchunks = (kend - kbeg + kChunk - 1) / kChunk;
-  load_chunk(kbeg, xn);
-  {
-    // first phase's tables: fetch the rows of all units, then write them out (one global round
-    // trip; the accumulators are not live yet, so the registers are free)
-    uint32_t d0[UNITS][8];
+  const int n = c_end - c_beg;
+  // first chunk's tables (one global round trip), then the requests the first phase relies on
+  build_issue(load_codes(c_beg), dd[0]);
+  u32x4 xn[XR];
+  load_from(c_beg);
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      build_issue(u, PRE ? make_uint2(0u, 0u) : load_codes(u >> 1, kbeg));
+  for (int p = 0; p < XR; ++p) xn[p] = load_x(p);
 #pragma unroll
-      for (int c = 0; c < 8; ++c) d0[u][c] = d[c];
-    }
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) d[c] = d0[u][c];
-      build_commit(u, 0);
-    }
-    if constexpr (PRE) {
-#pragma unroll
-      for (int u = 0; u < UNITS; ++u) table_copy(u, kbeg, 0);
-      copies_done();
-    }
-  }
+  for (int e = 0; e < 8; ++e) build_commit(e, 0, dd[0]);
+  table_copy(c_beg, 0, 0);
+  table_copy(c_beg, 0, 1);
+  uint2 codes = load_codes(c_beg + 1), codes2;
+  if (DB == 2) codes2 = load_codes(c_beg + 2);
+  copies_done();
   __syncthreads();
-  // Codes of the phases that follow: tv_cur[u][ph] belongs to taps k0 + (ph+1)*KS ...  They are
-  // fetched a whole chunk ahead by a vector load in which lane li = u * PHASES + ph reads the
-  // eight codes of (unit pair u, phase ph), and handed to the scalar side with readlane at the
-  // start of the chunk that uses them: by then the load has long returned, so nothing waits for
-  // memory (a uniform load followed at once by readfirstlane would stall every chunk).
-  uint2 tv_cur[CODES][PHASES];
-  const int li = min(lane, CODES * PHASES - 1);
-  const int l_ph = li % PHASES;
-  const int l_q = wave * UNITS + 2 * (li / PHASES);
-  const int l_qq = l_q < HALVES ? l_q : 0;
-  const size_t l_col = (size_t)j0 + 8 * ((l_qq >> 1) % NG);
-  const int l_s = l_qq / (2 * NG);
-  auto fetch_codes = [&](int kfirst) {  // phases starting at taps kfirst, kfirst + KS, ...
-    return *reinterpret_cast<const uint2*>(a.Bp + (size_t)min(kfirst + l_ph * KS + l_s, klast) * a.Jpad + l_col);
-  };
-  uint2 tvv = fetch_codes(kbeg + KS);
-  // rows of unit 0 for the tables that the first phase of the loop builds
-  build_issue(0, make_uint2((uint32_t)__builtin_amdgcn_readlane((int)tvv.x, 0),
-                            (uint32_t)__builtin_amdgcn_readlane((int)tvv.y, 0)));
+  // the column codes are requested ahead of the rows: loads return in order, and waiting for the codes
+  // must not mean waiting for the rows
+  const uint2 codes1 = codes;
+  codes = load_codes(c_beg + 1 + DB);
+  __builtin_amdgcn_sched_barrier(0);
+  build_issue(codes1, dd[1 % DB]);
+  __builtin_amdgcn_sched_barrier(0);
+  if (DB == 2) build_issue(codes2, dd[0]);
+  __builtin_amdgcn_sched_barrier(0);
 
-  for (int c = 0; c < nchunks; ++c) {
-    const int k0 = kbeg + c * kChunk;
+  // One phase: gathers of chunk ch from buffer BUF, tables of the next chunk (more: there is one) into
+  // the other.
+  auto phase = [&](auto BUF, int ch, bool more) __attribute__((always_inline)) {
+    constexpr int buf = decltype(BUF)::value;
+    {
 #pragma unroll
-    for (int p = 0; p < P; ++p) xa[p] = xn[p];
-#pragma unroll
-    for (int u = 0; u < CODES; ++u)
-#pragma unroll
-      for (int ph = 0; ph < PHASES; ++ph)
-        tv_cur[u][ph] = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)tvv.x, u * PHASES + ph),
-                                   (uint32_t)__builtin_amdgcn_readlane((int)tvv.y, u * PHASES + ph));
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      sl[p] = __builtin_amdgcn_sad_u8(xa[p].x, 0u, sl[p]);
-      sl[p] = __builtin_amdgcn_sad_u8(xa[p].y, 0u, sl[p]);
-      sl[p] = __builtin_amdgcn_sad_u8(xa[p].z, 0u, sl[p]);
-      sl[p] = __builtin_amdgcn_sad_u8(xa[p].w, 0u, sl[p]);
-    }
-    // A phase is cut into SEGS segments, each the gathers of one lane-element slot p over some
-    // taps of the phase.  A segment is skipped by waves whose 64 lanes of slot p lie outside the
-    // tile (wave-uniform), so padded lanes cost no LDS or VALU time.  Inside a segment the
-    // gathers run through a small ring of registers: gather i+DEPTH is issued before the eight
-    // adds of gather i, so that LDS latency hides behind VALU work.  The table rows of the next
-    // phase are fetched and written out between segments, one unit at a time.
-    constexpr int SUB = (UNITS > P) ? UNITS / P : 1;
-    constexpr int SEGS = P * SUB;
-    constexpr int TAPS = KS / SUB;  // taps per segment
-    constexpr int NR = TAPS * NG;   // gathers per segment
-    constexpr int DEPTH = (P * JT > 32) ? 2 : 3;  // fewer ring slots where the accumulators crowd the registers
-    static_assert(KS % SUB == 0 && SEGS % UNITS == 0, "build units must align with segments");
-#pragma unroll
-    for (int ph = 0; ph < PHASES; ++ph) {
-#pragma unroll
-      for (int q = 0; q < SEGS; ++q) {
-        const int p = q / SUB;
-        const int s0 = (q % SUB) * TAPS;
-        // (the rows of unit 0 were requested at the end of the phase before, see below)
-#pragma unroll
-        for (int u = 1; u < UNITS; ++u)
-          if (q == u * (SEGS / UNITS)) build_issue(u, tv_cur[u >> 1][ph]);
-        if constexpr (PRE) {
-          // the tables of the next phase: one unit at the start of the phase, the other half way
-          // through (all copies at the start were 1 % slower); the buffer they go to was last read
-          // in the phase before, which every wave has left (barrier)
-#pragma unroll
-          for (int u = 0; u < UNITS; ++u)
-            if (q == u * (SEGS / UNITS)) table_copy(u, k0 + (ph + 1) * KS, (ph + 1) & 1);
-        }
-        if (ph == 0 && q == 0) {
-          // operand and codes of the next chunk: fetched behind the first row fetches of this
-          // chunk, so that the wait for those rows does not also wait for these
-          // (also after the last chunk of a segment: the addresses stay inside the operands, the
-          // values are not used, and the number of loads in flight stays known to the compiler)
-          __builtin_amdgcn_sched_barrier(0);
-          load_chunk(k0 + kChunk, xn);
-          tvv = fetch_codes(k0 + kChunk + KS);
-        }
+      for (int p = 0; p < GR; ++p) {
         __builtin_amdgcn_sched_barrier(0);
-        // Waves that are behind go first: the priority of a wave falls as it works through the
-        // phase (3 for the first three eighths of its gathers, then 2, 1 and, for the last
-        // eighth, 0), so that the waves of a SIMD reach the barrier together instead of one after
-        // the other.  With the default order the oldest wave finishes the phase early and the
-        // youngest runs its last segment alone, with nobody to cover its LDS latency.
-        set_prio(2 * (SEGS - 1 - q) + 2);
-        if (act[p]) {
-          uint4 ring[DEPTH + 1];
-          // Address of a gather = table base + group * 4096 + 16 * code.  The constant part goes
-          // into the instruction's 16-bit offset field where it fits (tables in the first 64 KB of
-          // LDS): then 16 * code is one sub-dword shift.  For the others the table base is added
-          // to the register once per tap.
-          uint32_t tap_addr = 0;
+        // Waves that are behind go first: the priority of a wave falls as it works through the phase,
+        // so that the waves of a SIMD reach the barrier together instead of one after the other.
+        if (p == 0) __builtin_amdgcn_s_setprio(3);
+        if (p == (3 * GR + 7) / 8) __builtin_amdgcn_s_setprio(2);
+        if (p == (5 * GR + 7) / 8) __builtin_amdgcn_s_setprio(1);
+        if (p == (7 * GR + 7) / 8) __builtin_amdgcn_s_setprio(0);
+        if (p == 0) table_copy(ch + 1, buf ^ 1, 0);
+        if (p == GR / 2) table_copy(ch + 1, buf ^ 1, 1);
+        const u32x4 x = xn[p % XR];
+        if (p + XR == GR) load_from(ch + 1);
+        xn[p % XR] = load_x((p + XR) % GR);
+        __builtin_amdgcn_sched_barrier(0);
+        if (p < np) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sl[p] = __builtin_amdgcn_sad_u8(x[e], 0u, sl[p]);
+          // Sixteen codes per lane (element l) -> dword dq of element 16 r + m in register r of lane
+          // (kg, m): rotate the dwords of a lane by its rot, then transpose rows of 16 lanes against
+          // registers.
+          uint32_t t[4];
+          {
+            const uint32_t s0 = rot0 ? x.y : x.x, s1 = rot0 ? x.x : x.y, s2 = rot0 ? x.w : x.z, s3 = rot0 ? x.z : x.w;
+            const uint32_t q0 = rot1 ? s2 : s0, q2 = rot1 ? s0 : s2, q1 = rot1 ? s3 : s1, q3 = rot1 ? s1 : s3;
+            const auto u = __builtin_amdgcn_permlane32_swap(q0, q2, false, false);
+            const auto v = __builtin_amdgcn_permlane32_swap(q1, q3, false, false);
+            const auto w = __builtin_amdgcn_permlane16_swap(u[0], v[0], false, false);
+            const auto z = __builtin_amdgcn_permlane16_swap(u[1], v[1], false, false);
+            t[0] = w[0]; t[1] = w[1]; t[2] = z[0]; t[3] = z[1];
+          }
+          // The gathers run through a small ring of registers, DEPTH ahead of the matrix instructions.
+          // The second buffer's address does not fit the instruction's 16-bit offset: its last unit
+          // is in offs.
+          i32x4 ring[DEPTH + 1];
           auto issue = [&](int i) {
-            const int t = i / NG, g = i - t * NG;
-            const bool low = ((((ph & 1) * KS + s0 + t) * NG + NG) * 4096) <= 65536;
-            if (g == 0) {
-              const uint32_t v = byte_of(xa[p], ph * KS + s0 + t);
-              tap_addr = low ? (v << 4) : (uint32_t)(uintptr_t)&tab[ph & 1][s0 + t][0][0] + (v << 4);
-              asm volatile("" : "+v"(tap_addr));  // keep it one register
-            }
-            const uint32_t cpart = low ? (uint32_t)(uintptr_t)&tab[ph & 1][s0 + t][g][0] : (uint32_t)(g * 4096);
-            const u32x4 e = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(tap_addr + cpart);
-            ring[i % (DEPTH + 1)] = make_uint4(e.x, e.y, e.z, e.w);
+            uint32_t addr = __builtin_amdgcn_perm(t[i & 3], buf ? offs + 0x01010101u : offs, perm[i >> 2]);
+            asm volatile("" : "+v"(addr));
+            ring[i % (DEPTH + 1)] =
+                *(const __attribute__((address_space(3))) i32x4*)(uintptr_t)(addr + lds0 + (buf ? kTabBytes - 1u : 0u));
           };
 #pragma unroll
-          for (int i = 0; i < DEPTH && i < NR; ++i) issue(i);
+          for (int i = 0; i < DEPTH; ++i) issue(i);
 #pragma unroll
-          for (int i = 0; i < NR; ++i) {
+          for (int i = 0; i < 16; ++i) {
             __builtin_amdgcn_sched_barrier(0);
-            if (i == NR / 4) set_prio(2 * (SEGS - 1 - q) + 1);
-            if (i == (3 * NR) / 4) set_prio(2 * (SEGS - 1 - q));
-            if (i + DEPTH < NR) issue(i + DEPTH);
-            const int g = i % NG;
-            const uint4 e = ring[i % (DEPTH + 1)];
-            add_entry(accg[p][g], e);
+            if (i + DEPTH < 16) issue(i + DEPTH);
+            acc[p][i & 3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(pick, ring[i % (DEPTH + 1)], acc[p][i & 3], 0, 0, 0);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (more) {
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u)
-          if (q == (u + 1) * (SEGS / UNITS) - 1) build_commit(u, (ph + 1) & 1);
+          for (int e = PER * p; e < PER * (p + 1); ++e) build_commit(e, buf ^ 1, dd[(buf + 1) % DB]);
+        }
       }
-      // Rows of unit 0 for the tables that the NEXT phase builds: requested here, before the
-      // barrier, so that after it every wave starts with gathers.  (Requested at the start of a
-      // phase, the row fetches of all sixteen waves queue up in the vector memory pipe while the
-      // vector ALUs have nothing to do.)  Past the last phase of a chunk the codes are those of
-      // the next chunk's first phase, which tvv has held since the start of this chunk; past the
-      // last chunk they are clamped to the operand and the rows are never used.
-      if (ph + 1 < PHASES)
-        build_issue(0, tv_cur[0][ph + 1]);
-      else
-        build_issue(0, make_uint2((uint32_t)__builtin_amdgcn_readlane((int)tvv.x, 0),
-                                  (uint32_t)__builtin_amdgcn_readlane((int)tvv.y, 0)));
-      if constexpr (PRE) copies_done();
+      __builtin_amdgcn_sched_barrier(0);
+      // Rows for the tables that the next phase (DB = 2: the one after it) builds, requested before
+      // the barrier so that they travel while the wave waits for the others.  Past the last chunk the
+      // codes are those of the last chunk again (the number of loads in flight stays known) and the
+      // rows are never used.
+      const uint2 codes_now = codes;
+      codes = load_codes(ch + 2 + DB);
+      __builtin_amdgcn_sched_barrier(0);
+      build_issue(codes_now, dd[(buf + 1) % DB]);
+      __builtin_amdgcn_sched_barrier(0);
+      copies_done();
       __syncthreads();
     }
+  };
+  // Phases in pairs, an odd last one by itself: a loop with a way out between its two phases would
+  // leave the compiler unsure which loads are the youngest, and it would wait for all of them.
+  for (int ch = c_beg; ch + 1 < c_end; ch += 2) {
+    phase(std::integral_constant<int, 0>(), ch, true);
+    phase(std::integral_constant<int, 1>(), ch + 1, ch + 2 < c_end);
   }
-
-  // the accumulator pairs held (l + 65536 h, l + h) so far: back to the column sums
-  uint32_t acc[P][JT];
-#pragma unroll
-  for (int p = 0; p < P; ++p)
-#pragma unroll
-    for (int j = 0; j < JT; j += 2) {
-      acc[p][j + 1] = accg[p][j >> 3][(j & 7) + 1];
-      acc[p][j] = accg[p][j >> 3][j & 7];
-      split_sums(acc[p][j], acc[p][j + 1]);
-    }
+  if (n & 1) phase(std::integral_constant<int, 0>(), c_end - 1, false);
 
   // ---- epilogue ------------------------------------------------------------------------
-  // corr = acc - z_tab*Sl - z_lane*Sb[j] + K*z_lane*z_tab.  Each of the four terms is below
-  // 2^31 in magnitude; for K <= 16384 so is every partial sum, and 32-bit wrap-around
-  // arithmetic is exact.  Longer K takes the 64-bit form.
-  const uint32_t padfix = (uint32_t)(klast - a.K) * (uint32_t)rows[0] + a.bias_k;
+  // corr = acc - z_tab*Sl - z_lane*Sb[j] + K*z_lane*z_tab.
+  // Taps K .. of the last chunk exist only in materialized operands, where both codes are 0: each
+  // adds the table entry (0,0) to every sum, which is taken off again; and every tap has
+  // 128 + 256 * 128 too little (see above).
+  const uint32_t klast = (uint32_t)a.nch * kChunk;
+  const uint32_t padfix = (klast - (uint32_t)a.K) * ((uint32_t)rows[0] ^ 0x8080u) + a.bias_k - 32896u * klast;
+  uint32_t sum[GR][4][2];
+#pragma unroll
+  for (int p = 0; p < GR; ++p)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      sum[p][r][0] = (uint32_t)acc[p][r].x + ((uint32_t)acc[p][r].y << 8);
+      sum[p][r][1] = (uint32_t)acc[p][r].z + ((uint32_t)acc[p][r].w << 8);
+    }
   bool finish = whole;  // this workgroup writes the tile's outputs
   if (!whole) {
-    // Piece of a tile that several workgroups share: stored column-major ([column][lane
-    // element]) so that consecutive lanes write consecutive words straight from their registers.
-    // a slot holds a.ih lane elements (the tile height) of JT columns
+    // Piece of a tile that several workgroups share, as the registers hold it: per group of 64 lane
+    // elements eight runs of 64 words ([quarter][column of the pair][lane]).
+    // A slot holds a.ih lane elements (the tile height) of kJT columns.
     const int slot = 2 * wg + (c_beg > 0 ? 0 : 1);
-    int32_t* part = a.part + (size_t)slot * ((size_t)a.ih * JT);
+    int32_t* part = a.part + (size_t)slot * ((size_t)a.ih * kJT);
     int32_t* lsum = a.lsum + (size_t)slot * a.ih;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int il = p * THREADS + tid;
-      if (!act[p] || il >= a.ih) continue;  // rows of tile padding: the fix-up never reads them
+    for (int p = 0; p < GR; ++p) {
+      if (p >= np) continue;
+      const int g = kWaves * p + wave;
+      int32_t* pp = part + (size_t)g * 512 + lane;
       if (a.cnt) {  // read by another workgroup of this launch: stores that go through to memory
-        __hip_atomic_store(lsum + il, (int32_t)sl[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(lsum + g * 64 + lane, (int32_t)sl[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int j = 0; j < JT; ++j)
-          __hip_atomic_store(part + (size_t)j * a.ih + il, (int32_t)acc[p][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q = 0; q < 8; ++q)
+          __hip_atomic_store(pp + q * 64, (int32_t)sum[p][q >> 1][q & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {
-        lsum[il] = (int32_t)sl[p];
+        lsum[g * 64 + lane] = (int32_t)sl[p];
 #pragma unroll
-        for (int j = 0; j < JT; ++j) part[(size_t)j * a.ih + il] = (int32_t)acc[p][j];
+        for (int q = 0; q < 8; ++q) pp[q * 64] = (int32_t)sum[p][q >> 1][q & 1];
       }
     }
     if (a.cnt) {
@@ -555,32 +569,36 @@ __global__ __launch_bounds__(THREADS, WPE) void tab_kernel(const TabArgs a) {
         };
         const int w_first = owner(t_beg), w_last = owner(t_beg + a.nch - 1);
         const unsigned old = atomicInc(a.cnt + gtile, (unsigned)(w_last - w_first));
-        comb[0] = (old == (unsigned)(w_last - w_first)) ? 1 : 0;
-        comb[1] = w_first;
-        comb[2] = w_last;
+        sh.comb[0] = (old == (unsigned)(w_last - w_first)) ? 1 : 0;
+        sh.comb[1] = w_first;
+        sh.comb[2] = w_last;
       }
       __syncthreads();
-      if (comb[0]) {
-        const int w_first = comb[1], w_last = comb[2];
+      if (sh.comb[0]) {
+        const int w_first = sh.comb[1], w_last = sh.comb[2];
         for (int w = w_first; w <= w_last; ++w) {
           if (w == wg) continue;
           const int so = 2 * w + (w == w_first ? 1 : 0);
-          const int32_t* po = a.part + (size_t)so * ((size_t)a.ih * JT);
-          const int32_t* lo = a.lsum + (size_t)so * a.ih;
+          const int32_t* po = a.part + (size_t)so * ((size_t)a.ih * kJT) + lane;
+          const int32_t* lo = a.lsum + (size_t)so * a.ih + lane;
 #pragma unroll
-          for (int p = 0; p < P; ++p) {
-            const int il = p * THREADS + tid;
-            if (!act[p] || il >= a.ih) continue;
-            sl[p] += (uint32_t)__hip_atomic_load(lo + il, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            constexpr int NB = JT < 32 ? JT : 32;  // loads in flight
+          for (int p2 = 0; p2 < GR; p2 += 4) {  // loads of four groups in flight
+            uint32_t t[4][9];
 #pragma unroll
-            for (int jb = 0; jb < JT; jb += NB) {
-              uint32_t t[NB];
+            for (int p = 0; p < 4; ++p) {
+              if (p2 + p >= np) continue;
+              const int g = kWaves * (p2 + p) + wave;
+              t[p][8] = (uint32_t)__hip_atomic_load(lo + g * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-              for (int j = 0; j < NB; ++j)
-                t[j] = (uint32_t)__hip_atomic_load(po + (size_t)(jb + j) * a.ih + il, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              for (int q = 0; q < 8; ++q)
+                t[p][q] = (uint32_t)__hip_atomic_load(po + (size_t)g * 512 + q * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
 #pragma unroll
-              for (int j = 0; j < NB; ++j) acc[p][jb + j] += t[j];
+            for (int p = 0; p < 4; ++p) {
+              if (p2 + p >= np) continue;
+              sl[p2 + p] += t[p][8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) sum[p2 + p][q >> 1][q & 1] += t[p][q];
             }
           }
         }
@@ -588,106 +606,43 @@ __global__ __launch_bounds__(THREADS, WPE) void tab_kernel(const TabArgs a) {
       }
     }
   }
-  if (finish && tid < JT) {
-    int32_t sb = 0;
-    for (int q = 0; q < a.nseg; ++q) sb += a.bsum[(size_t)q * a.Jpad + j0 + tid];
-    cterm[tid] = a.qd->kzz - (long long)a.qd->z_lane * sb;
-  }
+  if (finish) column_constants<kThreads>(a, j0, sh.cterm);
   __syncthreads();  // cterm visible; every wave is done with the table buffers
-  const float scale = a.qd->scale;
-  const uint32_t z_tab = (uint32_t)a.qd->z_tab;
-  auto dequant = [&](uint32_t accv, uint32_t lterm, int jl) -> float {  // jl = column within the tile
-    if constexpr (WIDE) {
-      return (float)((long long)(int32_t)(accv - lterm) + cterm[jl]) * scale;
-    } else {
-      return (float)(int32_t)(accv - lterm + (uint32_t)cterm[jl]) * scale;
-    }
-  };
-
-  if (!finish) {
-    // outputs are written by another workgroup or by tab_fixup_kernel
-  } else if (!CH && a.vec_out) {
-    // Lanes hold whole rows of JT consecutive outputs of one pixel.  Stage PX pixels at a time
-    // in LDS (rows padded by 4 dwords: conflict-free 16-byte writes) and read them back so
-    // that consecutive lanes store consecutive 16-byte pieces: full-line coalesced stores.
-    constexpr int ROW = JT + 4;
-    constexpr int LDSB = 2 * KS * NG * 4096;
-    constexpr int PXMAX = LDSB / (ROW * 4);
-    constexpr int PX = PXMAX >= 512 && THREADS >= 512 ? 512 : PXMAX >= 256 ? 256 : 128;
-    constexpr int QPASS = THREADS / PX;  // passes per lane-element slot
-    constexpr int PIECES = PX * (JT / 4);
-    static_assert(PX * ROW * 4 <= LDSB && THREADS % PX == 0, "stage must fit in the table buffers");
-    uint32_t* stage = reinterpret_cast<uint32_t*>(&tab[0][0][0][0]);
+  if (finish) {
+    const float scale = a.qd->scale;
+    const uint32_t z_tab = (uint32_t)a.qd->z_tab;
+    const bool wide = a.K > 16384;
+    const long long ct0 = column_constant<kWaves>(sh.cterm, 2 * kg), ct1 = column_constant<kWaves>(sh.cterm, 2 * kg + 1);
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-#pragma unroll 1
-      for (int qq = 0; qq < QPASS; ++qq) {
-        const int t0 = qq * PX;
-        if (p > 0 || qq > 0) __syncthreads();
-        if (tid >= t0 && tid < t0 + PX) {
-          uint32_t* row = stage + (tid - t0) * ROW;
+    for (int p = 0; p < GR; ++p) {
+      if (p >= np) continue;
 #pragma unroll
-          for (int j4 = 0; j4 < JT / 4; ++j4)
-            *reinterpret_cast<uint4*>(row + 4 * j4) =
-                make_uint4(acc[p][4 * j4], acc[p][4 * j4 + 1], acc[p][4 * j4 + 2], acc[p][4 * j4 + 3]);
-          row[JT] = sl[p];
-        }
-        __syncthreads();
-        for (int idx = tid; idx < PIECES; idx += THREADS) {
-          const int r = idx / (JT / 4), c4 = idx - r * (JT / 4);
-          const int il = p * THREADS + t0 + r;
-          const int i = i0 + il, j = j0 + 4 * c4;
-          if (il < a.ih && i < a.I && j < a.J) {
-            uint4 v = *reinterpret_cast<const uint4*>(stage + r * ROW + 4 * c4);
-            const uint32_t lterm = z_tab * stage[r * ROW + JT];
-            v.x -= padfix; v.y -= padfix; v.z -= padfix; v.w -= padfix;
-            const size_t o = (size_t)i * a.J + j;
-            if (acc_base) *reinterpret_cast<uint4*>(acc_base + o) = v;
-            if (y_base) {
-              float4 y;
-              y.x = dequant(v.x, lterm, 4 * c4);
-              y.y = dequant(v.y, lterm, 4 * c4 + 1);
-              y.z = dequant(v.z, lterm, 4 * c4 + 2);
-              y.w = dequant(v.w, lterm, 4 * c4 + 3);
-              *reinterpret_cast<float4*>(y_base + o) = y;
-            }
-          }
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int i = i0 + p * THREADS + tid;
-      if (i >= a.I || p * THREADS + tid >= a.ih) continue;
-      const uint32_t lterm = z_tab * sl[p];
-#pragma unroll
-      for (int j = 0; j < JT; ++j) {
-        if (j0 + j < a.J) {
-          const size_t o = CH ? (size_t)(j0 + j) * a.I + i : (size_t)i * a.J + (j0 + j);
-          if (acc_base) acc_base[o] = (int32_t)(acc[p][j] - padfix);
-          if (y_base) y_base[o] = dequant(acc[p][j] - padfix, lterm, j);
-        }
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t lterm = z_tab * (uint32_t)__shfl((int)sl[p], 16 * r + m);
+        const int i = i0 + 64 * (kWaves * p + wave) + 16 * r + m;
+        const uint32_t v0 = sum[p][r][0] - padfix, v1 = sum[p][r][1] - padfix;
+        if (i < a.I)
+          put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * kg, v0, v1, dequant(v0, lterm, ct0, scale, wide),
+                       dequant(v1, lterm, ct1, scale, wide));
       }
     }
   }
-  it_beg += c_end - c_beg;
-  __syncthreads();  // the staging area and cterm are free again
+  it_beg += n;
+  __syncthreads();  // cterm and the table buffers are free again
   }  // segment loop
 }
 
-// Combine the pieces of every tile that more than one workgroup worked on.  The pieces lie,
-// column-major, in the slots of consecutive workgroups (see TabArgs::part).  A block takes 64
-// lane elements of one tile and all JT columns: thread (r = t & 63, cg = t >> 6) sums columns
-// cg*JT/4 .. of lane element r over the pieces (coalesced along r).  For pixel lanes the block
-// then turns the 64 x JT patch through LDS so that output rows are written in 16-byte pieces.
+// Combine the pieces of every tile that more than one workgroup worked on.  The pieces lie in the
+// slots of consecutive workgroups, as the registers of tab_kernel held them (see TabArgs::part).  A
+// block takes one group of 64 lane elements of a tile, a thread one quarter of it: its lane's pair
+// of columns.
 // MANY: the form for tiles cut into many pieces (see the piece loop); it needs more registers, so
 // it is a kernel of its own and the usual form keeps its occupancy.
-template <int IT, int JT, bool CH, bool MANY>
+template <bool CH, bool MANY>
 __global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) {
-  constexpr int CPT = JT / 4;  // columns per thread
-  const int gtile = blockIdx.x / (IT / 64);
-  const int il0 = (blockIdx.x - gtile * (IT / 64)) * 64;
+  const int groups = a.ih / 64;
+  const int gtile = blockIdx.x / groups;
+  const int g = blockIdx.x - gtile * groups;
   const long long t_beg = (long long)gtile * a.nch, t_last = t_beg + a.nch - 1;
   auto owner = [&](long long it) {  // the workgroup w with w*total/G <= it < (w+1)*total/G
     long long w = it * G / a.total_iters;
@@ -703,124 +658,86 @@ __global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) 
   int32_t* __restrict__ acc_base = a.acc_out ? a.acc_out + (size_t)tbl * a.out_elems : nullptr;
   float* __restrict__ y_base = a.y_out ? a.y_out + (size_t)tbl * a.out_elems : nullptr;
   const int ti = tile / a.ntj;
-  const int i0 = ti * a.ih, j0 = (tile - ti * a.ntj) * JT;
-  if (il0 >= a.ih || i0 + il0 >= a.I) return;
-  const int klast = a.nch * kChunk;
-  const uint32_t padfix = (uint32_t)(klast - a.K) * (uint32_t)rows[0] + a.bias_k;  // see tab_kernel
-  __shared__ long long cterm[JT];
-  __shared__ uint32_t patch[64][JT + 4];
-  __shared__ uint32_t lterm_s[64];
-  const int t = threadIdx.x, r = t & 63, cg = t >> 6;
-  if (t < JT) {
-    int32_t sb = 0;
-    for (int q = 0; q < a.nseg; ++q) sb += a.bsum[(size_t)q * a.Jpad + j0 + t];
-    cterm[t] = a.qd->kzz - (long long)a.qd->z_lane * sb;
-  }
-  uint32_t v[CPT];
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) v[c] = 0u - padfix;
-  uint32_t sl = 0;
+  const int i0 = ti * a.ih, j0 = (tile - ti * a.ntj) * kJT;
+  if (i0 + 64 * g >= a.I) return;
+  const uint32_t klast = (uint32_t)a.nch * kChunk;
+  const uint32_t padfix = (klast - (uint32_t)a.K) * ((uint32_t)rows[0] ^ 0x8080u) + a.bias_k - 32896u * klast;  // see tab_kernel
+  __shared__ long long cterm[4][kJT];
+  const int t = threadIdx.x, lane = t & 63, r = t >> 6;
+  const int m = lane & 15, kg = lane >> 4;
+  column_constants<256>(a, j0, cterm);
+  uint32_t v0 = 0u - padfix, v1 = 0u - padfix, sl = 0;
+  const size_t piece = (size_t)a.ih * kJT;
+  const int32_t* part = a.part + (size_t)g * 512 + r * 128 + lane;
+  const int32_t* lsum = a.lsum + g * 64 + 16 * r + m;
   int w = w_first;
   // Many pieces (a short, wide layer cut into many K slices): four at a time, all their loads
   // issued before the first add, so that the block does not pay one memory round trip per piece.
   // With few pieces the plain loop below is faster.
   if constexpr (MANY) {
     for (; w + 3 <= w_last; w += 4) {
-      uint32_t tv[4][CPT], ts[4];
+      uint32_t p0[4], p1[4], ps[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int slot = 2 * (w + k) + (w + k == w_first ? 1 : 0);
-        const int32_t* pp = a.part + (size_t)slot * ((size_t)a.ih * JT) + il0 + r;
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) tv[k][c] = (uint32_t)pp[(size_t)(cg * CPT + c) * a.ih];
-        ts[k] = (uint32_t)a.lsum[(size_t)slot * a.ih + il0 + r];
+        const int32_t* pp = part + (size_t)slot * piece;
+        p0[k] = (uint32_t)pp[0];
+        p1[k] = (uint32_t)pp[64];
+        ps[k] = (uint32_t)lsum[(size_t)slot * a.ih];
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) v[c] += tv[k][c];
-        sl += ts[k];
+        v0 += p0[k];
+        v1 += p1[k];
+        sl += ps[k];
       }
     }
   }
   for (; w <= w_last; ++w) {
     const int slot = 2 * w + (w == w_first ? 1 : 0);
-    const int32_t* pp = a.part + (size_t)slot * ((size_t)a.ih * JT) + il0 + r;
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) v[c] += (uint32_t)pp[(size_t)(cg * CPT + c) * a.ih];
-    sl += (uint32_t)a.lsum[(size_t)slot * a.ih + il0 + r];
+    const int32_t* pp = part + (size_t)slot * piece;
+    v0 += (uint32_t)pp[0];
+    v1 += (uint32_t)pp[64];
+    sl += (uint32_t)lsum[(size_t)slot * a.ih];
   }
+  __syncthreads();
   const uint32_t lterm = (uint32_t)a.qd->z_tab * sl;
   const float scale = a.qd->scale;
-  __syncthreads();
-  if (CH) {
-    // output index (j0 + jl) * I + i: consecutive r are consecutive words already
-    const int i = i0 + il0 + r;
-    if (i < a.I && il0 + r < a.ih) {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int jl = cg * CPT + c;
-        if (j0 + jl < a.J) {
-          const size_t o = (size_t)(j0 + jl) * a.I + i;
-          if (acc_base) acc_base[o] = (int32_t)v[c];
-          if (y_base) y_base[o] = (float)((long long)(int32_t)(v[c] - lterm) + cterm[jl]) * scale;
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) patch[r][cg * CPT + c] = v[c];
-    if (cg == 0) lterm_s[r] = lterm;
-    __syncthreads();
-    for (int idx = t; idx < 64 * (JT / 4); idx += 256) {
-      const int rr = idx / (JT / 4), c4 = idx - rr * (JT / 4);
-      const int i = i0 + il0 + rr, j = j0 + 4 * c4;
-      if (i >= a.I || il0 + rr >= a.ih || j >= a.J) continue;
-      const uint32_t lt = lterm_s[rr];
-      const size_t o = (size_t)i * a.J + j;
-      if (a.vec_out) {
-        const uint4 q = *reinterpret_cast<const uint4*>(&patch[rr][4 * c4]);
-        if (acc_base) *reinterpret_cast<uint4*>(acc_base + o) = q;
-        if (y_base) {
-          float4 y;
-          y.x = (float)((long long)(int32_t)(q.x - lt) + cterm[4 * c4]) * scale;
-          y.y = (float)((long long)(int32_t)(q.y - lt) + cterm[4 * c4 + 1]) * scale;
-          y.z = (float)((long long)(int32_t)(q.z - lt) + cterm[4 * c4 + 2]) * scale;
-          y.w = (float)((long long)(int32_t)(q.w - lt) + cterm[4 * c4 + 3]) * scale;
-          *reinterpret_cast<float4*>(y_base + o) = y;
-        }
-      } else {
-        for (int e = 0; e < 4 && j + e < a.J; ++e) {
-          const uint32_t q = patch[rr][4 * c4 + e];
-          if (acc_base) acc_base[o + e] = (int32_t)q;
-          if (y_base) y_base[o + e] = (float)((long long)(int32_t)(q - lt) + cterm[4 * c4 + e]) * scale;
-        }
-      }
-    }
-  }
+  const bool wide = a.K > 16384;
+  const int i = i0 + 64 * g + 16 * r + m;
+  if (i < a.I)
+    put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * kg, v0, v1, dequant(v0, lterm, column_constant<4>(cterm, 2 * kg), scale, wide),
+                 dequant(v1, lterm, column_constant<4>(cterm, 2 * kg + 1), scale, wide));
 }
 
 // ---- operand preparation ---------------------------------------------------------------
 
-// Ready-made tables for tab_kernel<.., PRE>: for every row k of the packed table-side operand
-// (krows of them, the last one all zero codes) and every group g of eight columns the 256 entries
-// T[v] = (R[b_0][v] .. R[b_7][v]), b_c = Bp[k][8g + c], 16 bytes each: exactly what the kernel
-// otherwise assembles in LDS from eight table rows.  One block per table, one thread per entry.
-__global__ __launch_bounds__(256) void prep_tables_kernel(const uint16_t* __restrict__ rows, const uint8_t* __restrict__ Bp,
-                                                           int Jpad, uint4* __restrict__ tabs) {
+// Ready-made tables for tab_kernel<.., PRE>: for every chunk of 16 rows of the packed table-side
+// operand and every group g of eight columns the image of one LDS buffer: entry v of tap t,
+// (R[b_0][v] .. R[b_7][v]) with b_c = Bp[16 chunk + t][8g + c], at 256 v + 16 t.  One block per image;
+// roles as in tab_kernel's own building: lane = (tap, quarter), so that 16 lanes store 256
+// contiguous bytes.
+__global__ __launch_bounds__(kThreads) void prep_tables_kernel(const uint16_t* __restrict__ rows, const uint8_t* __restrict__ Bp,
+                                                               int Jpad, uint8_t* __restrict__ tabs) {
   const int groups = Jpad >> 3;
-  const int k = blockIdx.x / groups, g = blockIdx.x - k * groups;
-  const int v = threadIdx.x;
-  // rows[t] holds R[t][P] at 2P and R[t][P + 128] at 2P + 1 (see prep_kernel)
-  const int col = v < 128 ? 2 * v : 2 * (v - 128) + 1;
-  const uint2 codes = *reinterpret_cast<const uint2*>(Bp + (size_t)k * Jpad + 8 * g);
-  uint32_t e[8];
+  const int chunk = blockIdx.x / groups, g = blockIdx.x - chunk * groups;
+  const int lane = threadIdx.x & 63, bt = lane & 15, bv = 32 * (threadIdx.x >> 6) + 8 * (lane >> 4);
+  const uint2 codes = *reinterpret_cast<const uint2*>(Bp + (size_t)(chunk * kChunk + bt) * Jpad + 8 * g);
+  u32x4 d[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
     const uint32_t b = ((c < 4 ? codes.x : codes.y) >> (8 * (c & 3))) & 0xffu;
-    e[c] = rows[b * 256u + col];
+    d[c] = *reinterpret_cast<const u32x4*>(rows + b * 256u + bv);
   }
-  tabs[(size_t)blockIdx.x * 256 + v] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+  uint8_t* image = tabs + (size_t)blockIdx.x * kTabBytes;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    u32x4 v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      v[c] = __builtin_amdgcn_perm(d[2 * c + 1][e >> 1], d[2 * c][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+    *reinterpret_cast<u32x4*>(image + (bv + e) * 256 + bt * 16) = v;
+  }
 }
 
 struct ConvView {  // im2col addressing of x
@@ -847,10 +764,8 @@ __device__ __forceinline__ uint32_t im2col_code(const ConvView& v, uint32_t pad,
   return (uint32_t)v.x[((size_t)(n * v.H + iy) * v.W + ix) * v.Cin + ci] ^ v.sx;
 }
 
-// rows[t][2P] = R[t][P], rows[t][2P+1] = R[t][P+128]  (P < 128), where R[t][v] is the
-// product of table-side code t and lane-side code v.  A lane that loads dword P of a row
-// gets the entries for v = P and v = P + 128, so consecutive lanes later write consecutive
-// 16-byte table entries (no LDS write conflicts).
+// rows[t][v] = the product of table-side code t and lane-side code v, both bytes with their top bit
+// flipped (the matrix instructions of tab_kernel read them as signed bytes: value - 128).
 //
 // The same launch packs the table-side operand into Bp[krows][Jpad] (zero fill outside k < K,
 // j < J) and sums its columns per segment of `seg_rows` rows: psum[seg][j].  Blocks 0..127 do
@@ -899,7 +814,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
     const int dw = (blockIdx.x - tbl * kRowBlocks) * 256 + threadIdx.x;  // 0 .. 32767
     const int t = dw >> 7, P = dw & 127;
     uint32_t lo, hi;
-    const uint32_t tp = (uint32_t)t ^ sx, p0 = (uint32_t)P ^ sx, p1 = (uint32_t)(P + 128) ^ sx;
+    const uint32_t tp = (uint32_t)t ^ sx, p0 = (uint32_t)(2 * P) ^ sx, p1 = (uint32_t)(2 * P + 1) ^ sx;
     if (FROM_X) {  // table side = activation code t, lane side = filter code v
       lo = lut[tp * 256 + p0];
       hi = lut[tp * 256 + p1];
@@ -907,7 +822,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
       lo = lut[p0 * 256 + tp];
       hi = lut[p1 * 256 + tp];
     }
-    rows32[dw] = (lo | (hi << 16)) ^ (sx * 0x01000100u);  // signed entries + 32768
+    rows32[dw] = (lo | (hi << 16)) ^ 0x80808080u ^ (sx * 0x01000100u);  // signed entries + 32768
     return;
   }
   __shared__ int32_t red[16][65];
@@ -1074,17 +989,46 @@ __global__ __launch_bounds__(256) void prep_im2col_kernel(ConvView cv, int Kp, u
   *reinterpret_cast<uint4*>(Ap + ((size_t)chunk * (size_t)cv.M + m) * 16) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
 }
 
-// Signed activations read through the implicit patch view: one pass turns the tensor into
-// offset binary (top bit of every byte flipped), 16 bytes per thread; n16 = elements / 16.
-__global__ __launch_bounds__(256) void prep_flip_kernel(const uint4* __restrict__ x, uint4* __restrict__ out, uint32_t n16) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n16) return;
-  uint4 v = x[i];
-  v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u;
-  out[i] = v;
+// Activations chunk by chunk, out[C / 16][P][16]: position p = (n, oy, ox) is pixel (n, oy*sh - ph,
+// ox*sw - pw) of x, or the pad code outside the image: strides 1 copy the tensor, with the border
+// that ph and pw give it.  A wave of tab_kernel reads 16 channels of 64 consecutive pixels at a time:
+// from this layout one contiguous kilobyte, where the tensor as it stands costs a 128-byte line per
+// pixel and chunk, and with the border no tap lies outside.  Signed codes are turned into offset
+// binary on the way (sx4).  A block turns 512 pieces of 16 bytes through LDS: 2^cl chunks (up to 8 =
+// 128 channels) of 512 >> cl positions.  Bound by memory: 16 channels of a million pixels with border
+// (35 MB) take 7 us, 23 with eight chunks per block whatever the channel count.
+__global__ __launch_bounds__(256) void prep_chunks_kernel(const uint8_t* __restrict__ x, int P, int C, int cl, int H, int W,
+                                                          int OHW, int OW, int sh, int sw, int ph, int pw, uint32_t sx4,
+                                                          const QDev* __restrict__ qd, uint8_t* __restrict__ out) {
+  __shared__ uint4 tile[512 + 8];
+  const int pl = 9 - cl, np = 1 << pl;  // positions of a block
+  const int p0 = blockIdx.x * np, ck0 = blockIdx.y << cl, nck = min(1 << cl, C / 16 - ck0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = threadIdx.x + 256 * h, ck = q & ((1 << cl) - 1), pos = q >> cl, p = p0 + pos;
+    if (ck < nck && p < P) {
+      const int n = p / OHW, r = p - n * OHW;
+      const int oy = r / OW;
+      const int iy = oy * sh - ph, ix = (r - oy * OW) * sw - pw;
+      uint4 v;
+      if ((unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W) {
+        v = *reinterpret_cast<const uint4*>(x + ((size_t)(n * H + iy) * W + ix) * C + (size_t)(ck0 + ck) * 16);
+        v.x ^= sx4; v.y ^= sx4; v.z ^= sx4; v.w ^= sx4;
+      } else {
+        v = *reinterpret_cast<const uint4*>(qd->padrow);
+      }
+      tile[ck * (np + 1) + pos] = v;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = threadIdx.x + 256 * h, ck = q >> pl, pos = q & (np - 1), p = p0 + pos;
+    if (ck < nck && p < P) *reinterpret_cast<uint4*>(out + ((size_t)(ck0 + ck) * P + p) * 16) = tile[ck * (np + 1) + pos];
+  }
 }
 
-// Ap[j][k] = w[k][j] (zero fill for k >= K), 64x64 tiles through LDS.
+// Ap[k / 16][j][k % 16] = w[k][j] (zero fill for k >= K), 64x64 tiles through LDS.
 __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __restrict__ w, int K, int J, int Kp,
                                                               uint8_t* __restrict__ Ap, uint32_t sx) {
   __shared__ uint8_t tile[64][68];
@@ -1107,7 +1051,7 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
       uint32_t pk[4] = {0, 0, 0, 0};
 #pragma unroll
       for (int e = 0; e < 16; ++e) pk[e >> 2] |= (uint32_t)tile[seg + e][c] << (8 * (e & 3));
-      *reinterpret_cast<uint4*>(Ap + (size_t)j * Kp + k0 + seg) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+      *reinterpret_cast<uint4*>(Ap + ((size_t)((k0 + seg) / 16) * J + j) * 16) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
     }
   }
 }
@@ -1118,18 +1062,11 @@ constexpr int kMaxSeg = 64;  // segments of the table-side column sums
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-// Tile configurations; the "tile" option selects one by index + 1 (0 = automatic choice).
-struct TileCfg { int threads, P, NG, KS, wpe; };
-static const TileCfg kTiles[] = {
-    {512, 2, 8, 1, 2},   // 1: 1024 x 64 tile, 8 waves with up to 256 registers
-    {1024, 1, 8, 2, 4},  // 2: 1024 x 64 tile, 16 waves
-    {1024, 2, 4, 4, 4},  // 3: 2048 x 32 tile, four taps per barrier (128 KB of tables)
-    {1024, 2, 2, 4, 4},  // 4: 2048 x 16 tile
-    {1024, 2, 2, 8, 4},  // 5: 2048 x 16 tile, eight taps per barrier (128 KB of tables)
-    {512, 2, 2, 4, 4},   // 6: 1024 x 16 tile, two workgroups per compute unit
-    {512, 2, 4, 2, 4},   // 7: 1024 x 32 tile, two workgroups per compute unit
-};
+// Tile configurations: the greatest height of a tile in lane elements (tiles are 8 columns wide).  The
+// "tile" option selects one by index + 1; the automatic choice is the full height of the kernel.
+static const int kTiles[] = {512, 1024, kIT, 1536, 2048, 2560, 3072};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kFullTile = 2;
 int tab_num_tiles() { return kNumTiles; }
 
 bool reads_in_place(const Geom& g, const void* x) { return g.Cin % 16 == 0 && ((uintptr_t)x & 15) == 0; }
@@ -1139,7 +1076,7 @@ bool tab_supported(const Geom& g) {
   if (g.mult || g.groups > 1) return false;  // depthwise: every output channel has its own lane-side operand;
                                               // grouped: the channel blocks would each need strided views
   const long long chunks = cdiv(g.K, kChunk);
-  // tile indices over all tables and the fix-up grid are 32-bit: tiles hold at least 64 x 16 outputs
+  // tile indices over all tables and the fix-up grid are 32-bit: tiles hold at least 64 x 8 outputs
   if ((double)g.M * g.Cout * g.T >= 5.0e10) return false;
   return (long long)g.M * chunks < (1LL << 31) && (long long)g.Cout * chunks < (1LL << 31);
 }
@@ -1158,20 +1095,20 @@ int cu_count() {
 }
 
 // Number of partial tile pieces that a grid of G workgroups produces (see tab_kernel); the
-// largest number of pieces that one tile is cut into, and the number of tiles cut into pieces.
-static int count_partials(int ntiles, int nch, int G, int* most_per_tile = nullptr, int* shared_tiles = nullptr) {
+// largest number of pieces that one tile is cut into and of segments that one workgroup runs.
+static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* most_segs) {
   const long long total = (long long)ntiles * nch;
-  int n = 0, most = 0, run = 0, shared = 0;
+  int n = 0, most = 0, run = 0, segs = 0;
   long long run_tile = -1;
   for (int w = 0; w < G; ++w) {
     long long b = (long long)w * total / G;
     const long long e = (long long)(w + 1) * total / G;
+    segs = std::max(segs, (int)((e - 1) / nch - b / nch) + 1);
     while (b < e) {
       const long long t = b / nch;
       const long long c0 = b - t * nch, c1 = std::min<long long>(nch, c0 + (e - b));
       if (!(c0 == 0 && c1 == nch)) {
         ++n;
-        if (t != run_tile) ++shared;
         run = (t == run_tile) ? run + 1 : 1;
         run_tile = t;
         most = std::max(most, run);
@@ -1179,28 +1116,28 @@ static int count_partials(int ntiles, int nch, int G, int* most_per_tile = nullp
       b += c1 - c0;
     }
   }
-  if (most_per_tile) *most_per_tile = most;
-  if (shared_tiles) *shared_tiles = shared;
+  *most_per_tile = most;
+  *most_segs = segs;
   return n;
 }
 
-// Cost model of one (tile configuration, lane assignment, grid size) choice, in seconds.
-//   - a chunk (16 taps) of a full tile runs at ~75 G lookups/s on a compute unit; tiles are `ih`
-//     high (in steps of 64) and waves without real lane elements skip most of the work;
-//   - every segment a workgroup runs costs a fixed ~5 us (first tables, pipeline fill, stores);
-//   - a partial piece is written once and read once (~2.5 TB/s), and needs the fix-up launch;
+// Cost model of one (tile height, lane assignment, grid size) choice, in seconds; measured on dense and
+// convolution layers with the heights, cuts and combinations forced.
+//   - a phase (a chunk of 16 taps) of a tile of ih lane elements takes 1.2 us for its tables, barrier
+//     and latencies (1.05 us with ready-made tables) and 0.6 ns per lane element;
+//   - every segment a workgroup runs costs its first tables, the pipeline fill and its stores;
+//   - tiles cut into pieces: a launch of the fix-up kernel and the pieces once written and once read,
+//     or, combined inside the main kernel, the reading of the others' pieces one after another;
 //   - grids larger than the machine run in rounds.
 //   - the lane dimension may be cut into more (lower) tiles than it needs, when that makes the
-//     tile count fill whole rounds of the machine.
-struct PlanChoice { int tile, variant, G, partials, nti, ih; double cost; int most, shared; };
-// Tiles cut into few pieces are combined inside tab_kernel by the workgroup that finishes last:
-// up to three pieces per tile, or four unless every workgroup holds just one short piece (under
-// kCombineLong chunks) and all of them therefore end at the same moment (measured on the ResNet-50
-// layers: 3-9 us per layer less than with the second launch; that last case loses 10 us, since
-// the one workgroup reads the others' pieces one after another at the very end of the launch).  More pieces per tile (short, wide layers cut into many K slices) go
-// through tab_fixup_kernel, which spreads the sums of one tile over many blocks.
-constexpr int kCombineMost = 4;
-constexpr int kCombineLong = 24;
+//     tile count fill whole rounds of the machine, or whole multiples of it with K slices.
+struct PlanChoice { int tile, variant, G, partials, nti, ih; double cost; int most; };
+// Pieces are combined inside tab_kernel by the workgroup that finishes last where it has to read at
+// most kCombineElems lane elements of them, one piece after another at the very end of the launch; larger
+// ones go through tab_fixup_kernel, which spreads the sums of one tile over many blocks (three others
+// of 1568: 85.5 us in the kernel, 87 with the second launch; of 3136: 89.9 and 87.5; one of 512: 22.9
+// in the kernel).
+constexpr int kCombineElems = 768;
 // Ready-made tables that a layer gets without being asked to: any set of up to kPreTablesSmall
 // bytes (it stays in the L2s and the memory-side cache whichever workgroup reads which part:
 // the CIFAR-shaped layers with K slices gain 25 %), larger sets (up to kPreTablesMax bytes) for
@@ -1209,38 +1146,28 @@ constexpr size_t kPreTablesSmall = (size_t)20 << 20;
 constexpr size_t kPreTablesMax = (size_t)32 << 20;
 constexpr int kPreRowTiles = 8;
 
-static PlanChoice plan_choice_nti(const Geom& g, int tile, int v, int forced_split, int nti);
-
-static PlanChoice plan_choice(const Geom& g, int tile, int v, int forced_split, int forced_rows) {
-  const TileCfg& tc = kTiles[tile];
-  const long long I = (v == 2) ? g.M : g.Cout;
-  const long long J = (v == 2) ? g.Cout : g.M;
-  const int kIT = tc.threads * tc.P, kJT = tc.NG * 8;
-  const int base = cdiv(I, kIT), ntj = cdiv(J, kJT) * g.T;  // column tiles of all tables
-  if (forced_rows > 0)
-    return plan_choice_nti(g, tile, v, forced_split, std::max(base, std::min(forced_rows, cdiv(I, 64))));
-  PlanChoice best = plan_choice_nti(g, tile, v, forced_split, base);
-  if (forced_split > 0) return best;
-  const int per_cu = (tc.threads == 512 && tc.wpe == 4) ? 2 : 1;
-  const int slots = cu_count() * per_cu;
-  // the largest row-tile count whose tiles still fit r rounds, for the first r where that is more
-  // than the minimum (and the tiles stay at least 64 lane elements high)
-  for (int r = 1; r <= 64; ++r) {
-    const long long n = (long long)r * slots / ntj;
-    if (n <= base) continue;
-    if (n > cdiv(I, 64) || n > 8LL * base + 1) break;
-    const PlanChoice c = plan_choice_nti(g, tile, v, 0, (int)n);
-    if (c.cost < best.cost * 0.97) best = c;
-    break;
-  }
-  return best;
+// Pieces are combined by the main kernel (see kCombineElems).
+static bool combines(const Options& o, int partials, int most, int ih) {
+  return partials > 0 && (o.combine ? o.combine == 2 : (long long)(most - 1) * ih <= kCombineElems);
+}
+// Ready-made tables (one 4 KiB table per tap and group of eight columns) where the filters are
+// the table side and one multiplier table is used.  Every workgroup reads the tables of its taps
+// and columns from global memory, so they pay where many tiles along the lane dimension read the
+// same tables at about the same time (the reads then meet in the L2s) or where all of them stay in
+// the caches.
+static size_t table_bytes(const Geom& g) {
+  return ((size_t)cdiv(g.K, kChunk) * kChunk + 1) * ((size_t)cdiv(g.Cout, 64) * 64 / 8) * 4096;
+}
+static bool ready_made(const Geom& g, const Options& o, int v, int partials, int nti) {
+  const size_t bytes = table_bytes(g);
+  if (v != 2 || g.T != 1 || bytes > ((size_t)1 << 30)) return false;
+  if (o.tables) return o.tables == 2;
+  return bytes <= kPreTablesSmall || (partials == 0 && nti >= kPreRowTiles && bytes <= kPreTablesMax);
 }
 
-static PlanChoice plan_choice_nti(const Geom& g, int tile, int v, int forced_split, int nti_wanted) {
-  const TileCfg& tc = kTiles[tile];
+static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int v, int nti_wanted) {
   const long long I = (v == 2) ? g.M : g.Cout;
   const long long J = (v == 2) ? g.Cout : g.M;
-  const int kIT = tc.threads * tc.P, kJT = tc.NG * 8;
   // balanced tile height (padding spread over all tiles, in steps of one wave), then as many
   // tiles as that height needs (rounding the height up can free the last one)
   const int ih = cdiv(cdiv(I, nti_wanted), 64) * 64;
@@ -1248,38 +1175,58 @@ static PlanChoice plan_choice_nti(const Geom& g, int tile, int v, int forced_spl
   const int ntiles = nti * cdiv(J, kJT) * g.T;
   const int nch = cdiv(g.K, kChunk);
   const long long total = (long long)ntiles * nch;
-  const int per_cu = (tc.threads == 512 && tc.wpe == 4) ? 2 : 1;  // workgroups resident per compute unit
-  const int slots = cu_count() * per_cu;
-  // waves without real lanes skip the gathers, but tables, barriers and latencies stay: ~30 % of a
-  // chunk's time does not shrink with the tile height
-  const double rate = (tc.NG >= 4 ? 80e9 : 75e9) / per_cu;  // wider tiles spend less on gather addresses
-  const double t_chunk = 16.0 * (0.3 * kIT + 0.7 * ih) * kJT / rate;
-  const double t_piece = 2.0 * kIT * kJT * 4.0 / 6.0e12;
-  auto cost = [&](int Gc, int* np_out, int* most_out, int* shared_out) {
+  const int slots = cu_count();
+  auto evaluate = [&](int Gc) {
+    PlanChoice c{tile, v, Gc, 0, nti, ih, 0.0, 0};
+    int segs = 1;
+    c.partials = count_partials(ntiles, nch, Gc, &c.most, &segs);
+    const double t_chunk = (ready_made(g, o, v, c.partials, nti) ? 1.05e-6 : 1.2e-6) + 0.6e-9 * ih;
+    const double t_seg = 2.5e-6 + 1.6e-9 * ih;
     const double rounds = std::ceil((double)Gc / slots);
     const double iters = std::ceil((double)total / Gc);
-    const double segs = std::ceil(iters / nch) + (Gc == ntiles ? 0.0 : 1.0);
-    const int np = count_partials(ntiles, nch, Gc, most_out, shared_out);
-    *np_out = np;
-    return rounds * (iters * t_chunk + segs * 5e-6) + np * t_piece + (np ? 8e-6 : 0.0);
+    c.cost = rounds * (iters * t_chunk + segs * t_seg);
+    if (combines(o, c.partials, c.most, ih))
+      c.cost += 2.32e-6 + (c.most - 1) * 0.5e-9 * ih;
+    else if (c.partials)
+      c.cost += 5e-6 + c.partials * 2.0 * ih * kJT * 4.0 / 4.0e12;
+    return c;
   };
-  PlanChoice best{tile, v, ntiles, 0, nti, ih, 0.0, 0, 0};
-  if (forced_split > 0) {
-    best.G = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(total, 4LL * slots), (long long)ntiles * forced_split));
-    best.cost = cost(best.G, &best.partials, &best.most, &best.shared);
-    return best;
-  }
-  best.cost = cost(ntiles, &best.partials, &best.most, &best.shared);
+  if (o.split_k > 0)
+    return evaluate((int)std::max<long long>(1, std::min<long long>(std::min<long long>(total, 4LL * slots), (long long)ntiles * o.split_k)));
+  PlanChoice best = evaluate(ntiles);
   std::vector<int> cand;
   if (total >= 2) cand.push_back((int)std::min<long long>(slots, total / 2));
   for (int sdiv = 2; sdiv <= 16; ++sdiv)
     if ((long long)ntiles * sdiv <= slots && nch / sdiv >= 2) cand.push_back(ntiles * sdiv);
   for (int Gc : cand) {
     if (Gc < 1) continue;
-    int np = 0, most = 0, shared = 0;
-    const double c = cost(Gc, &np, &most, &shared);
-    if (c < best.cost * 0.97) { best.cost = c; best.G = Gc; best.partials = np; best.most = most; best.shared = shared; }
+    const PlanChoice c = evaluate(Gc);
+    if (c.cost < best.cost) best = c;
   }
+  return best;
+}
+
+static PlanChoice plan_choice(const Geom& g, const Options& o, int tile, int v) {
+  const long long I = (v == 2) ? g.M : g.Cout;
+  const long long J = (v == 2) ? g.Cout : g.M;
+  const int base = cdiv(I, kTiles[tile]), ntj = cdiv(J, kJT) * g.T;  // column tiles of all tables
+  const int most = (int)std::min<long long>(cdiv(I, 64), 8LL * base + 1);
+  if (o.row_tiles > 0) return plan_choice_nti(g, o, tile, v, std::max(base, std::min(o.row_tiles, cdiv(I, 64))));
+  PlanChoice best = plan_choice_nti(g, o, tile, v, base);
+  if (o.split_k > 0) return best;
+  // more, lower tiles: those that make 1 .. 4 rounds of the machine, or a half, a third .. an
+  // eighth of one for K slices
+  const int slots = cu_count();
+  int tried = base;
+  auto attempt = [&](long long n) {
+    if (n <= base || n > most || n == tried) return;
+    tried = (int)n;
+    const PlanChoice c = plan_choice_nti(g, o, tile, v, (int)n);
+    if (c.cost < best.cost) best = c;
+  };
+  for (int r = 1; r <= 4; ++r) attempt((long long)r * slots / ntj);
+  for (int r = 2; r <= 8; ++r) attempt(slots / ((long long)r * ntj));
+  attempt(most);
   return best;
 }
 
@@ -1342,44 +1289,47 @@ TabPlan tab_plan(const Geom& g, const Options& o) {
 
 static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   TabPlan p{};
-  // Lane assignment: pixels on the lanes unless channels fill the lane tiles clearly better.
-  int v = o.variant;
-  if (v != 2 && v != 3) {
-    auto fill = [](long long n) { return (double)n / ((double)cdiv(n, 2048) * 2048.0); };
-    v = (fill(g.Cout) > fill(g.M) + 0.30) ? 3 : 2;
-  }
-  // Tile and grid: the forced tile, else the cheaper of the two 2048-lane tiles by the cost model.
-  PlanChoice best{0, 0, 0, 0, 0, 0, 1e30, 0, 0};
-  for (int tile = 0; tile < kNumTiles; ++tile) {
-    if (o.tile >= 1 ? tile != o.tile - 1 : (tile != 2 && tile != 4)) continue;
-    const PlanChoice c = plan_choice(g, tile, v, o.split_k, o.row_tiles);
+  // Lane assignment and tiles: the cheaper by the cost model, with what a call does around the main kernel
+  // (launches, the copy or patch matrix of the activations for pixel lanes, the packed patches for
+  // channel lanes): over the ResNet-50 layers at batch 1 to 4 and dense layers a run takes the model's
+  // time plus 3 to 8 us (activations read 16 channels at a time), plus 9 and 0.8 us a megabyte (patch
+  // matrix; 3.5 without a staged form) or plus 7 to 12 (channel lanes).
+  const double xbytes = (double)g.M * g.K;
+  const ConvView rows{nullptr, g.H, g.W, g.Cin, g.KW, g.sh, g.sw, g.ph, g.pw, g.OH, g.OW, g.M, g.K, 0, nullptr, g.dh, g.dw, 0};
+  const bool staged = im2col_staged_fits(rows, g.KH, cdiv(g.K, kChunk) * kChunk);
+  const double around[2] = {g.Cin % 16 == 0 ? 6e-6 : 9e-6 + (staged ? 0.8e-12 : 3.5e-12) * xbytes, 9.1e-6 + 5e-12 * xbytes};
+  PlanChoice best{0, 0, 0, 0, 0, 0, 1e30, 0};
+  for (int v = 2; v <= 3; ++v) {
+    if ((o.variant == 2 || o.variant == 3) && v != o.variant) continue;
+    PlanChoice c = plan_choice(g, o, o.tile >= 1 ? o.tile - 1 : kFullTile, v);
+    c.cost += around[v - 2];
     if (c.cost < best.cost) best = c;
   }
+  const int v = best.variant;
+  p.cost = best.cost;
   p.variant = best.variant;
   p.tile = best.tile;
   p.G = best.G;
   p.partials = best.partials;
-  p.combine = (best.partials > 0 && (o.combine ? o.combine == 2 : (best.most < kCombineMost || (best.most == kCombineMost && (best.partials > best.G || cdiv(g.K, kChunk) >= kCombineMost * kCombineLong))))) ? 1 : 0;
+  p.combine = combines(o, best.partials, best.most, best.ih) ? 1 : 0;
   p.nti = best.nti;
   p.ih = best.ih;
-  const TileCfg& tc = kTiles[best.tile];
   {
     // numbering of the shares: whichever lets the XCDs' L2s fetch less (ties and very large
     // iteration spaces, not worth walking: XCD by XCD)
-    const int ntj = cdiv((v == 2) ? g.Cout : g.M, tc.NG * 8), nchk = cdiv(g.K, kChunk);
+    const int ntj = cdiv((v == 2) ? g.Cout : g.M, kJT), nchk = cdiv(g.K, kChunk);
     p.xcd = 1;
     if (o.share_order) {
       p.xcd = o.share_order - 1;
     } else if ((long long)p.nti * ntj * nchk * g.T <= (1LL << 22) && best.G >= 16) {
-      const double f1 = xcd_fetch_bytes(1, best.G, p.nti, ntj, nchk, g.T, p.ih, tc.NG * 8);
-      const double f0 = xcd_fetch_bytes(0, best.G, p.nti, ntj, nchk, g.T, p.ih, tc.NG * 8);
+      const double f1 = xcd_fetch_bytes(1, best.G, p.nti, ntj, nchk, g.T, p.ih, kJT);
+      const double f0 = xcd_fetch_bytes(0, best.G, p.nti, ntj, nchk, g.T, p.ih, kJT);
       if (f0 < 0.9 * f1) p.xcd = 0;
     }
   }
   const int G = best.G;
   const long long I = (v == 2) ? g.M : g.Cout;
   const long long J = (v == 2) ? g.Cout : g.M;
-  const int kJT = tc.NG * 8;
   const int nch = cdiv(g.K, kChunk);
 
   const size_t Kp = (size_t)nch * kChunk;
@@ -1390,33 +1340,15 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   const size_t bpack = up256((Kp + 1) * Jpad), bsum = up256(Jpad * 4 * kMaxSeg);
   // materialized lane operand, or (signed codes, implicit patch view) the offset-binary copy of x
   const size_t apack = up256(std::max((size_t)I * Kp, v == 2 ? (size_t)g.N * g.H * g.W * g.Cin : (size_t)0));
+  const double bordered = (double)g.N * (g.H + 2.0 * g.ph) * (g.W + 2.0 * g.pw);  // pixels with the border the taps see
+  p.border = v == 2 && bordered * g.Cin <= (double)apack && bordered < 268435456.0 ? 1 : 0;  // 16 * pixels: 32 bits
   size_t prep = 0, ws = 0;
   p.off_rows = prep;  prep += up256((size_t)131072 * g.T);
   p.off_qd = prep;    prep += 256;
   p.off_cnt = prep;
   if (p.combine) prep += up256((size_t)p.nti * cdiv(J, kJT) * g.T * 4);
-  // Ready-made tables (one 4 KiB table per tap and group of eight columns) where the filters are
-  // the table side, one multiplier table is used and the tile has a kernel for them.  Every
-  // workgroup reads the tables of its taps and columns from global memory, so they pay where
-  // many tiles along the lane dimension read the same tables at about the same time (the reads
-  // then meet in the L2s) or where all of them stay in the caches; measured on the ResNet-50 layers
-  // at batch 32: 2-9 % faster with 13 or more row tiles and whole tiles per workgroup, 5-40 %
-  // slower with four row tiles or K slices.
-  const size_t tabs_bytes = (Kp + 1) * (Jpad / 8) * 4096;
-  const bool pre_pays = tabs_bytes <= kPreTablesSmall ||
-                        (best.partials == 0 && best.nti >= kPreRowTiles && tabs_bytes <= kPreTablesMax);
-  p.pre = (v == 2 && g.T == 1 && g.K <= 16384 && (best.tile == 2 || best.tile == 4) && tabs_bytes <= ((size_t)1 << 30) &&
-           (o.tables ? o.tables == 2 : pre_pays)) ? 1 : 0;
-  // Expected time of a call, for the choice against fewpix_kernel: the model above, corrected by what
-  // the ResNet-50 layers at batch 1 to 8 and dense layers of 1 to 256 rows measured.  It overrates
-  // layers with pieces (measured / model 0.7-0.75 with ready-made tables, 0.75-0.83 without, 0.95 with channel lanes) and
-  // underrates whole tiles (1.2), the packing of the activations for channel lanes (a launch of
-  // about 9 us) and fix-up passes over many pieces of a tile (0.15 us each: 1 x 2048 x 1000 42 us).
-  // Over 680 random prepared layers (K 64 to 32768, 4e6 to 1e9 lookups) a run takes 0.84 to 1.4 of the
-  // corrected time with pixel lanes (10 to 90 % 0.9 to 1.25) and 0.76 to 1.04 with channel lanes; a call
-  // that prepares its constants itself takes 1.24 and 1.0 of it in the middle.
-  p.cost = best.cost * (!best.partials ? 1.15 : p.pre ? 0.72 : v == 3 ? 0.95 : 0.8) + (v == 3 ? 9e-6 : 0.0) +
-           (best.partials && !p.combine ? 0.15e-6 * best.most : 0.0);
+  const size_t tabs_bytes = table_bytes(g);
+  p.pre = ready_made(g, o, v, best.partials, best.nti) ? 1 : 0;
   p.off_tabs = prep;
   if (p.pre) prep += up256(tabs_bytes);
   if (v == 2) {
@@ -1454,50 +1386,37 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
     if (e_ != hipSuccess) return e_;                \
   } while (0)
 
-template <int THREADS, int P, int NG, int KS, int WPE, bool CH, bool CANPRE = false>
-static hipError_t launch_cfg(const TabArgs& a, int G, int ntiles, int phases, int reps, hipStream_t s) {
+// phases: kPhMain and / or kPhFixup (the latter only for plans with partial pieces)
+template <int GR, bool CH>
+static void launch_tab_kernel(const TabArgs& a, int G, hipStream_t s) {
+  void (*k)(TabArgs) = CH                      ? tab_kernel<GR, true, false, false>  // the lane side is the transposed filters
+                       : a.tabs && a.padded    ? tab_kernel<GR, false, true, true>
+                       : a.tabs                ? tab_kernel<GR, false, true, false>
+                       : a.padded              ? tab_kernel<GR, false, false, true>
+                                               : tab_kernel<GR, false, false, false>;
+  hipLaunchKernelGGL(k, dim3(G), dim3(kThreads), 0, s, a);
+}
+template <bool CH>
+static hipError_t launch_main(const TabArgs& a, int G, int ntiles, int phases, int reps, hipStream_t s) {
   for (int r = 0; r < reps && (phases & kPhMain); ++r) {
-    if constexpr (CANPRE) {
-      if (a.tabs) {  // planned only for K <= 16384
-        hipLaunchKernelGGL((tab_kernel<THREADS, P, NG, KS, WPE, CH, false, true>), dim3(G), dim3(THREADS), 0, s, a);
-        AX_LAUNCHED();
-        continue;
-      }
-    }
-    if (a.tabs) return hipErrorInvalidValue;  // a plan with ready-made tables for a kernel without them
-    if (a.K > 16384)
-      hipLaunchKernelGGL((tab_kernel<THREADS, P, NG, KS, WPE, CH, true>), dim3(G), dim3(THREADS), 0, s, a);
+    if (a.ih <= kIT / 2)
+      launch_tab_kernel<4, CH>(a, G, s);
     else
-      hipLaunchKernelGGL((tab_kernel<THREADS, P, NG, KS, WPE, CH, false>), dim3(G), dim3(THREADS), 0, s, a);
+      launch_tab_kernel<8, CH>(a, G, s);
     AX_LAUNCHED();
   }
   if (!(phases & kPhFixup) || a.cnt) return hipSuccess;
+  const dim3 grid((unsigned)(ntiles * (a.ih / 64)));
   if (G >= 16 * ntiles)
-    hipLaunchKernelGGL((tab_fixup_kernel<THREADS * P, NG * 8, CH, true>), dim3(ntiles * (THREADS * P / 64)), dim3(256), 0, s, a, G);
+    hipLaunchKernelGGL((tab_fixup_kernel<CH, true>), grid, dim3(256), 0, s, a, G);
   else
-    hipLaunchKernelGGL((tab_fixup_kernel<THREADS * P, NG * 8, CH, false>), dim3(ntiles * (THREADS * P / 64)), dim3(256), 0, s, a, G);
+    hipLaunchKernelGGL((tab_fixup_kernel<CH, false>), grid, dim3(256), 0, s, a, G);
   return hipGetLastError();
 }
 
-// phases: kPhMain and / or kPhFixup (the latter only for plans with partial pieces)
-template <bool CH>
-static hipError_t launch_main(const TileCfg& t, const TabArgs& a, int G, int ntiles, int phases, int reps, hipStream_t s) {
-  const int key = t.threads * 10000 + t.P * 1000 + t.NG * 100 + t.KS * 10 + t.wpe;
-  switch (key) {
-    case 5120000 + 2812: return launch_cfg<512, 2, 8, 1, 2, CH>(a, G, ntiles, phases, reps, s);
-    case 10240000 + 1824: return launch_cfg<1024, 1, 8, 2, 4, CH>(a, G, ntiles, phases, reps, s);
-    case 10240000 + 2444: return launch_cfg<1024, 2, 4, 4, 4, CH, !CH>(a, G, ntiles, phases, reps, s);
-    case 10240000 + 2244: return launch_cfg<1024, 2, 2, 4, 4, CH>(a, G, ntiles, phases, reps, s);
-    case 10240000 + 2284: return launch_cfg<1024, 2, 2, 8, 4, CH, !CH>(a, G, ntiles, phases, reps, s);
-    case 5120000 + 2244: return launch_cfg<512, 2, 2, 4, 4, CH>(a, G, ntiles, phases, reps, s);
-    case 5120000 + 2424: return launch_cfg<512, 2, 4, 2, 4, CH>(a, G, ntiles, phases, reps, s);
-    default: return hipErrorInvalidValue;  // a tile configuration without an instantiated kernel
-  }
-}
-
 hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const uint8_t* x, const uint8_t* w,
-                      const uint16_t* lut, int32_t* acc_out, float* y_out, void* prepared, void* scratch, int phases,
-                      int main_reps, hipStream_t s) {
+                      const uint16_t* lut, int32_t* acc_out, float* y_out, void* prepared, void* scratch, bool full_scratch,
+                      int phases, int main_reps, hipStream_t s) {
   uint8_t* pb = static_cast<uint8_t*>(prepared);
   uint8_t* sb = static_cast<uint8_t*>(scratch);
   const bool ch = (p.variant == 3);
@@ -1505,8 +1424,6 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   const int J = ch ? g.M : g.Cout;
   const int nchunks = cdiv(g.K, kChunk);
   const int Kp = nchunks * kChunk;
-  const TileCfg& tc = kTiles[p.tile];
-  const int kJT = tc.NG * 8;
   const int Jpad = cdiv(J, 64) * 64;
   uint16_t* rows = reinterpret_cast<uint16_t*>(pb + p.off_rows);
   QDev* qd = reinterpret_cast<QDev*>(pb + p.off_qd);
@@ -1527,6 +1444,14 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   const int seg_rows = cdiv(cdiv(krows, nseg), 16) * 16;
   const int row_blocks = kRowBlocks * g.T, pack_blocks = nseg * (Jpad / 64);
   const bool implicit_view = !ch && reads_in_place(g, x);
+  // Activations re-laid out chunk by chunk (prep_chunks_kernel): by output pixel for 1 x 1 filters without
+  // padding (only the pixels that are read), else the whole tensor, with its border where the scratch
+  // block holds that.  Signed codes need a copy in any case.
+  const bool by_output = g.KH == 1 && g.KW == 1 && g.ph == 0 && g.pw == 0;
+  const bool border = !by_output && full_scratch && p.border;
+  const bool chunked = implicit_view && (g.sgn || (full_scratch && (g.Cin > 16 || (border && (g.ph || g.pw)))));
+  const int bh = chunked && border ? g.ph : 0, bw = chunked && border ? g.pw : 0;
+  const int ch_h = by_output ? g.OH : g.H + 2 * bh, ch_w = by_output ? g.OW : g.W + 2 * bw;  // the copy's positions
   uint32_t* rows32 = reinterpret_cast<uint32_t*>(rows);
   uint32_t* cnt = reinterpret_cast<uint32_t*>(pb + p.off_cnt);
   const int ncnt = p.combine ? ntiles : 0;
@@ -1552,14 +1477,16 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
       AX_LAUNCHED();
     }
     if ((phases & kPhConst) && p.pre) {
-      hipLaunchKernelGGL(prep_tables_kernel, dim3((unsigned)(krows * (Jpad / 8))), dim3(256), 0, s, rows, Bp, Jpad,
-                         reinterpret_cast<uint4*>(pb + p.off_tabs));
+      hipLaunchKernelGGL(prep_tables_kernel, dim3((unsigned)(nchunks * (Jpad / 8))), dim3(kThreads), 0, s, rows, Bp, Jpad,
+                         pb + p.off_tabs);
       AX_LAUNCHED();
     }
-    if ((phases & kPhCall) && implicit_view && g.sgn) {  // N*H*W*Cin is a multiple of 16 here
-      const uint32_t n16 = (uint32_t)(((size_t)g.N * g.H * g.W * g.Cin) / 16);
-      hipLaunchKernelGGL(prep_flip_kernel, dim3(cdiv(n16, 256)), dim3(256), 0, s, reinterpret_cast<const uint4*>(x),
-                         reinterpret_cast<uint4*>(Ap), n16);
+    if ((phases & kPhCall) && chunked) {
+      const int pos = g.N * ch_h * ch_w;
+      const int cl = g.Cin <= 16 ? 0 : g.Cin <= 32 ? 1 : g.Cin <= 64 ? 2 : 3;
+      hipLaunchKernelGGL(prep_chunks_kernel, dim3(cdiv(pos, 512 >> cl), cdiv(g.Cin, 16 << cl)), dim3(256), 0, s, x, pos, g.Cin,
+                         cl, g.H, g.W, ch_h * ch_w, ch_w, by_output ? g.sh : 1, by_output ? g.sw : 1, bh, bw,
+                         cv.sx * 0x01010101u, qd, Ap);
       AX_LAUNCHED();
     } else if ((phases & kPhCall) && !implicit_view) {
       if (im2col_staged_fits(cv, g.KH, Kp) && g.OH <= 65535 && g.N <= 65535) {
@@ -1580,18 +1507,21 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
 
   TabArgs a{};
   a.I = I;
-  if (implicit_view) {
-    a.A = g.sgn ? Ap : x;
-    a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.KW = g.KW; a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw;
+  if (implicit_view && !(chunked && by_output)) {
+    a.A = chunked ? Ap : x;
+    a.H = chunked ? ch_h : g.H; a.W = chunked ? ch_w : g.W; a.Cin = g.Cin; a.KW = g.KW; a.sh = g.sh; a.sw = g.sw;
+    a.ph = g.ph - bh; a.pw = g.pw - bw;
     a.OHW = g.OH * g.OW; a.OW = g.OW;
     a.dh = g.dh; a.dw = g.dw;
-    a.a_ps = (uint32_t)g.Cin; a.a_cs = 1;
-  } else {  // materialized operand: I lane elements of Kp bytes, seen as I pixels of a 1 x 1 image
+    a.a_ps = chunked ? 16u : (uint32_t)g.Cin;
+    a.a_cs = chunked ? (uint32_t)(g.N * ch_h * ch_w) : 1u;
+    // taps outside the image: with padding only (OH and OW count the positions whose taps all lie inside)
+    if (a.ph || a.pw) a.padded = g.H + g.ph < 32768 && g.W + g.pw < 32768 ? 1 : 2;
+  } else {  // materialized operand: I lane elements of Kp bytes, chunk by chunk, seen as I pixels of a 1 x 1 image
     a.A = Ap;
     a.H = 1; a.W = 1; a.Cin = Kp; a.KW = 1; a.sh = 1; a.sw = 1; a.ph = 0; a.pw = 0; a.OHW = 1; a.OW = 1;
     a.dh = 1; a.dw = 1;
-    if (ch) { a.a_ps = (uint32_t)Kp; a.a_cs = 1; }        // transposed filters: row by row
-    else    { a.a_ps = 16; a.a_cs = (uint32_t)I; }          // patches: chunk by chunk
+    a.a_ps = 16; a.a_cs = (uint32_t)I;
   }
   a.Bp = Bp; a.Jpad = Jpad; a.J = J; a.bsum = bsum; a.nseg = cdiv(krows, seg_rows); a.rows = rows;
   a.K = g.K;
@@ -1610,10 +1540,10 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   a.tabs_bytes = p.pre ? (uint32_t)((size_t)krows * (Jpad / 8) * 4096) : 0u;
   a.out_elems = (long long)g.M * g.Cout;
   a.xcd = p.xcd;
-  a.vec_out = (!ch && J % 4 == 0 && (((uintptr_t)acc_out | (uintptr_t)y_out) & 15) == 0) ? 1 : 0;
+  a.vec_out = (!ch && J % 2 == 0 && (((uintptr_t)acc_out | (uintptr_t)y_out) & 7) == 0) ? 1 : 0;
 
-  return ch ? launch_main<true>(tc, a, p.G, ntiles, run, main_reps, s)
-            : launch_main<false>(tc, a, p.G, ntiles, run, main_reps, s);
+  return ch ? launch_main<true>(a, p.G, ntiles, run, main_reps, s)
+            : launch_main<false>(a, p.G, ntiles, run, main_reps, s);
 }
 
 }  // namespace ax
