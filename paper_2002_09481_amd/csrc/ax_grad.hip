@@ -46,6 +46,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kTR = 128;         // tile rows
 constexpr int kStage = 32;       // contraction elements per stage
+constexpr int kFold = 4;          // stages after which the matrix instructions' sums are added to the running ones: the
+                                 // rounding errors of a long contraction stay those of short ones added up
 constexpr int kLd = kStage + 8;  // LDS row length in bf16 elements: rows start 16-byte aligned, and the
                                  // 16 rows that one pass of a 16-byte read touches fall into disjoint banks
 
@@ -173,10 +175,12 @@ __global__ __launch_bounds__(256) void grad_wint_kernel(const uint8_t* __restric
 // class (iy mod sh, ix mod sw) of their pixel: whether tap (ky, kx) can reach a pixel depends on
 // that class alone, so a tile of one class skips the taps that never reach it (three of four for
 // stride 2) instead of multiplying zeros.  blockIdx = (tile within the class, Cin tile, class).
-// A wave takes 32 rows and all TC columns: every piece read from LDS feeds TC / 32 matrix
-// instructions.
-template <int TC, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void dgrad_kernel(const GradArgs a) {
+// A wave takes 32 rows and all TC columns (two waves share them where there are eight): every piece
+// read from LDS feeds several matrix instructions.
+// FOLD: running sums beside the matrix instructions' (see kFold); slices of at most eight stages go without,
+// which saves the registers of the narrow tiles.
+template <int TC, int WAVES, bool FOLD>
+__global__ __launch_bounds__(64 * WAVES, TC == 128 && FOLD ? 4 : TC == 256 ? 2 : 1) void dgrad_kernel(const GradArgs a) {
   constexpr int THREADS = 64 * WAVES;
   constexpr int CG = WAVES / 4;                 // waves side by side; four rows of waves cover the 128 tile rows
   constexpr int NB = TC / (32 * CG);            // 32 x 32 blocks per wave
@@ -210,11 +214,23 @@ __global__ __launch_bounds__(64 * WAVES) void dgrad_kernel(const GradArgs a) {
   const int ci = ci0 + br;
   const bool ci_ok = ci < a.Cin;
 
-  f32x16 acc[NB];
+  f32x16 acc[NB], sum[NB];  // sums of the last stages, of the ones before
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc[b][i] = sum[b][i] = 0.f;
+  int unfolded = 0;
+  auto fold = [&]() {
+    if (!FOLD || ++unfolded < kFold) return;  // uniform
+    unfolded = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        sum[b][i] += acc[b][i];
+        acc[b][i] = 0.f;
+      }
+  };
   const int mr = lane & 31, kg = (lane >> 5) * 8;
   const int wrow = (wave & 3) * 32, wcol = (wave >> 2) * (TC / CG);
 
@@ -299,6 +315,7 @@ __global__ __launch_bounds__(64 * WAVES) void dgrad_kernel(const GradArgs a) {
     const bool h2 = h1 && next();
     if (h2) load_stage(R0);
     compute();
+    fold();
     __syncthreads();
     if (h1) store_stage(R1);
     __syncthreads();
@@ -307,6 +324,7 @@ __global__ __launch_bounds__(64 * WAVES) void dgrad_kernel(const GradArgs a) {
     const bool h3 = h2 && next();
     if (h3) load_stage(R1);
     compute();
+    fold();
     __syncthreads();
     if (h2) store_stage(R0);
     __syncthreads();
@@ -327,15 +345,21 @@ __global__ __launch_bounds__(64 * WAVES) void dgrad_kernel(const GradArgs a) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int col = ci0 + wcol + 32 * b + mr;
-      if (col < a.Cin) orow[col] = acc[b][i] * oscale;
+      if (col < a.Cin) orow[col] = (sum[b][i] + acc[b][i]) * oscale;
     }
   }
 }
 
 // gw: output matrix [K taps] x [Cout], contraction over the output pixels of this split.
 // blockIdx = (tap tile, Cout tile, split).  A wave takes 64 taps x TC / 2 channels.
-template <int TR, int TC, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
+// The activation side is gathered as codes and converted when it goes to LDS.  VEC (channel count
+// divisible by four, x aligned to four bytes): a thread takes four neighbouring channels of four
+// pixels, a dword per pixel; otherwise one channel of 16 pixels, a byte per pixel.  The byte loads alone
+// kept the address path busy for longer than the matrix instructions of a stage take (128 wave loads of 16
+// clocks against 1545 clocks).  VEC keeps tap 4 q + j of the tile in LDS row j * TR / 4 + q, so
+// that consecutive lanes store to consecutive rows.
+template <int TR, int TC, int WAVES, bool VEC>
+__global__ __launch_bounds__(64 * WAVES, TC == 64 ? 1 : 2) void wgrad_kernel(const GradArgs a) {
   constexpr int THREADS = 64 * WAVES;
   constexpr int RG = TR / 64;                  // rows of waves: a wave takes 64 taps
   constexpr int CG = WAVES / RG;               // waves side by side
@@ -348,7 +372,7 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
   const int k0 = blockIdx.x * TR, co0 = blockIdx.y * TC, split = blockIdx.z;
   // staging roles: tap row ar, stage pixels as .. as+15 (consecutive lanes take consecutive taps, i.e.
   // consecutive input channels: one pixel's bytes are read together); channel bc, stage pixels bs .. bs+BM-1
-  const int ar = t % TR, as = (t / TR) * 16;
+  const int ar = VEC ? 4 * (t % (TR / 4)) : t % TR, as = VEC ? 4 * (t / (TR / 4)) : (t / TR) * 16;
   const int bc = t % TC, bs = (t / TC) * BM;
   const int k = k0 + ar;
   const bool k_ok = k < a.K;
@@ -363,33 +387,54 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
   const int m_beg = split * a.m_per_split, m_end = min(a.M, m_beg + a.m_per_split);
   const int ohw = a.OH * a.OW;
 
-  f32x16 acc[2][NBC];
+  f32x16 acc[2][NBC], sum[2][NBC];  // sums of the last stages, of the ones before
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int c = 0; c < NBC; ++c)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[b][c][i] = 0.f;
+      for (int i = 0; i < 16; ++i) acc[b][c][i] = sum[b][c][i] = 0.f;
+  int unfolded = 0;
+  auto fold = [&]() {
+    if (++unfolded < kFold) return;  // uniform
+    unfolded = 0;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int c = 0; c < NBC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          sum[b][c][i] += acc[b][c][i];
+          acc[b][c][i] = 0.f;
+        }
+  };
   const int mr = lane & 31, kg = (lane >> 5) * 8;
   const int wrow = (wave % RG) * 64, wcol = (wave / RG) * (TC / CG);
 
+  constexpr int NX = VEC ? 4 : 16;  // pixels per thread on the activation side
   struct StageRegs {
-    uint32_t xa[16];  // raw activation codes of the stage (converted when they go to LDS)
+    uint32_t xa[NX];  // raw activation codes of the stage (converted when they go to LDS)
     bf16x8 rb[3][BM / 8];
   };
+  // VEC: codes as offset binary, so that signed and unsigned ones convert alike
+  const uint32_t flip = a.sgn ? 0x80808080u : 0u;
+  const float x_zero = (float)(a.x_zp + (a.sgn ? 128 : 0));
   auto load_stage = [&](StageRegs& R, int m0) {
     int m = m0 + as;
     int n = m / ohw;
     int rem = m - n * ohw;
     int oy = rem / a.OW, ox = rem - (rem / a.OW) * a.OW;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      uint32_t v = zero_code;  // rows beyond K and pixels beyond the split contribute nothing
+    for (int e = 0; e < NX; ++e) {
+      constexpr uint32_t kAll = VEC ? 0x01010101u : 1u;
+      uint32_t v = zero_code * kAll;  // rows beyond K and pixels beyond the split contribute nothing
       if (k_ok && m < m_end) {
         const int iy = oy * a.sh - a.ph + tdy, ix = ox * a.sw - a.pw + tdx;
-        v = pad_code;
-        if ((unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W)
-          v = a.x[(((size_t)n * a.H + iy) * a.W + ix) * a.Cin + tci];
+        v = pad_code * kAll;
+        if ((unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W) {
+          const uint8_t* src = a.x + (((size_t)n * a.H + iy) * a.W + ix) * a.Cin + tci;
+          v = VEC ? *reinterpret_cast<const uint32_t*>(src) : *src;
+        }
       }
       R.xa[e] = v;
       ++m;
@@ -404,11 +449,22 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
     }
   };
   auto store_stage = [&](const StageRegs& R) {
-    bf16x8 xv[2];
+    if constexpr (VEC) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) xv[e >> 3][e & 7] = bf16_of_small_int(code_of((uint8_t)R.xa[e], a.sgn) - a.x_zp);
-    *reinterpret_cast<bf16x8*>(&As[ar][as]) = xv[0];
-    *reinterpret_cast<bf16x8*>(&As[ar][as + 8]) = xv[1];
+      for (int j = 0; j < 4; ++j) {  // channel j of the four pixels
+        uint32_t f[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = __float_as_uint((float)(((R.xa[e] ^ flip) >> (8 * j)) & 0xffu) - x_zero);
+        *reinterpret_cast<uint2*>(&As[j * (TR / 4) + (ar >> 2)][as]) =
+            make_uint2((f[0] >> 16) | (f[1] & 0xffff0000u), (f[2] >> 16) | (f[3] & 0xffff0000u));
+      }
+    } else {
+      bf16x8 xv[2];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) xv[(e & 15) >> 3][e & 7] = bf16_of_small_int(code_of((uint8_t)R.xa[e % NX], a.sgn) - a.x_zp);
+      *reinterpret_cast<bf16x8*>(&As[ar][as]) = xv[0];
+      *reinterpret_cast<bf16x8*>(&As[ar][as + 8]) = xv[1];
+    }
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
@@ -446,12 +502,14 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
     // LDS: stage s; R1: stage s + 1 (if h1), in flight; R0: free
     const bool h2 = h1 && next(R0);
     compute();
+    fold();
     __syncthreads();
     if (h1) store_stage(R1);
     __syncthreads();
     if (!h1) break;
     const bool h3 = h2 && next(R1);
     compute();
+    fold();
     __syncthreads();
     if (h2) store_stage(R0);
     __syncthreads();
@@ -465,9 +523,10 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_kernel(const GradArgs a) {
     for (int c = 0; c < NBC; ++c)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int row = k0 + wrow + 32 * b + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+        const int lrow = wrow + 32 * b + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+        const int row = k0 + (VEC ? 4 * (lrow % (TR / 4)) + lrow / (TR / 4) : lrow);
         const int col = co0 + wcol + 32 * c + mr;
-        if (row < a.K && col < a.Cout) part[(size_t)row * a.Cout + col] = acc[b][c][i];
+        if (row < a.K && col < a.Cout) part[(size_t)row * a.Cout + col] = sum[b][c][i] + acc[b][c][i];
       }
 }
 
@@ -519,6 +578,7 @@ struct GradPlan {
   int tc_d, tc_w;  // column tile of dgrad (over Cin) and of wgrad (over Cout)
   int tr_w;        // row tile of wgrad (over the taps)
   int dsplits;     // slices of dgrad's contraction
+  bool dfold;      // they are longer than eight stages
   uint8_t cls_order[16];
   size_t off_part, off_dpart, off_P, off_PT, off_wi, ws_bytes;
 };
@@ -556,13 +616,27 @@ GradPlan grad_plan(const Geom& g) {
   if (ncls <= 16)
     std::stable_sort(p.cls_order, p.cls_order + ncls, [&](uint8_t x, uint8_t y) { return taps_of[x] > taps_of[y]; });
   const long long stages_max = (long long)max_taps * (p.Cp / kStage);
-  long long ds = (4LL * cu_count() + std::max(1LL, dt) - 1) / std::max(1LL, dt);
-  ds = std::max(1LL, std::min(std::min(ds, stages_max / 8), 64LL));
-  p.dsplits = (int)ds;
+  // Slices of the contractions, by expected time: workgroups of `slices` x tiles run in rounds of what the
+  // machine holds at once, each for a start and its stages (us, measured on 7 x 7 to 56 x 56 layers), and the
+  // slices are written and added.  Four times as many workgroups as compute units, whatever the tile, cost
+  // up to a quarter of the pass in half-filled second rounds and in slices.
+  auto slices_of = [&](long long tiles, long long stages, int least, int most, double fit, double start, double stage,
+                       double out_bytes) {
+    int best = 1;
+    double best_t = 1e30;
+    for (int n = 1; n <= most && (n == 1 || stages / n >= least); ++n) {
+      const double rounds = std::ceil((double)tiles * n / (fit * cu_count()));
+      const double t = rounds * (start + stage * (double)((stages + n - 1) / n)) + (n > 1 ? 5.0 + n * out_bytes / 3.5e6 : 0.0);
+      if (t < best_t) { best_t = t; best = n; }
+    }
+    return best;
+  };
+  p.dsplits = slices_of(std::max(1LL, dt), stages_max, 4, 64, p.tc_d == 256 ? 1.0 : 2.0, 8.0, p.tc_d == 256 ? 2.0 : 1.7,
+                        4.0 * g.N * g.H * g.W * g.Cin);
+  p.dfold = stages_max > 8LL * p.dsplits;
   const long long tiles = (long long)((g.K + p.tr_w - 1) / p.tr_w) * ((g.Cout + p.tc_w - 1) / p.tc_w);
-  // enough workgroups to fill the machine several times, at least 256 pixels per split
-  long long s = (4LL * cu_count() + tiles - 1) / tiles;
-  s = std::max(1LL, std::min(s, (long long)(g.M + 255) / 256));
+  const long long s = slices_of(tiles, p.Mp / kStage, 8, 512, p.tr_w == 256 ? 1.0 : 2.0, 8.0, p.tr_w == 256 ? 1.9 : 1.4,
+                                4.0 * g.K * g.Cout);
   int per = (int)(((g.M + s - 1) / s + kStage - 1) / kStage) * kStage;
   p.m_per_split = per;
   p.splits = (g.M + per - 1) / per;
@@ -643,12 +717,10 @@ extern "C" int ax_conv2d_backward(const ax_conv_desc_t* desc, const ax_quant_t* 
     const long long rows = (long long)g.N * ((g.H + g.sh - 1) / g.sh) * ((g.W + g.sw - 1) / g.sw);
     const dim3 grid((unsigned)((rows + kTR - 1) / kTR), (unsigned)((g.Cin + p.tc_d - 1) / p.tc_d),
                     (unsigned)(g.sh * g.sw * p.dsplits));
-    if (p.tc_d == 256)
-      hipLaunchKernelGGL((dgrad_kernel<256, 8>), grid, dim3(512), 0, s, a);
-    else if (p.tc_d == 128)
-      hipLaunchKernelGGL((dgrad_kernel<128, 4>), grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgrad_kernel<64, 4>), grid, dim3(256), 0, s, a);
+    void (*dk)(GradArgs) = p.tc_d == 256   ? dgrad_kernel<256, 8, true>
+                           : p.tc_d == 128 ? p.dfold ? dgrad_kernel<128, 8, true> : dgrad_kernel<128, 4, false>
+                                           : p.dfold ? dgrad_kernel<64, 4, true> : dgrad_kernel<64, 4, false>;
+    hipLaunchKernelGGL(dk, grid, dim3(p.tc_d == 256 || (p.tc_d == 128 && p.dfold) ? 512 : 256), 0, s, a);
     AX_GRAD_LAUNCHED();
     if (p.dsplits > 1) {
       const size_t n = (size_t)g.N * g.H * g.W * g.Cin;
@@ -659,12 +731,11 @@ extern "C" int ax_conv2d_backward(const ax_conv_desc_t* desc, const ax_quant_t* 
   if (gw_out) {
     a.out = reinterpret_cast<float*>(ws + p.off_part);
     const dim3 grid((unsigned)((g.K + p.tr_w - 1) / p.tr_w), (unsigned)((g.Cout + p.tc_w - 1) / p.tc_w), (unsigned)p.splits);
-    if (p.tr_w == 256)
-      hipLaunchKernelGGL((wgrad_kernel<256, 128, 8>), grid, dim3(512), 0, s, a);
-    else if (p.tc_w == 128)
-      hipLaunchKernelGGL((wgrad_kernel<128, 128, 4>), grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((wgrad_kernel<128, 64, 4>), grid, dim3(256), 0, s, a);
+    const bool vec = g.Cin % 4 == 0 && ((uintptr_t)x & 3) == 0;
+    void (*wk)(GradArgs) = p.tr_w == 256   ? vec ? wgrad_kernel<256, 128, 8, true> : wgrad_kernel<256, 128, 8, false>
+                           : p.tc_w == 128 ? vec ? wgrad_kernel<128, 128, 4, true> : wgrad_kernel<128, 128, 4, false>
+                                           : vec ? wgrad_kernel<128, 64, 4, true> : wgrad_kernel<128, 64, 4, false>;
+    hipLaunchKernelGGL(wk, grid, dim3(p.tr_w == 256 ? 512 : 256), 0, s, a);
     AX_GRAD_LAUNCHED();
     const size_t n = (size_t)g.K * g.Cout;
     launch_sum_slices(reinterpret_cast<const float*>(ws + p.off_part), p.splits, n, q->x_scale, gw_out, s);
