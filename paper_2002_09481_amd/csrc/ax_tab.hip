@@ -636,21 +636,30 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 // slots of consecutive workgroups, as the registers of tab_kernel held them (see TabArgs::part).  A
 // block takes one group of 64 lane elements of a tile, a thread one quarter of it: its lane's pair
 // of columns.
-// MANY: the form for tiles cut into many pieces (see the piece loop); it needs more registers, so
-// it is a kernel of its own and the usual form keeps its occupancy.
-template <bool CH, bool MANY>
+// Bound: memory round trips, a block reads a few kilobytes.  So the loads of four pieces are issued
+// before the first is waited for, those of the constants after them, and which workgroups share the
+// tile is found with 32-bit divisions where the numbers allow it (SMALL): 25.7 MB of pieces
+// (3136 x 8, four per tile) 22 -> 17 us.
+template <bool CH, bool SMALL>
 __global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) {
   const int groups = a.ih / 64;
   const int gtile = blockIdx.x / groups;
   const int g = blockIdx.x - gtile * groups;
-  const long long t_beg = (long long)gtile * a.nch, t_last = t_beg + a.nch - 1;
-  auto owner = [&](long long it) {  // the workgroup w with w*total/G <= it < (w+1)*total/G
-    long long w = it * G / a.total_iters;
-    while ((w + 1) * a.total_iters / G <= it) ++w;
-    while (w * a.total_iters / G > it) --w;
+  auto owner = [&](auto it) {  // the workgroup w with w*total/G <= it < (w+1)*total/G
+    const decltype(it) total = (decltype(it))a.total_iters;
+    auto w = it * G / total;
+    while ((w + 1) * total / G <= it) ++w;
+    while (w * total / G > it) --w;
     return (int)w;
   };
-  const int w_first = owner(t_beg), w_last = owner(t_last);
+  int w_first, w_last;
+  if (SMALL) {
+    w_first = owner((uint32_t)gtile * (uint32_t)a.nch);
+    w_last = owner((uint32_t)gtile * (uint32_t)a.nch + (uint32_t)a.nch - 1u);
+  } else {
+    w_first = owner((long long)gtile * a.nch);
+    w_last = owner((long long)gtile * a.nch + a.nch - 1);
+  }
   if (w_first == w_last) return;  // finished inside tab_kernel
   const int tbl = gtile / a.ntiles1;
   const int tile = gtile - tbl * a.ntiles1;
@@ -660,46 +669,37 @@ __global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) 
   const int ti = tile / a.ntj;
   const int i0 = ti * a.ih, j0 = (tile - ti * a.ntj) * kJT;
   if (i0 + 64 * g >= a.I) return;
-  const uint32_t klast = (uint32_t)a.nch * kChunk;
-  const uint32_t padfix = (klast - (uint32_t)a.K) * ((uint32_t)rows[0] ^ 0x8080u) + a.bias_k - 32896u * klast;  // see tab_kernel
   __shared__ long long cterm[4][kJT];
   const int t = threadIdx.x, lane = t & 63, r = t >> 6;
   const int m = lane & 15, kg = lane >> 4;
-  column_constants<256>(a, j0, cterm);
-  uint32_t v0 = 0u - padfix, v1 = 0u - padfix, sl = 0;
+  uint32_t v0 = 0, v1 = 0, sl = 0;
   const size_t piece = (size_t)a.ih * kJT;
   const int32_t* part = a.part + (size_t)g * 512 + r * 128 + lane;
   const int32_t* lsum = a.lsum + g * 64 + 16 * r + m;
-  int w = w_first;
-  // Many pieces (a short, wide layer cut into many K slices): four at a time, all their loads
-  // issued before the first add, so that the block does not pay one memory round trip per piece.
-  // With few pieces the plain loop below is faster.
-  if constexpr (MANY) {
-    for (; w + 3 <= w_last; w += 4) {
-      uint32_t p0[4], p1[4], ps[4];
+  for (int w = w_first; w <= w_last; w += 4) {
+    uint32_t p0[4], p1[4], ps[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int slot = 2 * (w + k) + (w + k == w_first ? 1 : 0);
-        const int32_t* pp = part + (size_t)slot * piece;
-        p0[k] = (uint32_t)pp[0];
-        p1[k] = (uint32_t)pp[64];
-        ps[k] = (uint32_t)lsum[(size_t)slot * a.ih];
-      }
+    for (int k = 0; k < 4; ++k) {  // past the last piece: the last one again, not added
+      const int wk = min(w + k, w_last);
+      const int slot = 2 * wk + (wk == w_first ? 1 : 0);
+      const int32_t* pp = part + (size_t)slot * piece;
+      p0[k] = (uint32_t)pp[0];
+      p1[k] = (uint32_t)pp[64];
+      ps[k] = (uint32_t)lsum[(size_t)slot * a.ih];
+    }
+    if (w == w_first) column_constants<256>(a, j0, cterm);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        v0 += p0[k];
-        v1 += p1[k];
-        sl += ps[k];
-      }
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t on = w + k <= w_last ? 1u : 0u;
+      v0 += on ? p0[k] : 0u;
+      v1 += on ? p1[k] : 0u;
+      sl += on ? ps[k] : 0u;
     }
   }
-  for (; w <= w_last; ++w) {
-    const int slot = 2 * w + (w == w_first ? 1 : 0);
-    const int32_t* pp = part + (size_t)slot * piece;
-    v0 += (uint32_t)pp[0];
-    v1 += (uint32_t)pp[64];
-    sl += (uint32_t)lsum[(size_t)slot * a.ih];
-  }
+  const uint32_t klast = (uint32_t)a.nch * kChunk;
+  const uint32_t padfix = (klast - (uint32_t)a.K) * ((uint32_t)rows[0] ^ 0x8080u) + a.bias_k - 32896u * klast;  // see tab_kernel
+  v0 -= padfix;
+  v1 -= padfix;
   __syncthreads();
   const uint32_t lterm = (uint32_t)a.qd->z_tab * sl;
   const float scale = a.qd->scale;
@@ -1133,11 +1133,12 @@ static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* m
 //     tile count fill whole rounds of the machine, or whole multiples of it with K slices.
 struct PlanChoice { int tile, variant, G, partials, nti, ih; double cost; int most; };
 // Pieces are combined inside tab_kernel by the workgroup that finishes last where it has to read at
-// most kCombineElems lane elements of them, one piece after another at the very end of the launch; larger
-// ones go through tab_fixup_kernel, which spreads the sums of one tile over many blocks (three others
-// of 1568: 85.5 us in the kernel, 87 with the second launch; of 3136: 89.9 and 87.5; one of 512: 22.9
-// in the kernel).
-constexpr int kCombineElems = 768;
+// most kCombineElems lane elements of them (one piece of 512: 22.9 us, 25 with the second launch), and up to
+// kCombineMost pieces of sums of at least kCombineLong chunks, whose workgroups do not all end at once
+// (28 x 28 x 128 3 x 3 at batch 32, two pieces of 3136 x 8: 133.5 us, 144 with the second launch; 7 x 7 x 512
+// 3 x 3, four of 1568: 160.5 and 168).  Others go through tab_fixup_kernel, which spreads the sums of one
+// tile over many blocks (128 x 2048 x 2048, sixteen pieces: 44.8 us, 52 in the kernel).
+constexpr int kCombineElems = 768, kCombineMost = 4, kCombineLong = 64;
 // Ready-made tables that a layer gets without being asked to: any set of up to kPreTablesSmall
 // bytes (it stays in the L2s and the memory-side cache whichever workgroup reads which part:
 // the CIFAR-shaped layers with K slices gain 25 %), larger sets (up to kPreTablesMax bytes) for
@@ -1147,8 +1148,10 @@ constexpr size_t kPreTablesMax = (size_t)32 << 20;
 constexpr int kPreRowTiles = 8;
 
 // Pieces are combined by the main kernel (see kCombineElems).
-static bool combines(const Options& o, int partials, int most, int ih) {
-  return partials > 0 && (o.combine ? o.combine == 2 : (long long)(most - 1) * ih <= kCombineElems);
+static bool combines(const Options& o, int partials, int most, int ih, int nch) {
+  if (partials == 0) return false;
+  if (o.combine) return o.combine == 2;
+  return (long long)(most - 1) * ih <= kCombineElems || (most <= kCombineMost && nch >= kCombineLong);
 }
 // Ready-made tables (one 4 KiB table per tap and group of eight columns) where the filters are
 // the table side and one multiplier table is used.  Every workgroup reads the tables of its taps
@@ -1185,7 +1188,7 @@ static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int
     const double rounds = std::ceil((double)Gc / slots);
     const double iters = std::ceil((double)total / Gc);
     c.cost = rounds * (iters * t_chunk + segs * t_seg);
-    if (combines(o, c.partials, c.most, ih))
+    if (combines(o, c.partials, c.most, ih, nch))
       c.cost += 2.32e-6 + (c.most - 1) * 0.5e-9 * ih;
     else if (c.partials)
       c.cost += 5e-6 + c.partials * 2.0 * ih * kJT * 4.0 / 4.0e12;
@@ -1311,7 +1314,7 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   p.tile = best.tile;
   p.G = best.G;
   p.partials = best.partials;
-  p.combine = combines(o, best.partials, best.most, best.ih) ? 1 : 0;
+  p.combine = combines(o, best.partials, best.most, best.ih, cdiv(g.K, kChunk)) ? 1 : 0;
   p.nti = best.nti;
   p.ih = best.ih;
   {
@@ -1407,7 +1410,7 @@ static hipError_t launch_main(const TabArgs& a, int G, int ntiles, int phases, i
   }
   if (!(phases & kPhFixup) || a.cnt) return hipSuccess;
   const dim3 grid((unsigned)(ntiles * (a.ih / 64)));
-  if (G >= 16 * ntiles)
+  if ((double)a.total_iters * (G + 1) < 4.0e9)  // (w + 1) * total and it * G fit 32 bits
     hipLaunchKernelGGL((tab_fixup_kernel<CH, true>), grid, dim3(256), 0, s, a, G);
   else
     hipLaunchKernelGGL((tab_fixup_kernel<CH, false>), grid, dim3(256), 0, s, a, G);
