@@ -866,91 +866,92 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
 
 // Materialized im2col, Ap[Kp / 16][m][16] (zero fill for k >= K): used when the implicit view cannot be
 // read in aligned 16-byte pieces (Cin not a multiple of 16, or a misaligned base pointer).
-// Staged form of the same materialization for the usual case (few input channels, e.g. the
-// first layer of a network): a block takes kStripe consecutive output pixels of one output row
-// and copies the input rows they touch into LDS once (every input byte is used by about
-// KH*KW/(sh*sw) patches).  The position of a patch byte in that stage is the same for every pixel
-// up to a constant step, so the four offsets of each output dword are decoded once per block
-// (one table entry per dword of a patch); the block's part of Ap is contiguous and is then
-// written dword by dword, consecutive threads to consecutive addresses, with no division or
-// multiplication per element.  Used when both LDS areas are small enough (im2col_staged_fits).
-constexpr int kStripe = 32;
-static inline size_t im2col_row_bytes(const ConvView& cv) {
-  return (size_t)((kStripe - 1) * cv.sw + (cv.KW - 1) * cv.dw + 1) * cv.Cin;
-}
-static inline size_t im2col_stage_bytes(const ConvView& cv, int KH) { return (im2col_row_bytes(cv) * KH + 15) & ~(size_t)15; }
-static inline bool im2col_staged_fits(const ConvView& cv, int KH, int Kp) {
-  return im2col_stage_bytes(cv, KH) <= 16384 && Kp <= 4096;
-}
-__global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int KH, int Kp, int row_bytes, int stage_bytes,
+// Staged form of the same materialization for the usual case (few input channels, e.g. the first layer of a
+// network): a block takes r output rows of a stripe of pw output pixels and copies the input rows
+// they touch into LDS once (every input byte is used by about KH*KW/(sh*sw) patches).  The stage offsets of
+// a chunk's sixteen bytes are the same for every pixel up to the pixel's own offset, so they are decoded
+// once per block; a thread then gathers the 16 bytes of one pixel and chunk from LDS and writes them with
+// one store, neighbouring threads neighbouring pixels, a wave a contiguous kilobyte.
+// Bound: the writes of Ap, beside one LDS read per byte of it.  Blocks of up to 512 pixels, so that the
+// round trip of the stage's loads and the decoding are paid seldom: 32 x 32 x 3, 3 x 3, batch 1000 (33 MB
+// of patches) 61 us with stripes of 32 pixels and a dword per thread, 17 us now; 224 x 224 x 3, 7 x 7 with
+// stride 2, batch 32 (64 MB) 47 us, 28 us now.  Smaller blocks where fewer than
+// four per CU would be left (8: 18 and 34 us; 1024 pixels: 22 and 28), narrower ones where fewer than one.
+struct Im2colTile {
+  int pw, r;              // output pixels per row of a block, output rows of a block
+  int nstripe, nrows;     // blocks across and down an image
+  int npix;               // pw * r
+  int row_bytes;          // staged bytes of an input row
+  int stage_bytes;        // of the whole stage, a multiple of 16
+  uint32_t pw_mul, npix_mul, row_mul;  // floor(i / pw) = umulhi(2 * i, pw_mul), exact for i * pw < 2^31; the others alike
+};
+__global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int KH, int nch, Im2colTile t,
                                                               uint8_t* __restrict__ Ap) {
   extern __shared__ __align__(16) uint8_t smem[];
-  uint8_t* stage = smem;                                     // [KH][row_bytes] input bytes
-  int4* offtab = reinterpret_cast<int4*>(smem + stage_bytes);  // [Kp / 4] stage offsets of a dword's bytes, -1: zero
+  uint8_t* stage = smem;                                                 // [input rows][row_bytes]
+  uint16_t* offtab = reinterpret_cast<uint16_t*>(smem + t.stage_bytes);  // [nch * 16] stage offsets of a patch's bytes
   const uint32_t pad = pad_of(cv);
-  const int ox0 = blockIdx.x * kStripe, oy = blockIdx.y, n = blockIdx.z;
-  const int ix0 = ox0 * cv.sw - cv.pw;
+  const int n = blockIdx.x / (t.nstripe * t.nrows), rest = blockIdx.x - n * (t.nstripe * t.nrows);
+  const int rb = rest / t.nstripe;
+  const int oy0 = rb * t.r, ox0 = (rest - rb * t.nstripe) * t.pw;
+  const int nr = min(t.r, cv.OH - oy0), npx = min(t.pw, cv.OW - ox0);
+  const int ix0 = ox0 * cv.sw - cv.pw, iy0 = oy0 * cv.sh - cv.ph;
+  const int total = ((nr - 1) * cv.sh + (KH - 1) * cv.dh + 1) * t.row_bytes;
   // Byte b of a staged row is byte ix0 * Cin + b of the input row: in the image for
   // lo_b <= b < hi_b, padding outside.
-  const int lo_b = max(0, -ix0) * cv.Cin;
-  const int hi_b = min(row_bytes, (cv.W - ix0) * cv.Cin);
-  // Eight filter rows at a time, every load unconditional and from an address clamped into the
-  // image (what lies outside is replaced afterwards): the loads of a thread are then issued back
-  // to back instead of one memory round trip per row.
-  const bool any_col = hi_b > lo_b;
-  for (int ky0 = 0; ky0 < KH && any_col; ky0 += 8) {
-    for (int b = threadIdx.x; b < row_bytes; b += 256) {
-      const bool col_in = b >= lo_b && b < hi_b;
-      const int bc = min(max(b, lo_b), hi_b - 1);
+  const int lo_b = min(max(0, -ix0), t.row_bytes / cv.Cin) * cv.Cin;
+  const int hi_b = min(cv.W - ix0, t.row_bytes / cv.Cin) * cv.Cin;
+  // Eight bytes per thread at a time, every load unconditional and from an address clamped into the image
+  // (what lies outside is replaced afterwards), so that the loads are issued back to back.
+  if (hi_b > lo_b) {
+    const uint8_t* img = cv.x + (long long)n * cv.H * cv.W * cv.Cin + (long long)ix0 * cv.Cin;
+    for (int i0 = threadIdx.x; i0 < total; i0 += 256 * 8) {
       uint32_t v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int iy = oy * cv.sh - cv.ph + min(ky0 + j, KH - 1) * cv.dh;
-        const int iyc = min(max(iy, 0), cv.H - 1);
-        v[j] = cv.x[((long long)(n * cv.H + iyc) * cv.W + ix0) * cv.Cin + bc];
+        const int i = min(i0 + 256 * j, total - 1);
+        const int row = (int)__umulhi(2u * (uint32_t)i, t.row_mul), b = i - row * t.row_bytes;
+        v[j] = img[(long long)min(max(iy0 + row, 0), cv.H - 1) * cv.W * cv.Cin + min(max(b, lo_b), hi_b - 1)];
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int iy = oy * cv.sh - cv.ph + (ky0 + j) * cv.dh;
-        const bool in = col_in && (unsigned)iy < (unsigned)cv.H;
-        if (ky0 + j < KH) stage[(ky0 + j) * row_bytes + b] = (uint8_t)(in ? v[j] ^ cv.sx : pad);
+        const int i = i0 + 256 * j;
+        const int row = (int)__umulhi(2u * (uint32_t)i, t.row_mul), b = i - row * t.row_bytes;
+        const bool in = b >= lo_b && b < hi_b && (unsigned)(iy0 + row) < (unsigned)cv.H;
+        if (i < total) stage[i] = (uint8_t)(in ? v[j] ^ cv.sx : pad);
       }
     }
+  } else {  // the whole stripe reads padding columns only
+    for (int i = threadIdx.x; i < total; i += 256) stage[i] = (uint8_t)pad;
   }
-  if (!any_col)  // the whole stripe reads padding columns only
-    for (int idx = threadIdx.x; idx < KH * row_bytes; idx += 256) stage[idx] = (uint8_t)pad;
-  const int ndw = Kp / 4;
-  for (int j = threadIdx.x; j < ndw; j += 256) {
-    int o[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = 4 * j + e;
-      const int tap = k / cv.Cin, ci = k - tap * cv.Cin;
-      const int ky = tap / cv.KW, kx = tap - ky * cv.KW;
-      o[e] = k < cv.K ? ky * row_bytes + kx * cv.dw * cv.Cin + ci : -1;
-    }
-    offtab[j] = make_int4(o[0], o[1], o[2], o[3]);
+  for (int k = threadIdx.x; k < nch * 16; k += 256) {
+    const int tap = k / cv.Cin, ci = k - tap * cv.Cin;
+    const int ky = tap / cv.KW, kx = tap - ky * cv.KW;
+    offtab[k] = k < cv.K ? (uint16_t)(ky * cv.dh * t.row_bytes + kx * cv.dw * cv.Cin + ci) : (uint16_t)0;
   }
   __syncthreads();
-  const int npix = min(kStripe, cv.OW - ox0);
-  const int pix_step = cv.sw * cv.Cin;  // stage bytes between neighbouring output pixels
-  // Ap lies chunk by chunk, [Kp / 16][M][16]: the block's pixels form one run of npix * 16 bytes
-  // per chunk.  Element idx = (chunk c, pixel p, dword jj of the chunk); consecutive threads
-  // write consecutive dwords of a run.
-  const size_t m0 = ((size_t)n * cv.OH + oy) * cv.OW + ox0;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(Ap);
-  const int run = npix * 4;
-  for (int idx = threadIdx.x; idx < npix * ndw; idx += 256) {
-    const int c = idx / run, rem = idx - c * run;
-    const int pl = rem >> 2, jj = rem & 3;
-    const int4 o = offtab[4 * c + jj];
-    const int base = pl * pix_step;
-    uint32_t v = 0;
-    if (o.x >= 0) v = stage[o.x + base];
-    if (o.y >= 0) v |= (uint32_t)stage[o.y + base] << 8;
-    if (o.z >= 0) v |= (uint32_t)stage[o.z + base] << 16;
-    if (o.w >= 0) v |= (uint32_t)stage[o.w + base] << 24;
-    dst[((size_t)c * (size_t)cv.M + m0 + pl) * 4 + jj] = v;
+  const size_t m0 = ((size_t)n * cv.OH + oy0) * cv.OW + ox0;
+  for (int i = threadIdx.x; i < nch * t.npix; i += 256) {
+    const int c = (int)__umulhi(2u * (uint32_t)i, t.npix_mul), px = i - c * t.npix;
+    const int r = (int)__umulhi(2u * (uint32_t)px, t.pw_mul), ox = px - r * t.pw;
+    const bool in = r < nr && ox < npx;
+    const uint8_t* from = stage + (in ? r * cv.sh * t.row_bytes + ox * cv.sw * cv.Cin : 0);
+    const uint4* op = reinterpret_cast<const uint4*>(offtab + c * 16);
+    const uint4 oa = op[0], ob = op[1];
+    const uint32_t o[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
+    uint32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = (uint32_t)from[o[2 * q] & 0xffffu] | (uint32_t)from[o[2 * q] >> 16] << 8 |
+             (uint32_t)from[o[2 * q + 1] & 0xffffu] << 16 | (uint32_t)from[o[2 * q + 1] >> 16] << 24;
+    const int left = cv.K - c * 16;  // bytes of this chunk that belong to the patch
+    if (left < 16) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] &= left >= 4 * q + 4 ? ~0u : left <= 4 * q ? 0u : (1u << (8 * (left - 4 * q))) - 1u;
+    }
+    if (in)
+      *reinterpret_cast<uint4*>(Ap + ((size_t)c * (size_t)cv.M + m0 + (size_t)r * cv.OW + ox) * 16) =
+          make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -1061,6 +1062,35 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
 constexpr int kMaxSeg = 64;  // segments of the table-side column sums
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
+
+// False where no stage of a useful stripe fits: prep_im2col_kernel.
+static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t) {
+  if (Kp > 4096) return false;
+  const long long rows1 = (long long)(KH - 1) * cv.dh + 1;
+  auto row_bytes = [&](int pw) { return ((long long)(pw - 1) * cv.sw + (long long)(cv.KW - 1) * cv.dw + 1) * cv.Cin; };
+  int pw = cdiv(cv.OW, cdiv(cv.OW, 256));
+  while (row_bytes(pw) * rows1 > 32768 && pw > 1) pw = cdiv(pw, 2);
+  while ((long long)N * cv.OH * cdiv(cv.OW, pw) < 256 && cdiv(pw, 2) * (Kp / 16) >= 64 && pw > 1) pw = cdiv(pw, 2);
+  const long long rb = row_bytes(pw);
+  if (rb * rows1 > 32768) return false;
+  const int nstripe = cdiv(cv.OW, pw);
+  int r = 1;
+  while (r < cv.OH && pw * (r + 1) <= 512 && rb * ((long long)r * cv.sh + rows1) <= 16384 &&
+         (long long)N * nstripe * cdiv(cv.OH, r + 1) >= 1024)
+    ++r;
+  if ((long long)N * nstripe * cdiv(cv.OH, r) > 0x7fffffffLL) return false;
+  auto mul = [](int d) { return (uint32_t)(((1ull << 31) + d - 1) / d); };
+  const int stage = (int)((rb * ((long long)(r - 1) * cv.sh + rows1) + 15) & ~15ll);
+  *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, mul(pw), mul(pw * r), mul((int)rb)};
+  return true;
+}
+// 1 x 1 filters that read every pixel: the images as one row of pixels.
+static void im2col_flatten(ConvView* cv, int KH, int* N) {
+  if (KH != 1 || cv->KW != 1 || cv->ph || cv->pw || cv->sh != 1 || cv->sw != 1) return;
+  if (cv->OH != cv->H || cv->OW != cv->W) return;
+  cv->W = cv->OW = cv->M;
+  cv->H = cv->OH = *N = 1;
+}
 
 // Tile configurations: the greatest height of a tile in lane elements (tiles are 8 columns wide).  The
 // "tile" option selects one by index + 1; the automatic choice is the full height of the kernel.
@@ -1298,8 +1328,11 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   // time plus 3 to 8 us (activations read 16 channels at a time), plus 9 and 0.8 us a megabyte (patch
   // matrix; 3.5 without a staged form) or plus 7 to 12 (channel lanes).
   const double xbytes = (double)g.M * g.K;
-  const ConvView rows{nullptr, g.H, g.W, g.Cin, g.KW, g.sh, g.sw, g.ph, g.pw, g.OH, g.OW, g.M, g.K, 0, nullptr, g.dh, g.dw, 0};
-  const bool staged = im2col_staged_fits(rows, g.KH, cdiv(g.K, kChunk) * kChunk);
+  ConvView rows{nullptr, g.H, g.W, g.Cin, g.KW, g.sh, g.sw, g.ph, g.pw, g.OH, g.OW, g.M, g.K, 0, nullptr, g.dh, g.dw, 0};
+  int images = g.N;
+  im2col_flatten(&rows, g.KH, &images);
+  Im2colTile stripe;
+  const bool staged = im2col_tile(rows, g.KH, images, cdiv(g.K, kChunk) * kChunk, &stripe);
   const double around[2] = {g.Cin % 16 == 0 ? 6e-6 : 9e-6 + (staged ? 0.8e-12 : 3.5e-12) * xbytes, 9.1e-6 + 5e-12 * xbytes};
   PlanChoice best{0, 0, 0, 0, 0, 0, 1e30, 0};
   for (int v = 2; v <= 3; ++v) {
@@ -1492,11 +1525,13 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
                          cv.sx * 0x01010101u, qd, Ap);
       AX_LAUNCHED();
     } else if ((phases & kPhCall) && !implicit_view) {
-      if (im2col_staged_fits(cv, g.KH, Kp) && g.OH <= 65535 && g.N <= 65535) {
-        const size_t stage_bytes = im2col_stage_bytes(cv, g.KH);
-        hipLaunchKernelGGL(prep_im2col_lds_kernel, dim3(cdiv(g.OW, kStripe), g.OH, g.N), dim3(256),
-                           (unsigned)(stage_bytes + (size_t)Kp * 4), s, cv, g.KH, Kp, (int)im2col_row_bytes(cv),
-                           (int)stage_bytes, Ap);
+      ConvView rows = cv;
+      int images = g.N;
+      im2col_flatten(&rows, g.KH, &images);
+      Im2colTile t;
+      if (im2col_tile(rows, g.KH, images, Kp, &t)) {
+        hipLaunchKernelGGL(prep_im2col_lds_kernel, dim3((unsigned)((long long)images * t.nstripe * t.nrows)), dim3(256),
+                           (unsigned)(t.stage_bytes + (size_t)Kp * 2), s, rows, g.KH, nchunks, t, Ap);
       } else {
         const long long pieces = (long long)g.M * (Kp / 16);
         hipLaunchKernelGGL(prep_im2col_kernel, dim3((unsigned)cdiv(pieces, 256)), dim3(256), 0, s, cv, Kp, Ap);

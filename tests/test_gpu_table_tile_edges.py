@@ -1,0 +1,119 @@
+"""Table tiles and what prepares their activations, at the sizes where each form begins and ends: heights of
+a tile, odd and even chunk counts, activations read in place and from their copy, patch stripes of
+whole and partial rows, pieces of shared tiles.  Against the oracle: int32 accumulators bit exact."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2002_09481_amd import binding as ax
+from paper_2002_09481_amd import inputs as I
+
+import gpu_common as G
+from test_gpu_variants import _operands
+
+pytestmark = pytest.mark.gpu
+
+TUNE = dict(variant=2, split_k=0, tile=0, row_tiles=0, share_order=0, combine=0, tables=0)
+
+
+def _run(shape, stride, pad, dilation, signed, tune, small_workspace=False, offset=0):
+    x, w, q = _operands(shape, sum(shape) + 2 * signed, signed)
+    lut = I.lut_signed_random_error(7) if signed else I.lut_random_error(7)
+    want, y_want = oracle.conv2d_ex(x, w, lut, stride, pad, q, dilation=dilation, signed=signed)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, stride, pad, dilation, signed=signed), q,
+                    tune=dict(TUNE, **tune)) as h:
+        assert h.plan()["variant"] == tune.get("variant", 2)
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        buf = torch.empty(x.size + offset, dtype=torch.int8 if signed else torch.uint8, device="cuda")
+        xd = buf[offset:].view(x.shape)
+        xd.copy_(G.to_dev(x))
+        ws = torch.empty(256, dtype=torch.uint8, device="cuda") if small_workspace else None
+        for call in range(2):
+            acc, y = h.run(xd, workspace=ws)
+            torch.cuda.synchronize()
+            G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), want, y_want, "%s %s call %d" % (shape, tune, call))
+        return h.plan()
+
+
+# one tile of every height class: 64 lane elements, the last with double-buffered rows (2048), the first
+# without (2049), the tallest (4096) and one more; one, two and three chunks, five with a ragged last one
+@pytest.mark.parametrize("tables", [1, 2])
+@pytest.mark.parametrize("K", [16, 32, 48, 70])
+@pytest.mark.parametrize("M", [1, 64, 65, 2048, 2049, 4096, 4097])
+def test_tile_heights_and_chunk_counts(M, K, tables):
+    _run((M, 1, 1, K, 1, 1, 9), 1, 0, 1, False, dict(row_tiles=1 if M <= 4096 else 2, split_k=1, tables=tables))
+
+
+# (shape, stride, pad, dilation): copies with border, by output pixel, with other strides and dilations; rows of
+# more than 32767 pixels with padding
+VIEWS = [
+    ((2, 9, 11, 16, 3, 3, 9), 1, 1, 1), ((2, 9, 11, 32, 3, 3, 8), 2, 1, 1), ((1, 12, 10, 48, 3, 3, 17), 1, 2, 2),
+    ((3, 7, 9, 144, 1, 1, 8), 2, 0, 1), ((2, 6, 5, 64, 1, 1, 70), 1, 0, 1), ((1, 8, 8, 16, 5, 3, 8), 1, (4, 0), 1),
+    ((1, 2, 32800, 16, 1, 3, 5), 1, (0, 1), 1),
+]
+
+
+@pytest.mark.parametrize("signed, small_workspace", [(False, False), (False, True), (True, False)])  # signed codes need their copy
+@pytest.mark.parametrize("case", VIEWS, ids=lambda c: "x".join(map(str, c[0])))
+def test_activations_in_place_and_from_their_copy(case, signed, small_workspace):
+    _run(*case, signed, dict(split_k=1), small_workspace)
+
+
+# channel counts or base addresses that rule out aligned 16-byte reads: stripes of one pixel, of a ragged last
+# column and row, of several rows, wholly in the padding; strides beyond the filter, wide dilations; the images
+# as one row; too wide for the stage
+PATCHES = [
+    ((1, 1, 1, 1, 1, 1, 5), 1, 0, 1), ((3, 17, 1, 3, 3, 1, 8), 1, (1, 0), 1), ((1, 5, 300, 3, 3, 3, 8), 1, 1, 1),
+    ((70, 19, 23, 3, 3, 3, 4), 1, 1, 1), ((300, 9, 6, 1, 2, 2, 4), 1, 0, 1), ((2, 21, 26, 5, 3, 3, 8), 5, 1, 1),
+    ((1, 6, 6, 4, 1, 1, 8), 1, 7, 1), ((2, 30, 28, 7, 3, 3, 8), 1, 9, 9), ((40, 1, 1, 100, 1, 1, 8), 1, 0, 1),
+    ((5, 8, 6, 21, 1, 1, 8), 1, 0, 1), ((5, 9, 7, 21, 1, 1, 8), 2, 0, 1), ((2, 5, 40, 1030, 3, 3, 8), 1, 1, 1),
+    ((2, 3, 3, 4097, 1, 1, 8), 1, 0, 1),
+]
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("case", PATCHES, ids=lambda c: "x".join(map(str, c[0])))
+def test_patches_copied_out(case, signed):
+    _run(*case, signed, {})
+
+
+def test_activations_at_any_byte():
+    for offset in (1, 4, 8):
+        _run((2, 9, 11, 32, 3, 3, 9), 1, 1, 1, False, {}, offset=offset)
+
+
+@pytest.mark.parametrize("combine", [1, 2])
+@pytest.mark.parametrize("split", [2, 3, 7])
+@pytest.mark.parametrize("case", [((3, 5, 5, 64, 3, 3, 20), 1, 1, 1), ((1, 48, 48, 64, 3, 3, 9), 1, 1, 1), ((130, 1, 1, 500, 1, 1, 30), 1, 0, 1)],
+                         ids=lambda c: "x".join(map(str, c[0])))
+def test_pieces_of_shared_tiles(case, split, combine):
+    plan = _run(*case, False, dict(split_k=split, combine=combine))
+    assert plan["pieces"] > 0 and plan["combine"] == combine
+
+
+def test_channel_lanes_and_a_sum_of_more_taps_than_sixteen_bits_hold():
+    _run((60, 1, 1, 200, 1, 1, 70), 1, 0, 1, False, dict(variant=3))
+    for variant in (2, 3):  # 32768 taps of the largest codes
+        _run((3, 1, 1, 32768, 1, 1, 9), 1, 0, 1, False, dict(variant=variant))
+
+
+def test_stripes_against_the_general_patch_copy():
+    """The staged copy and the general one (sums of more than 4096 taps) give the same patches: a layer, and the same
+    layer with zero channels appended until only the general form takes it, differ by the table's value at
+    code 0 alone."""
+    rng = np.random.default_rng(3)
+    x = rng.integers(0, 256, (2, 7, 9, 5), dtype=np.uint8)
+    w = rng.integers(0, 256, (3, 3, 5, 6), dtype=np.uint8)
+    lut = I.lut_random_error(11).copy().reshape(256, 256)
+    lut[0, 0] = 0
+    q = I.Quant(0.02, 0, 0.01, 0, None)
+    wide_x, wide_w = np.zeros((2, 7, 9, 501), np.uint8), np.zeros((3, 3, 501, 6), np.uint8)
+    wide_x[..., :5], wide_w[:, :, :5] = x, w
+    out = []
+    for a, b in ((x, w), (wide_x, wide_w)):
+        with ax.AxLayer(ax._conv_desc(a.shape, b.shape, 1, 1), q, tune=TUNE) as h:
+            h.prepare(G.to_dev(b), ax.lut_to_device(lut))
+            out.append(h.run(G.to_dev(a))[0].cpu().numpy())
+    assert np.array_equal(out[0], out[1])
