@@ -330,8 +330,10 @@ int run_prepared(const ax_layer* layer, const void* x, int32_t* acc_out, float* 
   const TabPlan& p = layer->r.p;
   const size_t need = scratch_need(layer, x);
   if (need && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return AX_ERR_WORKSPACE;
+  // A call that needs no scratch takes any buffer; one that is too small or not aligned stays unused.
+  const bool full = workspace && workspace_bytes >= p.ws_total && ((uintptr_t)workspace & 255) == 0;
   const hipError_t e = launch_tab(layer->g, layer->qp, p, xb, layer->w, layer->lut, acc_out, y_out, layer->prepared,
-                                  workspace, workspace && workspace_bytes >= p.ws_total, phases, main_reps, s);
+                                  workspace, full, phases, main_reps, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 }  // namespace ax

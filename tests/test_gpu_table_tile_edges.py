@@ -117,3 +117,20 @@ def test_stripes_against_the_general_patch_copy():
             h.prepare(G.to_dev(b), ax.lut_to_device(lut))
             out.append(h.run(G.to_dev(a))[0].cpu().numpy())
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("offset", [1, 16, 128, 0])
+def test_a_workspace_off_its_alignment_stays_unused(offset):
+    """A layer that reads its activations in place and has no shared tiles needs no scratch: a buffer that is not
+    256-byte aligned is accepted and not written, an aligned one of the full size receives the copy."""
+    x, w, q = _operands((2, 9, 11, 32, 3, 3, 9), 60, False)
+    lut = I.lut_random_error(7)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 1), q, tune=dict(TUNE, split_k=1)) as h:
+        assert h.plan()["pieces"] == 0
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        buf = torch.full((h.workspace_bytes + 512,), 0xA5, dtype=torch.uint8, device="cuda")
+        start = -buf.data_ptr() % 256
+        acc, y = h.run(G.to_dev(x), workspace=buf[start + offset:start + offset + h.workspace_bytes])
+        torch.cuda.synchronize()
+        G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *oracle.conv2d_ex(x, w, lut, 1, 1, q))
+        assert bool((buf == 0xA5).all()) == (offset != 0)
