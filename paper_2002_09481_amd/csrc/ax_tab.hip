@@ -1078,7 +1078,7 @@ static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t
   while (r < cv.OH && pw * (r + 1) <= 512 && rb * ((long long)r * cv.sh + rows1) <= 16384 &&
          (long long)N * nstripe * cdiv(cv.OH, r + 1) >= 1024)
     ++r;
-  if ((long long)N * nstripe * cdiv(cv.OH, r) > 0x7fffffffLL) return false;
+  if ((long long)N * nstripe * cdiv(cv.OH, r) >= (1LL << 24)) return false;  // a launch holds fewer than 2^32 threads
   auto mul = [](int d) { return (uint32_t)(((1ull << 31) + d - 1) / d); };
   const int stage = (int)((rb * ((long long)(r - 1) * cv.sh + rows1) + 15) & ~15ll);
   *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, mul(pw), mul(pw * r), mul((int)rb)};

@@ -134,3 +134,19 @@ def test_a_workspace_off_its_alignment_stays_unused(offset):
         torch.cuda.synchronize()
         G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *oracle.conv2d_ex(x, w, lut, 1, 1, q))
         assert bool((buf == 0xA5).all()) == (offset != 0)
+
+
+def test_more_images_than_a_launch_holds_blocks():
+    """A block per image would be a launch of 2^32 threads."""
+    N = 1 << 24
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.randint(0, 256, (N, 2, 2, 1), generator=g, device="cuda", dtype=torch.uint8)
+    w = np.array([3, 200, 0, 255, 17, 90, 128, 64], np.uint8).reshape(2, 2, 1, 2)
+    lut = I.lut_random_error(2)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 0), I.Quant(1.0, 0, 1.0, 0, None), tune=TUNE) as h:
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        acc, _ = h.run(x, y_out=False)
+    table = torch.from_numpy(lut.astype(np.int32).reshape(256, 256)).cuda()
+    want = sum(table[x.view(N, 4)[:, t].long()][:, torch.from_numpy(w.reshape(4, 2)[t].astype(np.int64)).cuda()] for t in range(4))
+    assert torch.equal(acc.view(N, 2), want)
