@@ -877,13 +877,17 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
 // of patches) 61 us with stripes of 32 pixels and a dword per thread, 17 us now; 224 x 224 x 3, 7 x 7 with
 // stride 2, batch 32 (64 MB) 47 us, 28 us now.  Smaller blocks where fewer than
 // four per CU would be left (8: 18 and 34 us; 1024 pixels: 22 and 28), narrower ones where fewer than one.
+// Where the rows that a block's taps read are fewer than those it spans (dilated filters), they are staged one by one.
 struct Im2colTile {
   int pw, r;              // output pixels per row of a block, output rows of a block
   int nstripe, nrows;     // blocks across and down an image
   int npix;               // pw * r
   int row_bytes;          // staged bytes of an input row
   int stage_bytes;        // of the whole stage, a multiple of 16
-  uint32_t pw_mul, npix_mul, row_mul;  // floor(i / pw) = umulhi(2 * i, pw_mul), exact for i * pw < 2^31; the others alike
+  // Staged row s is input row first + s: every row that the block spans (group = all of them), or only the rows
+  // that its taps read, filter row by filter row (group = KH): first + (s / group) * sh + (s % group) * dh.
+  int group, srow, spix, stap;  // input rows per row of a group; stage rows per output row, per filter row
+  uint32_t pw_mul, npix_mul, row_mul, group_mul;  // floor(i / pw) = umulhi(2 * i, pw_mul), exact for i * pw < 2^31; the others alike
 };
 __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int KH, int nch, Im2colTile t,
                                                               uint8_t* __restrict__ Ap) {
@@ -896,7 +900,11 @@ __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int K
   const int oy0 = rb * t.r, ox0 = (rest - rb * t.nstripe) * t.pw;
   const int nr = min(t.r, cv.OH - oy0), npx = min(t.pw, cv.OW - ox0);
   const int ix0 = ox0 * cv.sw - cv.pw, iy0 = oy0 * cv.sh - cv.ph;
-  const int total = ((nr - 1) * cv.sh + (KH - 1) * cv.dh + 1) * t.row_bytes;
+  const int total = ((nr - 1) * t.spix + (KH - 1) * t.stap + 1) * t.row_bytes;
+  auto input_row = [&](int row) {
+    const int g = (int)__umulhi(2u * (uint32_t)row, t.group_mul);
+    return iy0 + g * cv.sh + (row - g * t.group) * t.srow;
+  };
   // Byte b of a staged row is byte ix0 * Cin + b of the input row: in the image for
   // lo_b <= b < hi_b, padding outside.
   const int lo_b = min(max(0, -ix0), t.row_bytes / cv.Cin) * cv.Cin;
@@ -911,13 +919,13 @@ __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int K
       for (int j = 0; j < 8; ++j) {
         const int i = min(i0 + 256 * j, total - 1);
         const int row = (int)__umulhi(2u * (uint32_t)i, t.row_mul), b = i - row * t.row_bytes;
-        v[j] = img[(long long)min(max(iy0 + row, 0), cv.H - 1) * cv.W * cv.Cin + min(max(b, lo_b), hi_b - 1)];
+        v[j] = img[(long long)min(max(input_row(row), 0), cv.H - 1) * cv.W * cv.Cin + min(max(b, lo_b), hi_b - 1)];
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int i = i0 + 256 * j;
         const int row = (int)__umulhi(2u * (uint32_t)i, t.row_mul), b = i - row * t.row_bytes;
-        const bool in = b >= lo_b && b < hi_b && (unsigned)(iy0 + row) < (unsigned)cv.H;
+        const bool in = b >= lo_b && b < hi_b && (unsigned)input_row(row) < (unsigned)cv.H;
         if (i < total) stage[i] = (uint8_t)(in ? v[j] ^ cv.sx : pad);
       }
     }
@@ -927,7 +935,7 @@ __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int K
   for (int k = threadIdx.x; k < nch * 16; k += 256) {
     const int tap = k / cv.Cin, ci = k - tap * cv.Cin;
     const int ky = tap / cv.KW, kx = tap - ky * cv.KW;
-    offtab[k] = k < cv.K ? (uint16_t)(ky * cv.dh * t.row_bytes + kx * cv.dw * cv.Cin + ci) : (uint16_t)0;
+    offtab[k] = k < cv.K ? (uint16_t)(ky * t.stap * t.row_bytes + kx * cv.dw * cv.Cin + ci) : (uint16_t)0;
   }
   __syncthreads();
   const size_t m0 = ((size_t)n * cv.OH + oy0) * cv.OW + ox0;
@@ -935,7 +943,7 @@ __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int K
     const int c = (int)__umulhi(2u * (uint32_t)i, t.npix_mul), px = i - c * t.npix;
     const int r = (int)__umulhi(2u * (uint32_t)px, t.pw_mul), ox = px - r * t.pw;
     const bool in = r < nr && ox < npx;
-    const uint8_t* from = stage + (in ? r * cv.sh * t.row_bytes + ox * cv.sw * cv.Cin : 0);
+    const uint8_t* from = stage + (in ? r * t.spix * t.row_bytes + ox * cv.sw * cv.Cin : 0);
     const uint4* op = reinterpret_cast<const uint4*>(offtab + c * 16);
     const uint4 oa = op[0], ob = op[1];
     const uint32_t o[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
@@ -1063,25 +1071,40 @@ constexpr int kMaxSeg = 64;  // segments of the table-side column sums
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-// False where no stage of a useful stripe fits: prep_im2col_kernel.
+// False: prep_im2col_kernel, where the stage cannot hold a block or is the slower form.  Staged, a block takes 1.5 ns of
+// the machine and 1.2 ps per staged byte.  The other form takes 5 ps per 16-byte piece and up to 30 ps for the lines
+// that a wave's byte loads touch (`step`: bytes between neighbouring pixels), 60 where the images do not fit the L2s, since
+// every chunk of taps walks through all of them.
+// Fitted to 1460 random layers (1 to 300000 images, dilations, strides): the rule's sum of times is 2 % above that of the
+// better form each time, 18 layers are on one that is more than 20 % slower; always staged 28 % above, never 85 %.
+// Many small images are the case where it matters (120191 of 4 x 4 x 4, 2 x 1 filter: staged 143 us, 19 otherwise).
 static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t) {
   if (Kp > 4096) return false;
-  const long long rows1 = (long long)(KH - 1) * cv.dh + 1;
+  const int nch = Kp / 16;
   auto row_bytes = [&](int pw) { return ((long long)(pw - 1) * cv.sw + (long long)(cv.KW - 1) * cv.dw + 1) * cv.Cin; };
+  // staged rows for r output rows: all that they span, or their taps' rows one by one
+  auto spanned = [&](int r) { return (long long)(r - 1) * cv.sh + (long long)(KH - 1) * cv.dh + 1; };
+  auto rows = [&](int r) { return std::min(spanned(r), (long long)r * KH); };
   int pw = cdiv(cv.OW, cdiv(cv.OW, 256));
-  while (row_bytes(pw) * rows1 > 32768 && pw > 1) pw = cdiv(pw, 2);
-  while ((long long)N * cv.OH * cdiv(cv.OW, pw) < 256 && cdiv(pw, 2) * (Kp / 16) >= 64 && pw > 1) pw = cdiv(pw, 2);
+  while (row_bytes(pw) * rows(1) > 32768 && pw > 1) pw = cdiv(pw, 2);
+  while ((long long)N * cv.OH * cdiv(cv.OW, pw) < 256 && cdiv(pw, 2) * nch >= 64 && pw > 1) pw = cdiv(pw, 2);
   const long long rb = row_bytes(pw);
-  if (rb * rows1 > 32768) return false;
+  if (rb * rows(1) > 32768) return false;
   const int nstripe = cdiv(cv.OW, pw);
   int r = 1;
-  while (r < cv.OH && pw * (r + 1) <= 512 && rb * ((long long)r * cv.sh + rows1) <= 16384 &&
-         (long long)N * nstripe * cdiv(cv.OH, r + 1) >= 1024)
-    ++r;
-  if ((long long)N * nstripe * cdiv(cv.OH, r) >= (1LL << 24)) return false;  // a launch holds fewer than 2^32 threads
+  while (r < cv.OH && pw * (r + 1) <= 512 && rb * rows(r + 1) <= 16384 && (long long)N * nstripe * cdiv(cv.OH, r + 1) >= 1024) ++r;
+  const long long blocks = (long long)N * nstripe * cdiv(cv.OH, r), bytes = rb * rows(r);
+  if (blocks >= (1LL << 24)) return false;  // a launch holds fewer than 2^32 threads
+  const double span_h = (double)spanned(cv.OH), span_w = (double)(cv.OW - 1) * cv.sw + (double)(cv.KW - 1) * cv.dw + 1.0;
+  const double pieces = (double)N * cv.OH * cv.OW * nch, inside = std::min(1.0, cv.H / span_h) * std::min(1.0, cv.W / span_w);
+  const double xbytes = (double)N * cv.H * cv.W * cv.Cin, step = std::max((double)cv.Cin * cv.sw, xbytes / ((double)N * cv.OH * cv.OW));
+  const double general = pieces * (0.005 + (xbytes > 16e6 ? 0.06 : 0.03) * inside * std::min(1.0, step / 128.0));
+  if (blocks * (1.5 + 1.2e-3 * bytes) > general + 500.0) return false;  // ns; half a microsecond decides nothing
+  const bool taps = rows(r) < spanned(r);
   auto mul = [](int d) { return (uint32_t)(((1ull << 31) + d - 1) / d); };
-  const int stage = (int)((rb * ((long long)(r - 1) * cv.sh + rows1) + 15) & ~15ll);
-  *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, mul(pw), mul(pw * r), mul((int)rb)};
+  const int stage = (int)((bytes + 15) & ~15ll), group = taps ? KH : (int)spanned(r);
+  *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, group, taps ? cv.dh : 1, taps ? KH : cv.sh, taps ? 1 : cv.dh,
+        mul(pw), mul(pw * r), mul((int)rb), mul(group)};
   return true;
 }
 // 1 x 1 filters that read every pixel: the images as one row of pixels.

@@ -70,6 +70,8 @@ PATCHES = [
     ((1, 6, 6, 4, 1, 1, 8), 1, 7, 1), ((2, 30, 28, 7, 3, 3, 8), 1, 9, 9), ((40, 1, 1, 100, 1, 1, 8), 1, 0, 1),
     ((5, 8, 6, 21, 1, 1, 8), 1, 0, 1), ((5, 9, 7, 21, 1, 1, 8), 2, 0, 1), ((2, 5, 40, 1030, 3, 3, 8), 1, 1, 1),
     ((2, 3, 3, 4097, 1, 1, 8), 1, 0, 1),
+    # only the rows that taps read: one output row a block, several with a ragged last one, a stride beyond the filter, one filter row
+    ((1, 40, 50, 3, 3, 3, 8), 1, 12, 12), ((130, 21, 12, 3, 3, 3, 4), 1, 8, 8), ((200, 41, 6, 5, 2, 2, 4), (6, 1), 1, 1), ((300, 26, 9, 3, 1, 3, 4), (5, 1), 0, 1),
 ]
 
 
