@@ -631,7 +631,9 @@ GradPlan grad_plan(const Geom& g) {
     }
     return best;
   };
-  p.dsplits = slices_of(std::max(1LL, dt), stages_max, 4, 64, p.tc_d == 256 ? 1.0 : 2.0, 8.0, p.tc_d == 256 ? 2.0 : 1.7,
+  // (a class and a slice per block row of the launch, of which there are 65535 at most)
+  const int most_d = (int)std::max(1LL, std::min(64LL, 65535LL / std::max(1LL, (long long)g.sh * g.sw)));
+  p.dsplits = slices_of(std::max(1LL, dt), stages_max, 4, most_d, p.tc_d == 256 ? 1.0 : 2.0, 8.0, p.tc_d == 256 ? 2.0 : 1.7,
                         4.0 * g.N * g.H * g.W * g.Cin);
   p.dfold = stages_max > 8LL * p.dsplits;
   const long long tiles = (long long)((g.K + p.tr_w - 1) / p.tr_w) * ((g.Cout + p.tc_w - 1) / p.tc_w);

@@ -22,6 +22,7 @@ SHAPES = [
     (3, 10, 10, 20, 3, 3, 40, 2, 1, 1),    # 128 x 64 tiles, classes of a stride
     (1, 3, 3, 512, 3, 3, 160, 1, 1, 1),    # nine pixels, 144 stages of the input gradient
     (16, 24, 24, 8, 3, 3, 16, 1, 1, 2),    # many pixels, few taps: many slices; dilation
+    (1, 46, 46, 4, 1, 1, 5280, 45, 0, 1),  # 2025 classes of a stride, 165 stages: a launch holds 32 slices of them
 ]
 
 
