@@ -177,10 +177,11 @@ __global__ __launch_bounds__(256) void grad_wint_kernel(const uint8_t* __restric
 // stride 2) instead of multiplying zeros.  blockIdx = (tile within the class, Cin tile, class).
 // A wave takes 32 rows and all TC columns (two waves share them where there are eight): every piece
 // read from LDS feeds several matrix instructions.
-// FOLD: running sums beside the matrix instructions' (see kFold); slices of at most eight stages go without,
-// which saves the registers of the narrow tiles.
+// FOLD: running sums beside the matrix instructions' (see kFold); slices of at most eight stages (four, whose sums
+// are the same bits, on tiles of 256 columns) go without, which saves the registers.  (Narrow tiles with them: bounded to three waves per SIMD, as those without take; two cost up
+// to 30 %.)
 template <int TC, int WAVES, bool FOLD>
-__global__ __launch_bounds__(64 * WAVES, TC == 128 && FOLD ? 4 : TC == 256 ? 2 : 1) void dgrad_kernel(const GradArgs a) {
+__global__ __launch_bounds__(64 * WAVES, TC == 128 && FOLD ? 4 : TC == 256 ? 2 : TC == 64 && FOLD ? 3 : 1) void dgrad_kernel(const GradArgs a) {
   constexpr int THREADS = 64 * WAVES;
   constexpr int CG = WAVES / 4;                 // waves side by side; four rows of waves cover the 128 tile rows
   constexpr int NB = TC / (32 * CG);            // 32 x 32 blocks per wave
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(64 * WAVES, TC == 128 && FOLD ? 4 : TC == 256 ? 2 :
 // clocks against 1545 clocks).  VEC keeps tap 4 q + j of the tile in LDS row j * TR / 4 + q, so
 // that consecutive lanes store to consecutive rows.
 template <int TR, int TC, int WAVES, bool VEC>
-__global__ __launch_bounds__(64 * WAVES, TC == 64 ? 1 : 2) void wgrad_kernel(const GradArgs a) {
+__global__ __launch_bounds__(64 * WAVES, TC == 64 ? (VEC ? 1 : 3) : 2) void wgrad_kernel(const GradArgs a) {
   constexpr int THREADS = 64 * WAVES;
   constexpr int RG = TR / 64;                  // rows of waves: a wave takes 64 taps
   constexpr int CG = WAVES / RG;               // waves side by side
@@ -534,22 +535,23 @@ __global__ __launch_bounds__(64 * WAVES, TC == 64 ? 1 : 2) void wgrad_kernel(con
 // contraction was cut into slices (scale alpha2).  A block takes 32 outputs; its eight groups of
 // threads each add every eighth slice, and the eight sums are added in group order: a fixed
 // order, so the same bits in every run, and no thread walks hundreds of slices alone (the filter
-// gradient of a layer with few filters and many pixels has that many).
+// gradient of a layer with few filters and many pixels has that many).  The slices are added in 64 bits, which
+// the loads hide, so that many short slices round no more than few long ones.
 __global__ __launch_bounds__(256) void sum_slices_kernel(const float* __restrict__ part, int splits, size_t n,
                                                           float scale, float* __restrict__ out) {
-  __shared__ float red[8][32];
+  __shared__ double red[8][32];
   const int o = threadIdx.x & 31, sg = threadIdx.x >> 5;
   const size_t i = (size_t)blockIdx.x * 32 + o;
-  float s = 0.f;
+  double s = 0.0;
   if (i < n)
     for (int q = sg; q < splits; q += 8) s += part[(size_t)q * n + i];
   red[sg][o] = s;
   __syncthreads();
   if (sg == 0 && i < n) {
-    float tot = red[0][o];
+    double tot = red[0][o];
 #pragma unroll
     for (int g = 1; g < 8; ++g) tot += red[g][o];
-    out[i] = tot * scale;
+    out[i] = (float)(tot * scale);
   }
 }
 
@@ -558,9 +560,9 @@ __global__ __launch_bounds__(256) void sum_few_slices_kernel(const float* __rest
                                                               float scale, float* __restrict__ out) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  float s = 0.f;
+  double s = 0.0;
   for (int q = 0; q < splits; ++q) s += part[(size_t)q * n + i];
-  out[i] = s * scale;
+  out[i] = (float)(s * scale);
 }
 
 void launch_sum_slices(const float* part, int splits, size_t n, float scale, float* out, hipStream_t s) {
@@ -578,7 +580,7 @@ struct GradPlan {
   int tc_d, tc_w;  // column tile of dgrad (over Cin) and of wgrad (over Cout)
   int tr_w;        // row tile of wgrad (over the taps)
   int dsplits;     // slices of dgrad's contraction
-  bool dfold;      // they are longer than eight stages
+  bool dfold;      // they are longer than eight stages (tiles of 256 columns: four)
   uint8_t cls_order[16];
   size_t off_part, off_dpart, off_P, off_PT, off_wi, ws_bytes;
 };
@@ -590,8 +592,7 @@ GradPlan grad_plan(const Geom& g) {
   // integers and 1 for the activation codes), so their tiles are wide along the other operand.
   p.tc_w = g.Cout > 64 ? 128 : 64;
   p.tr_w = (p.tc_w == 128 && g.K > 128) ? 256 : 128;
-  // dgrad: the widest column tile the layer fills, then slices of the contraction (at least eight
-  // stages each) until the grid has four workgroups per compute unit
+  // dgrad: the widest column tile the layer fills
   // The classes (iy mod sh, ix mod sw) of input pixels differ in the taps that reach them (none at
   // all for three of the four classes of a 1 x 1 layer with stride 2): the grid is sized by the
   // tiles of the classes that have work, and takes the classes with the most taps first, so that
@@ -616,29 +617,43 @@ GradPlan grad_plan(const Geom& g) {
   if (ncls <= 16)
     std::stable_sort(p.cls_order, p.cls_order + ncls, [&](uint8_t x, uint8_t y) { return taps_of[x] > taps_of[y]; });
   const long long stages_max = (long long)max_taps * (p.Cp / kStage);
-  // Slices of the contractions, by expected time: workgroups of `slices` x tiles run in rounds of what the
+  // Slices of the input gradient's contraction (at least four stages each), by expected time: workgroups of `slices` x tiles run in rounds of what the
   // machine holds at once, each for a start and its stages (us, measured on 7 x 7 to 56 x 56 layers), and the
   // slices are written and added.  Four times as many workgroups as compute units, whatever the tile, cost
   // up to a quarter of the pass in half-filled second rounds and in slices.
-  auto slices_of = [&](long long tiles, long long stages, int least, int most, double fit, double start, double stage,
-                       double out_bytes) {
-    int best = 1;
-    double best_t = 1e30;
-    for (int n = 1; n <= most && (n == 1 || stages / n >= least); ++n) {
-      const double rounds = std::ceil((double)tiles * n / (fit * cu_count()));
-      const double t = rounds * (start + stage * (double)((stages + n - 1) / n)) + (n > 1 ? 5.0 + n * out_bytes / 3.5e6 : 0.0);
-      if (t < best_t) { best_t = t; best = n; }
-    }
-    return best;
-  };
   // (a class and a slice per block row of the launch, of which there are 65535 at most)
   const int most_d = (int)std::max(1LL, std::min(64LL, 65535LL / std::max(1LL, (long long)g.sh * g.sw)));
-  p.dsplits = slices_of(std::max(1LL, dt), stages_max, 4, most_d, p.tc_d == 256 ? 1.0 : 2.0, 8.0, p.tc_d == 256 ? 2.0 : 1.7,
-                        4.0 * g.N * g.H * g.W * g.Cin);
-  p.dfold = stages_max > 8LL * p.dsplits;
-  const long long tiles = (long long)((g.K + p.tr_w - 1) / p.tr_w) * ((g.Cout + p.tc_w - 1) / p.tc_w);
-  const long long s = slices_of(tiles, p.Mp / kStage, 8, 512, p.tr_w == 256 ? 1.0 : 2.0, 8.0, p.tr_w == 256 ? 1.9 : 1.4,
-                                4.0 * g.K * g.Cout);
+  p.dsplits = 1;
+  double best_d = 1e30;
+  for (int n = 1; n <= most_d && (n == 1 || stages_max / n >= 4); ++n) {
+    const double rounds = std::ceil((double)std::max(1LL, dt) * n / ((p.tc_d == 256 ? 1.0 : 2.0) * cu_count()));
+    const double t = rounds * (8.0 + (p.tc_d == 256 ? 2.0 : 1.7) * (double)((stages_max + n - 1) / n)) +
+                     (n > 1 ? 5.0 + n * 4.0 * g.N * g.H * g.W * g.Cin / 3.5e6 : 0.0);
+    if (t < best_d) { best_d = t; p.dsplits = n; }
+  }
+  p.dfold = stages_max > (p.tc_d == 256 ? (long long)kFold : 8LL) * p.dsplits;
+  // Filter gradient: workgroups on a compute unit (`resident` of them at once) take `lat` us a stage each, or `busy` us a
+  // stage together where that is longer.  Measured over 3077 random layers with 1 to 512 slices: the choice costs 1 to 2 %
+  // over the best slices of each kernel, and the pass takes 94 us where slices of eight stages and more at 1.4 to 1.9 us a
+  // stage took 128 and four times as many workgroups as compute units 129 (sums in thousands).  The byte form of the
+  // activation side (see wgrad_kernel) takes twice the time of the dword form and wants shorter slices.  It is priced by
+  // the channel count: at a base address that is no multiple of four a dword layer's slices stay.
+  struct Rate { double lat, busy, resident, start; };
+  const bool dwords = g.Cin % 4 == 0;
+  const Rate rate = p.tr_w == 256   ? dwords ? Rate{1.8, 1.6, 1, 4} : Rate{3.5, 1.6, 1, 6}
+                    : p.tc_w == 128 ? dwords ? Rate{1.8, 1.2, 2, 8} : Rate{2.9, 1.2, 2, 8}
+                                    : dwords ? Rate{1.25, 0.55, 3, 1} : Rate{2.4, 1.1, 3, 1};
+  const long long tiles = (long long)((g.K + p.tr_w - 1) / p.tr_w) * ((g.Cout + p.tc_w - 1) / p.tc_w), stages_w = p.Mp / kStage;
+  long long s = 1;
+  double best_t = 1e30;
+  for (long long n = 1; n <= std::min(512LL, stages_w); ++n) {
+    const long long len = (stages_w + n - 1) / n;
+    if (n > 1 && (stages_w + len - 1) / len != n) continue;  // no shorter slices than fewer have
+    const double on_cu = std::ceil((double)tiles * n / cu_count()), rounds = std::ceil(on_cu / rate.resident);
+    const double t = rate.start * rounds + len * std::max(rate.lat * rounds, rate.busy * on_cu) +
+                     (n > 1 ? 1.5 + n * 4.0 * g.K * g.Cout / 3.5e6 : 0.0);
+    if (t < best_t) { best_t = t; s = n; }
+  }
   int per = (int)(((g.M + s - 1) / s + kStage - 1) / kStage) * kStage;
   p.m_per_split = per;
   p.splits = (g.M + per - 1) / per;
@@ -719,7 +734,7 @@ extern "C" int ax_conv2d_backward(const ax_conv_desc_t* desc, const ax_quant_t* 
     const long long rows = (long long)g.N * ((g.H + g.sh - 1) / g.sh) * ((g.W + g.sw - 1) / g.sw);
     const dim3 grid((unsigned)((rows + kTR - 1) / kTR), (unsigned)((g.Cin + p.tc_d - 1) / p.tc_d),
                     (unsigned)(g.sh * g.sw * p.dsplits));
-    void (*dk)(GradArgs) = p.tc_d == 256   ? dgrad_kernel<256, 8, true>
+    void (*dk)(GradArgs) = p.tc_d == 256   ? p.dfold ? dgrad_kernel<256, 8, true> : dgrad_kernel<256, 8, false>
                            : p.tc_d == 128 ? p.dfold ? dgrad_kernel<128, 8, true> : dgrad_kernel<128, 4, false>
                                            : p.dfold ? dgrad_kernel<64, 4, true> : dgrad_kernel<64, 4, false>;
     hipLaunchKernelGGL(dk, grid, dim3(p.tc_d == 256 || (p.tc_d == 128 && p.dfold) ? 512 : 256), 0, s, a);
