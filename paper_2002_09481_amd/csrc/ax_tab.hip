@@ -884,11 +884,12 @@ struct Im2colTile {
   int npix;               // pw * r
   int row_bytes;          // staged bytes of an input row
   int stage_bytes;        // of the whole stage, a multiple of 16
-  // Staged row s is input row first + s: every row that the block spans (group = all of them), or only the rows
-  // that its taps read, filter row by filter row (group = KH): first + (s / group) * sh + (s % group) * dh.
-  int group, srow, spix, stap;  // input rows per row of a group; stage rows per output row, per filter row
+  // Staged row s is input row first + s: every row that the block spans (group = 0), or only the rows that its taps
+  // read, filter row by filter row (GROUPS, group = KH): first + (s / group) * sh + (s % group) * dh.
+  int group, spix, stap;  // stage rows per output row, per filter row
   uint32_t pw_mul, npix_mul, row_mul, group_mul;  // floor(i / pw) = umulhi(2 * i, pw_mul), exact for i * pw < 2^31; the others alike
 };
+template <bool GROUPS>
 __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int KH, int nch, Im2colTile t,
                                                               uint8_t* __restrict__ Ap) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -902,8 +903,9 @@ __global__ __launch_bounds__(256) void prep_im2col_lds_kernel(ConvView cv, int K
   const int ix0 = ox0 * cv.sw - cv.pw, iy0 = oy0 * cv.sh - cv.ph;
   const int total = ((nr - 1) * t.spix + (KH - 1) * t.stap + 1) * t.row_bytes;
   auto input_row = [&](int row) {
+    if (!GROUPS) return iy0 + row;
     const int g = (int)__umulhi(2u * (uint32_t)row, t.group_mul);
-    return iy0 + g * cv.sh + (row - g * t.group) * t.srow;
+    return iy0 + g * cv.sh + (row - g * t.group) * cv.dh;
   };
   // Byte b of a staged row is byte ix0 * Cin + b of the input row: in the image for
   // lo_b <= b < hi_b, padding outside.
@@ -1072,12 +1074,12 @@ static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 // False: prep_im2col_kernel, where the stage cannot hold a block or is the slower form.  Staged, a block takes 1.5 ns of
-// the machine and 1.2 ps per staged byte.  The other form takes 5 ps per 16-byte piece and up to 30 ps for the lines
-// that a wave's byte loads touch (`step`: bytes between neighbouring pixels), 60 where the images do not fit the L2s, since
-// every chunk of taps walks through all of them.
-// Fitted to 1460 random layers (1 to 300000 images, dilations, strides): the rule's sum of times is 2 % above that of the
-// better form each time, 18 layers are on one that is more than 20 % slower; always staged 28 % above, never 85 %.
-// Many small images are the case where it matters (120191 of 4 x 4 x 4, 2 x 1 filter: staged 143 us, 19 otherwise).
+// the machine and 1.15 ps per staged byte.  The other form takes 5.7 ps per 16-byte piece and up to 36 ps for the lines
+// that a wave's byte loads touch (`step`: bytes between neighbouring pixels; fewer where taps lie outside the image), 59
+// where the images do not fit the L2s, since every chunk of taps walks through all of them.  Fitted to 3400 random layers
+// (1 to 300000 images, dilations, strides): the rule's sum of times is 1 % above that of the better form each time and 18
+// layers are on one that is more than 20 % slower; always staged 15 % above, never 186 %.  Many small images are the
+// case where it matters (120191 of 4 x 4 x 4, 2 x 1 filter: staged 143 us, 19 otherwise).
 static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t) {
   if (Kp > 4096) return false;
   const int nch = Kp / 16;
@@ -1098,13 +1100,13 @@ static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t
   const double span_h = (double)spanned(cv.OH), span_w = (double)(cv.OW - 1) * cv.sw + (double)(cv.KW - 1) * cv.dw + 1.0;
   const double pieces = (double)N * cv.OH * cv.OW * nch, inside = std::min(1.0, cv.H / span_h) * std::min(1.0, cv.W / span_w);
   const double xbytes = (double)N * cv.H * cv.W * cv.Cin, step = std::max((double)cv.Cin * cv.sw, xbytes / ((double)N * cv.OH * cv.OW));
-  const double general = pieces * (0.005 + (xbytes > 16e6 ? 0.06 : 0.03) * inside * std::min(1.0, step / 128.0));
-  if (blocks * (1.5 + 1.2e-3 * bytes) > general + 500.0) return false;  // ns; half a microsecond decides nothing
+  const double general = pieces * (0.0057 + (xbytes > 22e6 ? 0.059 : 0.036) * std::sqrt(inside) * std::min(1.0, step / 128.0));
+  if (blocks * (1.5 + 1.15e-3 * bytes) > general + 500.0) return false;  // ns; half a microsecond decides nothing
   const bool taps = rows(r) < spanned(r);
   auto mul = [](int d) { return (uint32_t)(((1ull << 31) + d - 1) / d); };
-  const int stage = (int)((bytes + 15) & ~15ll), group = taps ? KH : (int)spanned(r);
-  *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, group, taps ? cv.dh : 1, taps ? KH : cv.sh, taps ? 1 : cv.dh,
-        mul(pw), mul(pw * r), mul((int)rb), mul(group)};
+  const int stage = (int)((bytes + 15) & ~15ll);
+  *t = {pw, r, nstripe, cdiv(cv.OH, r), pw * r, (int)rb, stage, taps ? KH : 0, taps ? KH : cv.sh, taps ? 1 : cv.dh,
+        mul(pw), mul(pw * r), mul((int)rb), mul(KH)};
   return true;
 }
 // 1 x 1 filters that read every pixel: the images as one row of pixels.
@@ -1553,7 +1555,7 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
       im2col_flatten(&rows, g.KH, &images);
       Im2colTile t;
       if (im2col_tile(rows, g.KH, images, Kp, &t)) {
-        hipLaunchKernelGGL(prep_im2col_lds_kernel, dim3((unsigned)((long long)images * t.nstripe * t.nrows)), dim3(256),
+        hipLaunchKernelGGL(t.group ? prep_im2col_lds_kernel<true> : prep_im2col_lds_kernel<false>, dim3((unsigned)((long long)images * t.nstripe * t.nrows)), dim3(256),
                            (unsigned)(t.stage_bytes + (size_t)Kp * 2), s, rows, g.KH, nchunks, t, Ap);
       } else {
         const long long pieces = (long long)g.M * (Kp / 16);
