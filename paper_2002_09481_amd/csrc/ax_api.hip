@@ -134,7 +134,8 @@ int run_layer(const Geom& g, const QParams& qp, const Options& o, const uint8_t*
   if (!r.tab) return run_untiled(g, qp, o, r, x, w, lut, acc_out, y_out, s);
   if (!ws || ws_bytes < r.p.prep_total + r.p.ws_total || ((uintptr_t)ws & 255)) return AX_ERR_WORKSPACE;
   uint8_t* wsb = static_cast<uint8_t*>(ws);
-  const hipError_t e = launch_tab(g, qp, r.p, x, w, lut, acc_out, y_out, wsb, wsb + r.p.prep_total, true, kPhAll, 1, s);
+  const hipError_t e = launch_tab(g, qp, r.p, x, w, lut, acc_out, y_out, wsb, wsb + r.p.prep_total,
+                                  ws_bytes - r.p.prep_total, kPhAll, 1, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 
@@ -291,7 +292,7 @@ extern "C" int ax_layer_prepare(ax_layer_t* layer, const void* w, const void* lu
   if (layer->r.tab) {
     if (!prepared || prepared_bytes < layer->r.p.prep_total || ((uintptr_t)prepared & 255)) return AX_ERR_WORKSPACE;
     const hipError_t e = launch_tab(layer->g, layer->qp, layer->r.p, nullptr, static_cast<const uint8_t*>(w),
-                                    static_cast<const uint16_t*>(luts), nullptr, nullptr, prepared, nullptr, false,
+                                    static_cast<const uint16_t*>(luts), nullptr, nullptr, prepared, nullptr, 0,
                                     kPhConst, 1, (hipStream_t)hip_stream);
     if (e != hipSuccess) return AX_ERR_HIP;
   }
@@ -330,10 +331,10 @@ int run_prepared(const ax_layer* layer, const void* x, int32_t* acc_out, float* 
   const TabPlan& p = layer->r.p;
   const size_t need = scratch_need(layer, x);
   if (need && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return AX_ERR_WORKSPACE;
-  // A call that needs no scratch takes any buffer; one that is too small or not aligned stays unused.
-  const bool full = workspace && workspace_bytes >= p.ws_total && ((uintptr_t)workspace & 255) == 0;
+  // A call that needs no scratch takes any buffer; one that is not aligned stays unused.
+  const size_t usable = workspace && ((uintptr_t)workspace & 255) == 0 ? workspace_bytes : 0;
   const hipError_t e = launch_tab(layer->g, layer->qp, p, xb, layer->w, layer->lut, acc_out, y_out, layer->prepared,
-                                  workspace, full, phases, main_reps, s);
+                                  workspace, usable, phases, main_reps, s);
   return e == hipSuccess ? AX_OK : AX_ERR_HIP;
 }
 }  // namespace ax

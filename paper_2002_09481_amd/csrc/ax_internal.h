@@ -113,7 +113,6 @@ struct TabPlan {
   int G;            // workgroups of the main kernel
   int partials;     // partial tile pieces that grid produces
   int combine;      // 1: the main kernel combines them itself (arrival counters), 0: fix-up pass
-  int border;       // 1: the scratch block holds a copy of the activations with the padding around every image
   int pre;          // 1: the main kernel copies ready-made tables from the prepared block
   int nti;          // tiles along the lane dimension
   int ih;           // their height in lane elements (multiple of 64, nti * ih >= I)
@@ -146,10 +145,11 @@ struct Route {
 };
 Route choose_route(const Geom& g, const Options& o);
 // Enqueue the parts named by `phases`; the main kernel `main_reps` times (measurement helpers
-// launch it repeatedly between two events; layer calls pass 1).
+// launch it repeatedly between two events; layer calls pass 1).  scratch_bytes: what `scratch` holds, at least
+// what the call needs; a copy of the activations is made where there is room for it.
 hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const uint8_t* x,
                       const uint8_t* w, const uint16_t* lut, int32_t* acc_out, float* y_out,
-                      void* prepared, void* scratch, bool full_scratch, int phases, int main_reps, hipStream_t s);
+                      void* prepared, void* scratch, size_t scratch_bytes, int phases, int main_reps, hipStream_t s);
 
 }  // namespace ax
 

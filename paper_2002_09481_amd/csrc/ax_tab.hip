@@ -1401,8 +1401,6 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   const size_t bpack = up256((Kp + 1) * Jpad), bsum = up256(Jpad * 4 * kMaxSeg);
   // materialized lane operand, or (signed codes, implicit patch view) the offset-binary copy of x
   const size_t apack = up256(std::max((size_t)I * Kp, v == 2 ? (size_t)g.N * g.H * g.W * g.Cin : (size_t)0));
-  const double bordered = (double)g.N * (g.H + 2.0 * g.ph) * (g.W + 2.0 * g.pw);  // pixels with the border the taps see
-  p.border = v == 2 && bordered * g.Cin <= (double)apack && bordered < 268435456.0 ? 1 : 0;  // 16 * pixels: 32 bits
   size_t prep = 0, ws = 0;
   p.off_rows = prep;  prep += up256((size_t)131072 * g.T);
   p.off_qd = prep;    prep += 256;
@@ -1476,7 +1474,7 @@ static hipError_t launch_main(const TabArgs& a, int G, int ntiles, int phases, i
 }
 
 hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const uint8_t* x, const uint8_t* w,
-                      const uint16_t* lut, int32_t* acc_out, float* y_out, void* prepared, void* scratch, bool full_scratch,
+                      const uint16_t* lut, int32_t* acc_out, float* y_out, void* prepared, void* scratch, size_t scratch_bytes,
                       int phases, int main_reps, hipStream_t s) {
   uint8_t* pb = static_cast<uint8_t*>(prepared);
   uint8_t* sb = static_cast<uint8_t*>(scratch);
@@ -1507,10 +1505,14 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   const bool implicit_view = !ch && reads_in_place(g, x);
   // Activations re-laid out chunk by chunk (prep_chunks_kernel): by output pixel for 1 x 1 filters without
   // padding (only the pixels that are read), else the whole tensor, with its border where the scratch
-  // block holds that.  Signed codes need a copy in any case.
+  // block has room for that (behind the pieces of shared tiles).  Signed codes need a copy in any case, and have
+  // the whole block; others are read in place where there is no room.
   const bool by_output = g.KH == 1 && g.KW == 1 && g.ph == 0 && g.pw == 0;
-  const bool border = !by_output && full_scratch && p.border;
-  const bool chunked = implicit_view && (g.sgn || (full_scratch && (g.Cin > 16 || (border && (g.ph || g.pw)))));
+  const double room = scratch_bytes > p.off_apack ? (double)(scratch_bytes - p.off_apack) : 0.0;
+  const double bordered = (double)g.N * (g.H + 2.0 * g.ph) * (g.W + 2.0 * g.pw);  // pixels with the border the taps see
+  const bool border = !by_output && bordered * g.Cin <= std::min(room, (double)p.ws_apack) && bordered < 268435456.0;  // 16 * pixels: 32 bits
+  const bool fits = border || (by_output ? (double)g.M : (double)g.N * g.H * g.W) * g.Cin <= room;
+  const bool chunked = implicit_view && (g.sgn || (fits && (g.Cin > 16 || (border && (g.ph || g.pw)))));
   const int bh = chunked && border ? g.ph : 0, bw = chunked && border ? g.pw : 0;
   const int ch_h = by_output ? g.OH : g.H + 2 * bh, ch_w = by_output ? g.OW : g.W + 2 * bw;  // the copy's positions
   uint32_t* rows32 = reinterpret_cast<uint32_t*>(rows);

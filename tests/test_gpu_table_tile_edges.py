@@ -55,6 +55,36 @@ VIEWS = [
 ]
 
 
+@pytest.mark.parametrize("copied", [True, False])
+@pytest.mark.parametrize("case", VIEWS, ids=lambda c: "x".join(map(str, c[0])))
+def test_a_workspace_with_room_for_the_copy_receives_it(case, copied):
+    """Without shared tiles the copy of the activations is all that a call keeps in its workspace: a buffer of just
+    its size is written from end to end, one that is a byte short of the copy without border is left alone and the
+    activations are read in place."""
+    (N, H, W, C, KH, KW, _), stride, pad, dilation = case
+    ph, pw = ax._pair(pad)
+    x, w, q = _operands(case[0], sum(case[0]), False)
+    lut = I.lut_random_error(7)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, stride, pad, dilation), q, tune=dict(TUNE, split_k=1)) as h:
+        plain = h.out_shape()[1] * h.out_shape()[2] if KH == KW == 1 and not pad else H * W
+        border = (H + 2 * ph) * (W + 2 * pw) if pad else plain
+        if N * border * C > h.workspace_bytes:  # no room for the border in any workspace that the layer asks for
+            border = plain
+        copied = copied and (C > 16 or border != H * W)
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        buf = torch.empty(N * (border if copied else plain) * C - (0 if copied else 1), dtype=torch.uint8, device="cuda")
+        want = oracle.conv2d_ex(x, w, lut, stride, pad, q, dilation=dilation)
+        for fill in (0xA5, 0x5A):  # a byte that is the filler in one run is another in the next
+            buf.fill_(fill)
+            acc, y = h.run(G.to_dev(x), workspace=buf)
+            torch.cuda.synchronize()
+            G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *want)
+            kept = buf == fill
+            assert bool(kept.all()) == (not copied)
+            left = kept if fill == 0xA5 else left & kept
+        assert not copied or not bool(left.any())
+
+
 @pytest.mark.parametrize("signed, small_workspace", [(False, False), (False, True), (True, False)])  # signed codes need their copy
 @pytest.mark.parametrize("case", VIEWS, ids=lambda c: "x".join(map(str, c[0])))
 def test_activations_in_place_and_from_their_copy(case, signed, small_workspace):
