@@ -49,12 +49,27 @@ struct QDev {
 };
 static_assert(sizeof(QDev) == 48 && offsetof(QDev, padrow) == 32, "padrow must be 16-byte aligned");
 
+// i / d = umulhi(2 i, mul) >> shift for 0 <= i < 2^31: mul = ceil(2^(31 + shift) / d) with shift = ceil(log2 d) is at most
+// 2^32 - 1, and too large by less than d / (2^(31 + shift)) of the quotient's unit, which 2 i < 2^32 leaves under one.
+// (A division by a variable is some thirty dependent instructions, in 64 bits a hundred and more.)
+struct Divisor {
+  uint32_t mul;
+  int shift;
+  Divisor() = default;
+  explicit Divisor(int d) : mul(0), shift(0) {
+    while ((1LL << shift) < d) ++shift;
+    mul = (uint32_t)(((1ull << (31 + shift)) + d - 1) / d);
+  }
+  __device__ __forceinline__ int operator()(int i) const { return (int)(__umulhi(2u * (uint32_t)i, mul) >> shift); }
+};
+
 struct TabArgs {
   // lane-side operand, addressed as an implicit im2col view of an [N,H,W,Cin] tensor
   const uint8_t* A;
   int I;   // valid lane elements
   int ih;  // lane elements per tile (multiple of 64, at most the kernel's tile height)
   int H, W, Cin, KW, sh, sw, ph, pw, OHW, OW;
+  Divisor by_ohw, by_ow, by_cin, by_kw, by_ntiles1, by_ntj;
   // byte offset of the 16 codes (pixel, channels ci0 .. ci0+15) = pixel * a_ps + ci0 * a_cs:
   // (Cin, 1) for a tensor read in place; (16, I) for materialized patches, which lie chunk by
   // chunk ([K16 / 16][I][16]) so that the lanes of a wave read one contiguous kilobyte
@@ -70,6 +85,9 @@ struct TabArgs {
   // takes iterations [w*total/G, (w+1)*total/G) of the tile-major iteration space
   int ntj, nch;
   long long total_iters;
+  int small;                    // total_iters below 2^31 and G at most 46340: shares and tiles by 32-bit arithmetic:
+  int share, rest;              // total_iters = share * G + rest
+  Divisor by_grid, by_nch;
   const struct QDev* qd;  // zero points, scale and pad code as the kernels use them (written by prep_kernel)
   int dh, dw;        // dilation of the implicit im2col view
   uint32_t bias_k;   // 32768 * K for signed tables (their entries are stored with that offset), else 0
@@ -114,15 +132,23 @@ __device__ __forceinline__ long long uniform(long long v) {
 
 // Column constants K z_lane z_tab - z_lane * (column sum) of a tile's eight columns, into red[THREADS / 64][8]
 // (the sum over its rows is a column's constant): thread = (segment, column), so that the loads of
-// all segments are in flight together.  The caller has a barrier before the constants are read.
+// all segments (kMaxSeg at most) are in flight together.  The caller has a barrier before the constants are read.
+constexpr int kMaxSeg = 64;  // segments of the table-side column sums
 template <int THREADS>
-__device__ __forceinline__ void column_constants(const TabArgs& a, int j0, long long (*red)[8]) {
+__device__ __forceinline__ int32_t column_sum_part(const TabArgs& a, int j0, int tid) {
   int32_t sb = 0;
-  for (int seg = (int)threadIdx.x >> 3; seg < a.nseg; seg += THREADS / 8) sb += a.bsum[(size_t)seg * a.Jpad + j0 + (threadIdx.x & 7)];
+#pragma unroll
+  for (int s = 0; s < kMaxSeg; s += THREADS / 8) {
+    const int seg = s + (tid >> 3);
+    if (seg < a.nseg) sb += a.bsum[(size_t)seg * a.Jpad + j0 + (tid & 7)];
+  }
+  return sb;
+}
+template <int THREADS>
+__device__ __forceinline__ void column_constants(int32_t sb, long long kzz, int z_lane, int tid, long long (*red)[8]) {
 #pragma unroll
   for (int o = 8; o < 64; o *= 2) sb += __shfl_xor(sb, o);
-  if ((threadIdx.x & 63) < 8)
-    red[threadIdx.x >> 6][threadIdx.x & 7] = (threadIdx.x < 8 ? a.qd->kzz : 0LL) - (long long)a.qd->z_lane * sb;
+  if ((tid & 63) < 8) red[tid >> 6][tid & 7] = (tid < 8 ? kzz : 0LL) - (long long)z_lane * sb;
 }
 template <int WAVES>
 __device__ __forceinline__ long long column_constant(const long long (*red)[8], int col) {
@@ -201,6 +227,11 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // PRE: the tables of a chunk lie ready-made in global memory as an image of the LDS buffer
 // (prep_tables_kernel) and are copied straight into LDS (buffer loads with the lds modifier).
 //
+// What a segment costs beside its phases: shares, tiles and pixels are found by multiplication (Divisor), the column
+// constants and coefficients are requested with the first tables instead of after the last phase, and nothing is
+// requested past the last chunk where the tables are ready-made: 100352 x 16 x 256 (1024 tiles of one phase, one
+// output) 75 -> 61 us, 100352 x 64 x 256 115 -> 98.
+//
 // Bound: LDS.  Per phase of a full tile 1 MiB of gathers (165-200 bytes per clock measured) and 64
 // KiB of table writes at 70 bytes per clock, against 4096 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
@@ -249,8 +280,12 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   // fetched into eight.  (Where tiles are cut into a multiple of eight shares the launch order
   // already gives every XCD one slice of K of all tiles; the planner picks per layer.)
   const int wg = a.xcd ? xcd_major((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-  long long it_beg = uniform((long long)wg * a.total_iters / gridDim.x);
-  const long long it_end = uniform((long long)(wg + 1) * a.total_iters / gridDim.x);
+  auto share_begin = [&](int w) -> long long {  // w * total / G
+    return a.small ? (long long)(w * a.share + __builtin_amdgcn_readfirstlane(a.by_grid(w * a.rest)))
+                   : uniform((long long)w * a.total_iters / gridDim.x);
+  };
+  long long it_beg = share_begin(wg);
+  const long long it_end = share_begin(wg + 1);
 
   // builder roles: tap bt, entries bv .. bv + 7
   const int bt = lane >> 2, bv = 32 * wave + 8 * (lane & 3);
@@ -261,16 +296,20 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   tabs_words.w = 0x00020000u;
 
   while (it_beg < it_end) {
-  const int gtile = __builtin_amdgcn_readfirstlane((int)(it_beg / a.nch));
+  // The lane as the parts of a segment outside its main loop use it: what depends on it is computed anew for every
+  // segment, where kept across the loop it would be spilled.
+  int ls = lane;
+  asm volatile("" : "+v"(ls));
+  const int gtile = __builtin_amdgcn_readfirstlane(a.small ? a.by_nch((int)it_beg) : (int)(it_beg / a.nch));
   const int c_beg = (int)(it_beg - (long long)gtile * a.nch);
-  const int tbl = __builtin_amdgcn_readfirstlane(gtile / a.ntiles1);  // which multiplier table
+  const int tbl = __builtin_amdgcn_readfirstlane(a.by_ntiles1(gtile));  // which multiplier table
   const int tile = gtile - tbl * a.ntiles1;
   const uint16_t* __restrict__ rows = a.rows + (size_t)tbl * 65536;
   int32_t* __restrict__ acc_base = a.acc_out ? a.acc_out + (size_t)tbl * a.out_elems : nullptr;
   float* __restrict__ y_base = a.y_out ? a.y_out + (size_t)tbl * a.out_elems : nullptr;
   const int c_end = (int)min((long long)a.nch, c_beg + (it_end - it_beg));
   const bool whole = (c_beg == 0) && (c_end == a.nch);
-  const int ti = __builtin_amdgcn_readfirstlane(tile / a.ntj);
+  const int ti = __builtin_amdgcn_readfirstlane(a.by_ntj(tile));
   const int i0 = ti * a.ih;  // tiles are a.ih <= kIT lane elements high (a multiple of 64)
   const int tj = tile - ti * a.ntj;
   const int j0 = tj * kJT;
@@ -287,24 +326,30 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   uint32_t pix[GR];
   int yx[GR];
   auto first_tap = [&](int p, int& by, int& bx) {  // position of tap (0, 0); returns the image
-    const int i = min(i0 + 64 * (kWaves * p + wave) + lane, a.I - 1);
-    const int n = i / a.OHW;
+    const int i = min(i0 + 64 * (kWaves * p + wave) + ls, a.I - 1);
+    const int n = a.by_ohw(i);
     const int r = i - n * a.OHW;
-    const int oy = r / a.OW;
+    const int oy = a.by_ow(r);
     by = oy * a.sh - a.ph;
     bx = (r - oy * a.OW) * a.sw - a.pw;
     return n;
   };
+  if (!PADDED && a.OHW == 1 && a.H == 1 && a.W == 1) {  // an element is a pixel: the copy by output pixel, the patches, the filters
 #pragma unroll
-  for (int p = 0; p < GR; ++p) {
-    int by, bx;
-    const int n = first_tap(p, by, bx);
-    pix[p] = (uint32_t)((n * a.H + by) * a.W + bx);
-    if (PADDED) yx[p] = (int)((uint32_t)by * 65536u + (uint32_t)bx);
+    for (int p = 0; p < GR; ++p) pix[p] = (uint32_t)min(i0 + 64 * (kWaves * p + wave) + ls, a.I - 1);
+  } else {
+#pragma unroll
+    for (int p = 0; p < GR; ++p) {
+      int by, bx;
+      const int n = first_tap(p, by, bx);
+      pix[p] = (uint32_t)((n * a.H + by) * a.W + bx);
+      if (PADDED) yx[p] = (int)((uint32_t)by * 65536u + (uint32_t)bx);
+    }
   }
   uint32_t pix0 = 0;  // the pixel of the tile's first element
   if (!PADDED) {
-    const int n = i0 / a.OHW, r = i0 - n * a.OHW, oy = r / a.OW;
+    const int n = a.by_ohw(i0), r = i0 - n * a.OHW;
+    const int oy = a.by_ow(r);
     pix0 = (uint32_t)__builtin_amdgcn_readfirstlane((n * a.H + oy * a.sh) * a.W + (r - oy * a.OW) * a.sw);
 #pragma unroll
     for (int p = 0; p < GR; ++p) pix[p] = (pix[p] - pix0) * a.a_ps;
@@ -313,8 +358,8 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   const uint8_t* xsrc = a.A;       // its channels
   auto load_from = [&](int chunk) {
     const int k0 = min(chunk, a.nch - 1) * kChunk;
-    const int tap = __builtin_amdgcn_readfirstlane(k0 / a.Cin);
-    const int ky = __builtin_amdgcn_readfirstlane(tap / a.KW);
+    const int tap = __builtin_amdgcn_readfirstlane(a.by_cin(k0));
+    const int ky = __builtin_amdgcn_readfirstlane(a.by_kw(tap));
     xdy = ky * a.dh;
     xdx = (tap - ky * a.KW) * a.dw;
     xoff = xdy * a.W + xdx;
@@ -401,6 +446,16 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   }
   const int n = c_end - c_beg;
   // first chunk's tables (one global round trip), then the requests the first phase relies on
+  const int32_t sb = column_sum_part<kThreads>(a, j0, 64 * wave + ls);
+  int none = 0;  // in a vector register: values that the compiler knows to be uniform it would wait for at once
+  asm volatile("" : "+v"(none));
+  const QDev* qd = a.qd + none;
+  const long long kzz = qd->kzz;
+  const int z_lane = qd->z_lane;
+  const int z_tab_v = qd->z_tab, row0_v = rows[none], scale_v = __float_as_int(qd->scale);
+  __builtin_amdgcn_sched_barrier(0);
+  table_copy(c_beg, 0, 0);
+  table_copy(c_beg, 0, 1);
   build_issue(load_codes(c_beg), dd[0]);
   u32x4 xn[XR];
   load_from(c_beg);
@@ -408,8 +463,13 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   for (int p = 0; p < XR; ++p) xn[p] = load_x(p);
 #pragma unroll
   for (int e = 0; e < 8; ++e) build_commit(e, 0, dd[0]);
-  table_copy(c_beg, 0, 0);
-  table_copy(c_beg, 0, 1);
+  // what the epilogue needs has travelled with them
+  column_constants<kThreads>(sb, kzz, z_lane, 64 * wave + ls, sh.cterm);
+  const uint32_t z_tab = (uint32_t)__builtin_amdgcn_readfirstlane(z_tab_v);
+  const float scale = __int_as_float(__builtin_amdgcn_readfirstlane(scale_v));
+  const uint32_t klast = (uint32_t)a.nch * kChunk;
+  const uint32_t padfix =
+      (klast - (uint32_t)a.K) * ((uint32_t)__builtin_amdgcn_readfirstlane(row0_v) ^ 0x8080u) + a.bias_k - 32896u * klast;
   uint2 codes = load_codes(c_beg + 1), codes2;
   if (DB == 2) codes2 = load_codes(c_beg + 2);
   copies_done();
@@ -438,11 +498,12 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
         if (p == (3 * GR + 7) / 8) __builtin_amdgcn_s_setprio(2);
         if (p == (5 * GR + 7) / 8) __builtin_amdgcn_s_setprio(1);
         if (p == (7 * GR + 7) / 8) __builtin_amdgcn_s_setprio(0);
-        if (p == 0) table_copy(ch + 1, buf ^ 1, 0);
-        if (p == GR / 2) table_copy(ch + 1, buf ^ 1, 1);
+        // (PRE waits for all its loads at the end of the phase and issues none past the last chunk.)
+        if (p == 0 && more) table_copy(ch + 1, buf ^ 1, 0);
+        if (p == GR / 2 && more) table_copy(ch + 1, buf ^ 1, 1);
         const u32x4 x = xn[p % XR];
         if (p + XR == GR) load_from(ch + 1);
-        xn[p % XR] = load_x((p + XR) % GR);
+        if (!PRE || more) xn[p % XR] = load_x((p + XR) % GR);
         __builtin_amdgcn_sched_barrier(0);
         if (p < np) {
 #pragma unroll
@@ -512,8 +573,6 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   // Taps K .. of the last chunk exist only in materialized operands, where both codes are 0: each
   // adds the table entry (0,0) to every sum, which is taken off again; and every tap has
   // 128 + 256 * 128 too little (see above).
-  const uint32_t klast = (uint32_t)a.nch * kChunk;
-  const uint32_t padfix = (klast - (uint32_t)a.K) * ((uint32_t)rows[0] ^ 0x8080u) + a.bias_k - 32896u * klast;
   uint32_t sum[GR][4][2];
 #pragma unroll
   for (int p = 0; p < GR; ++p)
@@ -534,14 +593,14 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
     for (int p = 0; p < GR; ++p) {
       if (p >= np) continue;
       const int g = kWaves * p + wave;
-      int32_t* pp = part + (size_t)g * 512 + lane;
+      int32_t* pp = part + (size_t)g * 512 + ls;
       if (a.cnt) {  // read by another workgroup of this launch: stores that go through to memory
-        __hip_atomic_store(lsum + g * 64 + lane, (int32_t)sl[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(lsum + g * 64 + ls, (int32_t)sl[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int q = 0; q < 8; ++q)
           __hip_atomic_store(pp + q * 64, (int32_t)sum[p][q >> 1][q & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {
-        lsum[g * 64 + lane] = (int32_t)sl[p];
+        lsum[g * 64 + ls] = (int32_t)sl[p];
 #pragma unroll
         for (int q = 0; q < 8; ++q) pp[q * 64] = (int32_t)sum[p][q >> 1][q & 1];
       }
@@ -579,8 +638,8 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
         for (int w = w_first; w <= w_last; ++w) {
           if (w == wg) continue;
           const int so = 2 * w + (w == w_first ? 1 : 0);
-          const int32_t* po = a.part + (size_t)so * ((size_t)a.ih * kJT) + lane;
-          const int32_t* lo = a.lsum + (size_t)so * a.ih + lane;
+          const int32_t* po = a.part + (size_t)so * ((size_t)a.ih * kJT) + ls;
+          const int32_t* lo = a.lsum + (size_t)so * a.ih + ls;
 #pragma unroll
           for (int p2 = 0; p2 < GR; p2 += 4) {  // loads of four groups in flight
             uint32_t t[4][9];
@@ -606,12 +665,9 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
       }
     }
   }
-  if (finish) column_constants<kThreads>(a, j0, sh.cterm);
-  __syncthreads();  // cterm visible; every wave is done with the table buffers
   if (finish) {
-    const float scale = a.qd->scale;
-    const uint32_t z_tab = (uint32_t)a.qd->z_tab;
     const bool wide = a.K > 16384;
+    const int m = ls & 15, kg = ls >> 4;
     const long long ct0 = column_constant<kWaves>(sh.cterm, 2 * kg), ct1 = column_constant<kWaves>(sh.cterm, 2 * kg + 1);
 #pragma unroll
     for (int p = 0; p < GR; ++p) {
@@ -628,7 +684,7 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
     }
   }
   it_beg += n;
-  __syncthreads();  // cterm and the table buffers are free again
+  __syncthreads();  // cterm is free again
   }  // segment loop
 }
 
@@ -687,7 +743,7 @@ __global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) 
       p1[k] = (uint32_t)pp[64];
       ps[k] = (uint32_t)lsum[(size_t)slot * a.ih];
     }
-    if (w == w_first) column_constants<256>(a, j0, cterm);
+    if (w == w_first) column_constants<256>(column_sum_part<256>(a, j0, t), a.qd->kzz, a.qd->z_lane, t, cterm);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const uint32_t on = w + k <= w_last ? 1u : 0u;
@@ -1069,7 +1125,6 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
 
 // ---- host side -------------------------------------------------------------------------
 
-constexpr int kMaxSeg = 64;  // segments of the table-side column sums
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
@@ -1588,6 +1643,7 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
     a.dh = 1; a.dw = 1;
     a.a_ps = 16; a.a_cs = (uint32_t)I;
   }
+  a.by_ohw = Divisor(a.OHW); a.by_ow = Divisor(a.OW); a.by_cin = Divisor(a.Cin); a.by_kw = Divisor(a.KW);
   a.Bp = Bp; a.Jpad = Jpad; a.J = J; a.bsum = bsum; a.nseg = cdiv(krows, seg_rows); a.rows = rows;
   a.K = g.K;
   a.ntj = cdiv(J, kJT);
@@ -1595,6 +1651,10 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   a.ih = p.ih;
   a.ntiles1 = ntiles1;
   a.total_iters = (long long)ntiles * nchunks;
+  a.by_ntiles1 = Divisor(a.ntiles1); a.by_ntj = Divisor(a.ntj); a.by_grid = Divisor(p.G); a.by_nch = Divisor(a.nch);
+  a.small = a.total_iters < (1LL << 31) && p.G <= 46340;
+  a.share = (int)std::min<long long>(a.total_iters / p.G, 0x7fffffff);
+  a.rest = (int)(a.total_iters % p.G);
   a.qd = qd;
   a.bias_k = g.sgn ? 32768u * (uint32_t)g.K : 0u;
   a.acc_out = acc_out; a.y_out = y_out;
