@@ -101,7 +101,7 @@ struct TabArgs {
   uint32_t tabs_bytes;
   long long out_elems;   // outputs per table (M * Cout)
   int ntiles1;           // tiles of one table; tile index space = table * ntiles1 + tile (several tables: ax_conv2d_multi_lut)
-  int vec_out;  // outputs may be written in aligned 8-byte pieces along j
+  int vec_out;  // outputs may be written along j in aligned pieces of 8 bytes (1), of 16 bytes (2)
   int padded;   // 0: every tap of every pixel lies in the image, 1: not, 2: not and positions need more than 16 bits
   int xcd;      // 1: shares of work are numbered XCD by XCD (see xcd_major), 0: in launch order
 };
@@ -672,14 +672,42 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 #pragma unroll
     for (int p = 0; p < GR; ++p) {
       if (p >= np) continue;
+      float yv[4][2];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const uint32_t lterm = z_tab * (uint32_t)__shfl((int)sl[p], 16 * r + m);
-        const int i = i0 + 64 * (kWaves * p + wave) + 16 * r + m;
-        const uint32_t v0 = sum[p][r][0] - padfix, v1 = sum[p][r][1] - padfix;
-        if (i < a.I)
-          put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * kg, v0, v1, dequant(v0, lterm, ct0, scale, wide),
-                       dequant(v1, lterm, ct1, scale, wide));
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          sum[p][r][c] -= padfix;
+          yv[r][c] = dequant(sum[p][r][c], lterm, c ? ct1 : ct0, scale, wide);
+        }
+      }
+      if (!CH && a.vec_out == 2) {
+        // Rows of 16 lanes trade quarters for columns and store 16 bytes per lane, two lanes the 32 bytes that a tile has of
+        // an output row: with 8 bytes per lane the stores took as long as three phases (100352 x 64 x 256, both outputs: 118
+        // us, 102 so; one output 98 and 90).
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+          const int i = i0 + 64 * (kWaves * p + wave) + 16 * (r + (kg & 1)) + m, j = j0 + 4 * (kg >> 1);
+          const size_t o = (size_t)i * a.J + j;
+          const bool in = i < a.I && j < a.J;
+          if (acc_base) {
+            const auto c0 = __builtin_amdgcn_permlane16_swap(sum[p][r][0], sum[p][r + 1][0], false, false);
+            const auto c1 = __builtin_amdgcn_permlane16_swap(sum[p][r][1], sum[p][r + 1][1], false, false);
+            if (in) *reinterpret_cast<uint4*>(acc_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
+          }
+          if (y_base) {
+            const auto c0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][0]), __float_as_uint(yv[r + 1][0]), false, false);
+            const auto c1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][1]), __float_as_uint(yv[r + 1][1]), false, false);
+            if (in) *reinterpret_cast<uint4*>(y_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = i0 + 64 * (kWaves * p + wave) + 16 * r + m;
+          if (i < a.I) put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * kg, sum[p][r][0], sum[p][r][1], yv[r][0], yv[r][1]);
+        }
       }
     }
   }
@@ -1665,7 +1693,8 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
   a.tabs_bytes = p.pre ? (uint32_t)((size_t)krows * (Jpad / 8) * 4096) : 0u;
   a.out_elems = (long long)g.M * g.Cout;
   a.xcd = p.xcd;
-  a.vec_out = (!ch && J % 2 == 0 && (((uintptr_t)acc_out | (uintptr_t)y_out) & 7) == 0) ? 1 : 0;
+  const uintptr_t outs = (uintptr_t)acc_out | (uintptr_t)y_out;
+  a.vec_out = ch ? 0 : J % 4 == 0 && (outs & 15) == 0 ? 2 : J % 2 == 0 && (outs & 7) == 0 ? 1 : 0;
 
   return ch ? launch_main<true>(a, p.G, ntiles, run, main_reps, s)
             : launch_main<false>(a, p.G, ntiles, run, main_reps, s);

@@ -182,3 +182,23 @@ def test_more_images_than_a_launch_holds_blocks():
     table = torch.from_numpy(lut.astype(np.int32).reshape(256, 256)).cuda()
     want = sum(table[x.view(N, 4)[:, t].long()][:, torch.from_numpy(w.reshape(4, 2)[t].astype(np.int64)).cuda()] for t in range(4))
     assert torch.equal(acc.view(N, 2), want)
+
+
+@pytest.mark.parametrize("split", [1, 2])
+@pytest.mark.parametrize("offset", [0, 1, 2, 4])
+@pytest.mark.parametrize("channels", [1, 2, 4, 6, 12, 20, 23])
+def test_output_pieces_of_every_alignment(channels, offset, split):
+    """Outputs in pieces of 16, 8 and 4 bytes, by channel count and start of the tensors; last columns and rows of a tile."""
+    x, w, q = _operands((5, 7, 9, 16, 3, 3, channels), channels, False)
+    lut = I.lut_random_error(7)
+    want = oracle.conv2d_ex(x, w, lut, 1, 1, q)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 1), q, tune=dict(TUNE, split_k=split, combine=2)) as h:
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        n = 5 * 7 * 9 * channels
+        bufs = [torch.full((n + 16,), 77, dtype=t, device="cuda") for t in (torch.int32, torch.float32)]
+        views = [b[offset:offset + n].view(h.out_shape()) for b in bufs]
+        acc, y = h.run(G.to_dev(x), *views)
+        torch.cuda.synchronize()
+        G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *want)
+        for b in bufs:
+            assert bool((b[:offset] == 77).all()) and bool((b[offset + n:] == 77).all())
