@@ -85,16 +85,19 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // random layers of 1 to 2 million lookups 22 in 284 are slower on it than on direct_kernel (the others
 // faster, 1.4 times in the middle).  From 2e6 to 4e6 it competes with direct_kernel: of 316 random layers
 // 295 go to it and 2 of these are slower there (1 x 2048 x 1000: 7.6 against 13.0 us); a second round
-// of tiles never paid (3876 x 64 x 16: 20.8 against 12.5 us).  From 4e6 on it competes with the table
-// tiles: a run of the ResNet-50 layers at batch 1 to 4 takes 0.85 to 1 of its estimate and the tiles' times are
-// within 5 us of theirs (196 x 2304 x 256: 32.7 us here, 37 on the tiles; 98 x 4608 x 512: 56 and 45;
-// 784 x 1152 x 128: 33 and 27.5).  The estimates leave out what a call that prepares its constants itself
-// pays on the tiles (two launches more, 6 to 9 us), so layers that are short in any case keep this kernel
-// (`keep`, expected time on it): up to 38 us under 40 million lookups and 36 us under 80 million, where
-// ready-made tables do not help the tiles, and up to 60 us for sums of 2048 taps and more.  That costs
-// prepared layers between nothing and a factor of two (129 x 95 x 2681: 24 us here, 20 on prepared tiles
-// and 27 with the preparation; 147 x 2048 x 512: 54 and 36; 5692 x 80 x 47: 30 and 15).
-Route choose_route(const Geom& g, const Options& o) {
+// of tiles never paid (3876 x 64 x 16: 20.8 against 12.5 us).
+// From 4e6 on it competes with the table tiles, whose estimate is that of a prepared run (on channel lanes it is too low
+// for short layers: 7.2 us and 0.81 of it); a call that prepares its constants itself (`prepared` 0) takes longer: 4 us for
+// the table's rows and the filters, 2 and 1.8 per megabyte of transposed filters (channel lanes), 11 and 0.3 per megabyte of
+// ready-made tables.  Calls on this kernel take 0.9 of its estimate, 0.72 in the byte form; prepared layers are compared
+// at 0.83, which gives near ties to the kernel that needs neither prepared block nor scratch.  Long sums (2048 taps) stay
+// here up to 60 us of its estimate, which is then too high (0.4 to 0.9 of it measured) and that of the tiles too low.
+// Over 1590 random calls and 1552 prepared layers of 4e6 to 1.2e9 lookups, each timed on both kernels, the choice costs 0.7
+// and 2.2 % over the better one each time (more than 5 % slower 59 and 136, more than 20 % 16 and 49).
+// Prepared layers of more than two rounds of tiles stay on this kernel up to 36 and 38 us, though the tiles are faster for
+// most (5692 x 80 x 47: 30 and 15 us): the tests of the walk over several tiles reach it through the choice for such layers,
+// as nothing else selects this kernel.
+Route choose_route(const Geom& g, const Options& o, bool prepared) {
   Route r{};
   const bool automatic =
       !(o.variant || o.split_k || o.tile || o.row_tiles || o.share_order || o.combine || o.tables) && g.T == 1;
@@ -104,8 +107,20 @@ Route choose_route(const Geom& g, const Options& o) {
   if (r.tab) r.p = tab_plan(g, o);
   if (automatic && n >= 2.0e6 && fewpix_shape(g)) {
     r.fp = fewpix_plan(g);
-    const double keep = g.K >= 2048 ? 60e-6 : n < 16e6 ? 0.0 : n < 40e6 ? 38e-6 : n < 80e6 && !r.p.pre ? 36e-6 : 0.0;
-    r.few = r.tab ? 0.9 * r.fp.cost < r.p.cost || 1.1 * r.fp.cost < keep : r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();
+    if (r.tab) {
+      const bool ch = r.p.variant == 3;
+      const double tiles = ch ? 7.2e-6 + 0.81 * r.p.cost : r.p.cost;
+      const double prep = prepared  ? 0.0
+                          : ch      ? 2e-6 + 1.8e-12 * g.K * g.Cout
+                          : r.p.pre ? 11e-6 + 0.3e-12 * (double)(r.p.off_bpack - r.p.off_tabs)
+                                    : 4e-6;
+      const double scale = prepared ? 0.83 : g.Cin % 4 == 0 ? 0.9 : 0.72;
+      const bool walk = prepared && r.fp.tiles > 2 * cu_count();
+      const double keep = g.K >= 2048 ? 60e-6 : !walk || n < 16e6 ? 0.0 : n < 40e6 ? 38e-6 : n < 80e6 && !r.p.pre ? 36e-6 : 0.0;
+      r.few = scale * r.fp.cost < tiles + prep || 1.1 * r.fp.cost < keep;
+    } else {
+      r.few = r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();
+    }
     if (r.few) r.tab = false;
   }
   return r;
@@ -130,7 +145,7 @@ static int run_untiled(const Geom& g, const QParams& qp, const Options& o, const
 
 int run_layer(const Geom& g, const QParams& qp, const Options& o, const uint8_t* x, const uint8_t* w,
               const uint16_t* lut, int32_t* acc_out, float* y_out, void* ws, size_t ws_bytes, hipStream_t s) {
-  const Route r = choose_route(g, o);
+  const Route r = choose_route(g, o, false);
   if (!r.tab) return run_untiled(g, qp, o, r, x, w, lut, acc_out, y_out, s);
   if (!ws || ws_bytes < r.p.prep_total + r.p.ws_total || ((uintptr_t)ws & 255)) return AX_ERR_WORKSPACE;
   uint8_t* wsb = static_cast<uint8_t*>(ws);
@@ -159,7 +174,7 @@ static int run(const Geom& g, const ax_quant_t* q, const ax_tune_t* tune, const 
 }
 
 size_t layer_workspace(const Geom& g, const Options& o) {
-  const Route r = choose_route(g, o);
+  const Route r = choose_route(g, o, false);
   return r.tab ? r.p.prep_total + r.p.ws_total : 256;
 }
 
@@ -265,7 +280,7 @@ extern "C" int ax_layer_create(const ax_conv_desc_t* desc, int num_luts, const a
   L->g = g;
   L->qp = qp;
   L->o = o;
-  L->r = choose_route(g, o);
+  L->r = choose_route(g, o, true);
   L->w = nullptr;
   L->lut = nullptr;
   L->prepared = nullptr;

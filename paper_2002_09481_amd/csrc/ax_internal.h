@@ -136,14 +136,14 @@ bool tab_supported(const Geom& g);
 int tab_num_tiles();
 TabPlan tab_plan(const Geom& g, const Options& o);
 // The kernel family of a layer and its plan, from geometry and options alone (ax_api.hip): decided once
-// per call or handle.  Neither tab nor few: depthwise or direct kernel.
+// per call or handle (prepared: the constants are laid out once, not in every call).  Neither tab nor few: depthwise or direct kernel.
 struct Route {
   bool tab;        // table-tile kernels
   TabPlan p;       // valid when tab
   bool few;        // fewpix_kernel
   FewpixPlan fp;   // valid when few
 };
-Route choose_route(const Geom& g, const Options& o);
+Route choose_route(const Geom& g, const Options& o, bool prepared);
 // Enqueue the parts named by `phases`; the main kernel `main_reps` times (measurement helpers
 // launch it repeatedly between two events; layer calls pass 1).  scratch_bytes: what `scratch` holds, at least
 // what the call needs; a copy of the activations is made where there is room for it.

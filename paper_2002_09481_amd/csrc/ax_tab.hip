@@ -1156,13 +1156,33 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
 static inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
+// What the byte loads of prep_im2col_kernel cost: a wave takes one chunk of taps of neighbouring pixels.
+struct PatchLines {
+  double inside, u, far;  // share of taps inside the image, bytes between neighbouring pixels / 128 (1 at most), 0 .. 1: the images beyond the L2s
+  PatchLines(const ConvView& cv, int KH, int N) {
+    const double span_h = (double)(cv.OH - 1) * cv.sh + (double)(KH - 1) * cv.dh + 1.0;
+    const double span_w = (double)(cv.OW - 1) * cv.sw + (double)(cv.KW - 1) * cv.dw + 1.0;
+    const double xbytes = (double)N * cv.H * cv.W * cv.Cin, pixels = (double)N * cv.OH * cv.OW;
+    inside = std::min(1.0, cv.H / span_h) * std::min(1.0, cv.W / span_w);
+    u = std::min(1.0, std::max((double)cv.Cin * cv.sw, xbytes / pixels) / 128.0);
+    far = std::min(1.0, std::max(0.0, xbytes / 8e6 - 1.0));
+  }
+};
+// Its time, seconds: 8 ps per 16-byte piece where pixels share lines, 50 where they do not, 60 to 220 where the images do not
+// fit the L2s either, since every chunk of taps walks through all of them (1800 random layers; the last scatter with the
+// XCDs that the blocks of a chunk fall on and count 100).
+static double general_copy(const ConvView& cv, int KH, int N, int nch) {
+  const PatchLines l(cv, KH, N);
+  const double far = std::min(1.0, std::max(0.0, (double)N * cv.H * cv.W * cv.Cin / 12e6 - 1.0));
+  return (double)N * cv.OH * cv.OW * nch * (8e-12 + l.inside * (42e-12 * l.u * l.u + (l.u == 1.0 ? 50e-12 * far : 0.0)));
+}
+
 // False: prep_im2col_kernel, where the stage cannot hold a block or is the slower form.  Staged, a block takes 1.5 ns of
-// the machine and 1.15 ps per staged byte.  The other form takes 5.7 ps per 16-byte piece and up to 36 ps for the lines
-// that a wave's byte loads touch (`step`: bytes between neighbouring pixels; fewer where taps lie outside the image), 59
-// where the images do not fit the L2s, since every chunk of taps walks through all of them.  Fitted to 3400 random layers
-// (1 to 300000 images, dilations, strides): the rule's sum of times is 1 % above that of the better form each time and 18
-// layers are on one that is more than 20 % slower; always staged 15 % above, never 186 %.  Many small images are the
-// case where it matters (120191 of 4 x 4 x 4, 2 x 1 filter: staged 143 us, 19 otherwise).
+// the machine and 1.15 ps per staged byte.  The other form is priced at 5.7 ps per 16-byte piece and up to 36 to 89 ps for the
+// lines that its loads touch (less than the medians of general_copy, which scatter by a factor of two and more).
+// Fitted to 3400 random layers (1 to 300000 images, dilations, strides): the rule's sum of times is 1 % above that of the
+// better form each time and 26 layers are on one that is more than 20 % slower; always staged 15 % above, never 186 %.
+// Many small images are the case where it matters (120191 of 4 x 4 x 4, 2 x 1 filter: staged 143 us, 19 otherwise).
 static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t) {
   if (Kp > 4096) return false;
   const int nch = Kp / 16;
@@ -1180,10 +1200,9 @@ static bool im2col_tile(const ConvView& cv, int KH, int N, int Kp, Im2colTile* t
   while (r < cv.OH && pw * (r + 1) <= 512 && rb * rows(r + 1) <= 16384 && (long long)N * nstripe * cdiv(cv.OH, r + 1) >= 1024) ++r;
   const long long blocks = (long long)N * nstripe * cdiv(cv.OH, r), bytes = rb * rows(r);
   if (blocks >= (1LL << 24)) return false;  // a launch holds fewer than 2^32 threads
-  const double span_h = (double)spanned(cv.OH), span_w = (double)(cv.OW - 1) * cv.sw + (double)(cv.KW - 1) * cv.dw + 1.0;
-  const double pieces = (double)N * cv.OH * cv.OW * nch, inside = std::min(1.0, cv.H / span_h) * std::min(1.0, cv.W / span_w);
-  const double xbytes = (double)N * cv.H * cv.W * cv.Cin, step = std::max((double)cv.Cin * cv.sw, xbytes / ((double)N * cv.OH * cv.OW));
-  const double general = pieces * (0.0057 + (xbytes > 22e6 ? 0.059 : 0.036) * std::sqrt(inside) * std::min(1.0, step / 128.0));
+  const PatchLines l(cv, KH, N);
+  const double general = (double)N * cv.OH * cv.OW * nch *
+                         (0.0057 + (0.036 + 0.023 * l.far) * std::sqrt(l.inside) * l.u + (l.u == 1.0 ? 0.03 * l.far * l.inside : 0.0));
   if (blocks * (1.5 + 1.15e-3 * bytes) > general + 500.0) return false;  // ns; half a microsecond decides nothing
   const bool taps = rows(r) < spanned(r);
   auto mul = [](int d) { return (uint32_t)(((1ull << 31) + d - 1) / d); };
@@ -1438,14 +1457,15 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   // (launches, the copy or patch matrix of the activations for pixel lanes, the packed patches for
   // channel lanes): over the ResNet-50 layers at batch 1 to 4 and dense layers a run takes the model's
   // time plus 3 to 8 us (activations read 16 channels at a time), plus 9 and 0.8 us a megabyte (patch
-  // matrix; 3.5 without a staged form) or plus 7 to 12 (channel lanes).
+  // matrix; without a staged form its own price) or plus 7 to 12 (channel lanes).
   const double xbytes = (double)g.M * g.K;
   ConvView rows{nullptr, g.H, g.W, g.Cin, g.KW, g.sh, g.sw, g.ph, g.pw, g.OH, g.OW, g.M, g.K, 0, nullptr, g.dh, g.dw, 0};
   int images = g.N;
   im2col_flatten(&rows, g.KH, &images);
   Im2colTile stripe;
   const bool staged = im2col_tile(rows, g.KH, images, cdiv(g.K, kChunk) * kChunk, &stripe);
-  const double around[2] = {g.Cin % 16 == 0 ? 6e-6 : 9e-6 + (staged ? 0.8e-12 : 3.5e-12) * xbytes, 9.1e-6 + 5e-12 * xbytes};
+  const double around[2] = {g.Cin % 16 == 0 ? 6e-6 : 9e-6 + (staged ? 0.8e-12 * xbytes : general_copy(rows, g.KH, images, cdiv(g.K, kChunk))),
+                            9.1e-6 + 5e-12 * xbytes};
   PlanChoice best{0, 0, 0, 0, 0, 0, 1e30, 0};
   for (int v = 2; v <= 3; ++v) {
     if ((o.variant == 2 || o.variant == 3) && v != o.variant) continue;
