@@ -1253,25 +1253,32 @@ int cu_count() {
 
 // Number of partial tile pieces that a grid of G workgroups produces (see tab_kernel); the
 // largest number of pieces that one tile is cut into and of segments that one workgroup runs.
+// Walks the shares by addition (position = tile, chunk of it): it is asked for dozens of grids per layer.
 static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* most_segs) {
   const long long total = (long long)ntiles * nch;
-  int n = 0, most = 0, run = 0, segs = 0;
-  long long run_tile = -1;
+  const long long share = total / G, rest = total % G;
+  const int step_t = (int)(share / nch), step_c = (int)(share % nch);
+  int n = 0, most = 0, run = 0, segs = 0, t = 0, c = 0, run_tile = -1;
+  long long carry = 0;
+  auto piece = [&](int tile) {
+    ++n;
+    run = tile == run_tile ? run + 1 : 1;
+    run_tile = tile;
+    most = std::max(most, run);
+  };
   for (int w = 0; w < G; ++w) {
-    long long b = (long long)w * total / G;
-    const long long e = (long long)(w + 1) * total / G;
-    segs = std::max(segs, (int)((e - 1) / nch - b / nch) + 1);
-    while (b < e) {
-      const long long t = b / nch;
-      const long long c0 = b - t * nch, c1 = std::min<long long>(nch, c0 + (e - b));
-      if (!(c0 == 0 && c1 == nch)) {
-        ++n;
-        run = (t == run_tile) ? run + 1 : 1;
-        run_tile = t;
-        most = std::max(most, run);
-      }
-      b += c1 - c0;
+    int t1 = t + step_t, c1 = c + step_c;  // end of the share
+    if ((carry += rest) >= G) { carry -= G; ++c1; }
+    if (c1 >= nch) { c1 -= nch; ++t1; }
+    if (t1 == t) {  // within one tile
+      if (c1 > c) { segs = std::max(segs, 1); piece(t); }
+    } else {
+      segs = std::max(segs, t1 - t + (c1 ? 1 : 0));
+      if (c) piece(t);
+      if (c1) piece(t1);
     }
+    t = t1;
+    c = c1;
   }
   *most_per_tile = most;
   *most_segs = segs;
@@ -1402,7 +1409,19 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o);
 // multi-table call share both operands.
 static double xcd_fetch_bytes(int xcd, int G, int nti, int ntj, int nch, int T, int ih, int jt) {
   const long long total = (long long)nti * ntj * nch * T;
-  std::vector<uint8_t> seen_a((size_t)nti * nch), seen_b((size_t)ntj * nch);
+  const int words = (nch + 63) / 64;  // a bit per chunk
+  std::vector<uint64_t> seen_a((size_t)nti * words), seen_b((size_t)ntj * words);
+  auto mark = [&](uint64_t* seen, int c0, int c1) {  // chunks c0 .. c1 - 1; returns how many are new
+    int fresh = 0;
+    for (int k = c0 / 64; k <= (c1 - 1) / 64; ++k) {
+      uint64_t m = ~0ull;
+      if (k == c0 / 64) m &= ~0ull << (c0 & 63);
+      if (k == (c1 - 1) / 64) m &= ~0ull >> (63 - ((c1 - 1) & 63));
+      fresh += __builtin_popcountll(m & ~seen[k]);
+      seen[k] |= m;
+    }
+    return fresh;
+  };
   const int q = G >> 3, r = G & 7;
   double bytes = 0.0;
   for (int x = 0; x < 8; ++x) {
@@ -1413,16 +1432,16 @@ static double xcd_fetch_bytes(int xcd, int G, int nti, int ntj, int nch, int T, 
     const int nw = q + (x < r ? 1 : 0);
     for (int k = 0; k < nw; ++k) {
       const int w = xcd ? w0 + k : x + 8 * k;
-      const long long b = (long long)w * total / G, e = (long long)(w + 1) * total / G;
-      for (long long it = b; it < e; ++it) {
+      long long it = (long long)w * total / G;
+      const long long e = (long long)(w + 1) * total / G;
+      while (it < e) {
         const long long gt = it / nch;
-        const int ch = (int)(it - gt * nch);
+        const int c0 = (int)(it - gt * nch), c1 = (int)std::min<long long>(nch, c0 + (e - it));
         const int tile = (int)(gt % ((long long)nti * ntj));
         const int ti = tile / ntj, tj = tile - ti * ntj;
-        uint8_t& sa = seen_a[(size_t)ti * nch + ch];
-        uint8_t& sb = seen_b[(size_t)tj * nch + ch];
-        na += !sa; sa = 1;
-        nb += !sb; sb = 1;
+        na += mark(&seen_a[(size_t)ti * words], c0, c1);
+        nb += mark(&seen_b[(size_t)tj * words], c0, c1);
+        it += c1 - c0;
       }
     }
     bytes += 16.0 * ((double)na * ih + (double)nb * jt);
