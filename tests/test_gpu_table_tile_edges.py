@@ -127,8 +127,29 @@ def test_pieces_of_shared_tiles(case, split, combine):
 
 def test_channel_lanes_and_a_sum_of_more_taps_than_sixteen_bits_hold():
     _run((60, 1, 1, 200, 1, 1, 70), 1, 0, 1, False, dict(variant=3))
-    for variant in (2, 3):  # 32768 taps of the largest codes
+    for variant in (2, 3):
         _run((3, 1, 1, 32768, 1, 1, 9), 1, 0, 1, False, dict(variant=variant))
+
+
+@pytest.mark.parametrize("split, combine", [(1, 0), (3, 1), (3, 2)])
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("entry", [65535, 0, 32767, -32768])
+def test_longest_sums_of_the_largest_entries(entry, variant, split, combine):
+    """32768 taps of one entry: byte sums, their corrections and the 64-bit dequantization at their limits (the unsigned
+    sum ends just under 2^31), whole and in pieces."""
+    signed = entry in (32767, -32768)
+    x, w, q = _operands((3, 1, 1, 32768, 1, 1, 9), 5 + signed, signed)
+    q = I.Quant(q.x_scale, 127 if signed else 255, q.w_scale, -128 if signed else 255, None)
+    lut = np.full(65536, entry, np.int16 if signed else np.uint16)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 0, signed=signed), q,
+                    tune=dict(TUNE, variant=variant, split_k=split, combine=combine)) as h:
+        assert (h.plan()["pieces"] > 0) == (split > 1)
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        acc, y = h.run(G.to_dev(x))
+        torch.cuda.synchronize()
+    want, y_want = oracle.conv2d_ex(x, w, lut, 1, 0, q, signed=signed)
+    assert bool((want == 32768 * entry).all())
+    G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), want, y_want)
 
 
 def test_stripes_against_the_general_patch_copy():
