@@ -233,10 +233,11 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // output) 75 -> 61 us, 100352 x 64 x 256 115 -> 98.
 //
 // Bound: LDS.  Per phase of a full tile 1 MiB of gathers (165-200 bytes per clock measured) and 64
-// KiB of table writes at 70 bytes per clock, against 4096 clocks of matrix instructions per SIMD.
+// KiB of table writes (1150 clocks, 57 bytes per clock), against 4096 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
 // copied with their border, see prep_chunks_kernel); the other form has no position per lane
-// element and no comparisons.
+// element and no comparisons.  At full height it spills around each segment (132 bytes per lane, 64 with
+// ready-made tables), PADDED 268 and 136 (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).
 // GR: groups of 64 lane elements per wave.  Tiles of at most half the height take GR = 4, whose free
 // registers hold the lane operands and the table rows a whole phase ahead: with few groups to gather
 // a phase is shorter than a round trip to memory.
@@ -1289,7 +1290,8 @@ static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* m
 // convolution layers with the heights, cuts and combinations forced.
 //   - a phase (a chunk of 16 taps) of a tile of ih lane elements takes 1.2 us for its tables, barrier
 //     and latencies (1.05 us with ready-made tables) and 0.6 ns per lane element;
-//   - every segment a workgroup runs costs its first tables, the pipeline fill and its stores;
+//   - every segment a workgroup runs costs its first tables, the pipeline fill and its stores (fitted before
+//     its set-up was shortened by some 3 us; the order of the choices is what it is used for);
 //   - tiles cut into pieces: a launch of the fix-up kernel and the pieces once written and once read,
 //     or, combined inside the main kernel, the reading of the others' pieces one after another;
 //   - grids larger than the machine run in rounds.
