@@ -1362,7 +1362,14 @@ static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int
   };
   if (o.split_k > 0)
     return evaluate((int)std::max<long long>(1, std::min<long long>(std::min<long long>(total, 4LL * slots), (long long)ntiles * o.split_k)));
-  PlanChoice best = evaluate(ntiles);
+  // A workgroup per tile, or the fewest whole tiles per workgroup that a launch (fewer than 2^32 threads) holds.
+  constexpr int kMostGroups = (int)((1LL << 32) / kThreads) - 1;
+  int whole = ntiles;
+  for (int d = ntiles / kMostGroups + 1; whole > kMostGroups; ++d) {
+    if (d > 4096) whole = slots;
+    else if (ntiles % d == 0) whole = ntiles / d;
+  }
+  PlanChoice best = evaluate(whole);
   std::vector<int> cand;
   if (total >= 2) cand.push_back((int)std::min<long long>(slots, total / 2));
   for (int sdiv = 2; sdiv <= 16; ++sdiv)

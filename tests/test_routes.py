@@ -57,3 +57,11 @@ def test_tiles_cover_the_layer():
 @pytest.mark.parametrize("m, k, n", [(2520, 64, 22), (3876, 64, 16), (3174, 128, 9)])
 def test_no_second_round_of_tiles_under_four_million_lookups(m, k, n):
     assert route(ax._dense_desc(m, k, n))["kernel"] == "direct"
+
+
+@pytest.mark.parametrize("m, k, n", [(1, 16, 1024), (1, 40, 1024), (1, 16, 4096), (64, 200, 1030), (1, 16, 4095 * 8)])
+def test_grids_stay_below_two_to_the_32_threads(m, k, n):
+    """65536 tables on pixel lanes: more tiles of eight columns than a launch holds workgroups of 512 threads."""
+    tables = 65536 if n <= 4096 else 65521  # the second is a prime: tiles that no small number divides evenly
+    with ax.AxLayer(ax._dense_desc(m, k, n), Q, num_luts=tables, tune=dict(ZERO, variant=2)) as h:
+        assert 0 < h.plan()["workgroups"] * 512 < 2**32
