@@ -726,10 +726,12 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 // tile is found with 32-bit divisions where the numbers allow it (SMALL): 25.7 MB of pieces
 // (3136 x 8, four per tile) 22 -> 17 us.
 template <bool CH, bool SMALL>
-__global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G) {
+__global__ __launch_bounds__(256) void tab_fixup_kernel(const TabArgs a, int G, int ntiles) {
   const int groups = a.ih / 64;
-  const int gtile = blockIdx.x / groups;
-  const int g = blockIdx.x - gtile * groups;
+  const int block = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  const int gtile = block / groups;
+  const int g = block - gtile * groups;
+  if (gtile >= ntiles) return;  // uniform; the last row of the launch is filled up
   auto owner = [&](auto it) {  // the workgroup w with w*total/G <= it < (w+1)*total/G
     const decltype(it) total = (decltype(it))a.total_iters;
     auto w = it * G / total;
@@ -1600,11 +1602,13 @@ static hipError_t launch_main(const TabArgs& a, int G, int ntiles, int phases, i
     AX_LAUNCHED();
   }
   if (!(phases & kPhFixup) || a.cnt) return hipSuccess;
-  const dim3 grid((unsigned)(ntiles * (a.ih / 64)));
+  // rows of 2^20 blocks: one row of threads of a launch is shorter than 2^32
+  const unsigned blocks = (unsigned)ntiles * (unsigned)(a.ih / 64), row = std::min(blocks, 1u << 20);
+  const dim3 grid(row, (blocks + row - 1) / row);
   if ((double)a.total_iters * (G + 1) < 4.0e9)  // (w + 1) * total and it * G fit 32 bits
-    hipLaunchKernelGGL((tab_fixup_kernel<CH, true>), grid, dim3(256), 0, s, a, G);
+    hipLaunchKernelGGL((tab_fixup_kernel<CH, true>), grid, dim3(256), 0, s, a, G, ntiles);
   else
-    hipLaunchKernelGGL((tab_fixup_kernel<CH, false>), grid, dim3(256), 0, s, a, G);
+    hipLaunchKernelGGL((tab_fixup_kernel<CH, false>), grid, dim3(256), 0, s, a, G, ntiles);
   return hipGetLastError();
 }
 

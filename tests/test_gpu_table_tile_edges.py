@@ -223,3 +223,22 @@ def test_output_pieces_of_every_alignment(channels, offset, split):
         G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), *want)
         for b in bufs:
             assert bool((b[:offset] == 77).all()) and bool((b[offset + n:] == 77).all())
+
+
+def test_pieces_of_more_tiles_than_one_row_of_a_launch():
+    """The second kernel takes 64 lane elements per block: 16 tables of 67 million pixels are 2^24 blocks and some."""
+    M, K, T = (1 << 26) + 64, 17, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    x = torch.randint(0, 256, (M, K), generator=g, device="cuda", dtype=torch.uint8)
+    w = torch.randint(0, 256, (K, 1), generator=g, device="cuda", dtype=torch.uint8)
+    luts = torch.randint(-32768, 32768, (T, 65536), generator=g, device="cuda", dtype=torch.int16)
+    with ax.AxLayer(ax._dense_desc(M, K, 1), I.Quant(1.0, 0, 1.0, 0, None), T, tune=dict(TUNE, split_k=1, combine=1)) as h:
+        assert h.plan()["pieces"] > 0 and h.plan()["combine"] == 1
+        h.prepare(w, luts)
+        acc = h.run(x, y_out=False)[0].view(T, M)
+    for t in (0, 7, 15):
+        table = (luts[t].to(torch.int32) & 0xFFFF).view(256, 256)
+        for part in (slice(0, 1 << 20), slice(M // 2, M // 2 + (1 << 20)), slice(M - (1 << 20), M)):
+            want = sum(table[:, int(w[k, 0])][x[part, k].long()] for k in range(K))
+            assert torch.equal(acc[t, part], want)
