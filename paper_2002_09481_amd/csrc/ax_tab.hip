@@ -236,7 +236,7 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // KiB of table writes (1150 clocks, 57 bytes per clock), against 4096 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
 // copied with their border, see prep_chunks_kernel); the other form has no position per lane
-// element and no comparisons.  At full height it spills around each segment (132 bytes per lane, 64 with
+// element and no comparisons.  At full height it spills around each segment (132 bytes per lane, 60 with
 // ready-made tables), PADDED 268 and 136 (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).
 // GR: groups of 64 lane elements per wave.  Tiles of at most half the height take GR = 4, whose free
 // registers hold the lane operands and the table rows a whole phase ahead: with few groups to gather
