@@ -108,6 +108,7 @@ struct TabArgs {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 512;           // 8 waves of up to 256 registers
 constexpr int kWaves = kThreads / 64;
@@ -251,7 +252,6 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   constexpr int XR = PRE ? GR : 4;  // groups whose lane operands are in registers or in flight
   constexpr int DB = !PRE && GR < kGroups ? 2 : 1;  // chunks whose table rows are
   constexpr int PER = 8 / GR;      // entries stored after a group's gathers
-  constexpr int DEPTH = 3;         // gathers in flight ahead of the matrix instructions
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -260,10 +260,13 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   const uint8_t* padrow = reinterpret_cast<const uint8_t*>(a.qd->padrow);
   const uint32_t lds0 = (uint32_t)(uintptr_t)sh.tab;
 
-  // constant operand of the matrix instruction: row m has a 1 at byte m of every 16
+  // constant operand of the matrix instruction: row m has a 1 at byte m of every 16.  It is sparse, two
+  // values of every four with their places in pick_at: (m % 4, 3) or, for m % 4 = 3, (0, 3).
   i32x4 pick;
+  const int high = (m & 3) == 3;
 #pragma unroll
-  for (int d = 0; d < 4; ++d) pick[d] = (m >> 2) == d ? 1 << (8 * (m & 3)) : 0;
+  for (int d = 0; d < 4; ++d) pick[d] = (m >> 3) == (d & 1) ? 1 << (16 * (m >> 2 & 1) + 8 * high) : 0;
+  const int pick_at = (high ? 0xc : 0xc | (m & 3)) * 0x11111111;
   // gather addresses: perm[s] takes byte s of offs (16 * tap) and the code of that tap
   const int rot = (((m >> 2) ^ (m >> 3)) & 1) << 1 | (m >> 3);
   uint32_t offs = 0, perm[4];
@@ -522,23 +525,26 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
             const auto z = __builtin_amdgcn_permlane16_swap(u[1], v[1], false, false);
             t[0] = w[0]; t[1] = w[1]; t[2] = z[0]; t[3] = z[1];
           }
-          // The gathers run through a small ring of registers, DEPTH ahead of the matrix instructions.
+          // Two gathers, eight taps, go into one sparse matrix instruction; two pairs are in flight or being summed.
           // The second buffer's address does not fit the instruction's 16-bit offset: its last unit
           // is in offs.
-          i32x4 ring[DEPTH + 1];
-          auto issue = [&](int i) {
-            uint32_t addr = __builtin_amdgcn_perm(t[i & 3], buf ? offs + 0x01010101u : offs, perm[i >> 2]);
-            asm volatile("" : "+v"(addr));
-            ring[i % (DEPTH + 1)] =
-                *(const __attribute__((address_space(3))) i32x4*)(uintptr_t)(addr + lds0 + (buf ? kTabBytes - 1u : 0u));
+          union { i32x8 pair; i32x4 half[2]; } ring[2];
+          auto issue = [&](int i) {  // pair i: step 2 (i / 4) and the one after it, of quarter i % 4
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              uint32_t addr = __builtin_amdgcn_perm(t[i & 3], buf ? offs + 0x01010101u : offs, perm[2 * (i >> 2) + h]);
+              asm volatile("" : "+v"(addr));
+              ring[i & 1].half[h] =
+                  *(const __attribute__((address_space(3))) i32x4*)(uintptr_t)(addr + lds0 + (buf ? kTabBytes - 1u : 0u));
+            }
           };
+          issue(0);
+          issue(1);
 #pragma unroll
-          for (int i = 0; i < DEPTH; ++i) issue(i);
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
+          for (int i = 0; i < 8; ++i) {
             __builtin_amdgcn_sched_barrier(0);
-            if (i + DEPTH < 16) issue(i + DEPTH);
-            acc[p][i & 3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(pick, ring[i % (DEPTH + 1)], acc[p][i & 3], 0, 0, 0);
+            acc[p][i & 3] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(pick, ring[i & 1].pair, acc[p][i & 3], pick_at, 0, 0);
+            if (i + 2 < 8) issue(i + 2);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
