@@ -8,9 +8,9 @@
 //   for a tap k and a group of 8 columns j..j+7, the workgroup builds in LDS a table of 256
 //   entries of 16 bytes, entry v = the eight 16-bit products LUT(v, B[k][j..j+7]);
 //   every lane element's entry A[i][k] is fetched with ONE 16-byte LDS read, and a matrix instruction
-//   adds the bytes of 64 such entries (16 elements, four taps) to int32 accumulators.
+//   adds the bytes of 128 such entries (16 elements, eight taps) to int32 accumulators.
 //
-// So a lookup-MAC costs 2 bytes of LDS read bandwidth and a 512th of a matrix instruction, instead of
+// So a lookup-MAC costs 2 bytes of LDS read bandwidth and a 1024th of a matrix instruction, instead of
 // one conflict-prone 2-byte gather and an addition per MAC.  The 128 kB truth table itself stays in L2:
 // the tables are assembled from a row-major re-layout of it ("rows": for each code of the
 // table-side operand the 256 products against every lane-side code, 512 contiguous bytes),
@@ -197,12 +197,15 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 //
 // Gathers and sums.  The wave's 64 lanes are 16 lane elements (m = lane % 16) times four taps
 // (kg = lane / 16): every lane fetches the entry of ITS element's code at ITS tap, 16 bytes = eight
-// products = what v_mfma_i32_16x16x64_i8 takes from a lane as 16 contraction elements of column m.
-// The other operand is a constant: row r of it picks byte r of every 16, so the instruction adds,
-// for 16 lane elements at once, the low and the high bytes of the eight products over the four
-// taps: one matrix instruction per 512 lookups where adding in vector registers takes eight
-// vector instructions.  The bytes count as signed, so the tables hold every byte with its top bit
-// flipped (value - 128) and the epilogue adds 128 * (1 + 256) per tap.
+// products; two such fetches are what v_smfmac_i32_16x16x128_i8 takes from a lane as 32 contraction elements
+// of column m.  The other operand is a constant: row r of it picks byte r of every 16, so the instruction adds,
+// for 16 lane elements at once, the low and the high bytes of the eight products over eight
+// taps: one matrix instruction per 1024 lookups where adding in vector registers takes
+// sixteen vector instructions.  A row has one value in every 16, so the sparse form (two of every four) holds it and
+// takes twice the bytes of v_mfma_i32_16x16x64_i8 in the same 16 clocks: with that one a phase of a full tile was 4096
+// clocks of matrix instructions per SIMD beside 4096 of gathers, and the two do not overlap fully: 3.44 us, 3.10 now
+// (2048 elements 2.08 and 1.96, 512 elements 1.22 and 1.20).  The bytes count as signed, so the tables hold every
+// byte with its top bit flipped (value - 128) and the epilogue adds 128 * (1 + 256) per tap.
 //
 // Table layout.  LDS holds two buffers of 16 tables, interleaved entry by entry: entry v of tap t
 // lies at 256 v + 16 t, so the bank of a gather depends on the tap alone.  The LDS serves a 16-byte
@@ -234,7 +237,7 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // output) 75 -> 61 us, 100352 x 64 x 256 115 -> 98.
 //
 // Bound: LDS.  Per phase of a full tile 1 MiB of gathers (165-200 bytes per clock measured) and 64
-// KiB of table writes (1150 clocks, 57 bytes per clock), against 4096 clocks of matrix instructions per SIMD.
+// KiB of table writes (1150 clocks, 57 bytes per clock), against 2048 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
 // copied with their border, see prep_chunks_kernel); the other form has no position per lane
 // element and no comparisons.  At full height it spills around each segment (132 bytes per lane, 60 with
