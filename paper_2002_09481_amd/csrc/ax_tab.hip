@@ -212,10 +212,12 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // read in passes of 16 lanes that are not consecutive: measured times single out lanes 0-3, 12-15,
 // 20-23 and 24-27 of 32 (and their complement), two quarters from each of two neighbouring kg.  A
 // pass is therefore free of conflicts, whatever the codes are, when its 16 lanes are at 16
-// different taps: lane (kg, m) walks the four taps of dword dq = kg ^ rot(m / 4) of its element's
-// sixteen codes in the order s ^ (m % 4), rot = 0, 2, 3, 1.  (With the tables one after another
-// and random codes in the bank index, gathers took 1.6-2.2 times as long; with rot(m / 4) = m / 4
-// 1.5 times.)  The address is one byte permute: byte 1 is the code, byte 0 the constant 16 t.
+// different taps: lane (kg, m) walks the four taps of dword dq of its element's sixteen codes in the order
+// s ^ (m % 4), with dq = kg where m / 4 is even and kg ^ 2 where it is odd.  (With the tables one after another
+// and random codes in the bank index, gathers took 1.6-2.2 times as long; with dq = kg ^ (m / 4)
+// 1.5 times.  Full rotations kg ^ 0, 2, 3, 1 are free of conflicts too, but take eight selects per group of 64
+// elements to turn the codes, these four: a phase of a full tile 3.06 -> 3.03 us, 2.82 -> 2.70 ready-made.)
+// The address is one byte permute: byte 1 is the code, byte 0 the constant 16 t.
 //
 // Work is spread over the grid by iterations, not by tiles (G workgroups, one per compute
 // unit, each takes an equal contiguous share of tiles x chunks): a workgroup runs through one or
@@ -271,15 +273,14 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   for (int d = 0; d < 4; ++d) pick[d] = (m >> 3) == (d & 1) ? 1 << (16 * (m >> 2 & 1) + 8 * high) : 0;
   const int pick_at = (high ? 0xc : 0xc | (m & 3)) * 0x11111111;
   // gather addresses: perm[s] takes byte s of offs (16 * tap) and the code of that tap
-  const int rot = (((m >> 2) ^ (m >> 3)) & 1) << 1 | (m >> 3);
+  const bool swap = m >> 2 & 1;
   uint32_t offs = 0, perm[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     const uint32_t b = (uint32_t)(s ^ (m & 3));
-    offs |= 16u * (4u * (uint32_t)(kg ^ rot) + b) << (8 * s);
+    offs |= 16u * (4u * (uint32_t)(swap ? kg ^ 2 : kg) + b) << (8 * s);
     perm[s] = 0x0c0c0000u | (4u + b) << 8 | (uint32_t)s;
   }
-  const bool rot0 = rot & 1, rot1 = rot & 2;
 
   // Workgroups go to the eight XCDs (each with its own L2) in turn.  With a.xcd the share of work
   // is taken by a renumbered index under which every XCD holds a contiguous run of shares:
@@ -516,12 +517,11 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) sl[p] = __builtin_amdgcn_sad_u8(x[e], 0u, sl[p]);
           // Sixteen codes per lane (element l) -> dword dq of element 16 r + m in register r of lane
-          // (kg, m): rotate the dwords of a lane by its rot, then transpose rows of 16 lanes against
+          // (kg, m): trade the dwords of lanes whose dq is kg ^ 2, then transpose rows of 16 lanes against
           // registers.
           uint32_t t[4];
           {
-            const uint32_t s0 = rot0 ? x.y : x.x, s1 = rot0 ? x.x : x.y, s2 = rot0 ? x.w : x.z, s3 = rot0 ? x.z : x.w;
-            const uint32_t q0 = rot1 ? s2 : s0, q2 = rot1 ? s0 : s2, q1 = rot1 ? s3 : s1, q3 = rot1 ? s1 : s3;
+            const uint32_t q0 = swap ? x.z : x.x, q2 = swap ? x.x : x.z, q1 = swap ? x.w : x.y, q3 = swap ? x.y : x.w;
             const auto u = __builtin_amdgcn_permlane32_swap(q0, q2, false, false);
             const auto v = __builtin_amdgcn_permlane32_swap(q1, q3, false, false);
             const auto w = __builtin_amdgcn_permlane16_swap(u[0], v[0], false, false);
