@@ -228,8 +228,13 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // A phase is one chunk of 16 taps: the waves gather from one buffer and fill the other with the
 // tables of the next chunk, then meet at a barrier.  Without PRE a wave builds 32 entries of all 16
 // tables: lane = (tap, quarter), eight 16-byte loads (one per column, from the 512-byte row of the
-// column's code; the four lanes of a tap read 64 contiguous bytes), requested before the barrier
-// that ends the phase before, and one entry interleaved and stored after every group of gathers.
+// column's code; the four lanes of a tap read 64 contiguous bytes), interleaved and stored entry by entry.
+// Of the two waves of a SIMD one stores its entries and requests the next rows before it gathers, the other (late)
+// requests its rows first and stores after its gathers: one keeps the vector unit and the LDS writes busy while the
+// other one's gathers keep the LDS reads and the matrix unit, and their row requests do not queue up behind each other.
+// With the entries of all waves stored between their gathers and the rows requested before the barrier a phase took
+// 1.20 us at 512 elements, 1.45 at 1024, 1.72 at 1568, 2.16 at 2112, 2.60 at 3136 and 3.04 at 4096; so it takes
+// 0.96, 1.23, 1.58, 1.93, 2.52 and 3.03.  (The rows of 64 KB of tables alone take 0.56 us, the stores 0.45.)
 // PRE: the tables of a chunk lie ready-made in global memory as an image of the LDS buffer
 // (prep_tables_kernel) and are copied straight into LDS (buffer loads with the lds modifier).
 //
@@ -254,9 +259,8 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
     long long cterm[kWaves][kJT];  // column constants of the current tile, see the epilogue
     int comb[3];                 // last piece of a shared tile? / first and last share of the tile
   } sh;
-  constexpr int XR = PRE ? GR : 4;  // groups whose lane operands are in registers or in flight
+  constexpr int XR = PRE ? GR : GR < kGroups ? 4 : 2;  // groups whose lane operands are in registers or in flight
   constexpr int DB = !PRE && GR < kGroups ? 2 : 1;  // chunks whose table rows are
-  constexpr int PER = 8 / GR;      // entries stored after a group's gathers
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -478,24 +482,35 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
   const uint32_t klast = (uint32_t)a.nch * kChunk;
   const uint32_t padfix =
       (klast - (uint32_t)a.K) * ((uint32_t)__builtin_amdgcn_readfirstlane(row0_v) ^ 0x8080u) + a.bias_k - 32896u * klast;
-  uint2 codes = load_codes(c_beg + 1), codes2;
+  uint2 codes = load_codes(c_beg + 1), codes2 = codes;
   if (DB == 2) codes2 = load_codes(c_beg + 2);
   copies_done();
   __syncthreads();
-  // the column codes are requested ahead of the rows: loads return in order, and waiting for the codes
-  // must not mean waiting for the rows
-  const uint2 codes1 = codes;
-  codes = load_codes(c_beg + 1 + DB);
-  __builtin_amdgcn_sched_barrier(0);
-  build_issue(codes1, dd[1 % DB]);
-  __builtin_amdgcn_sched_barrier(0);
-  if (DB == 2) build_issue(codes2, dd[0]);
-  __builtin_amdgcn_sched_barrier(0);
 
   // One phase: gathers of chunk ch from buffer BUF, tables of the next chunk (more: there is one) into
   // the other.
-  auto phase = [&](auto BUF, int ch, bool more) __attribute__((always_inline)) {
+  auto phase = [&](auto LATE, auto BUF, int ch, bool more) __attribute__((always_inline)) {
+    constexpr bool late = decltype(LATE)::value;
     constexpr int buf = decltype(BUF)::value;
+    auto entries = [&]() __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) build_commit(e, buf ^ 1, dd[(buf + 1) % DB]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Rows of a later chunk, into the registers whose entries are stored.  The column codes are requested ahead of the
+    // rows: loads return in order, and waiting for the codes must not mean waiting for the rows.  Past the last chunk
+    // the codes are those of the last chunk again (the number of loads in flight stays known) and the rows are never used.
+    auto rows_ahead = [&](int set) __attribute__((always_inline)) {
+      const uint2 codes_now = codes;
+      codes = load_codes(ch + (late ? 1 : 2) + DB);
+      __builtin_amdgcn_sched_barrier(0);
+      build_issue(codes_now, dd[set % DB]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (late) rows_ahead(buf);
     {
 #pragma unroll
       for (int p = 0; p < GR; ++p) {
@@ -513,6 +528,10 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
         if (p + XR == GR) load_from(ch + 1);
         if (!PRE || more) xn[p % XR] = load_x((p + XR) % GR);
         __builtin_amdgcn_sched_barrier(0);
+        if (!late && p == 0) {
+          entries();
+          rows_ahead(buf + 1);
+        }
         if (p < np) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) sl[p] = __builtin_amdgcn_sad_u8(x[e], 0u, sl[p]);
@@ -550,33 +569,34 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
             if (i + 2 < 8) issue(i + 2);
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) {
-#pragma unroll
-          for (int e = PER * p; e < PER * (p + 1); ++e) build_commit(e, buf ^ 1, dd[(buf + 1) % DB]);
-        }
       }
       __builtin_amdgcn_sched_barrier(0);
-      // Rows for the tables that the next phase (DB = 2: the one after it) builds, requested before
-      // the barrier so that they travel while the wave waits for the others.  Past the last chunk the
-      // codes are those of the last chunk again (the number of loads in flight stays known) and the
-      // rows are never used.
-      const uint2 codes_now = codes;
-      codes = load_codes(ch + 2 + DB);
-      __builtin_amdgcn_sched_barrier(0);
-      build_issue(codes_now, dd[(buf + 1) % DB]);
-      __builtin_amdgcn_sched_barrier(0);
+      if (late) entries();
       copies_done();
       __syncthreads();
     }
   };
   // Phases in pairs, an odd last one by itself: a loop with a way out between its two phases would
   // leave the compiler unsure which loads are the youngest, and it would wait for all of them.
-  for (int ch = c_beg; ch + 1 < c_end; ch += 2) {
-    phase(std::integral_constant<int, 0>(), ch, true);
-    phase(std::integral_constant<int, 1>(), ch + 1, ch + 2 < c_end);
-  }
-  if (n & 1) phase(std::integral_constant<int, 0>(), c_end - 1, false);
+  auto phases = [&](auto LATE) __attribute__((always_inline)) {
+    constexpr bool late = decltype(LATE)::value;
+    const uint2 codes1 = codes;
+    codes = !late ? load_codes(c_beg + 1 + DB) : codes2;
+    __builtin_amdgcn_sched_barrier(0);
+    if (!late || DB == 2) build_issue(codes1, dd[1 % DB]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!late && DB == 2) build_issue(codes2, dd[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int ch = c_beg; ch + 1 < c_end; ch += 2) {
+      phase(LATE, std::integral_constant<int, 0>(), ch, true);
+      phase(LATE, std::integral_constant<int, 1>(), ch + 1, ch + 2 < c_end);
+    }
+    if (n & 1) phase(LATE, std::integral_constant<int, 0>(), c_end - 1, false);
+  };
+  if (!PRE && wave >= kWaves / 2)
+    phases(std::true_type());
+  else
+    phases(std::false_type());
 
   // ---- epilogue ------------------------------------------------------------------------
   // corr = acc - z_tab*Sl - z_lane*Sb[j] + K*z_lane*z_tab.
