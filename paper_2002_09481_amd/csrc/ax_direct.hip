@@ -450,14 +450,6 @@ __global__ __launch_bounds__(1024) void dw3_kernel(Geom g, QParams qp_in, const 
   }
 }
 
-// One load of a T from an address of any alignment (the unaligned access mode of global loads).
-template <typename T>
-__device__ __forceinline__ T load_any(const void* p) {
-  T v;
-  __builtin_memcpy(&v, p, sizeof(T));
-  return v;
-}
-
 // Layers of few output pixels (the deep layers of a network at batch 1, a fully connected layer at a
 // small batch).  A table tile would spend more on assembling its tables than on the lookups they
 // serve; here every workgroup keeps the whole table in LDS, as the depthwise kernel does, and

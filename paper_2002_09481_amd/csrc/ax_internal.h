@@ -9,6 +9,14 @@
 
 namespace ax {
 
+// One load of a T from an address of any alignment (the unaligned access mode of global loads).
+template <typename T>
+__device__ __forceinline__ T load_any(const void* p) {
+  T v;
+  __builtin_memcpy(&v, p, sizeof(T));
+  return v;
+}
+
 // Geometry of one layer call after validation.  A dense layer is a 1x1 convolution over
 // M "images" of one pixel.
 struct Geom {

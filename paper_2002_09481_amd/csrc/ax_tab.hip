@@ -868,18 +868,6 @@ __device__ __forceinline__ uint32_t pad_of(const ConvView& v) {
   return (((uint32_t)(v.dq ? v.dq->x_zp : v.pad_code)) & 0xffu) ^ v.sx;
 }
 
-__device__ __forceinline__ uint32_t im2col_code(const ConvView& v, uint32_t pad, int m, int k) {
-  const int ohw = v.OH * v.OW;
-  const int n = m / ohw;
-  const int r = m - n * ohw;
-  const int oy = r / v.OW, ox = r - (r / v.OW) * v.OW;
-  const int tap = k / v.Cin, ci = k - tap * v.Cin;
-  const int ky = tap / v.KW, kx = tap - ky * v.KW;
-  const int iy = oy * v.sh - v.ph + ky * v.dh, ix = ox * v.sw - v.pw + kx * v.dw;
-  if ((unsigned)iy >= (unsigned)v.H || (unsigned)ix >= (unsigned)v.W) return pad;
-  return (uint32_t)v.x[((size_t)(n * v.H + iy) * v.W + ix) * v.Cin + ci] ^ v.sx;
-}
-
 // rows[t][v] = the product of table-side code t and lane-side code v, both bytes with their top bit
 // flipped (the matrix instructions of tab_kernel read them as signed bytes: value - 128).
 //
@@ -951,16 +939,42 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
   const bool fast = !FROM_X && (J % 4 == 0) && (((uintptr_t)w & 3) == 0) && (j + 3 < J);
   int32_t s[4] = {0, 0, 0, 0};
   const uint32_t pad = FROM_X ? pad_of(cv) : 0u;
+  int py[4] = {0, 0, 0, 0}, px[4] = {0, 0, 0, 0};  // FROM_X: the column's pixel under tap (0, 0), and its image
+  const uint8_t* image[4] = {cv.x, cv.x, cv.x, cv.x};
+  if (FROM_X) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int ohw = cv.OH * cv.OW, m = min(j + e, J - 1);
+      const int n = m / ohw, r = m - n * ohw;
+      const int oy = r / cv.OW;
+      py[e] = oy * cv.sh - cv.ph;
+      px[e] = (r - oy * cv.OW) * cv.sw - cv.pw;
+      image[e] = cv.x + (size_t)n * cv.H * cv.W * cv.Cin;
+    }
+  }
   for (int k = kbeg + r; k < kend; k += 16) {
     uint32_t pk = 0;
     if (k < K) {
       if (fast) {
         pk = *reinterpret_cast<const uint32_t*>(w + (size_t)k * J + j) ^ (sx * 0x01010101u);
       } else {
+        int dy = 0, dx = 0, ci = 0;  // FROM_X: the tap
+        if (FROM_X) {
+          const int tap = k / cv.Cin, ky = tap / cv.KW;
+          ci = k - tap * cv.Cin;
+          dy = ky * cv.dh;
+          dx = (tap - ky * cv.KW) * cv.dw;
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           uint32_t bb = 0;
-          if (j + e < J) bb = FROM_X ? im2col_code(cv, pad, j + e, k) : ((uint32_t)w[(size_t)k * J + j + e] ^ sx);
+          if (FROM_X) {
+            const int iy = py[e] + dy, ix = px[e] + dx;
+            const bool in = (unsigned)iy < (unsigned)cv.H && (unsigned)ix < (unsigned)cv.W;
+            if (j + e < J) bb = in ? (uint32_t)image[e][((size_t)iy * cv.W + ix) * cv.Cin + ci] ^ cv.sx : pad;
+          } else if (j + e < J) {
+            bb = (uint32_t)w[(size_t)k * J + j + e] ^ sx;
+          }
           pk |= bb << (8 * e);
         }
       }
@@ -1155,32 +1169,45 @@ __global__ __launch_bounds__(256) void prep_chunks_kernel(const uint8_t* __restr
   }
 }
 
-// Ap[k / 16][j][k % 16] = w[k][j] (zero fill for k >= K), 64x64 tiles through LDS.
-__global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __restrict__ w, int K, int J, int Kp,
+// Ap[k / 16][j][k % 16] = w[k][j] (zero fill for k >= K).  A thread takes one chunk of sixteen rows and four
+// neighbouring columns: a dword per row, all in flight together, turned in registers (4 x 4 bytes in eight permutes),
+// and four 16-byte pieces.  Rows may start at any byte (dwords at their own alignment); columns past the last whole four
+// are read byte by byte.  Bound by memory: 4096 x 4096 (34 MB) 35 us with byte loads and a pass through LDS, 10 us now.
+__global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __restrict__ w, int K, int J,
                                                               uint8_t* __restrict__ Ap, uint32_t sx) {
-  __shared__ uint8_t tile[64][68];
-  const int k0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-  const int t = threadIdx.x;
-  {
-    const int r = t >> 2, seg = (t & 3) * 16;
-    const int k = k0 + r;
+  const int chunk = blockIdx.x, j = 4 * (blockIdx.y * 256 + threadIdx.x);
+  if (j >= J) return;
+  const int k0 = chunk * kChunk, nk = min(kChunk, K - k0);
+  const bool whole = j + 3 < J;
+  uint32_t v[kChunk];  // columns j .. j + 3 of a row
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int j = j0 + seg + e;
-      tile[r][seg + e] = (k < K && j < J) ? (uint8_t)(w[(size_t)k * J + j] ^ sx) : (uint8_t)0;
+  for (int e = 0; e < kChunk; ++e) {
+    const uint8_t* row = w + (size_t)(k0 + min(e, nk - 1)) * J + j;  // past the last row: that one again, cleared below
+    if (whole) {
+      v[e] = load_any<uint32_t>(row);
+    } else {
+      v[e] = row[0];
+      if (j + 1 < J) v[e] |= (uint32_t)row[1] << 8;
+      if (j + 2 < J) v[e] |= (uint32_t)row[2] << 16;
     }
   }
-  __syncthreads();
-  {
-    const int c = t >> 2, seg = (t & 3) * 16;
-    const int j = j0 + c;
-    if (j < J && k0 + seg < Kp) {
-      uint32_t pk[4] = {0, 0, 0, 0};
+  uint32_t piece[4][4];  // [column][four rows]
 #pragma unroll
-      for (int e = 0; e < 16; ++e) pk[e >> 2] |= (uint32_t)tile[seg + e][c] << (8 * (e & 3));
-      *reinterpret_cast<uint4*>(Ap + ((size_t)((k0 + seg) / 16) * J + j) * 16) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-    }
+  for (int q = 0; q < 4; ++q) {
+    uint32_t r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = 4 * q + e < nk ? v[4 * q + e] ^ (sx * 0x01010101u) : 0u;
+    const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+    const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    piece[0][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+    piece[1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+    piece[2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+    piece[3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
   }
+  uint4* out = reinterpret_cast<uint4*>(Ap) + (size_t)chunk * J + j;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (j + c < J) out[c] = make_uint4(piece[c][0], piece[c][1], piece[c][2], piece[c][3]);
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -1697,8 +1724,7 @@ hipError_t launch_tab(const Geom& g, const QParams& qp, const TabPlan& p, const 
       AX_LAUNCHED();
     }
     if (c) {
-      hipLaunchKernelGGL(prep_transpose_kernel, dim3(cdiv(Kp, 64), cdiv(g.Cout, 64)), dim3(256), 0, s, w, g.K,
-                         g.Cout, Kp, Ap, cv.sx);
+      hipLaunchKernelGGL(prep_transpose_kernel, dim3(nchunks, cdiv(g.Cout, 1024)), dim3(256), 0, s, w, g.K, g.Cout, Ap, cv.sx);
       AX_LAUNCHED();
     }
   } else {

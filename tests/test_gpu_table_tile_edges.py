@@ -242,3 +242,23 @@ def test_pieces_of_more_tiles_than_one_row_of_a_launch():
         for part in (slice(0, 1 << 20), slice(M // 2, M // 2 + (1 << 20)), slice(M - (1 << 20), M)):
             want = sum(table[:, int(w[k, 0])][x[part, k].long()] for k in range(K))
             assert torch.equal(acc[t, part], want)
+
+
+# filters turned for channel lanes: columns past the last whole four, one column, more than a block's 1024; rows of
+# less than a chunk and with a ragged last one; filters that start off a dword boundary
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("K,Cout", [(3, 1), (16, 3), (17, 70), (147, 4), (33, 1027), (64, 2048)])
+def test_channel_lanes_turn_filters_of_any_width_and_alignment(K, Cout, offset, signed):
+    x, w, q = _operands((5, 1, 1, K, 1, 1, Cout), K + Cout, signed)
+    lut = I.lut_signed_random_error(7) if signed else I.lut_random_error(7)
+    want, y_want = oracle.conv2d_ex(x, w, lut, 1, 0, q, signed=signed)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 0, signed=signed), q, tune=dict(TUNE, variant=3)) as h:
+        assert h.plan()["variant"] == 3
+        buf = torch.empty(w.size + offset, dtype=torch.int8 if signed else torch.uint8, device="cuda")
+        wd = buf[offset:].view(w.shape)
+        wd.copy_(G.to_dev(w))
+        h.prepare(wd, ax.lut_to_device(lut))
+        acc, y = h.run(G.to_dev(x))
+        torch.cuda.synchronize()
+        G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), want, y_want, "K %d Cout %d offset %d" % (K, Cout, offset))
