@@ -247,8 +247,8 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // KiB of table writes (1150 clocks, 57 bytes per clock), against 2048 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
 // copied with their border, see prep_chunks_kernel); the other form has no position per lane
-// element and no comparisons.  At full height it spills around each segment (132 bytes per lane, 60 with
-// ready-made tables), PADDED 268 and 136 (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).
+// element and no comparisons.  PADDED spills 204 bytes per lane at full height, the others none or next to none
+// (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).
 // GR: groups of 64 lane elements per wave.  Tiles of at most half the height take GR = 4, whose free
 // registers hold the lane operands and the table rows a whole phase ahead: with few groups to gather
 // a phase is shorter than a round trip to memory.
@@ -610,9 +610,58 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
     for (int r = 0; r < 4; ++r) {
       sum[p][r][0] = (uint32_t)acc[p][r].x + ((uint32_t)acc[p][r].y << 8);
       sum[p][r][1] = (uint32_t)acc[p][r].z + ((uint32_t)acc[p][r].w << 8);
+      // here, not where it is used: carried on as its four bytes' sums it would take twice the registers
+      asm volatile("" : "+v"(sum[p][r][0]), "+v"(sum[p][r][1]));
     }
-  bool finish = whole;  // this workgroup writes the tile's outputs
-  if (!whole) {
+  // Corrects, converts and writes the sums of group p: lane l = 16 kg + m holds columns 2 kg, 2 kg + 1 of element 16 r + m
+  // in v[r], and the code sum of element l.
+  const int em = ls & 15, ekg = ls >> 4;
+  const bool wide = a.K > 16384;
+  auto put_group = [&](int p, uint32_t (&v)[4][2], uint32_t codes_sum) __attribute__((always_inline)) {
+    const long long ct0 = column_constant<kWaves>(sh.cterm, 2 * ekg), ct1 = column_constant<kWaves>(sh.cterm, 2 * ekg + 1);
+    float yv[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t lterm = z_tab * (uint32_t)__shfl((int)codes_sum, 16 * r + em);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        v[r][c] -= padfix;
+        yv[r][c] = dequant(v[r][c], lterm, c ? ct1 : ct0, scale, wide);
+      }
+    }
+    if (!CH && a.vec_out == 2) {
+      // Rows of 16 lanes trade quarters for columns and store 16 bytes per lane, two lanes the 32 bytes that a tile has of
+      // an output row: with 8 bytes per lane the stores took as long as three phases (100352 x 64 x 256, both outputs: 118
+      // us, 102 so; one output 98 and 90).
+#pragma unroll
+      for (int r = 0; r < 4; r += 2) {
+        const int i = i0 + 64 * (kWaves * p + wave) + 16 * (r + (ekg & 1)) + em, j = j0 + 4 * (ekg >> 1);
+        const size_t o = (size_t)i * a.J + j;
+        const bool in = i < a.I && j < a.J;
+        if (acc_base) {
+          const auto c0 = __builtin_amdgcn_permlane16_swap(v[r][0], v[r + 1][0], false, false);
+          const auto c1 = __builtin_amdgcn_permlane16_swap(v[r][1], v[r + 1][1], false, false);
+          if (in) *reinterpret_cast<uint4*>(acc_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
+        }
+        if (y_base) {
+          const auto c0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][0]), __float_as_uint(yv[r + 1][0]), false, false);
+          const auto c1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][1]), __float_as_uint(yv[r + 1][1]), false, false);
+          if (in) *reinterpret_cast<uint4*>(y_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = i0 + 64 * (kWaves * p + wave) + 16 * r + em;
+        if (i < a.I) put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * ekg, v[r][0], v[r][1], yv[r][0], yv[r][1]);
+      }
+    }
+  };
+  if (whole) {
+#pragma unroll
+    for (int p = 0; p < GR; ++p)
+      if (p < np) put_group(p, sum[p], sl[p]);
+  } else {
     // Piece of a tile that several workgroups share, as the registers hold it: per group of 64 lane
     // elements eight runs of 64 words ([quarter][column of the pair][lane]).
     // A slot holds a.ih lane elements (the tile height) of kJT columns.
@@ -664,79 +713,48 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
       }
       __syncthreads();
       if (sh.comb[0]) {
+        // From memory, its own piece too, two pieces of four groups in flight at a time: with the own sums kept in
+        // registers the compiler spills around the whole segment (172 bytes per lane), also where no tile is cut.  A tile of
+        // one chunk at full height 19.1 -> 16.2 us, four chunks of 3136 elements 25.5 -> 22.8.
         const int w_first = sh.comb[1], w_last = sh.comb[2];
-        for (int w = w_first; w <= w_last; ++w) {
-          if (w == wg) continue;
-          const int so = 2 * w + (w == w_first ? 1 : 0);
-          const int32_t* po = a.part + (size_t)so * ((size_t)a.ih * kJT) + ls;
-          const int32_t* lo = a.lsum + (size_t)so * a.ih + ls;
+        for (int p0 = 0; p0 < np; p0 += 4) {
+          uint32_t v[4][4][2], vs[4];
 #pragma unroll
-          for (int p2 = 0; p2 < GR; p2 += 4) {  // loads of four groups in flight
-            uint32_t t[4][9];
+          for (int p = 0; p < 4; ++p) {
+            vs[p] = 0;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-              if (p2 + p >= np) continue;
-              const int g = kWaves * (p2 + p) + wave;
-              t[p][8] = (uint32_t)__hip_atomic_load(lo + g * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] = 0;
+          }
+          for (int w = w_first; w <= w_last; w += 2) {
+            uint32_t t[2][4][9];
 #pragma unroll
-              for (int q = 0; q < 8; ++q)
-                t[p][q] = (uint32_t)__hip_atomic_load(po + (size_t)g * 512 + q * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < 2; ++k) {  // past the last piece: that one again, not added
+              const int wk = min(w + k, w_last), slot_k = 2 * wk + (wk == w_first ? 1 : 0);
+              const int32_t* po = a.part + (size_t)slot_k * ((size_t)a.ih * kJT) + ls;
+              const int32_t* lo = a.lsum + (size_t)slot_k * a.ih + ls;
+#pragma unroll
+              for (int p = 0; p < 4; ++p) {
+                const int g = kWaves * min(p0 + p, np - 1) + wave;  // past the last group: that one again, not used
+                t[k][p][8] = (uint32_t)__hip_atomic_load(lo + g * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                  t[k][p][q] = (uint32_t)__hip_atomic_load(po + (size_t)g * 512 + q * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              }
             }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-              if (p2 + p >= np) continue;
-              sl[p2 + p] += t[p][8];
+            for (int k = 0; k < 2; ++k) {
+              if (w + k > w_last) continue;
 #pragma unroll
-              for (int q = 0; q < 8; ++q) sum[p2 + p][q >> 1][q & 1] += t[p][q];
+              for (int p = 0; p < 4; ++p) {
+                vs[p] += t[k][p][8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] += t[k][p][q];
+              }
             }
           }
-        }
-        finish = true;
-      }
-    }
-  }
-  if (finish) {
-    const bool wide = a.K > 16384;
-    const int m = ls & 15, kg = ls >> 4;
-    const long long ct0 = column_constant<kWaves>(sh.cterm, 2 * kg), ct1 = column_constant<kWaves>(sh.cterm, 2 * kg + 1);
 #pragma unroll
-    for (int p = 0; p < GR; ++p) {
-      if (p >= np) continue;
-      float yv[4][2];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t lterm = z_tab * (uint32_t)__shfl((int)sl[p], 16 * r + m);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          sum[p][r][c] -= padfix;
-          yv[r][c] = dequant(sum[p][r][c], lterm, c ? ct1 : ct0, scale, wide);
-        }
-      }
-      if (!CH && a.vec_out == 2) {
-        // Rows of 16 lanes trade quarters for columns and store 16 bytes per lane, two lanes the 32 bytes that a tile has of
-        // an output row: with 8 bytes per lane the stores took as long as three phases (100352 x 64 x 256, both outputs: 118
-        // us, 102 so; one output 98 and 90).
-#pragma unroll
-        for (int r = 0; r < 4; r += 2) {
-          const int i = i0 + 64 * (kWaves * p + wave) + 16 * (r + (kg & 1)) + m, j = j0 + 4 * (kg >> 1);
-          const size_t o = (size_t)i * a.J + j;
-          const bool in = i < a.I && j < a.J;
-          if (acc_base) {
-            const auto c0 = __builtin_amdgcn_permlane16_swap(sum[p][r][0], sum[p][r + 1][0], false, false);
-            const auto c1 = __builtin_amdgcn_permlane16_swap(sum[p][r][1], sum[p][r + 1][1], false, false);
-            if (in) *reinterpret_cast<uint4*>(acc_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
-          }
-          if (y_base) {
-            const auto c0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][0]), __float_as_uint(yv[r + 1][0]), false, false);
-            const auto c1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(yv[r][1]), __float_as_uint(yv[r + 1][1]), false, false);
-            if (in) *reinterpret_cast<uint4*>(y_base + o) = make_uint4(c0[0], c1[0], c0[1], c1[1]);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = i0 + 64 * (kWaves * p + wave) + 16 * r + m;
-          if (i < a.I) put_pair<CH>(a, acc_base, y_base, i, j0 + 2 * kg, sum[p][r][0], sum[p][r][1], yv[r][0], yv[r][1]);
+          for (int p = 0; p < 4; ++p)
+            if (p0 + p < np) put_group(p0 + p, v[p], vs[p]);
         }
       }
     }
