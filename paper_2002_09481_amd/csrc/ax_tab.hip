@@ -1410,6 +1410,23 @@ static bool ready_made(const Geom& g, const Options& o, int v, int partials, int
   return bytes <= kPreTablesSmall || (partials == 0 && nti >= kPreRowTiles && bytes <= kPreTablesMax);
 }
 
+// Whether a share of `iters` chunks in `segs` segments of ih lane elements is so much faster with tables assembled in the
+// kernel that a layer gives its ready-made ones up.  A phase, measured (us; assembled / ready-made): 512 elements 0.95 / 1.39,
+// 1024 1.24 / 1.56, 1568 1.57 / 1.67, 2048 1.80 / 1.83 (half-height form), 2112 1.93 / 2.12, 2560 2.22 / 2.19, 3136 2.51 / 2.45,
+// 4096 3.02 / 2.80; ready-made sets of up to 2 MB stay in the L2s whichever tiles an XCD has: 64 elements 0.90, 512 1.05,
+// 1024 1.35, 2048 1.90.  A segment's first tables take one round trip to memory instead of two, 2.5 us less from the L2s
+// (131072 x 27 x 16: 9.3 us, 14.0 assembled).  Near ties keep the ready-made tables: the sums are within a tenth of what
+// is measured.  128 x 16 x 16 x 32, 3 x 3 to 32 channels: 33 us ready-made, 27 assembled; 8 x 8 x 64 to 64 34 and 31.
+static bool assembled_faster(int ih, long long iters, int segs, size_t bytes) {
+  const bool half = ih <= kIT / 2;
+  const double far = std::min(1.0, std::max(0.0, ((double)bytes - 2e6) / 2e6));  // 0: in the L2s, 1: not
+  const double near_phase = std::max(0.90, 0.83 + 0.50e-3 * ih), far_phase = std::max(1.28, 1.15 + 0.34e-3 * ih);
+  const double ready = half ? near_phase + far * (far_phase - near_phase) : 1.35 + 0.35e-3 * ih;
+  const double assembled = half ? std::max(0.97, 0.70 + 0.54e-3 * ih) : 0.78 + 0.55e-3 * ih;
+  const double seg = 2.7 + 1.8e-3 * ih;
+  return iters * assembled + segs * seg < 0.89 * (iters * ready + segs * (seg - 2.5 + 3.0 * far));
+}
+
 static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int v, int nti_wanted) {
   const long long I = (v == 2) ? g.M : g.Cout;
   const long long J = (v == 2) ? g.Cout : g.M;
@@ -1619,6 +1636,12 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   if (p.combine) prep += up256((size_t)p.nti * cdiv(J, kJT) * g.T * 4);
   const size_t tabs_bytes = table_bytes(g);
   p.pre = ready_made(g, o, v, best.partials, best.nti) ? 1 : 0;
+  if (p.pre && !o.tables && (best.partials == 0 || p.combine)) {
+    const long long iters = (long long)best.nti * cdiv(J, kJT) * nch;
+    int most, segs;
+    count_partials(best.nti * cdiv(J, kJT), nch, best.G, &most, &segs);
+    if (assembled_faster(best.ih, cdiv(iters, best.G), segs, (size_t)nch * cdiv(J, kJT) * kTabBytes)) p.pre = 0;
+  }
   p.off_tabs = prep;
   if (p.pre) prep += up256(tabs_bytes);
   if (v == 2) {
