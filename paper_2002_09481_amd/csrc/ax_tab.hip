@@ -713,27 +713,28 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
       }
       __syncthreads();
       if (sh.comb[0]) {
-        // From memory, its own piece too, two pieces of four groups in flight at a time: with the own sums kept in
-        // registers the compiler spills around the whole segment (172 bytes per lane), also where no tile is cut.  A tile of
+        // From memory, its own piece too, two pieces of four groups in flight at a time (four of one group where a wave has
+        // no more): with the own sums kept in registers the compiler spills around the whole segment (172 bytes per lane), also where no tile is cut.  A tile of
         // one chunk at full height 19.1 -> 16.2 us, four chunks of 3136 elements 25.5 -> 22.8.
         const int w_first = sh.comb[1], w_last = sh.comb[2];
-        for (int p0 = 0; p0 < np; p0 += 4) {
-          uint32_t v[4][4][2], vs[4];
+        auto add_pieces = [&](auto GROUPS, auto PIECES, int p0) __attribute__((always_inline)) {
+          constexpr int PG = decltype(GROUPS)::value, PW = decltype(PIECES)::value;
+          uint32_t v[PG][4][2], vs[PG];
 #pragma unroll
-          for (int p = 0; p < 4; ++p) {
+          for (int p = 0; p < PG; ++p) {
             vs[p] = 0;
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] = 0;
           }
-          for (int w = w_first; w <= w_last; w += 2) {
-            uint32_t t[2][4][9];
+          for (int w = w_first; w <= w_last; w += PW) {
+            uint32_t t[PW][PG][9];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {  // past the last piece: that one again, not added
+            for (int k = 0; k < PW; ++k) {  // past the last piece: that one again, not added
               const int wk = min(w + k, w_last), slot_k = 2 * wk + (wk == w_first ? 1 : 0);
               const int32_t* po = a.part + (size_t)slot_k * ((size_t)a.ih * kJT) + ls;
               const int32_t* lo = a.lsum + (size_t)slot_k * a.ih + ls;
 #pragma unroll
-              for (int p = 0; p < 4; ++p) {
+              for (int p = 0; p < PG; ++p) {
                 const int g = kWaves * min(p0 + p, np - 1) + wave;  // past the last group: that one again, not used
                 t[k][p][8] = (uint32_t)__hip_atomic_load(lo + g * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
@@ -742,10 +743,10 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
               }
             }
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < PW; ++k) {
               if (w + k > w_last) continue;
 #pragma unroll
-              for (int p = 0; p < 4; ++p) {
+              for (int p = 0; p < PG; ++p) {
                 vs[p] += t[k][p][8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] += t[k][p][q];
@@ -753,8 +754,13 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
             }
           }
 #pragma unroll
-          for (int p = 0; p < 4; ++p)
+          for (int p = 0; p < PG; ++p)
             if (p0 + p < np) put_group(p0 + p, v[p], vs[p]);
+        };
+        if (np == 1) {  // low tiles: no group read four times over
+          add_pieces(std::integral_constant<int, 1>(), std::integral_constant<int, 4>(), 0);
+        } else {
+          for (int p0 = 0; p0 < np; p0 += 4) add_pieces(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(), p0);
         }
       }
     }

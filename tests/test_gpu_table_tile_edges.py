@@ -262,3 +262,13 @@ def test_channel_lanes_turn_filters_of_any_width_and_alignment(K, Cout, offset, 
         acc, y = h.run(G.to_dev(x))
         torch.cuda.synchronize()
         G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), want, y_want, "K %d Cout %d offset %d" % (K, Cout, offset))
+
+
+# pieces combined by the workgroup that ends last: one group of 64 elements per wave, one wave with two, half and full
+# height with ragged last groups; an even and an odd number of pieces
+@pytest.mark.parametrize("tables", [1, 2])
+@pytest.mark.parametrize("split_k", [2, 3, 5])
+@pytest.mark.parametrize("M", [40, 512, 513, 2000, 2049, 4033])
+def test_pieces_combined_in_the_kernel(M, split_k, tables):
+    plan = _run((M, 1, 1, 96, 1, 1, 9), 1, 0, 1, False, dict(row_tiles=1, split_k=split_k, combine=2, tables=tables))
+    assert plan["pieces"] > 0 and plan["combine"] == 2
