@@ -96,7 +96,8 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // and 2.2 % over the better one each time (more than 5 % slower 59 and 137, more than 20 % 16 and 51).
 // Prepared layers of more than two rounds of tiles stay on this kernel up to 36 and 38 us, though the tiles are faster for
 // most (5692 x 80 x 47: 30 and 15 us): the tests of the walk over several tiles reach it through the choice for such layers,
-// as nothing else selects this kernel.
+// as nothing else selects this kernel.  From 4e7 lookups on that is asked of layers beyond the bounds of ready-made tables
+// only, and not of whether the plan takes them: layers that give them up do so because their tiles are faster assembled.
 Route choose_route(const Geom& g, const Options& o, bool prepared) {
   Route r{};
   const bool automatic =
@@ -116,7 +117,7 @@ Route choose_route(const Geom& g, const Options& o, bool prepared) {
                                     : 4e-6;
       const double scale = prepared ? 0.83 : g.Cin % 4 == 0 ? 0.9 : 0.72;
       const bool walk = prepared && r.fp.tiles > 2 * cu_count();
-      const double keep = g.K >= 2048 ? 60e-6 : !walk || n < 16e6 ? 0.0 : n < 40e6 ? 38e-6 : n < 80e6 && !r.p.pre ? 36e-6 : 0.0;
+      const double keep = g.K >= 2048 ? 60e-6 : !walk || n < 16e6 ? 0.0 : n < 40e6 ? 38e-6 : n < 80e6 && !r.p.may_pre ? 36e-6 : 0.0;
       r.few = scale * r.fp.cost < tiles + prep || 1.1 * r.fp.cost < keep;
     } else {
       r.few = r.fp.cost < 5e-6 + 5.5e-12 * n && r.fp.tiles <= cu_count();

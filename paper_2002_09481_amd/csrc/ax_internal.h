@@ -122,6 +122,7 @@ struct TabPlan {
   int partials;     // partial tile pieces that grid produces
   int combine;      // 1: the main kernel combines them itself (arrival counters), 0: fix-up pass
   int pre;          // 1: the main kernel copies ready-made tables from the prepared block
+  int may_pre;      // 1: ready-made tables are within their bounds, also where assembled ones are taken as the faster form
   int nti;          // tiles along the lane dimension
   int ih;           // their height in lane elements (multiple of 64, nti * ih >= I)
   double cost;      // expected time of a call, seconds (the planner's model)

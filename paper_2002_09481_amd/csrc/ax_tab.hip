@@ -1641,7 +1641,7 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   p.off_cnt = prep;
   if (p.combine) prep += up256((size_t)p.nti * cdiv(J, kJT) * g.T * 4);
   const size_t tabs_bytes = table_bytes(g);
-  p.pre = ready_made(g, o, v, best.partials, best.nti) ? 1 : 0;
+  p.pre = p.may_pre = ready_made(g, o, v, best.partials, best.nti) ? 1 : 0;
   if (p.pre && !o.tables && (best.partials == 0 || p.combine)) {
     const long long iters = (long long)best.nti * cdiv(J, kJT) * nch;
     int most, segs;

@@ -59,6 +59,16 @@ def test_no_second_round_of_tiles_under_four_million_lookups(m, k, n):
     assert route(ax._dense_desc(m, k, n))["kernel"] == "direct"
 
 
+# handles between 4e7 and 8e7 lookups whose tables could be kept ready-made (timed on the few-pixel kernel and on tiles:
+# 4712 x 80 x 112 30.5 and 15.9 us, 4354 x 252 x 64 37.6 and 26.6), whichever form of tables their plan takes
+@pytest.mark.parametrize("desc", [ax._dense_desc(2521, 300, 58), ax._dense_desc(4444, 212, 62), ax._dense_desc(5087, 104, 86),
+                                  ax._dense_desc(5075, 204, 57), ax._dense_desc(4712, 80, 112), ax._dense_desc(4354, 252, 64),
+                                  ax._conv_desc((1, 48, 48, 20), (3, 3, 20, 110), 1, 1)],
+                         ids=lambda d: "%dx%dx%d" % (d.N * d.H * d.W, d.KH * d.KW * d.Cin, d.Cout))
+def test_the_form_of_the_tables_does_not_choose_the_kernel(desc):
+    assert route(desc)["kernel"] == "tiles"
+
+
 @pytest.mark.parametrize("m, k, n", [(1, 16, 1024), (1, 40, 1024), (1, 16, 4096), (64, 200, 1030), (1, 16, 4095 * 8)])
 def test_grids_stay_below_two_to_the_32_threads(m, k, n):
     """65536 tables on pixel lanes: more tiles of eight columns than a launch holds workgroups of 512 threads."""
