@@ -105,7 +105,7 @@ Route choose_route(const Geom& g, const Options& o, bool prepared) {
   const double n = (double)g.M * g.K * g.Cout;
   const bool tiny = n < 4.0e6 && o.variant != 2 && o.variant != 3;
   r.tab = o.variant != 1 && !tiny && tab_supported(g);
-  if (r.tab) r.p = tab_plan(g, o);
+  if (r.tab) r.p = tab_plan(g, o, prepared);
   if (automatic && n >= 2.0e6 && fewpix_shape(g)) {
     r.fp = fewpix_plan(g);
     if (r.tab) {

@@ -143,7 +143,7 @@ struct TabPlan {
 int cu_count();  // compute units of the current device
 bool tab_supported(const Geom& g);
 int tab_num_tiles();
-TabPlan tab_plan(const Geom& g, const Options& o);
+TabPlan tab_plan(const Geom& g, const Options& o, bool prepared);
 // The kernel family of a layer and its plan, from geometry and options alone (ax_api.hip): decided once
 // per call or handle (prepared: the constants are laid out once, not in every call).  Neither tab nor few: depthwise or direct kernel.
 struct Route {

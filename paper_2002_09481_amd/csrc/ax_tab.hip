@@ -1416,21 +1416,22 @@ static bool ready_made(const Geom& g, const Options& o, int v, int partials, int
   return bytes <= kPreTablesSmall || (partials == 0 && nti >= kPreRowTiles && bytes <= kPreTablesMax);
 }
 
-// Whether a share of `iters` chunks in `segs` segments of ih lane elements is so much faster with tables assembled in the
-// kernel that a layer gives its ready-made ones up.  A phase, measured (us; assembled / ready-made): 512 elements 0.95 / 1.39,
-// 1024 1.24 / 1.56, 1568 1.57 / 1.67, 2048 1.80 / 1.83 (half-height form), 2112 1.93 / 2.12, 2560 2.22 / 2.19, 3136 2.51 / 2.45,
-// 4096 3.02 / 2.80; ready-made sets of up to 2 MB stay in the L2s whichever tiles an XCD has: 64 elements 0.90, 512 1.05,
-// 1024 1.35, 2048 1.90.  A segment's first tables take one round trip to memory instead of two, 2.5 us less from the L2s
-// (131072 x 27 x 16: 9.3 us, 14.0 assembled).  Near ties keep the ready-made tables: the sums are within a tenth of what
-// is measured.  128 x 16 x 16 x 32, 3 x 3 to 32 channels: 33 us ready-made, 27 assembled; 8 x 8 x 64 to 64 34 and 31.
-static bool assembled_faster(int ih, long long iters, int segs, size_t bytes) {
-  const bool half = ih <= kIT / 2;
-  const double far = std::min(1.0, std::max(0.0, ((double)bytes - 2e6) / 2e6));  // 0: in the L2s, 1: not
-  const double near_phase = std::max(0.90, 0.83 + 0.50e-3 * ih), far_phase = std::max(1.28, 1.15 + 0.34e-3 * ih);
-  const double ready = half ? near_phase + far * (far_phase - near_phase) : 1.35 + 0.35e-3 * ih;
-  const double assembled = half ? std::max(0.97, 0.70 + 0.54e-3 * ih) : 0.78 + 0.55e-3 * ih;
-  const double seg = 2.7 + 1.8e-3 * ih;
-  return iters * assembled + segs * seg < 0.89 * (iters * ready + segs * (seg - 2.5 + 3.0 * far));
+// What a share of `iters` chunks in `segs` segments of ih lane elements (at most half the full height) gains, us, with tables
+// assembled in the kernel instead of ready-made ones, for the layers that give those up.  misses: the share of its table copies
+// that no other workgroup of the XCD has fetched, 0 for sets that stay in the L2s anyway.  Fitted to 1533 random layers, each
+// timed in both forms back to back and with 48 MB read and written in between (misses by 0.7 us rms): a phase is 0.24 us shorter
+// assembled, less 0.16 per 1024 elements, and another 0.70, less 0.18 per 1024, where ready-made tables come from beyond the
+// L2; a segment's first tables take two round trips to memory instead of one, 2 us more (1.4 from beyond the L2).
+// Prepared layers give their tables up for more than 0.5 us: of 2200 layers they then take 0.987 of the time with all tables
+// ready-made (cold 0.993), 10 are more than 3 % slower so and 2 more than 8 %.  From phases and segments measured one by one,
+// without regard to who shares the tables, shares of one to three chunks were given up as well (63 and 41 layers slower; 852 x 32 x
+// 869, two chunks: 15.2 us, 13.6 ready-made).  1113 x 78 x 379: 22.7 us ready-made, 17.7 assembled.  Where a second launch sums the
+// pieces the fit is worse and the line 1.5 us (128 x 8 x 8 x 64, 3 x 3 to 64: 37.3 us ready-made, 34.4 assembled, every
+// copy a miss; 3 x 28 x 28 x 64, one in four: 20.0 and 21.9).
+// Calls that prepare their constants spend 7 us and more on the tables (choose_route) and keep them for more than 3 us.
+// Not asked for tiles above half the height, where neither form is ahead by much (assembled -5 to +6 % of a launch).
+static double assembled_gain(int ih, long long iters, int segs, double misses) {
+  return iters * (0.24 - 0.16e-3 * ih + misses * (0.70 - 0.18e-3 * ih)) - segs * (2.0 - 0.6 * misses);
 }
 
 static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int v, int nti_wanted) {
@@ -1509,13 +1510,14 @@ static PlanChoice plan_choice(const Geom& g, const Options& o, int tile, int v) 
   return best;
 }
 
-static TabPlan tab_plan_uncached(const Geom& g, const Options& o);
+static TabPlan tab_plan_uncached(const Geom& g, const Options& o, bool prepared);
 
 // Operand bytes that the eight L2s fetch in total when share w of G (iterations w*total/G ..) runs
 // on XCD w % 8 (xcd = 0) or when the shares are dealt out XCD by XCD (xcd = 1): per XCD the
 // distinct (lane tile, chunk) and (column tile, chunk) pairs its shares touch.  The tables of a
-// multi-table call share both operands.
-static double xcd_fetch_bytes(int xcd, int G, int nti, int ntj, int nch, int T, int ih, int jt) {
+// multi-table call share both operands.  table_copies: how many (column tile, chunk) pairs of these there are.
+constexpr long long kMostWalked = 1LL << 22;  // iteration spaces beyond are not worth walking
+static double xcd_fetch_bytes(int xcd, int G, int nti, int ntj, int nch, int T, int ih, int jt, long long* table_copies = nullptr) {
   const long long total = (long long)nti * ntj * nch * T;
   const int words = (nch + 63) / 64;  // a bit per chunk
   std::vector<uint64_t> seen_a((size_t)nti * words), seen_b((size_t)ntj * words);
@@ -1553,32 +1555,33 @@ static double xcd_fetch_bytes(int xcd, int G, int nti, int ntj, int nch, int T, 
       }
     }
     bytes += 16.0 * ((double)na * ih + (double)nb * jt);
+    if (table_copies) *table_copies += nb;
   }
   return bytes;
 }
 
 // Planning walks over candidate grids and counts their partial pieces, which takes tens of
 // microseconds: as much as a small layer's kernels.  Plans are therefore remembered per
-// (geometry, options); the table is small and cleared when it grows past a bound.
-TabPlan tab_plan(const Geom& g, const Options& o) {
+// (geometry, options, whether constants are prepared beforehand); the table is small and cleared when it grows past a bound.
+TabPlan tab_plan(const Geom& g, const Options& o, bool prepared) {
   struct Key {
-    int v[24];
+    int v[25];
     bool operator<(const Key& other) const { return std::memcmp(v, other.v, sizeof(v)) < 0; }
   };
   static std::mutex mu;
   static std::map<Key, TabPlan> cache;
   const Key k{{g.N, g.H, g.W, g.Cin, g.KH, g.KW, g.Cout, g.sh, g.sw, g.ph, g.pw, g.dh, g.dw, g.sgn, g.mult, o.variant,
-               o.split_k, o.tile, o.row_tiles, cu_count(), g.T, o.share_order, o.combine, o.tables}};
+               o.split_k, o.tile, o.row_tiles, cu_count(), g.T, o.share_order, o.combine, o.tables, prepared}};
   std::lock_guard<std::mutex> lock(mu);
   auto it = cache.find(k);
   if (it != cache.end()) return it->second;
   if (cache.size() > 4096) cache.clear();
-  const TabPlan p = tab_plan_uncached(g, o);
+  const TabPlan p = tab_plan_uncached(g, o, prepared);
   cache.emplace(k, p);
   return p;
 }
 
-static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
+static TabPlan tab_plan_uncached(const Geom& g, const Options& o, bool prepared) {
   TabPlan p{};
   // Lane assignment and tiles: the cheaper by the cost model, with what a call does around the main kernel
   // (launches, the copy or patch matrix of the activations for pixel lanes, the packed patches for
@@ -1616,7 +1619,7 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
     p.xcd = 1;
     if (o.share_order) {
       p.xcd = o.share_order - 1;
-    } else if ((long long)p.nti * ntj * nchk * g.T <= (1LL << 22) && best.G >= 16) {
+    } else if ((long long)p.nti * ntj * nchk * g.T <= kMostWalked && best.G >= 16) {
       const double f1 = xcd_fetch_bytes(1, best.G, p.nti, ntj, nchk, g.T, p.ih, kJT);
       const double f0 = xcd_fetch_bytes(0, best.G, p.nti, ntj, nchk, g.T, p.ih, kJT);
       if (f0 < 0.9 * f1) p.xcd = 0;
@@ -1642,11 +1645,16 @@ static TabPlan tab_plan_uncached(const Geom& g, const Options& o) {
   if (p.combine) prep += up256((size_t)p.nti * cdiv(J, kJT) * g.T * 4);
   const size_t tabs_bytes = table_bytes(g);
   p.pre = p.may_pre = ready_made(g, o, v, best.partials, best.nti) ? 1 : 0;
-  if (p.pre && !o.tables && (best.partials == 0 || p.combine)) {
-    const long long iters = (long long)best.nti * cdiv(J, kJT) * nch;
+  if (p.pre && !o.tables && best.ih <= kIT / 2) {
+    const int ntj = cdiv(J, kJT);
+    const long long iters = (long long)best.nti * ntj * nch;
+    const double far = std::min(1.0, std::max(0.0, ((double)nch * ntj * kTabBytes - 2e6) / 4e6));  // 0: in the L2s, 1: not
+    long long copies = 0;
+    if (far > 0.0 && iters <= kMostWalked) xcd_fetch_bytes(p.xcd, best.G, p.nti, ntj, nch, 1, p.ih, kJT, &copies);
     int most, segs;
-    count_partials(best.nti * cdiv(J, kJT), nch, best.G, &most, &segs);
-    if (assembled_faster(best.ih, cdiv(iters, best.G), segs, (size_t)nch * cdiv(J, kJT) * kTabBytes)) p.pre = 0;
+    count_partials(best.nti * ntj, nch, best.G, &most, &segs);
+    const double gain = assembled_gain(best.ih, cdiv(iters, best.G), segs, far * copies / iters);
+    if (gain > (!prepared ? -3.0 : best.partials && !p.combine ? 1.5 : 0.5)) p.pre = 0;
   }
   p.off_tabs = prep;
   if (p.pre) prep += up256(tabs_bytes);

@@ -91,6 +91,15 @@ def test_automatic_choice_on_the_table_tiles(layer, want):
                             "%s call %d" % (layer.name, call))
 
 
+# both sides of the line between ready-made and assembled tables, whole tiles and pieces combined in the kernel
+@pytest.mark.parametrize("layer, want", [(L(852, 1, 1, 32, 1, 1, 869), (2, 0, 2)), (L(1113, 1, 1, 78, 1, 1, 379), (2, 0, 1)),
+                                         (L(698, 1, 1, 127, 1, 1, 142), (2, 2, 2)), (L(840, 1, 1, 531, 1, 1, 49), (2, 2, 1)),
+                                         (L(8, 5, 66, 32, 3, 3, 112), (2, 2, 1))],
+                         ids=lambda v: v.name if isinstance(v, I.Layer) else "")
+def test_tables_given_up_or_kept(layer, want):
+    test_automatic_choice_on_the_table_tiles(layer, want)
+
+
 def test_prepare_again_with_other_filters_and_table_and_another_block():
     """A handle can be prepared again (other filters, other table) into another device block: the
     calls that follow use the new constants, the old block is left alone."""

@@ -69,6 +69,29 @@ def test_the_form_of_the_tables_does_not_choose_the_kernel(desc):
     assert route(desc)["kernel"] == "tiles"
 
 
+# handles on pixel lanes, whole tiles and pieces combined in the kernel: the form of the tables that is faster (us ready-made and
+# assembled: 1104 x 16 x 600 7.1 and 8.6, 852 x 32 x 869 13.6 and 15.2, 698 x 127 x 142 14.6 and 16.3; 1113 x 78 x 379 22.7 and 17.7,
+# 667 x 78 x 283 20.1 and 16.0, 840 x 531 x 49 29.0 and 22.8)
+@pytest.mark.parametrize("m, k, n, tables", [(1104, 16, 600, 2), (852, 32, 869, 2), (340, 27, 442, 2), (698, 127, 142, 2),
+                                             (1353, 91, 95, 2), (1113, 78, 379, 1), (667, 78, 283, 1), (2030, 87, 282, 1),
+                                             (840, 531, 49, 1), (1664, 288, 112, 1)])
+def test_ready_made_tables_are_given_up_where_assembling_is_faster(m, k, n, tables):
+    with ax.AxLayer(ax._dense_desc(m, k, n), Q) as h:
+        plan = h.plan()
+        assert plan["variant"] == 2 and plan["tables"] == tables
+    for forced in (1, 2):
+        with ax.AxLayer(ax._dense_desc(m, k, n), Q, tune=dict(ZERO, tables=forced)) as h:
+            assert h.plan()["tables"] == forced
+    assert ax.ax_dense_workspace_bytes(m, k, n) < 4096 * k * (n // 8)  # a call that would prepare them does without
+
+
+@pytest.mark.parametrize("n, hw, tables", [(128, 8, 1), (1, 56, 1), (3, 28, 2)])
+def test_tables_of_layers_whose_pieces_a_second_launch_sums(n, hw, tables):
+    with ax.AxLayer(ax._conv_desc((n, hw, hw, 64), (3, 3, 64, 64), 1, 1), Q) as h:
+        plan = h.plan()
+        assert (plan["variant"], plan["combine"], plan["tables"]) == (2, 1, tables)
+
+
 @pytest.mark.parametrize("m, k, n", [(1, 16, 1024), (1, 40, 1024), (1, 16, 4096), (64, 200, 1030), (1, 16, 4095 * 8)])
 def test_grids_stay_below_two_to_the_32_threads(m, k, n):
     """65536 tables on pixel lanes: more tiles of eight columns than a launch holds workgroups of 512 threads."""
