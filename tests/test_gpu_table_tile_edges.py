@@ -272,3 +272,24 @@ def test_channel_lanes_turn_filters_of_any_width_and_alignment(K, Cout, offset, 
 def test_pieces_combined_in_the_kernel(M, split_k, tables):
     plan = _run((M, 1, 1, 96, 1, 1, 9), 1, 0, 1, False, dict(row_tiles=1, split_k=split_k, combine=2, tables=tables))
     assert plan["pieces"] > 0 and plan["combine"] == 2
+
+
+# activations read in place above half the height, whole tiles and pieces (summed by the workgroup that ends last and by a
+# second launch): odd and even chunk counts, one chunk more than pieces
+@pytest.mark.parametrize("tables", [1, 2])
+@pytest.mark.parametrize("split_k, combine", [(1, 0), (2, 1), (4, 2), (8, 2)])
+@pytest.mark.parametrize("C, KH, KW", [(16, 3, 3), (32, 3, 3), (16, 1, 2)])
+def test_tall_tiles_read_in_place(C, KH, KW, split_k, combine, tables):
+    x, w, q = _operands((1, 50, 52, C, KH, KW, 9), C + split_k, False)
+    lut = I.lut_random_error(7)
+    want, y_want = oracle.conv2d(x, w, lut, 1, 1, q)
+    with ax.AxLayer(ax._conv_desc(x.shape, w.shape, 1, 1), q,
+                    tune=dict(TUNE, row_tiles=1, split_k=split_k, combine=combine, tables=tables)) as h:
+        _, OH, OW, _ = h.out_shape()
+        height = -(-OH * OW // 64) * 64
+        assert 2048 < height <= 4096
+        pieces = 2 * h.plan()["workgroups"] * height * 36 if h.plan()["pieces"] else 256  # and no room for a copy
+        h.prepare(G.to_dev(w), ax.lut_to_device(lut))
+        acc, y = h.run(G.to_dev(x), workspace=torch.empty(pieces, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        G.assert_parity(acc.cpu().numpy(), y.cpu().numpy(), want, y_want, "%dx%dx%d %d" % (C, KH, KW, split_k))
