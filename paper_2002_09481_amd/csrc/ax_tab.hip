@@ -691,9 +691,9 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
     }
     if (a.cnt) {
       // Combination inside this kernel: every workgroup that has stored a piece counts itself in
-      // at the tile's counter, and the one that arrives last adds the other pieces to its
-      // registers and writes the outputs like the owner of a whole tile.  Nobody waits for
-      // anybody.  The counter wraps to 0 with the last arrival, ready for the next launch.
+      // at the tile's counter, and the one that arrives last adds all pieces up and writes the outputs
+      // like the owner of a whole tile.  Nobody waits for anybody.  The counter wraps to 0 with the
+      // last arrival, ready for the next launch.
       // Pieces travel between workgroups on different XCDs, each with an L2 of its own, so they
       // are stored and loaded with device-scope atomic accesses, which pass through the L2s to
       // memory; a device-scope fence would instead write back and invalidate whole L2s (measured:
@@ -718,12 +718,16 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
       }
       __syncthreads();
       if (sh.comb[0]) {
-        // From memory, its own piece too, two pieces of four groups in flight at a time (four of one group where a wave has
-        // no more): with the own sums kept in registers the compiler spills around the whole segment (172 bytes per lane), also where no tile is cut.  A tile of
-        // one chunk at full height 19.1 -> 16.2 us, four chunks of 3136 elements 25.5 -> 22.8.
+        // From memory, its own piece too: with the own sums kept in registers the compiler spills around the whole segment
+        // (172 bytes per lane), also where no tile is cut (a tile of one chunk at full height 19.1 -> 16.2 us).  Two groups and
+        // two pieces at a time, a last single group four pieces, and none read that is not added: with four groups at a
+        // time and the missing ones read again, waves of six groups read eight.  Bound by these reads and, in short launches, by
+        // the code around them, which more or larger steps lengthen (sums and outputs stand in it once per group of a step).
+        // 356 random layers combined here 0.985 of the time (four groups; with 4 + 2 + 1: 0.997), the cut layers of
+        // ResNet-50 0.99, launches of less than 18 us 0.986.
         const int w_first = sh.comb[1], w_last = sh.comb[2];
-        auto add_pieces = [&](auto GROUPS, auto PIECES, int p0) __attribute__((always_inline)) {
-          constexpr int PG = decltype(GROUPS)::value, PW = decltype(PIECES)::value;
+        auto add_pieces = [&](auto GROUPS, int p0) __attribute__((always_inline)) {
+          constexpr int PG = decltype(GROUPS)::value;
           uint32_t v[PG][4][2], vs[PG];
 #pragma unroll
           for (int p = 0; p < PG; ++p) {
@@ -731,16 +735,17 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] = 0;
           }
-          for (int w = w_first; w <= w_last; w += PW) {
+          auto add = [&](auto PIECES, int w) __attribute__((always_inline)) {  // pieces w .. of the groups from p0
+            constexpr int PW = decltype(PIECES)::value;
             uint32_t t[PW][PG][9];
 #pragma unroll
-            for (int k = 0; k < PW; ++k) {  // past the last piece: that one again, not added
-              const int wk = min(w + k, w_last), slot_k = 2 * wk + (wk == w_first ? 1 : 0);
+            for (int k = 0; k < PW; ++k) {
+              const int slot_k = 2 * (w + k) + (w + k == w_first ? 1 : 0);
               const int32_t* po = a.part + (size_t)slot_k * ((size_t)a.ih * kJT) + ls;
               const int32_t* lo = a.lsum + (size_t)slot_k * a.ih + ls;
 #pragma unroll
               for (int p = 0; p < PG; ++p) {
-                const int g = kWaves * min(p0 + p, np - 1) + wave;  // past the last group: that one again, not used
+                const int g = kWaves * (p0 + p) + wave;
                 t[k][p][8] = (uint32_t)__hip_atomic_load(lo + g * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
@@ -748,25 +753,33 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
               }
             }
 #pragma unroll
-            for (int k = 0; k < PW; ++k) {
-              if (w + k > w_last) continue;
+            for (int k = 0; k < PW; ++k)
 #pragma unroll
               for (int p = 0; p < PG; ++p) {
                 vs[p] += t[k][p][8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) v[p][q >> 1][q & 1] += t[k][p][q];
               }
-            }
+          };
+          const std::integral_constant<int, 1> one{};
+          const std::integral_constant<int, 2> two{};
+          const std::integral_constant<int, 3> three{};
+          int w = w_first;
+          if constexpr (PG == 1) {
+            for (; w + 3 <= w_last; w += 4) add(std::integral_constant<int, 4>(), w);
+            if (w + 2 == w_last) add(three, w);
+            else if (w + 1 == w_last) add(two, w);
+            else if (w == w_last) add(one, w);
+          } else {
+            for (; w < w_last; w += 2) add(two, w);
+            if (w == w_last) add(one, w);
           }
 #pragma unroll
-          for (int p = 0; p < PG; ++p)
-            if (p0 + p < np) put_group(p0 + p, v[p], vs[p]);
+          for (int p = 0; p < PG; ++p) put_group(p0 + p, v[p], vs[p]);
         };
-        if (np == 1) {  // low tiles: no group read four times over
-          add_pieces(std::integral_constant<int, 1>(), std::integral_constant<int, 4>(), 0);
-        } else {
-          for (int p0 = 0; p0 < np; p0 += 4) add_pieces(std::integral_constant<int, 4>(), std::integral_constant<int, 2>(), p0);
-        }
+        int p0 = 0;
+        for (; p0 + 2 <= np; p0 += 2) add_pieces(std::integral_constant<int, 2>(), p0);
+        if (p0 < np) add_pieces(std::integral_constant<int, 1>(), p0);
       }
     }
   }

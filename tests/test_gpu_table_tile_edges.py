@@ -274,6 +274,14 @@ def test_pieces_combined_in_the_kernel(M, split_k, tables):
     assert plan["pieces"] > 0 and plan["combine"] == 2
 
 
+# as above, every remainder of four pieces (a single group's step) and of two (a pair of groups'): 1, 2, 3 and 8 groups per wave
+@pytest.mark.parametrize("split_k", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("M", [64, 1024, 1100, 4096])
+def test_every_number_of_pieces_combined_in_the_kernel(M, split_k):
+    plan = _run((M, 1, 1, 128, 1, 1, 9), 1, 0, 1, False, dict(row_tiles=1, split_k=split_k, combine=2, tables=1))
+    assert plan["pieces"] == 2 * split_k and plan["combine"] == 2
+
+
 # activations read in place above half the height, whole tiles and pieces (summed by the workgroup that ends last and by a
 # second launch): odd and even chunk counts, one chunk more than pieces
 @pytest.mark.parametrize("tables", [1, 2])
