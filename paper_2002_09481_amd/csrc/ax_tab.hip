@@ -1399,12 +1399,13 @@ static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* m
 //     tile count fill whole rounds of the machine, or whole multiples of it with K slices.
 struct PlanChoice { int tile, variant, G, partials, nti, ih; double cost; int most; };
 // Pieces are combined inside tab_kernel by the workgroup that finishes last where it has to read at
-// most kCombineElems lane elements of them (one piece of 512: 22.9 us, 25 with the second launch), and up to
-// kCombineMost pieces of sums of at least kCombineLong chunks, whose workgroups do not all end at once
-// (28 x 28 x 128 3 x 3 at batch 32, two pieces of 3136 x 8: 133.5 us, 144 with the second launch; 7 x 7 x 512
-// 3 x 3, four of 1568: 160.5 and 168).  Others go through tab_fixup_kernel, which spreads the sums of one
-// tile over many blocks (128 x 2048 x 2048, sixteen pieces: 44.8 us, 52 in the kernel).
-constexpr int kCombineElems = 768, kCombineMost = 4, kCombineLong = 64;
+// most kCombineElems lane elements of the others (177 random layers 0.98 of the time with the second launch), and up to
+// kCombineMost pieces of sums of at least kCombineLong chunks (two or three pieces 0.99; 28 x 28 x 128 3 x 3 at batch 32, two pieces of
+// 3136 x 8: 130.2 us, 137.4 with the second launch).  Others go through tab_fixup_kernel, which spreads the sums of one
+// tile over many blocks: four pieces of long sums 0.96 (14 x 14 x 1024 1 x 1 to 256 at batch 32, four of 3136: 72.5 us, 89.3
+// in the kernel; 7 x 7 x 512 3 x 3, four of 1600: 148.2 and 152.5), where all workgroups end at once and a quarter
+// of them is left with the work.
+constexpr int kCombineElems = 768, kCombineMost = 3, kCombineLong = 64;
 // Ready-made tables that a layer gets without being asked to: any set of up to kPreTablesSmall
 // bytes (it stays in the L2s and the memory-side cache whichever workgroup reads which part:
 // the CIFAR-shaped layers with K slices gain 25 %), larger sets (up to kPreTablesMax bytes) for
@@ -1472,7 +1473,9 @@ static PlanChoice plan_choice_nti(const Geom& g, const Options& o, int tile, int
     const double rounds = std::ceil((double)Gc / slots);
     const double iters = std::ceil((double)total / Gc);
     c.cost = rounds * (iters * t_chunk + segs * t_seg);
-    if (combines(o, c.partials, c.most, ih, nch))
+    // four pieces of a long sum are priced like three: priced by their bytes, grids of three or fewer pieces are taken instead,
+    // which are slower (100 random layers 1.01)
+    if (combines(o, c.partials, c.most, ih, nch) || (c.partials && !o.combine && c.most == kCombineMost + 1 && nch >= kCombineLong))
       c.cost += 2.32e-6 + (c.most - 1) * 0.5e-9 * ih;
     else if (c.partials)
       c.cost += 5e-6 + c.partials * 2.0 * ih * kJT * 4.0 / 4.0e12;

@@ -92,6 +92,14 @@ def test_tables_of_layers_whose_pieces_a_second_launch_sums(n, hw, tables):
         assert (plan["variant"], plan["combine"], plan["tables"]) == (2, 1, tables)
 
 
+@pytest.mark.parametrize("hw, cin, k, cout, combine", [(28, 128, 3, 128, 2), (14, 1024, 1, 256, 1), (14, 256, 3, 256, 1), (7, 512, 3, 512, 1)])
+def test_pieces_of_long_sums(hw, cin, k, cout, combine):
+    """Batch 32: two pieces per tile are combined in the kernel, four by a second launch."""
+    with ax.AxLayer(ax._conv_desc((32, hw, hw, cin), (k, k, cin, cout), 1, k // 2), Q) as h:
+        plan = h.plan()
+        assert plan["pieces"] == plan["workgroups"] and plan["combine"] == combine
+
+
 @pytest.mark.parametrize("m, k, n", [(1, 16, 1024), (1, 40, 1024), (1, 16, 4096), (64, 200, 1030), (1, 16, 4095 * 8)])
 def test_grids_stay_below_two_to_the_32_threads(m, k, n):
     """65536 tables on pixel lanes: more tiles of eight columns than a launch holds workgroups of 512 threads."""
