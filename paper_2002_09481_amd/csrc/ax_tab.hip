@@ -203,8 +203,8 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // taps: one matrix instruction per 1024 lookups where adding in vector registers takes
 // sixteen vector instructions.  A row has one value in every 16, so the sparse form (two of every four) holds it and
 // takes twice the bytes of v_mfma_i32_16x16x64_i8 in the same 16 clocks: with that one a phase of a full tile was 4096
-// clocks of matrix instructions per SIMD beside 4096 of gathers, and the two do not overlap fully: 3.44 us, 3.10 now
-// (2048 elements 2.08 and 1.96, 512 elements 1.22 and 1.20).  The bytes count as signed, so the tables hold every
+// clocks of matrix instructions per SIMD beside 4096 of gathers, and the two do not overlap fully: a full tile took a
+// tenth longer, 512 elements a fiftieth.  The bytes count as signed, so the tables hold every
 // byte with its top bit flipped (value - 128) and the epilogue adds 128 * (1 + 256) per tap.
 //
 // Table layout.  LDS holds two buffers of 16 tables, interleaved entry by entry: entry v of tap t
@@ -216,7 +216,7 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // s ^ (m % 4), with dq = kg where m / 4 is even and kg ^ 2 where it is odd.  (With the tables one after another
 // and random codes in the bank index, gathers took 1.6-2.2 times as long; with dq = kg ^ (m / 4)
 // 1.5 times.  Full rotations kg ^ 0, 2, 3, 1 are free of conflicts too, but take eight selects per group of 64
-// elements to turn the codes, these four: a phase of a full tile 3.06 -> 3.03 us, 2.82 -> 2.70 ready-made.)
+// elements to turn the codes, these four: a hundredth of a phase of a full tile, three ready-made.)
 // The address is one byte permute: byte 1 is the code, byte 0 the constant 16 t.
 //
 // Work is spread over the grid by iterations, not by tiles (G workgroups, one per compute
@@ -232,9 +232,10 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // Of the two waves of a SIMD one stores its entries and requests the next rows before it gathers, the other (late)
 // requests its rows first and stores after its gathers: one keeps the vector unit and the LDS writes busy while the
 // other one's gathers keep the LDS reads and the matrix unit, and their row requests do not queue up behind each other.
-// With the entries of all waves stored between their gathers and the rows requested before the barrier a phase took
-// 1.20 us at 512 elements, 1.45 at 1024, 1.72 at 1568, 2.16 at 2112, 2.60 at 3136 and 3.04 at 4096; so it takes
-// 0.96, 1.23, 1.58, 1.93, 2.52 and 3.03.  (The rows of 64 KB of tables alone take 0.56 us, the stores 0.45.)
+// With the dense matrix instruction, the entries of all waves stored between their gathers and the rows requested before
+// the barrier a phase took 1.24 us at 512 elements, 1.53 at 1024, 1.83 at 1600, 2.36 at 2112, 2.90 at 3136 and 3.51 at
+// 4096; so it takes 0.98, 1.24, 1.58, 1.94, 2.55 and 3.11, ready-made 1.39, 1.56, 1.68, 2.15, 2.52 and 2.86 (the copies come
+// from beyond the L2s; side by side on one device).  The rows of 64 KB of tables alone take 0.56 us.
 // PRE: the tables of a chunk lie ready-made in global memory as an image of the LDS buffer
 // (prep_tables_kernel) and are copied straight into LDS (buffer loads with the lds modifier).
 //
@@ -243,12 +244,13 @@ __device__ __forceinline__ void put_pair(const TabArgs& a, int32_t* acc_base, fl
 // requested past the last chunk where the tables are ready-made: 100352 x 16 x 256 (1024 tiles of one phase, one
 // output) 75 -> 61 us, 100352 x 64 x 256 115 -> 98.
 //
-// Bound: LDS.  Per phase of a full tile 1 MiB of gathers (165-200 bytes per clock measured) and 64
-// KiB of table writes (1150 clocks, 57 bytes per clock), against 2048 clocks of matrix instructions per SIMD.
+// Bound: LDS.  Per phase of a full tile (7000 clocks) 1 MiB of gathers, 4097 clocks on their own (256 bytes per clock), and 64
+// KiB of table writes, 745 (88 bytes per clock), against 2048 clocks of matrix instructions per SIMD.
 // PADDED: taps may lie outside the image and read the pad row instead (operands that could not be
 // copied with their border, see prep_chunks_kernel); the other form has no position per lane
-// element and no comparisons.  PADDED spills 204 bytes per lane at full height, the others none or next to none
-// (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).
+// element and no comparisons.  PADDED spills 112 bytes per lane at full height, the others at most 20
+// (28 x 28 x 128, 3 x 3, batch 16: 203 us in place, 91 from the copy).  All forms keep 84 to 137 scalars in lanes of vector
+// registers; few of their moves lie in the loops, most where a segment begins and ends.
 // GR: groups of 64 lane elements per wave.  Tiles of at most half the height take GR = 4, whose free
 // registers hold the lane operands and the table rows a whole phase ahead: with few groups to gather
 // a phase is shorter than a round trip to memory.
@@ -423,7 +425,7 @@ __global__ __launch_bounds__(kThreads, 2) void tab_kernel(const TabArgs a) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_perm(d[2 * c + 1][e >> 1], d[2 * c][e >> 1], s);
     // the four lanes of a tap write to the same four banks: odd lanes store their halves in the other
-    // order (2-way instead of 4-way conflicts; 1150 instead of 2170 clocks for a phase's tables)
+    // order (2-way instead of 4-way conflicts: about half the clocks for a phase's tables)
     const bool odd = lane & 1;
     uint8_t* const dst = &sh.tab[buf * kTabBytes + (bv + e) * 256 + bt * 16];
     *reinterpret_cast<uint2*>(dst + (odd ? 8 : 0)) = make_uint2(odd ? v[2] : v[0], odd ? v[3] : v[1]);
@@ -1000,7 +1002,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
       if (fast) {
         pk = *reinterpret_cast<const uint32_t*>(w + (size_t)k * J + j) ^ (sx * 0x01010101u);
       } else {
-        int dy = 0, dx = 0, ci = 0;  // FROM_X: the tap
+        int dy = 0, dx = 0, ci = 0;  // FROM_X: the tap (256 patches of 4096: 9.0 us, 9.1 with pixel and tap decoded per byte)
         if (FROM_X) {
           const int tap = k / cv.Cin, ky = tap / cv.KW;
           ci = k - tap * cv.Cin;
@@ -1388,10 +1390,12 @@ static int count_partials(int ntiles, int nch, int G, int* most_per_tile, int* m
 
 // Cost model of one (tile height, lane assignment, grid size) choice, in seconds; measured on dense and
 // convolution layers with the heights, cuts and combinations forced.
-//   - a phase (a chunk of 16 taps) of a tile of ih lane elements takes 1.2 us for its tables, barrier
+//   - a phase (a chunk of 16 taps) of a tile of ih lane elements: 1.2 us for its tables, barrier
 //     and latencies (1.05 us with ready-made tables) and 0.6 ns per lane element;
-//   - every segment a workgroup runs costs its first tables, the pipeline fill and its stores (fitted before
-//     its set-up was shortened by some 3 us; the order of the choices is what it is used for);
+//   - every segment a workgroup runs: its first tables, the pipeline fill and its stores.
+//     Both are prices of earlier forms of the kernel (a phase is a fifth to an eighth shorter now and the ready-made
+//     one is the longer one on low tiles, see assembled_gain; a segment takes 3 us less).  They are used for the order of
+//     grids and heights and for the comparison with fewpix_kernel, which is fitted to them as they are;
 //   - tiles cut into pieces: a launch of the fix-up kernel and the pieces once written and once read,
 //     or, combined inside the main kernel, the reading of the others' pieces one after another;
 //   - grids larger than the machine run in rounds.
