@@ -92,8 +92,9 @@ int geom_of_desc(const ax_conv_desc_t* d, Geom* g) {
 // ready-made tables.  Calls on this kernel take 0.9 of its estimate, 0.72 in the byte form; prepared layers are compared
 // at 0.83, which gives near ties to the kernel that needs neither prepared block nor scratch.  Long sums (2048 taps) stay
 // here up to 60 us of its estimate, which is then too high (0.4 to 0.9 of it measured) and that of the tiles too low.
-// Over 1590 random calls and 1552 prepared layers of 4e6 to 1.2e9 lookups, each timed on both kernels, the choice costs 0.8
-// and 2.2 % over the better one each time (more than 5 % slower 59 and 137, more than 20 % 16 and 51).
+// Over 1768 random calls and 1842 prepared layers of 4e6 to 1.2e9 lookups, each timed on both kernels, the choice costs 1.2
+// and 2.8 % over the better one each time (more than 5 % slower 94 and 156, more than 20 % 35 and 89); when these lines were
+// fitted, to slower tiles, 0.8 and 2.2 %.
 // Prepared layers of more than two rounds of tiles stay on this kernel up to 36 and 38 us, though the tiles are faster for
 // most (5692 x 80 x 47: 30 and 15 us): the tests of the walk over several tiles reach it through the choice for such layers,
 // as nothing else selects this kernel.  From 4e7 lookups on that is asked of layers beyond the bounds of ready-made tables
