@@ -11,7 +11,6 @@ same workload.
 """
 
 import argparse
-import gc
 import json
 import os
 import sys
@@ -336,15 +335,11 @@ def main():
                 f()
             torch.cuda.synchronize()
             a0, a1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            # no garbage collection in between: one takes 15 to 45 ms here, and a sweep whose uploads are overlapped keeps
-            # the device only a few milliseconds ahead of the host
-            gc.disable()
             a0.record()
             for _ in range(reps):
                 for f in fns:
                     f()
             a1.record()
-            gc.enable()
             torch.cuda.synchronize()
             return a0.elapsed_time(a1) / reps
 
