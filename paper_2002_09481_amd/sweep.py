@@ -54,6 +54,7 @@ class TableSweep:
         self.staging = [torch.empty((self.per_upload, 65536), dtype=torch.int16, device=self.device) for _ in range(self.NBUF)]
         self.ready = [torch.cuda.Event() for _ in range(self.NBUF)]
         self.free = [torch.cuda.Event() for _ in range(self.NBUF)]
+        self._following, self._recorded = None, set()  # see run
 
     def _handle(self, li: int, n: int) -> ax.AxLayer:
         key = (li, n)
@@ -79,7 +80,8 @@ class TableSweep:
         False to skip).  overlap=False enqueues the copies on the compute stream instead (the
         serialized form, for comparison).  Returns (acc_out, y_out).  The device is not waited for at
         the end, but with overlap the host paces itself: before it enqueues the copy of upload unit
-        u it waits until unit u - 3 has finished on the device."""
+        u it waits until unit u - 3 has finished on the device, in the first units of a call that
+        follows another the units of that one."""
         T = int(host_tables.shape[0])
         if host_tables.dim() != 2 or host_tables.shape[1] != 65536 or host_tables.dtype not in (torch.int16, torch.uint16):
             raise ValueError("host_tables must be a 16-bit integer tensor [T, 65536]")
@@ -103,19 +105,29 @@ class TableSweep:
             if not overlap:
                 self.staging[b][:n].copy_(host_tables[t0:t0 + n], non_blocking=True)
                 return
-            if u >= self.NBUF:
-                # Unit u - 3 must have stopped reading this staging buffer.  The host waits for that
-                # here rather than the upload stream on the device: a queue that sits blocked on an
-                # event slows every kernel launch of the other queue (measured: 40 us per launch).
-                # This copy is enqueued before the launches of unit u - 1, so the device is then
-                # still working on unit u - 2 and has that unit's launches ahead of it.
+            if b in recorded:
+                # Unit u - 3, or the last one of the call before that had this staging buffer, must have
+                # stopped reading it.  The host waits for that here rather than the upload stream on the
+                # device: a queue that sits blocked on an event slows every kernel launch of the other
+                # queue (measured: 40 us per launch).  This copy is enqueued before the launches of unit
+                # u - 1, so the device is then still working on unit u - 2 and has that unit's launches
+                # ahead of it.
                 self.free[b].synchronize()
             with torch.cuda.stream(self.upload):
                 self.staging[b][:n].copy_(host_tables[t0:t0 + n], non_blocking=True)
                 self.ready[b].record(self.upload)
 
+        # Buffers whose `free` event was recorded by overlapped calls that followed each other on this stream, outside a
+        # capture.  Any other call begins with the upload stream waiting for whatever filled or read the staging buffers
+        # before; as the beginning of every call that wait cost a whole unit in one process of three (64 tables, eight
+        # per call: 23.3 ms, 21.0).
+        capturing = torch.cuda.is_current_stream_capturing()
+        following = overlap and not capturing and self._following == compute
+        recorded = self._recorded if following else set()
+        self._following = None
         if overlap:
-            self.upload.wait_stream(compute)  # whatever filled or read the staging buffers before this call
+            if not following:
+                self.upload.wait_stream(compute)
             enqueue_upload(0)
         for u, (t0, nu) in enumerate(units):
             b = u % self.NBUF
@@ -141,8 +153,11 @@ class TableSweep:
                     h.run(x, a, y, workspace=self._ws[(li, n)])
             if overlap:
                 self.free[b].record(compute)
+                recorded.add(b)
         if overlap:
             compute.wait_stream(self.upload)
+            if not capturing:
+                self._following, self._recorded = compute, recorded
         return acc_out, y_out
 
     def close(self):

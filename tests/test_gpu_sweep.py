@@ -52,3 +52,61 @@ def test_overlapped_sweep_equals_resident_tables(chunk, per_upload):
                 G.assert_parity(acc[li][T - 1].cpu().numpy(), y[li][T - 1].cpu().numpy(), a_ref, y_ref, l.name)
     finally:
         sweep.close()
+
+
+def _host_tables(T, seed):
+    tabs = [np.ascontiguousarray(I.lut_random_error(seed + t)).reshape(-1) for t in range(T)]
+    return torch.from_numpy(np.stack(tabs).view(np.int16).copy()).pin_memory()
+
+
+def _resident(dev_layers, host):
+    out = []
+    for desc, q, x, w in dev_layers:
+        with ax.AxLayer(desc, q) as h:
+            out.append([])
+            for t in host:
+                h.prepare(w, t.cuda())
+                out[-1].append(h.run(x))
+            torch.cuda.synchronize()
+    return out
+
+
+# one, two and seven units: fewer than staging buffers, and buffers that come round again within a call and in the next
+@pytest.mark.parametrize("T", [1, 2, 7])
+def test_calls_after_each_other(T):
+    """Calls whose tables differ, enqueued without a wait in between: overlapped ones that follow each other on one stream,
+    a serialized one and one on another stream in between, one recorded into a graph."""
+    dev_layers = [(ax._conv_desc(x.shape, w.shape, l.stride, l.pad), q, G.to_dev(x), G.to_dev(w)) for l, x, w, q in _layers()]
+    sweep = TableSweep(dev_layers, chunk=1, tables_per_upload=1)
+    other = torch.cuda.Stream()
+    calls, graph = [], None
+    try:
+        for i, mode in enumerate(["overlap", "overlap", "serial", "overlap", "overlap", "other", "overlap", "graph", "overlap", "overlap"]):
+            host = _host_tables(T, 500 + 10 * i)
+            if mode == "graph":
+                if T > sweep.NBUF:  # the host paces itself on events, which a capture does not allow
+                    continue
+                torch.cuda.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph):
+                    out = sweep.run(host)
+            elif mode == "other":
+                other.wait_stream(torch.cuda.current_stream())
+                with torch.cuda.stream(other):
+                    out = sweep.run(host)
+                torch.cuda.current_stream().wait_stream(other)
+            else:
+                out = sweep.run(host, overlap=mode == "overlap")
+            calls.append((mode, host, out))
+        torch.cuda.synchronize()
+        for mode, host, (acc, y) in calls:
+            want = _resident(dev_layers, host)
+            for _ in range(3 if mode == "graph" else 1):
+                if mode == "graph":
+                    graph.replay()
+                    torch.cuda.synchronize()
+                for li in range(len(dev_layers)):
+                    for t in range(T):
+                        assert torch.equal(acc[li][t], want[li][t][0]) and torch.equal(y[li][t], want[li][t][1]), (mode, li, t)
+    finally:
+        sweep.close()
