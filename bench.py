@@ -444,7 +444,7 @@ def main():
         # the same, with every table's 128 KB host-to-device copy (from page-locked host memory) inside
         # the timed region: (a) enqueued on the compute stream in front of the table's two layers,
         # (b) on a second stream, overlapping the layers that run on the previous table
-        # (sweep.TableSweep: two staging buffers, event-ordered).  Both go through layer handles
+        # (sweep.TableSweep: three staging buffers, event-ordered).  Both go through layer handles
         # (prepare + run per table and layer), like (c), the tables resident in device memory.
         from paper_2002_09481_amd.sweep import TableSweep
         host_all = torch.from_numpy(np.stack([np.ascontiguousarray(I.lut_random_error(sd)).reshape(-1)

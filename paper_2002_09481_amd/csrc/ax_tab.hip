@@ -1215,24 +1215,27 @@ __global__ __launch_bounds__(256) void prep_chunks_kernel(const uint8_t* __restr
 
 // Ap[k / 16][j][k % 16] = w[k][j] (zero fill for k >= K).  A thread takes one chunk of sixteen rows and four
 // neighbouring columns: a dword per row, all in flight together, turned in registers (4 x 4 bytes in eight permutes),
-// and four 16-byte pieces.  Rows may start at any byte (dwords at their own alignment); columns past the last whole four
-// are read byte by byte.  Bound by memory: 4096 x 4096 (34 MB) 35 us with byte loads and a pass through LDS, 10 us now.
+// and four 16-byte pieces.  Rows may start at any byte (dwords at their own alignment); for columns past the last whole four
+// the dword of the last four is moved down (read byte by byte, row after row, the one such thread kept its wave waiting:
+// 122 x 60 x 2819 22.9 us the call, 20.5 so).  Bound by memory: 4096 x 4096 (34 MB) 35 us with byte loads and a pass
+// through LDS, 10 us now.
 __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __restrict__ w, int K, int J,
                                                               uint8_t* __restrict__ Ap, uint32_t sx) {
   const int chunk = blockIdx.x, j = 4 * (blockIdx.y * 256 + threadIdx.x);
   if (j >= J) return;
   const int k0 = chunk * kChunk, nk = min(kChunk, K - k0);
-  const bool whole = j + 3 < J;
-  uint32_t v[kChunk];  // columns j .. j + 3 of a row
+  const int jb = min(j, J - 4), late = 8 * (j - jb);  // past the last whole four: the last four columns, moved down
+  uint32_t v[kChunk];  // columns j .. j + 3 of a row; past the last row: that one again, cleared below
+  if (J >= 4) {
 #pragma unroll
-  for (int e = 0; e < kChunk; ++e) {
-    const uint8_t* row = w + (size_t)(k0 + min(e, nk - 1)) * J + j;  // past the last row: that one again, cleared below
-    if (whole) {
-      v[e] = load_any<uint32_t>(row);
-    } else {
-      v[e] = row[0];
-      if (j + 1 < J) v[e] |= (uint32_t)row[1] << 8;
-      if (j + 2 < J) v[e] |= (uint32_t)row[2] << 16;
+    for (int e = 0; e < kChunk; ++e) v[e] = load_any<uint32_t>(w + (size_t)(k0 + min(e, nk - 1)) * J + jb);
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) v[e] >>= late;
+  } else {
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) {
+      const uint8_t* row = w + (size_t)(k0 + min(e, nk - 1)) * J;
+      v[e] = row[0] | (uint32_t)row[min(1, J - 1)] << 8 | (uint32_t)row[min(2, J - 1)] << 16;
     }
   }
   uint32_t piece[4][4];  // [column][four rows]
