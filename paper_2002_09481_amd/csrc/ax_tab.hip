@@ -1224,13 +1224,11 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
   const int chunk = blockIdx.x, j = 4 * (blockIdx.y * 256 + threadIdx.x);
   if (j >= J) return;
   const int k0 = chunk * kChunk, nk = min(kChunk, K - k0);
-  const int jb = min(j, J - 4), late = 8 * (j - jb);  // past the last whole four: the last four columns, moved down
+  const int jb = min(j, max(J - 4, 0)), late = J < 4 ? 0 : 8 * (j - jb);  // past the last whole four: the last four columns, moved down
   uint32_t v[kChunk];  // columns j .. j + 3 of a row; past the last row: that one again, cleared below
   if (J >= 4) {
 #pragma unroll
     for (int e = 0; e < kChunk; ++e) v[e] = load_any<uint32_t>(w + (size_t)(k0 + min(e, nk - 1)) * J + jb);
-#pragma unroll
-    for (int e = 0; e < kChunk; ++e) v[e] >>= late;
   } else {
 #pragma unroll
     for (int e = 0; e < kChunk; ++e) {
@@ -1243,7 +1241,7 @@ __global__ __launch_bounds__(256) void prep_transpose_kernel(const uint8_t* __re
   for (int q = 0; q < 4; ++q) {
     uint32_t r[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = 4 * q + e < nk ? v[4 * q + e] ^ (sx * 0x01010101u) : 0u;
+    for (int e = 0; e < 4; ++e) r[e] = 4 * q + e < nk ? (v[4 * q + e] >> late) ^ (sx * 0x01010101u) : 0u;
     const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
     const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
     piece[0][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
